@@ -63,9 +63,9 @@ __device__ __forceinline__ uint32_t loader_src_offset(int chunk, int lane, int l
 
 // a W x BK (or BK x W) tile is W * BK / 512 chunks of 1 KB; wave w moves chunks w, w + NW, ...
 template <int BK, int W, int NW>
-__device__ __forceinline__ void issue_tile_loads(const char* __restrict__ g, const uint32_t* off, char* __restrict__ lds, int wave) {
+__device__ __forceinline__ void issue_tile_loads(const char* __restrict__ g, uint32_t* off, char* __restrict__ lds, int wave) {
 #pragma unroll
-  for (int i = 0; i < W * BK / 512 / NW; i++) load16_to_lds(g + off[i], lds + (wave + NW * i) * 1024);
+  for (int i = 0; i < W * BK / 512 / NW; i++) load16_to_lds(g, off[i], lds + (wave + NW * i) * 1024);
 }
 
 // fragment (8 k-values for row/col = lane % 32 of a 32-wide block) for k-step ks (16 k each)
@@ -153,7 +153,7 @@ constexpr bool b_first() { return !AKS; }
 // k-steps 0 and 1 of k-block j; on entry f0 holds the fragments of k-step 0.  Starts the loads of the odd tile
 // of k-block j+1.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
-__device__ __forceinline__ void half_even(const char* gS, const uint32_t* offS, char* __restrict__ fill, const char* __restrict__ cA,
+__device__ __forceinline__ void half_even(const char* gS, uint32_t* offS, char* __restrict__ fill, const char* __restrict__ cA,
                                           const char* __restrict__ cB, Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f0,
                                           Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f1, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32],
                                           int wave, int wm, int wn, int lane) {
@@ -172,7 +172,7 @@ __device__ __forceinline__ void half_even(const char* gS, const uint32_t* offS, 
 // k-steps 2 and 3 of k-block j; on entry f0 holds the fragments of k-step 2.  Starts the loads of the even tile
 // of k-block j+2, waits for k-block j+1 (nA, nB) and leaves its first fragments in f0.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
-__device__ __forceinline__ void half_odd(const char* gF, const uint32_t* offF, char* __restrict__ fill, const char* __restrict__ cA,
+__device__ __forceinline__ void half_odd(const char* gF, uint32_t* offF, char* __restrict__ fill, const char* __restrict__ cA,
                                          const char* __restrict__ cB, const char* __restrict__ nA, const char* __restrict__ nB,
                                          Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f0, Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f1,
                                          f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], int wave, int wm, int wn, int lane) {
@@ -205,7 +205,7 @@ constexpr int NS = 4;   // stages in the LDS ring: loads run 3 stages ahead of t
 // MFMAs of k-step 1.  The restrict qualifiers tell the compiler that the three
 // slots are distinct, so LDS reads never wait for the loads in flight.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
-__device__ __forceinline__ void ring_step(const char* gA, const char* gB, const uint32_t* offA, const uint32_t* offB,
+__device__ __forceinline__ void ring_step(const char* gA, const char* gB, uint32_t* offA, uint32_t* offB,
                                           char* __restrict__ fA, char* __restrict__ fB, const char* __restrict__ cA,
                                           const char* __restrict__ cB, const char* __restrict__ nA, const char* __restrict__ nB,
                                           Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f0, Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f1,
@@ -348,8 +348,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
     const char* gF = BF ? gB : gA;
     const char* gS = BF ? gA : gB;
     const size_t stepF = BF ? stepB : stepA, stepS = BF ? stepA : stepB;
-    const uint32_t* offF = BF ? offB : offA;
-    const uint32_t* offS = BF ? offA : offB;
+    uint32_t* offF = BF ? offB : offA;
+    uint32_t* offS = BF ? offA : offB;
     const int np = g.K / BK, lastp = np - 1;
     // In the weight-gradient layout the k axis may be cut into pieces that live in different buffers (kernels.h):
     // the outer loop runs over the pieces (one piece for the other layouts), the inner one over the k-blocks of a
