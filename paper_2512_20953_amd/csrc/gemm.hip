@@ -10,7 +10,8 @@
 // with the transposing 8-byte LDS read, so no transposed copy is ever made.
 //
 // Work split: 256 threads = 4 waves in a 2 x 2 grid; each wave owns a
-// (BM/2) x (BN/2) sub-tile as 32 x 32 MFMA blocks.  The MFMA is issued with the
+// (BM/2) x (BN/2) sub-tile as 32 x 32 MFMA blocks (in the smallest tiles the
+// waves share a sub-tile and split the k axis).  The MFMA is issued with the
 // operands swapped (D = B^T A^T) so that a lane ends up with 4 consecutive
 // columns of one output row: 8-byte bf16 or 16-byte fp32 accesses in the epilogue.
 #include "common.h"
@@ -22,12 +23,12 @@
 
 namespace ah {
 
-// Two pipelines share the tile mapping, the LDS layouts, the fragment reads and the epilogue.  The forward and
+// Three pipelines share the tile mapping, the LDS layouts, the fragment reads and the epilogue.  The forward and
 // input-gradient products (at least one k-contiguous operand) use 64-wide k tiles in a ring of five operand
 // buffers, so that every loader instruction fetches whole 128-byte lines of the k-contiguous operand; the weight
 // gradient (both operands k-strided, rows of a tile are 256 or 512 bytes anyway) keeps 32-wide k stages in a ring of
 // four, whose loads all run 2.5 stages ahead.  Measured in the stage: the first is 2-13 % faster on the former
-// products, the second 1-5 % faster on the latter.
+// products, the second 1-5 % faster on the latter.  The third is that of the smallest tiles (namespace ksplit).
 
 // ---------------------------------------------------------------------------
 // LDS layouts, for a tile of BK = 64 or 32 k-values (all permutations are of 16-byte pieces, the unit of the loader)
@@ -36,12 +37,18 @@ namespace ah {
 //    groups for the fragment reads.  With BK = 64 a loader instruction fetches 8 rows x 128 B: full cache lines
 //    (64-byte row pieces, as BK = 32 gives, cost the memory pipeline twice the requests and showed up as ~10 % of
 //    MFMA utilisation where an operand is k-contiguous).
-//  k-strided tile: [BK k][W cols]; row = 2W bytes; the 64-byte granule g of row k is stored at granule g ^ (k & 3):
-//    the 4 rows x 64 B that half a wave fetches in one transposing read cover all banks once.
+//  k-strided tile: [BK k][W cols]; row = 2W bytes; the 64-byte granule g of row k is stored at granule g ^ (k & 3)
+//    (W = 64, two granules: g ^ (k >> 1 & 1)): the 4 rows x 64 B that half a wave fetches in one transposing read cover all banks once.
 // A k-strided tile may gather its columns from two column ranges of the matrix (`gw` > 0: tile columns in groups of
 // gw, even groups from columns c, odd groups from columns F + c): the fused gate|up product of the SwiGLU block then
 // has a gate column and its up column in the same wave's accumulators.
 // ---------------------------------------------------------------------------
+template <int W>
+__device__ __forceinline__ int granule_swizzle(int k) {  // a 64-wide row has two granules only: 4 rows x 64 B then span two bank cycles
+  static_assert(W >= 64, "a row holds whole granules");
+  return W >= 128 ? k & 3 : (k >> 1) & 1;
+}
+
 template <int BK, int W, bool KS>
 __device__ __forceinline__ uint32_t loader_src_offset(int chunk, int lane, int ld, int gw = 0, int F = 0) {  // in bytes
   const int pos = chunk * 1024 + lane * 16;
@@ -54,7 +61,7 @@ __device__ __forceinline__ uint32_t loader_src_offset(int chunk, int lane, int l
   } else {
     constexpr int RB = W * 2;
     const int k = pos / RB, q = (pos % RB) >> 4;
-    const int p = q ^ ((k & 3) << 2);
+    const int p = q ^ (granule_swizzle<W>(k) << 2);
     int col = p * 8;
     if (gw > 0) col = ((col / gw) & 1) * F + (col / (2 * gw)) * gw + col % gw;
     return (uint32_t)(k * ld + col) * 2u;
@@ -82,7 +89,7 @@ __device__ __forceinline__ bf16x8 read_frag(const char* __restrict__ lds, int ba
     constexpr int RB = W * 2;
     const int k = ks * 16 + (lane >> 5) * 8 + ((lane & 15) >> 2);
     const int c = base + blk * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
-    const int a0 = k * RB + ((((c >> 5) ^ (k & 3))) << 6) + ((c * 2) & 63);
+    const int a0 = k * RB + (((c >> 5) ^ granule_swizzle<W>(k)) << 6) + ((c * 2) & 63);
     bf16x4 lo = lds_read_tr4(lds + a0);
     bf16x4 hi = lds_read_tr4(lds + a0 + 4 * RB);
     return cat4(lo, hi);
@@ -106,16 +113,15 @@ struct Frags {
 // the NV global->LDS loads and the NR LDS reads issued for later steps, the LDS
 // reads within the first three quarters so their latency is covered by the rest.
 // Masks: 0x020 = vector memory read, 0x100 = LDS read, 0x008 = MFMA.
-template <int I, int NM, int NR, int NV>
+template <int I, int NM, int NR, int NV, int SPAN = (NM * 3 / 4 > 0 ? NM * 3 / 4 : 1)>
 __device__ __forceinline__ void interleave() {
   if constexpr (I < NM) {
-    constexpr int SPAN = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
     constexpr int v = (I + 1) * NV / NM - I * NV / NM;
     constexpr int r = I < SPAN ? (I + 1) * NR / SPAN - I * NR / SPAN : 0;
     if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(0x020, v, 0);
     if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    interleave<I + 1, NM, NR, NV>();
+    interleave<I + 1, NM, NR, NV, SPAN>();
   }
 }
 
@@ -227,30 +233,75 @@ __device__ __forceinline__ void ring_step(const char* gA, const char* gB, uint32
 
 }  // namespace k32
 
-template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
-  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN;
-  constexpr bool K32 = AKS && BKS;  // which pipeline
+namespace ksplit {
+// The pipeline of the tiles whose waves share a sub-tile and split the k axis: of the four k-steps of a 64-wide
+// k-block, wave wk takes 4 / WGK.  The partial sums meet in the epilogue's staging strips.
+// Two tiles use it, 64 x 64 with four shares and 64 x 128 with two, for outputs of fewer than 256 tiles of 128 x 128.
+// Such a launch lasts as long as one block's chain of k-blocks; these have four (two) times the blocks, and a chain
+// a quarter as long.  256 x 256 x 1024: 9.3 -> 5.5 us, 1024 x 1024 x 2048: 21.6 -> 8.8, 2048 x 1024 x 2048: 21.6 -> 13.2 (NT).
+constexpr int BK = 64;
+template <int BM, int BN> constexpr int stage_bytes() { return (BM + BN) * 2 * BK; }
+template <int BM, int BN> constexpr int stages() { return 81920 / stage_bytes<BM, BN>(); }   // half of a CU's LDS: two blocks share a CU
+
+// Second (or only) part of a k-block: the block's slot is free (its fragments are in registers, the barrier is
+// passed), so the loads of the stage NS ahead go there while the next stage's first fragments are read.  The two
+// slots are distinct: the restrict qualifiers keep the LDS reads from waiting for the loads in flight.
+template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
+__device__ __forceinline__ void last_step(const char* pA, const char* pB, uint32_t* offA, uint32_t* offB, char* __restrict__ fill,
+                                          const char* __restrict__ next, int ks, const Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f,
+                                          Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& fn, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], int wave,
+                                          int wm, int wn, int lane) {
+  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = 4;
+  constexpr int NR = TM * (AKS ? 2 : 1) + TN * (BKS ? 2 : 1), NM = TM * TN, LPS = (BM + BN) / 8 / NW;
+  issue_tile_loads<BK, BM, NW>(pA, offA, fill, wave);
+  issue_tile_loads<BK, BN, NW>(pB, offB, fill + BM * 2 * BK, wave);
+  fn.load(next, next + BM * 2 * BK, ks, wm, wn, lane);
+  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f, acc);
+  interleave<0, NM, NR, LPS, NM / 2>();
+}
+
+// First part of a two-step k-block
+template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
+__device__ __forceinline__ void first_step(const char* __restrict__ cur, int ks, const Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f,
+                                           Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& fn, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], int wm,
+                                           int wn, int lane) {
+  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
+  constexpr int NR = TM * (AKS ? 2 : 1) + TN * (BKS ? 2 : 1), NM = TM * TN;
+  fn.load(cur, cur + BM * 2 * BK, ks, wm, wn, lane);
+  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f, acc);
+  interleave<0, NM, NR, 0, NM / 2>();
+}
+
+}  // namespace ksplit
+
+template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
+__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
+  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN * WGK;
+  static_assert(NW == 4, "four waves per block");
+  constexpr bool SPLIT = WGK > 1;                // which pipeline
+  constexpr bool K32 = !SPLIT && AKS && BKS;
   // EPI_SWIGLU: the B tile gathers GW gate columns and their GW up columns per wave (see loader_src_offset); the
   // launch runs over N = 2 F tile columns that stand for F logical ones.
   constexpr bool SWIGLU = EPI == EPI_SWIGLU;
   constexpr int GW = SWIGLU ? BN / WGN / 2 : 0;
   static_assert(!SWIGLU || (!AKS && BKS), "the fused SwiGLU epilogue belongs to the forward layout");
   constexpr int BUF = (BM > BN ? BM : BN) * 128;        // k64: one ring buffer holds an A or a B tile
-  constexpr int RING = K32 ? k32::NS * (BM + BN) * 64 : k64::NB * BUF;
+  constexpr int RING = SPLIT ? ksplit::stages<BM, BN>() * ksplit::stage_bytes<BM, BN>() : K32 ? k32::NS * (BM + BN) * 64 : k64::NB * BUF;
   // the epilogue reuses the ring as staging space
   __shared__ __attribute__((aligned(1024))) char ring[RING];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps LDS bases in scalar registers
-  const int wm = wave / WGN, wn = wave % WGN;
+  const int wmn = wave / WGK, wk = wave % WGK;   // output sub-tile, share of the k axis
+  const int wm = wmn / WGN, wn = wmn % WGN;
 
   // block -> tile: consecutive logical tiles share an XCD (blocks are dealt to the
   // 8 XCDs round-robin), and run down groups of 8 tile-rows so that the tiles in
   // flight on one XCD reuse the same operand panels in its L2.
   const int tiles_m = g.M / BM, tiles_n = g.N / BN, ntiles = tiles_m * tiles_n;
+  // (Where the count is not a multiple of 8 the first ntiles % 8 XCDs take one tile more.)
   int logical = blockIdx.x;
-  if ((ntiles & 7) == 0 && g.xcd_remap) logical = (blockIdx.x & 7) * (ntiles >> 3) + (blockIdx.x >> 3);
+  if (g.xcd_remap) logical = (blockIdx.x & 7) * (ntiles >> 3) + min((int)(blockIdx.x & 7), ntiles & 7) + (blockIdx.x >> 3);
   const int GROUP = g.group;
   const int per_group = GROUP * tiles_n;
   const int gid = logical / per_group;
@@ -270,7 +321,83 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
 #pragma unroll
       for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
 
-  if constexpr (K32) {
+  if constexpr (SPLIT) {
+    using namespace ksplit;
+    constexpr int STAGE = stage_bytes<BM, BN>(), NS = stages<BM, BN>(), KPW = 4 / WGK, LA = BM / 8 / NW, LB = BN / 8 / NW, LPS = LA + LB;
+    const size_t stepA = (AKS ? (size_t)BK * g.lda : (size_t)BK) * 2;  // bytes per k-block
+    const size_t stepB = (BKS ? (size_t)BK * g.ldb : (size_t)BK) * 2;
+    uint32_t offA[LA], offB[LB];
+#pragma unroll
+    for (int i = 0; i < LA; i++) offA[i] = loader_src_offset<BK, BM, AKS>(wave + NW * i, lane, g.lda);
+#pragma unroll
+    for (int i = 0; i < LB; i++) offB[i] = loader_src_offset<BK, BN, BKS>(wave + NW * i, lane, g.ldb, GW, g.swiglu_F);
+    // The stage to be fetched next: pA, pB, moved on by scalar selects (a branch per stage would cut the loop into
+    // basic blocks).  Past the last stage it stays there: that stage is fetched again into dead slots, which keeps
+    // the number of loads in flight uniform for the counted wait.  Weight gradients may have their k axis in pieces
+    // (kernels.h): at the end of a piece the cursor moves to the next piece's base.
+    constexpr bool PIECES = AKS && BKS;
+    const int nk = g.K / BK;
+    const int nseg = (PIECES && g.n_seg > 0) ? g.n_seg : 1, seg_stages = nk / nseg;
+    const char *pA = gA, *pB = gB;
+    int fetched = 1, left = seg_stages, piece = 0;
+    const char *nextA = gA, *nextB = gB;   // where the next piece starts (segA[0], segB[0] are set for one piece too)
+    auto next_piece = [&]() {
+      const int nx = min(piece + 1, nseg - 1);
+      nextA = (const char*)((const bf16*)g.segA[nx] + m0);
+      nextB = (const char*)((const bf16*)g.segB[nx] + n0);
+    };
+    if constexpr (PIECES) next_piece();
+    auto advance = [&]() {
+      const bool more = fetched < nk;
+      fetched++;
+      const char *nA = pA + stepA, *nB = pB + stepB;
+      if constexpr (PIECES) {
+        left--;
+        const bool wrap = left == 0;
+        nA = wrap ? nextA : nA;
+        nB = wrap ? nextB : nB;
+        left = wrap ? seg_stages : left;
+        piece = min(piece + (wrap ? 1 : 0), nseg - 1);
+        next_piece();
+      }
+      pA = more ? nA : pA;
+      pB = more ? nB : pB;
+    };
+#pragma unroll
+    for (int t = 0; t < NS; t++) {
+      issue_tile_loads<BK, BM, NW>(pA, offA, ring + t * STAGE, wave);
+      issue_tile_loads<BK, BN, NW>(pB, offB, ring + t * STAGE + BM * 2 * BK, wave);
+      advance();
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 1) * LPS));
+    __builtin_amdgcn_s_barrier();
+    Frags<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
+    f0.load(ring, ring + BM * 2 * BK, wk * KPW, wm, wn, lane);
+    int c = 0;  // ring slot of k-block j (its wave's first fragments are in f0; with one k-step per block, in f0 and f1 by turns)
+    for (int j = 0; j < nk; j += 3 - KPW) {
+      const int n = c + 1 == NS ? 0 : c + 1;
+      if constexpr (KPW == 2) {
+        first_step<BM, BN, WGM, WGN, AKS, BKS>(ring + c * STAGE, wk * KPW + 1, f0, f1, acc, wm, wn, lane);
+        // the next stage has landed (own loads by count, the others' by the barrier) and this one is read out
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * LPS));
+        __builtin_amdgcn_s_barrier();
+        last_step<BM, BN, WGM, WGN, AKS, BKS>(pA, pB, offA, offB, ring + c * STAGE, ring + n * STAGE, wk * KPW, f1, f0, acc, wave, wm, wn, lane);
+        advance();
+        c = n;
+      } else {
+        const int n2 = n + 1 == NS ? 0 : n + 1;
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * LPS));
+        __builtin_amdgcn_s_barrier();
+        last_step<BM, BN, WGM, WGN, AKS, BKS>(pA, pB, offA, offB, ring + c * STAGE, ring + n * STAGE, wk, f0, f1, acc, wave, wm, wn, lane);
+        advance();
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * LPS));
+        __builtin_amdgcn_s_barrier();
+        last_step<BM, BN, WGM, WGN, AKS, BKS>(pA, pB, offA, offB, ring + n * STAGE, ring + n2 * STAGE, wk, f1, f0, acc, wave, wm, wn, lane);
+        advance();
+        c = n2;
+      }
+    }
+  } else if constexpr (K32) {
     using namespace k32;
     constexpr int LPS = (BM + BN) / 16 / NW;
     constexpr int SLOT = (BM + BN) * 64;  // ring slot t: A tile at t * SLOT, B tile behind it
@@ -404,11 +531,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
   // straight from that layout would touch 32 rows per instruction, 16 bytes each.  Instead each
   // wave passes its sub-tile through a private LDS strip, 32 rows at a time in fp32, and reads it
   // back row-major, so that every global access is 16 bytes per lane and whole rows per 16 lanes.
+  // Where waves split the k axis, the WGK waves of a sub-tile leave 64 rows at a time, each its own partial sums, and
+  // each takes 64 / WGK of those rows back, adding the partial sums in the order of the k shares.
   constexpr int WN = BN / WGN, WM = BM / WGM;
   constexpr int ROWB = WN * 4 + 16;                // padded strip row
-  static_assert(NW * 32 * ROWB <= RING, "staging strips must fit in the ring");
+  constexpr int SR = SPLIT ? 64 : 32;              // rows of a strip
+  constexpr int RPW = SR / WGK;                    // rows of it that a wave writes out
+  static_assert(NW * SR * ROWB + 2048 <= RING, "staging strips (and a row of column sums per wave) must fit in the ring");
   __syncthreads();                                  // every wave is done with the ring
-  char* strip = ring + wave * (32 * ROWB);
+  char* strip = ring + wave * (SR * ROWB);          // written by this wave
+  const char* strip_rd = SPLIT ? ring + (wmn * WGK) * (SR * ROWB) + wk * RPW * ROWB : strip;   // first of the WGK strips, at this wave's rows
   const bf16* bias = (const bf16*)g.bias;
   const bf16* aux = (const bf16*)g.aux;
   constexpr bool RESID = EPI == EPI_RESID || EPI == EPI_RESID_F32 || EPI == EPI_RESID_F32_OUT16;
@@ -416,7 +548,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
   constexpr bool OUT_F32 = EPI == EPI_F32_ACC || EPI == EPI_F32_SET || EPI == EPI_RESID_F32;
   const bool has_bias = (EPI == EPI_BF16 || EPI == EPI_GELU || RESID) && bias != nullptr;
   constexpr int PPR = WN / 8;                       // 8-column pieces per strip row
-  constexpr int NIT = 32 * PPR / 64;                // pieces per lane per strip
+  constexpr int NIT = RPW * PPR / 64;               // pieces per lane per strip
+  auto strip_piece = [&](int row, int piece) {      // 4 + 4 consecutive columns of a row, the partial sums added up
+    const char* p = strip_rd + row * ROWB + piece * 32;
+    f32x4 lo = *(const f32x4*)p, hi = *(const f32x4*)(p + 16);
+#pragma unroll
+    for (int k = 1; k < WGK; k++) {
+      lo += *(const f32x4*)(p + k * (SR * ROWB));
+      hi += *(const f32x4*)(p + k * (SR * ROWB) + 16);
+    }
+    struct { f32x4 lo, hi; } r = {lo, hi};
+    return r;
+  };
   static_assert(64 % PPR == 0, "a lane keeps its column piece across iterations");
   const int cp = lane % PPR, row0 = lane / PPR;     // piece it*64 + lane -> row row0 + it * (64 / PPR)
   // output column of the lane's piece.  SwiGLU: the first half of the wave's strip row holds GW gate columns, the
@@ -454,8 +597,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
     }
   }
 #pragma unroll
-  for (int tm = 0; tm < TM; tm++) {
-    const int mbase = m0 + wm * WM + tm * 32 + row0;
+  for (int tm = 0; tm < TM; tm += SR / 32) {
+    const int mbase = m0 + wm * WM + tm * 32 + wk * RPW + row0;
     if (EPI == EPI_ROPE && rot) {
       const float* t = g.rope_cs + ((size_t)(mbase % g.rope_S) * (g.rope_d >> 1) + rope_i0) * 2;
 #pragma unroll
@@ -484,20 +627,27 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
       }
     }
 #pragma unroll
-    for (int tn = 0; tn < TN; tn++)
+    for (int tr = 0; tr < SR / 32; tr++)
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        const int col = tn * 32 + 8 * q + 4 * (lane >> 5);
-        f32x4 v = {acc[tm][tn][4 * q], acc[tm][tn][4 * q + 1], acc[tm][tn][4 * q + 2], acc[tm][tn][4 * q + 3]};
-        *(f32x4*)(strip + (lane & 31) * ROWB + col * 4) = v;
-      }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
-    __builtin_amdgcn_wave_barrier();
+      for (int tn = 0; tn < TN; tn++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const int col = tn * 32 + 8 * q + 4 * (lane >> 5);
+          const f32x16& a = acc[tm + tr][tn];
+          f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+          *(f32x4*)(strip + (tr * 32 + (lane & 31)) * ROWB + col * 4) = v;
+        }
+    if constexpr (SPLIT) {
+      __syncthreads();
+    } else {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+      __builtin_amdgcn_wave_barrier();
+    }
 #pragma unroll
     for (int it = 0; it < NIT; it++) {
       const int row = row0 + it * (64 / PPR);
-      const f32x4 lo = *(const f32x4*)(strip + row * ROWB + cp * 32);
-      const f32x4 hi = *(const f32x4*)(strip + row * ROWB + cp * 32 + 16);
+      const auto pc = strip_piece(row, cp);
+      const f32x4 lo = pc.lo, hi = pc.hi;
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       const size_t m = (size_t)(mbase + it * (64 / PPR));
       if (OUT_F32) {
@@ -522,8 +672,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
         if (EPI == EPI_ROPE && rot) {
           // rotary embedding on the fp32 sums: the pair of column c of a head is c +- d/2, d/16 pieces away in the
           // same strip row (a wave's strip holds whole heads: WN % d == 0, checked by the caller)
-          const f32x4 plo = *(const f32x4*)(strip + row * ROWB + rope_pcp * 32);
-          const f32x4 phi = *(const f32x4*)(strip + row * ROWB + rope_pcp * 32 + 16);
+          const auto pp = strip_piece(row, rope_pcp);
+          const f32x4 plo = pp.lo, phi = pp.hi;
           const float pv[8] = {plo[0], plo[1], plo[2], plo[3], phi[0], phi[1], phi[2], phi[3]};
 #pragma unroll
           for (int i = 0; i < 8; i++) {
@@ -570,8 +720,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
         }
         if (SWIGLU && !up_piece) {
           // silu(gate) * up from the fp32 accumulators: the up piece sits PPR / 2 pieces further in the strip row
-          const f32x4 ulo = *(const f32x4*)(strip + row * ROWB + (cp + PPR / 2) * 32);
-          const f32x4 uhi = *(const f32x4*)(strip + row * ROWB + (cp + PPR / 2) * 32 + 16);
+          const auto up8 = strip_piece(row, cp + PPR / 2);
+          const f32x4 ulo = up8.lo, uhi = up8.hi;
           const float up[8] = {ulo[0], ulo[1], ulo[2], ulo[3], uhi[0], uhi[1], uhi[2], uhi[3]};
           bf16x8 o2;
 #pragma unroll
@@ -580,17 +730,36 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
         }
       }
     }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));  // strip reads are in registers before the next 32 rows overwrite it
-    __builtin_amdgcn_wave_barrier();
-    if (EPI == EPI_GELU_BWD && (tm & 1)) {
-      // two strips = one 64-row slab: lanes that share a column piece (lane % PPR) add up, the first PPR lanes write
+    if constexpr (SPLIT) {
+      __syncthreads();                                 // strip reads are in registers before the next 64 rows overwrite it
+    } else {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));  // the same within the wave, whose strip it is
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (EPI == EPI_GELU_BWD && (SPLIT || (tm & 1))) {
+      // one 64-row slab (two strips where a strip has 32 rows): lanes that share a column piece (lane % PPR) add up,
+      // and where waves share the slab's rows, these waves' sums through LDS; the first PPR lanes write
       if (want_colsum) {
 #pragma unroll
         for (int i = 0; i < 8; i++) {
 #pragma unroll
           for (int off = PPR; off < 64; off <<= 1) cs[i] += __shfl_xor(cs[i], off);
         }
-        if (lane < PPR) {
+        if constexpr (SPLIT) {
+          float* row = (float*)(ring + NW * SR * ROWB) + wave * WN;   // behind the strips
+          if (lane < PPR) {
+            *(f32x4*)(row + lane * 8) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+            *(f32x4*)(row + lane * 8 + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
+          }
+          __syncthreads();
+          if (wk == 0 && lane < PPR) {
+#pragma unroll
+            for (int k = 1; k < WGK; k++)
+#pragma unroll
+              for (int i = 0; i < 8; i++) cs[i] += row[k * WN + lane * 8 + i];
+          }
+        }
+        if (wk == 0 && lane < PPR) {
           float* dst = g.colsum_part + (size_t)((m0 + wm * WM + tm * 32) >> 6) * g.ld_colsum + n;
           if (g.colsum_acc) {
             const f32x4 o0 = *(const f32x4*)dst, o1 = *(const f32x4*)(dst + 4);
@@ -617,17 +786,23 @@ bool gemm_segments_ok(int seg_k, int n_seg) {
 
 namespace {
 
-// Tile choice: the 256-CU chip runs one block per CU, so a launch costs
-// ceil(tiles / 256) rounds of one tile's time.  Relative tile costs (per output
-// element) are measured constants: smaller tiles re-read more from LDS and L2
-// (4096 x 6144 x 4096, NN: 384 tiles of 256 x 256 in two rounds take 211 us, 768
-// tiles of 256 x 128 in three rounds 219 us, i.e. 1.35 per element; the weight
-// gradient, whose epilogue moves twice the bytes per tile, loses less: 1.25).
-struct TileCfg { int bm, bn, wgm, wgn; float cost, cost_tn; };
-const TileCfg kTiles[] = {{256, 256, 2, 2, 1.00f, 1.00f}, {256, 128, 2, 2, 1.35f, 1.25f}, {128, 256, 2, 2, 1.35f, 1.25f},
-                          {128, 128, 2, 2, 1.60f, 1.50f}};
+// Tile choice.  The chip's 256 CUs take the tiles of a launch in rounds, one or (where half the LDS suffices) two to
+// a CU; the time of a round is a + b K.  Both are measured, in us with K in units of 1024: 256 and 512 tiles of each
+// kind, K = 256 .. 16384, the weights read from HBM, replayed back to back, so that a includes the gap between
+// launches.  fwd is for the products with a k-contiguous operand (mean of NN and NT), tn for the weight gradient.
+// A round that leaves CUs idle is shorter (the board is limited by power, the caches by what all CUs ask of them):
+// 160 tiles of 256 x 256 take 0.78 and 64 of them 0.70 of the time of 256.
+struct Rate { float a, b; };
+struct TileCfg { int bm, bn, wgm, wgn, wgk; Rate fwd1, fwd2, tn1, tn2; };  // one, two tiles to a CU
+const TileCfg kTiles[] = {
+  {256, 256, 2, 2, 1, {11.5f, 23.1f}, {21.8f, 44.9f}, {16.3f, 23.3f}, {33.5f, 45.4f}},
+  {256, 128, 2, 2, 1, {7.1f, 14.1f}, {10.8f, 28.5f}, {12.3f, 12.7f}, {20.4f, 25.2f}},
+  {128, 256, 2, 2, 1, {7.4f, 13.7f}, {12.1f, 27.4f}, {11.0f, 12.8f}, {20.5f, 25.0f}},
+  {128, 128, 2, 2, 1, {4.4f, 9.0f}, {5.9f, 14.7f}, {8.2f, 8.0f}, {11.0f, 15.3f}},
+  {64, 128, 1, 2, 2, {3.8f, 5.7f}, {4.8f, 10.5f}, {5.6f, 6.0f}, {7.5f, 10.9f}},
+  {64, 64, 1, 1, 4, {3.6f, 3.3f}, {4.3f, 6.8f}, {4.5f, 3.8f}, {5.5f, 7.3f}}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-constexpr int kAutoTiles = 4;  // the automatic choice looks at the first kAutoTiles entries
+constexpr float kLaunchGap = 2.5f;   // the part of a that later rounds of the same launch do not pay
 
 int forced_tile() {
   static int forced = -2;
@@ -638,21 +813,31 @@ int forced_tile() {
   return forced;
 }
 
-// cost of covering an M x n output with tile i, in units of (tile area x relative cost) per round
-float tile_cost(int i, int M, int n, bool tn) {
-  const long tiles = (long)(M / kTiles[i].bm) * (n / kTiles[i].bn);
-  const long rounds = (tiles + 255) / 256;
-  return rounds * (tn ? kTiles[i].cost_tn : kTiles[i].cost) * kTiles[i].bm * kTiles[i].bn;
+bool tile_fits(int i, int M, int n) { return M % kTiles[i].bm == 0 && n % kTiles[i].bn == 0; }
+
+// time of covering an M x n output with tile i
+float tile_cost(int i, int M, int n, int K, bool tn) {
+  const TileCfg& t = kTiles[i];
+  const long tiles = (long)(M / t.bm) * (n / t.bn), full = tiles / 512, rest = tiles % 512;
+  const float k = K / 1024.f;
+  const Rate &r1 = tn ? t.tn1 : t.fwd1, &r2 = tn ? t.tn2 : t.fwd2;
+  float us = full * (r2.a + r2.b * k - kLaunchGap) + kLaunchGap;
+  if (rest > 0) {
+    const Rate& r = rest > 256 ? r2 : r1;
+    const float fill = (float)rest / (rest > 256 ? 512 : 256);
+    us += (r.a + r.b * k) * (0.65f + 0.35f * fill) - kLaunchGap;
+  }
+  return us;
 }
 
-int pick_tile(int M, int N, bool tn) {
+int pick_tile(int M, int N, int K, bool tn) {
   const int forced = forced_tile();
-  if (forced >= 0 && forced < kNumTiles && M % kTiles[forced].bm == 0 && N % kTiles[forced].bn == 0) return forced;
+  if (forced >= 0 && forced < kNumTiles && tile_fits(forced, M, N)) return forced;
   int best = -1;
   float best_t = 0;
-  for (int i = 0; i < kAutoTiles; i++) {
-    if (M % kTiles[i].bm || N % kTiles[i].bn) continue;
-    const float t = tile_cost(i, M, N, tn);
+  for (int i = 0; i < kNumTiles; i++) {
+    if (!tile_fits(i, M, N)) continue;
+    const float t = tile_cost(i, M, N, K, tn);
     if (best < 0 || t < best_t) { best = i; best_t = t; }
   }
   return best;
@@ -660,73 +845,68 @@ int pick_tile(int M, int N, bool tn) {
 
 // How a launch covers its output: with one tile shape, or as two launches over the column ranges [0, n0) and
 // [n0, N), each with its own tile shape.  The second form is for outputs whose tile count is not a good multiple
-// of the 256 CUs: 4096 x 6144 is 384 tiles of 256 x 256, i.e. two rounds of which the second is half empty (2.0
-// units), or 768 tiles of 256 x 128 in three rounds (2.0 .. 1.9); 256 tiles of 256 x 256 over the first 4096
-// columns and then 256 tiles of 256 x 128 over the rest is two full rounds of 1.0 + 0.63 .. 0.68 units.
+// of the 256 CUs: 4096 x 6144 is 384 tiles of 256 x 256, i.e. two rounds of which the second is half empty;
+// 256 tiles of 256 x 256 over the first 4096 columns and then 256 tiles of 256 x 128 over the rest is two full rounds.
 struct Plan { int parts; int tile[2]; int n0; };
-constexpr float kSplitCost = 0.15f * 256 * 256;  // the second launch's gap, prologue and epilogue, in the same units
+constexpr float kSecondLaunch = 2.f;  // us: the first launch's last tiles run alone
 
-Plan make_plan(int M, int N, bool tn) {
-  Plan p = {1, {pick_tile(M, N, tn), -1}, N};
+Plan make_plan(int M, int N, int K, bool tn) {
+  Plan p = {1, {pick_tile(M, N, K, tn), -1}, N};
   if (p.tile[0] < 0 || forced_tile() >= 0 || getenv("AH_GEMM_NOSPLIT")) return p;
-  float best = tile_cost(p.tile[0], M, N, tn);
+  float best = 0.96f * tile_cost(p.tile[0], M, N, K, tn);  // the model's accuracy: a second launch has to promise more
   for (int n0 = 128; n0 < N; n0 += 128)
-    for (int i = 0; i < kAutoTiles; i++) {
-      if (M % kTiles[i].bm || n0 % kTiles[i].bn) continue;
-      for (int j = 0; j < kAutoTiles; j++) {
-        if (j == i || M % kTiles[j].bm || (N - n0) % kTiles[j].bn) continue;
-        const float t = tile_cost(i, M, n0, tn) + tile_cost(j, M, N - n0, tn) + kSplitCost;
+    for (int i = 0; i < kNumTiles; i++) {
+      if (!tile_fits(i, M, n0)) continue;
+      for (int j = 0; j < kNumTiles; j++) {
+        if (j == i || !tile_fits(j, M, N - n0)) continue;
+        const float t = tile_cost(i, M, n0, K, tn) + tile_cost(j, M, N - n0, K, tn) + kSecondLaunch;
         if (t < best) { best = t; p = {2, {i, j}, n0}; }
       }
     }
   return p;
 }
 
-// make_plan is a search over a few thousand candidates: remembered per (M, N, layout class)
-Plan cached_plan(int M, int N, bool tn) {
-  struct Entry { int M, N; bool tn; Plan p; };
+// make_plan is a search over a few thousand candidates: remembered per (M, N, K, layout class)
+Plan cached_plan(int M, int N, int K, bool tn) {
+  struct Entry { int M, N, K; bool tn; Plan p; };
   static std::mutex mu;
   static std::vector<Entry> cache;
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : cache)
-    if (e.M == M && e.N == N && e.tn == tn) return e.p;
-  const Plan p = make_plan(M, N, tn);
-  if (cache.size() < 4096) cache.push_back({M, N, tn, p});
+    if (e.M == M && e.N == N && e.K == K && e.tn == tn) return e.p;
+  const Plan p = make_plan(M, N, K, tn);
+  if (cache.size() < 4096) cache.push_back({M, N, K, tn, p});
   return p;
 }
 
-template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
 hipError_t run(const GemmArgs& a, hipStream_t s) {
   dim3 grid((a.M / BM) * (a.N / BN));
-  hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, AKS, BKS, EPI>), grid, dim3(64 * WGM * WGN), 0, s, a);
+  hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI>), grid, dim3(64 * WGM * WGN * WGK), 0, s, a);
   return hipGetLastError();
 }
 
 template <bool AKS, bool BKS, int EPI>
 hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
   switch (t) {
-    case 0: return run<256, 256, 2, 2, AKS, BKS, EPI>(a, s);
-    case 1: return run<256, 128, 2, 2, AKS, BKS, EPI>(a, s);
-    case 2: return run<128, 256, 2, 2, AKS, BKS, EPI>(a, s);
-    default: return run<128, 128, 2, 2, AKS, BKS, EPI>(a, s);
+    case 0: return run<256, 256, 2, 2, 1, AKS, BKS, EPI>(a, s);
+    case 1: return run<256, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
+    case 2: return run<128, 256, 2, 2, 1, AKS, BKS, EPI>(a, s);
+    case 3: return run<128, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
+    case 4: return run<64, 128, 1, 2, 2, AKS, BKS, EPI>(a, s);
+    default: return run<64, 64, 1, 1, 4, AKS, BKS, EPI>(a, s);
   }
 }
 
 }  // namespace
 
-int gemm_min_wave_cols(int M, int N, GemmLayout layout) {
-  if (!gemm_shape_ok(M, N, 128)) return 0;
-  const Plan p = cached_plan(M, N, layout == GEMM_TN);
+int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout) {
+  if (!gemm_shape_ok(M, N, K)) return 0;
+  const Plan p = cached_plan(M, N, K, layout == GEMM_TN);
   if (p.tile[0] < 0) return 0;
   int w = kTiles[p.tile[0]].bn / kTiles[p.tile[0]].wgn;
   if (p.parts == 2) w = std::min(w, kTiles[p.tile[1]].bn / kTiles[p.tile[1]].wgn);
   return w;
-}
-
-int gemm_tile_area(int M, int N, GemmLayout layout) {
-  if (!gemm_shape_ok(M, N, 128)) return 0;
-  const Plan p = cached_plan(M, N, layout == GEMM_TN);
-  return p.tile[0] < 0 ? 0 : kTiles[p.tile[0]].bm * kTiles[p.tile[0]].bn;
 }
 
 namespace {
@@ -772,7 +952,7 @@ GemmArgs column_range(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, in
     b.B = (const bf16*)a.B + (size_t)c0 * a.ldb;  // B is [N, K]
   } else {
     b.B = (const bf16*)a.B + c0;                  // B is [K, N]
-    for (int i = 0; i < a.n_seg; i++) b.segB[i] = (const bf16*)a.segB[i] + c0;
+    for (int i = 0; i < std::max(a.n_seg, 1); i++) b.segB[i] = (const bf16*)a.segB[i] + c0;
   }
   return b;
 }
@@ -791,8 +971,11 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
       if (!a.segA[i] || !a.segB[i]) return hipErrorInvalidValue;
     a.A = a.segA[0];
     a.B = a.segB[0];
+  } else {
+    a.segA[0] = a.A;
+    a.segB[0] = a.B;
   }
-  const Plan p = cached_plan(a.M, a.N, layout == GEMM_TN);
+  const Plan p = cached_plan(a.M, a.N, a.K, layout == GEMM_TN);
   if (p.tile[0] < 0) return hipErrorInvalidValue;
   if (p.parts == 1) return dispatch(layout, epi, p.tile[0], a, s);
   hipError_t e = dispatch(layout, epi, p.tile[0], column_range(layout, epi, a, 0, p.n0), s);

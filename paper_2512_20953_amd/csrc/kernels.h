@@ -25,7 +25,7 @@ enum GemmEpilogue {
   EPI_SWIGLU_BWD = 9,
   // NN only, no bias: C = acc with the rotary embedding applied to columns [0, rope_cols) on the fp32 sums (heads of
   // rope_d columns, pairs (i, i + rope_d / 2), position = row % rope_S, table rope_cs[pos][i] = (cos, sin)).  Every
-  // tile's wave strip must hold whole heads: gemm_min_wave_cols(M, N) % rope_d == 0.
+  // tile's wave strip must hold whole heads: gemm_min_wave_cols(M, N, K) % rope_d == 0.
   EPI_ROPE = 10
 };
 
@@ -59,8 +59,7 @@ struct GemmArgs {
 // M, N, K multiples of 128, all leading dimensions multiples of 8.
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 bool gemm_shape_ok(int M, int N, int K);
-int gemm_min_wave_cols(int M, int N, GemmLayout layout);  // columns of a wave's sub-tile, the smallest over the launches that cover the output
-int gemm_tile_area(int M, int N, GemmLayout layout);  // rows x columns of the tile launch_gemm would pick for an M x N output
+int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout);  // columns of a wave's sub-tile, the smallest over the launches that cover the output
 bool gemm_segments_ok(int seg_k, int n_seg);  // seg_k a positive multiple of 128, 1 <= n_seg <= kMaxGemmSegments
 
 // ---- attention (d = 64 or 128, S multiple of 128) ----

@@ -122,22 +122,20 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->res32 = c->residual_fp32 != 0;
   s->group = c->wgrad_group > 1 ? c->wgrad_group : 1;
   {
-    // A deferred product runs at the end of its group with a k axis G times as long.  That pays for the outputs
-    // large enough for the 256-wide tiles (fewer fp32 passes over a large matrix, one prologue and epilogue).  A
-    // small output, which gets 128 x 128 tiles that use a CU poorly on their own, is better taken per micro-batch:
-    // the side stream runs it beside the rest of backward, and its read-modify-write is small anyway (measured on
-    // the BERT-Large stage, whose matrices are all of that kind: 26.7 ms per step undeferred, 29.1 deferred).
-    const char* e = getenv("AH_DEFER_MIN_TILE_AREA");  // tuning aid
-    const int min_area = e ? atoi(e) : 256 * 128;
+    // A deferred product runs at the end of its group with a k axis G times as long.  That pays for large outputs
+    // (fewer fp32 passes over a large matrix, one prologue and epilogue).  A small output, one round of 128 x 128 tiles
+    // or less, is better taken per micro-batch: the side stream runs it beside the rest of backward, and its
+    // read-modify-write is small anyway (measured on the BERT-Large stage, whose matrices are all of that kind:
+    // 26.7 ms per step undeferred, 29.1 deferred).
     const int Fu_ = (c->arch == AH_ARCH_LLAMA ? 2 : 1) * s->F;
     const int mn[4][2] = {{s->F, s->h}, {s->h, Fu_}, {s->hl, s->h}, {s->h, 3 * s->hl}};  // WG_FC2, WG_FC1, WG_WO, WG_QKV
-    for (int i = 0; i < 4; i++) s->defer_matrix[i] = gemm_tile_area(mn[i][0], mn[i][1], GEMM_TN) >= min_area;
+    for (int i = 0; i < 4; i++) s->defer_matrix[i] = (long)(mn[i][0] / 128) * (mn[i][1] / 128) > 256;
     // tuning and test aid: the choice given outright, bit i = matrix i (second MLP, first MLP, out-projection, QKV)
     if (const char* m = getenv("AH_DEFER_MATRICES"))
       for (int i = 0; i < 4; i++) s->defer_matrix[i] = (atoi(m) >> i) & 1;
   }
   {
-    const int wc = gemm_min_wave_cols(s->T, 3 * s->hl, GEMM_NN);
+    const int wc = gemm_min_wave_cols(s->T, 3 * s->hl, s->h, GEMM_NN);
     s->rope_in_gemm = s->llama && wc > 0 && wc % s->d == 0 && !getenv("AH_ROPE_KERNEL");  // the variable: tuning aid
   }
   s->eps = c->norm_eps > 0 ? c->norm_eps : (s->llama ? 1e-6f : 1e-5f);

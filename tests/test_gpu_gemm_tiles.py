@@ -1,0 +1,53 @@
+"""GEMM entry points at the sizes where a tile shape begins, ends or leaves a remainder, against float64 products.
+
+The launcher picks the tile by the output and k extents; the cases below reach every tile shape (64 x 64 and 64 x 128
+with the k axis split between waves, 128 x 128, the 256-wide ones), tile counts that are no multiple of the 8 XCDs,
+and k extents from one ring fill less (k = 128 is two k-blocks, the ring holds three to five) to several.
+
+Tolerance: a bf16 output is the fp32 sum rounded once, 2^-9 of its value at most (2^-8 between neighbouring values);
+an fp32 sum of k products of N(0,1) values in any order is within 1e-6 sqrt(k) max|ref| here."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_20953_amd as P
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(128, 128, 128), (128, 384, 256), (384, 640, 384), (256, 256, 1024), (640, 1152, 640), (1024, 1024, 512), (896, 1152, 384),
+          (1024, 2048, 128), (2048, 1024, 640), (1920, 1664, 256), (2048, 2048, 256), (1152, 4352, 128), (4096, 4096, 128)]
+
+
+def _close(got, ref, k, bf16):
+    tol = (2.0 ** -8) * ref.abs() * (1 if bf16 else 0) + 1e-6 * np.sqrt(k) * ref.abs().max()
+    bad = (got.double() - ref).abs() > tol
+    assert not bad.any(), "%d elements off, first at %s" % (int(bad.sum()), bad.nonzero()[0].tolist())
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_gemm_tiles(M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    A, B, bias = rnd(M, K), rnd(K, N), rnd(N)
+    ref = A.double() @ B.double()
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    P.gemm_nn(A, B, bias, C)
+    _close(C, ref + bias.double(), K, True)
+    C.fill_(float("nan"))
+    P.gemm_nt(A, B.t().contiguous(), C)
+    _close(C, ref, K, True)
+    D0 = torch.randn(M, N, generator=g, device="cuda")
+    D = D0.clone()
+    P.gemm_tn(A.t().contiguous(), B, D, 1)
+    _close(D, ref + D0.double(), K, False)
+    half = K // 256 * 128
+    if half:                                        # the k axis in two buffers of equal length
+        At, Bh = A.t().contiguous()[:2 * half], B[:2 * half]
+        P.gemm_tn_segmented([At[:half].clone(), At[half:].clone()], [Bh[:half].clone(), Bh[half:].clone()], D, 0)
+        _close(D, At.double().t().contiguous() @ Bh.double(), K, False)
+    if N % 256 == 0:                                # gate | up halves paired inside a tile
+        U = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+        Mo = torch.empty(M, N // 2, dtype=torch.bfloat16, device="cuda")
+        P.gemm_nn_swiglu(A, B, U, Mo)
+        _close(U, ref, K, True)
+        _close(Mo, torch.nn.functional.silu(ref[:, :N // 2]) * ref[:, N // 2:], K, True)
