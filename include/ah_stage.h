@@ -175,7 +175,7 @@ int ah_stage_forward(ah_stage_t* st, int slot, const void* x, void* y, void* hip
  * brought up to date when the G-th micro-batch of the group has had its
  * backward (that call takes the group's gradients and frees all G slots) or
  * at ah_stage_flush_grads; in between it may hold any mixture of old and new
- * sums (small matrices are still added per micro-batch). */
+ * sums. */
 int ah_stage_backward(ah_stage_t* st, int slot, const void* dy, void* dx, void* hip_stream);
 
 /* Closes an incomplete group of the gradient accumulation over micro-batches (Section III-A; see wgrad_group).

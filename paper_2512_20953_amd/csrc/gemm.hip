@@ -298,10 +298,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   // block -> tile: consecutive logical tiles share an XCD (blocks are dealt to the
   // 8 XCDs round-robin), and run down groups of 8 tile-rows so that the tiles in
   // flight on one XCD reuse the same operand panels in its L2.
-  const int tiles_m = g.M / BM, tiles_n = g.N / BN, ntiles = tiles_m * tiles_n;
+  // With the k axis shared by blocks (kernels.h) the shares follow each other: an XCD then works on one share's operands.
+  constexpr bool KSHARES = AKS && BKS && EPI == EPI_F32_SET;
+  const int shares = KSHARES ? g.k_shares : 1;
+  const int tiles_m = g.M / BM, tiles_n = g.N / BN, out_tiles = tiles_m * tiles_n, ntiles = out_tiles * shares;
   // (Where the count is not a multiple of 8 the first ntiles % 8 XCDs take one tile more.)
   int logical = blockIdx.x;
   if (g.xcd_remap) logical = (blockIdx.x & 7) * (ntiles >> 3) + min((int)(blockIdx.x & 7), ntiles & 7) + (blockIdx.x >> 3);
+  const int share = KSHARES ? logical / out_tiles : 0;
+  if (KSHARES) logical -= share * out_tiles;
   const int GROUP = g.group;
   const int per_group = GROUP * tiles_n;
   const int gid = logical / per_group;
@@ -313,6 +318,16 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 
   const char* gA = (const char*)((const bf16*)g.A + (AKS ? (size_t)m0 : (size_t)m0 * g.lda));
   const char* gB = (const char*)((const bf16*)g.B + (BKS ? (size_t)(SWIGLU ? n0 / 2 : n0) : (size_t)n0 * g.ldb));
+  // The block's part of the k axis: all of it, or share `share`, a whole number of its pieces (of its k-blocks where
+  // it is one piece).
+  const int kext = KSHARES ? g.K / shares : g.K;
+  const int pieces = (AKS && BKS) ? (KSHARES && g.n_seg > 1 ? g.n_seg / shares : max(g.n_seg, 1)) : 1;
+  const int piece0 = KSHARES && g.n_seg > 1 ? share * pieces : 0;
+  if constexpr (KSHARES) {
+    const size_t k0 = g.n_seg > 1 ? 0 : (size_t)share * kext;
+    gA = (const char*)((const bf16*)g.segA[piece0] + m0 + k0 * g.lda);
+    gB = (const char*)((const bf16*)g.segB[piece0] + n0 + k0 * g.ldb);
+  }
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; i++)
@@ -336,15 +351,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     // the number of loads in flight uniform for the counted wait.  Weight gradients may have their k axis in pieces
     // (kernels.h): at the end of a piece the cursor moves to the next piece's base.
     constexpr bool PIECES = AKS && BKS;
-    const int nk = g.K / BK;
-    const int nseg = (PIECES && g.n_seg > 0) ? g.n_seg : 1, seg_stages = nk / nseg;
+    const int nk = kext / BK;
+    const int nseg = pieces, seg_stages = nk / nseg;
     const char *pA = gA, *pB = gB;
     int fetched = 1, left = seg_stages, piece = 0;
     const char *nextA = gA, *nextB = gB;   // where the next piece starts (segA[0], segB[0] are set for one piece too)
     auto next_piece = [&]() {
       const int nx = min(piece + 1, nseg - 1);
-      nextA = (const char*)((const bf16*)g.segA[nx] + m0);
-      nextB = (const char*)((const bf16*)g.segB[nx] + n0);
+      nextA = (const char*)((const bf16*)g.segA[piece0 + nx] + m0);
+      nextB = (const char*)((const bf16*)g.segB[piece0 + nx] + n0);
     };
     if constexpr (PIECES) next_piece();
     auto advance = [&]() {
@@ -417,13 +432,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < BN / 16 / NW; i++) offB[i] = loader_src_offset<BK, BN, BKS>(wave + NW * i, lane, g.ldb, GW, g.swiglu_F);
     // nk is a multiple of 4 (K is a multiple of 128).  Stage t lives in ring slot t % 4.
-    const int nk = g.K / BK;
+    const int nk = kext / BK;
     // The k axis may be cut into pieces that live in different buffers (kernels.h): the outer loop runs over the
     // pieces, the inner one over the stages of a piece (a multiple of 4).  The stage fetched during local step t
     // is local stage t + 3; past the end of the piece that is a stage of the next piece, past the end of the last
     // piece the last stage again (fetched into a dead slot, which keeps the in-flight load count uniform).  The
     // choice is a scalar select, so the inner loop stays one basic block.
-    const int nseg = g.n_seg > 0 ? g.n_seg : 1;
+    const int nseg = pieces;
     const int seg_stages = nk / nseg;
     issue_tile_loads<BK, BM, NW>(gA, offA, sA0, wave);
     issue_tile_loads<BK, BN, NW>(gB, offB, sB0, wave);
@@ -439,8 +454,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     const char *curA = gA, *curB = gB;
     for (int sg = 0; sg < nseg; sg++) {
       const bool last_piece = sg + 1 == nseg;
-      const char* nxtA = last_piece ? curA : (const char*)((const bf16*)g.segA[sg + 1] + m0);
-      const char* nxtB = last_piece ? curB : (const char*)((const bf16*)g.segB[sg + 1] + n0);
+      const char* nxtA = last_piece ? curA : (const char*)((const bf16*)g.segA[piece0 + sg + 1] + m0);
+      const char* nxtB = last_piece ? curB : (const char*)((const bf16*)g.segB[piece0 + sg + 1] + n0);
       const int lim = last_piece ? seg_stages - 1 : seg_stages + 2;
 #define AH_STAGE_PTRS(u)                                                                                              \
   (min((u), lim) >= seg_stages ? nxtA + (size_t)(min((u), lim) - seg_stages) * stepA : curA + (size_t)min((u), lim) * stepA), \
@@ -478,13 +493,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     uint32_t* offF = BF ? offB : offA;
     uint32_t* offS = BF ? offA : offB;
     const int np = g.K / BK, lastp = np - 1;
-    // In the weight-gradient layout the k axis may be cut into pieces that live in different buffers (kernels.h):
-    // the outer loop runs over the pieces (one piece for the other layouts), the inner one over the k-blocks of a
-    // piece (an even number).  During local k-block j the tiles S_{j+1} and F_{j+2} are fetched; past the end of
-    // the piece those belong to the next piece, past the end of the last piece the last k-block is fetched again.
-    constexpr bool PIECES = AKS && BKS;
-    const int nseg = (PIECES && g.n_seg > 0) ? g.n_seg : 1;
-    const int seg_blocks = np / nseg;
+    // During k-block j the tiles S_{j+1} and F_{j+2} are fetched.
     issue_tile_loads<BK, WF, NW>(gF, offF, ring, wave);                                            // F_0 -> buffer 0
     issue_tile_loads<BK, WS, NW>(gS, offS, ring + BUF, wave);                                      // S_0 -> buffer 1
     issue_tile_loads<BK, WF, NW>(gF + (size_t)min(1, lastp) * stepF, offF, ring + 2 * BUF, wave);  // F_1 -> buffer 2
@@ -494,35 +503,20 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     Frags<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
     f0.load(ring + (BF ? BUF : 0), ring + (BF ? 0 : BUF), 0, wm, wn, lane);
     int jf = 0, js = 1;  // buffers of F_j and S_j
-    const char *curF = gF, *curS = gS;
-    for (int sg = 0; sg < nseg; sg++) {
-      const bool last_piece = sg + 1 == nseg;
-      const char *nxtF = curF, *nxtS = curS;
-      if constexpr (PIECES) {
-        if (!last_piece) {
-          nxtF = (const char*)((const bf16*)(BF ? g.segB[sg + 1] : g.segA[sg + 1]) + (BF ? n0 : m0));
-          nxtS = (const char*)((const bf16*)(BF ? g.segA[sg + 1] : g.segB[sg + 1]) + (BF ? m0 : n0));
-        }
-      }
-      const int lim = last_piece ? seg_blocks - 1 : seg_blocks + 1;
-      for (int j = 0; j < seg_blocks; j++) {
-        const int nf = jf + 2 >= NB ? jf + 2 - NB : jf + 2;  // F_{j+1}
-        const int ns = js + 2 >= NB ? js + 2 - NB : js + 2;  // S_{j+1}: loaded now, into the buffer of F_{j-1}
-        const int ff = jf + 4 >= NB ? jf + 4 - NB : jf + 4;  // F_{j+2}: into the buffer of S_{j-1}
-        const char* cA = ring + (BF ? js : jf) * BUF;
-        const char* cB = ring + (BF ? jf : js) * BUF;
-        const char* nA = ring + (BF ? ns : nf) * BUF;
-        const char* nB = ring + (BF ? nf : ns) * BUF;
-        const int us = min(j + 1, lim), uf = min(j + 2, lim);
-        const char* pS = (PIECES && us >= seg_blocks) ? nxtS + (size_t)(us - seg_blocks) * stepS : curS + (size_t)us * stepS;
-        const char* pF = (PIECES && uf >= seg_blocks) ? nxtF + (size_t)(uf - seg_blocks) * stepF : curF + (size_t)uf * stepF;
-        half_even<BM, BN, WGM, WGN, AKS, BKS>(pS, offS, ring + ns * BUF, cA, cB, f0, f1, acc, wave, wm, wn, lane);
-        half_odd<BM, BN, WGM, WGN, AKS, BKS>(pF, offF, ring + ff * BUF, cA, cB, nA, nB, f0, f1, acc, wave, wm, wn, lane);
-        jf = nf;
-        js = ns;
-      }
-      curF = nxtF;
-      curS = nxtS;
+    for (int j = 0; j < np; j++) {
+      const int nf = jf + 2 >= NB ? jf + 2 - NB : jf + 2;  // F_{j+1}
+      const int ns = js + 2 >= NB ? js + 2 - NB : js + 2;  // S_{j+1}: loaded now, into the buffer of F_{j-1}
+      const int ff = jf + 4 >= NB ? jf + 4 - NB : jf + 4;  // F_{j+2}: into the buffer of S_{j-1}
+      const char* cA = ring + (BF ? js : jf) * BUF;
+      const char* cB = ring + (BF ? jf : js) * BUF;
+      const char* nA = ring + (BF ? ns : nf) * BUF;
+      const char* nB = ring + (BF ? nf : ns) * BUF;
+      const char* pS = gS + (size_t)min(j + 1, lastp) * stepS;
+      const char* pF = gF + (size_t)min(j + 2, lastp) * stepF;
+      half_even<BM, BN, WGM, WGN, AKS, BKS>(pS, offS, ring + ns * BUF, cA, cB, f0, f1, acc, wave, wm, wn, lane);
+      half_odd<BM, BN, WGM, WGN, AKS, BKS>(pF, offF, ring + ff * BUF, cA, cB, nA, nB, f0, f1, acc, wave, wm, wn, lane);
+      jf = nf;
+      js = ns;
     }
   }
   __builtin_amdgcn_s_waitcnt(0);  // drain the redundant tail loads before the block's LDS is released
@@ -541,6 +535,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   __syncthreads();                                  // every wave is done with the ring
   char* strip = ring + wave * (SR * ROWB);          // written by this wave
   const char* strip_rd = SPLIT ? ring + (wmn * WGK) * (SR * ROWB) + wk * RPW * ROWB : strip;   // first of the WGK strips, at this wave's rows
+  float* const Cf = KSHARES && shares > 1 ? g.k_part + (size_t)share * g.M * g.N : (float*)g.C;   // fp32 outputs
+  const int ldcf = KSHARES && shares > 1 ? g.N : g.ldc;
   const bf16* bias = (const bf16*)g.bias;
   const bf16* aux = (const bf16*)g.aux;
   constexpr bool RESID = EPI == EPI_RESID || EPI == EPI_RESID_F32 || EPI == EPI_RESID_F32_OUT16;
@@ -651,7 +647,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       const size_t m = (size_t)(mbase + it * (64 / PPR));
       if (OUT_F32) {
-        float* cptr = (float*)g.C + m * g.ldc + n;
+        float* cptr = Cf + m * ldcf + n;
         if (EPI == EPI_F32_ACC || EPI == EPI_RESID_F32) {
           if (EPI == EPI_RESID_F32) {
 #pragma unroll
@@ -776,6 +772,19 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   }
 }
 
+// C[m, n] = beta C[m, n] + sum over the k shares of part[share][m, n], in the order of the shares.  Bound by memory:
+// every partial sum is read once; four columns per lane.
+__global__ __launch_bounds__(256) void k_shares_kernel(const float* __restrict__ part, float* __restrict__ C, int M, int N, int ldc, int shares, int beta) {
+  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4, n = (size_t)M * N;
+  if (i >= n) return;
+  float* c = C + (i / N) * ldc + i % N;
+  f32x4 s = *(const f32x4*)(part + i);
+#pragma unroll 4
+  for (int k = 1; k < shares; k++) s += *(const f32x4*)(part + (size_t)k * n + i);
+  if (beta) s += *(const f32x4*)c;
+  *(f32x4*)c = s;
+}
+
 bool gemm_shape_ok(int M, int N, int K) {
   return M > 0 && N > 0 && K > 0 && (M % 128) == 0 && (N % 128) == 0 && (K % 128) == 0;
 }
@@ -815,11 +824,11 @@ int forced_tile() {
 
 bool tile_fits(int i, int M, int n) { return M % kTiles[i].bm == 0 && n % kTiles[i].bn == 0; }
 
-// time of covering an M x n output with tile i
-float tile_cost(int i, int M, int n, int K, bool tn) {
+// time of covering an M x n output with tile i, the k axis cut into `shares` that run side by side
+float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
   const TileCfg& t = kTiles[i];
-  const long tiles = (long)(M / t.bm) * (n / t.bn), full = tiles / 512, rest = tiles % 512;
-  const float k = K / 1024.f;
+  const long tiles = (long)(M / t.bm) * (n / t.bn) * shares, full = tiles / 512, rest = tiles % 512;
+  const float k = K / 1024.f / shares;
   const Rate &r1 = tn ? t.tn1 : t.fwd1, &r2 = tn ? t.tn2 : t.fwd2;
   float us = full * (r2.a + r2.b * k - kLaunchGap) + kLaunchGap;
   if (rest > 0) {
@@ -847,41 +856,55 @@ int pick_tile(int M, int N, int K, bool tn) {
 // [n0, N), each with its own tile shape.  The second form is for outputs whose tile count is not a good multiple
 // of the 256 CUs: 4096 x 6144 is 384 tiles of 256 x 256, i.e. two rounds of which the second is half empty;
 // 256 tiles of 256 x 256 over the first 4096 columns and then 256 tiles of 256 x 128 over the rest is two full rounds.
-struct Plan { int parts; int tile[2]; int n0; };
+struct Plan { int parts; int tile[2]; int n0; int shares; };
 constexpr float kSecondLaunch = 2.f;  // us: the first launch's last tiles run alone
 
-Plan make_plan(int M, int N, int K, bool tn) {
-  Plan p = {1, {pick_tile(M, N, K, tn), -1}, N};
+// A weight gradient over many tokens with a small output (fewer tiles than CUs) may cut its k axis into shares, each a
+// launch's worth of tiles of its own, whose sums a second kernel adds up: 1024 x 4096 over 32768 tokens is 64 tiles of
+// 256 x 256 in four shares and 64 MB of partial sums instead of 256 tiles of 128 x 128 at 1.3 times the cost per flop.
+constexpr int kMaxShares = 16;
+float shares_cost(int M, int N, int shares) { return 4.f + (float)M * N * 4.f * (shares + 2) / 4.5e6f; }  // launch, and 4.5 TB/s
+
+Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats) {
+  Plan p = {1, {pick_tile(M, N, K, tn), -1}, N, 1};
   if (p.tile[0] < 0 || forced_tile() >= 0 || getenv("AH_GEMM_NOSPLIT")) return p;
   float best = 0.96f * tile_cost(p.tile[0], M, N, K, tn);  // the model's accuracy: a second launch has to promise more
+  for (int s = 2; tn && s <= kMaxShares && (size_t)M * N * s <= part_floats; s++) {
+    if (n_seg > 1 ? n_seg % s : K % (128 * s)) continue;
+    for (int i = 0; i < kNumTiles; i++) {
+      if (!tile_fits(i, M, N)) continue;
+      const float t = tile_cost(i, M, N, K, tn, s) + shares_cost(M, N, s);
+      if (t < best) { best = t; p = {1, {i, -1}, N, s}; }
+    }
+  }
   for (int n0 = 128; n0 < N; n0 += 128)
     for (int i = 0; i < kNumTiles; i++) {
       if (!tile_fits(i, M, n0)) continue;
       for (int j = 0; j < kNumTiles; j++) {
         if (j == i || !tile_fits(j, M, N - n0)) continue;
         const float t = tile_cost(i, M, n0, K, tn) + tile_cost(j, M, N - n0, K, tn) + kSecondLaunch;
-        if (t < best) { best = t; p = {2, {i, j}, n0}; }
+        if (t < best) { best = t; p = {2, {i, j}, n0, 1}; }
       }
     }
   return p;
 }
 
-// make_plan is a search over a few thousand candidates: remembered per (M, N, K, layout class)
-Plan cached_plan(int M, int N, int K, bool tn) {
-  struct Entry { int M, N, K; bool tn; Plan p; };
+// make_plan is a search over a few thousand candidates: remembered per problem
+Plan cached_plan(int M, int N, int K, bool tn, int n_seg = 1, size_t part_floats = 0) {
+  struct Entry { int M, N, K; bool tn; int n_seg; size_t part_floats; Plan p; };
   static std::mutex mu;
   static std::vector<Entry> cache;
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : cache)
-    if (e.M == M && e.N == N && e.K == K && e.tn == tn) return e.p;
-  const Plan p = make_plan(M, N, K, tn);
-  if (cache.size() < 4096) cache.push_back({M, N, K, tn, p});
+    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.n_seg == n_seg && e.part_floats == part_floats) return e.p;
+  const Plan p = make_plan(M, N, K, tn, n_seg, part_floats);
+  if (cache.size() < 4096) cache.push_back({M, N, K, tn, n_seg, part_floats, p});
   return p;
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
 hipError_t run(const GemmArgs& a, hipStream_t s) {
-  dim3 grid((a.M / BM) * (a.N / BN));
+  dim3 grid((a.M / BM) * (a.N / BN) * (AKS && BKS && EPI == EPI_F32_SET ? a.k_shares : 1));
   hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI>), grid, dim3(64 * WGM * WGN * WGK), 0, s, a);
   return hipGetLastError();
 }
@@ -907,6 +930,12 @@ int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout) {
   int w = kTiles[p.tile[0]].bn / kTiles[p.tile[0]].wgn;
   if (p.parts == 2) w = std::min(w, kTiles[p.tile[1]].bn / kTiles[p.tile[1]].wgn);
   return w;
+}
+
+size_t gemm_k_part_floats(int M, int N, int K, int n_seg) {
+  if (!gemm_shape_ok(M, N, K)) return 0;
+  const Plan p = cached_plan(M, N, K, true, n_seg, (size_t)M * N * kMaxShares);
+  return p.shares > 1 ? (size_t)M * N * p.shares : 0;
 }
 
 namespace {
@@ -975,8 +1004,20 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
     a.segA[0] = a.A;
     a.segB[0] = a.B;
   }
-  const Plan p = cached_plan(a.M, a.N, a.K, layout == GEMM_TN);
+  a.k_shares = 1;
+  const bool tn = layout == GEMM_TN;
+  const Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0);
   if (p.tile[0] < 0) return hipErrorInvalidValue;
+  if (p.shares > 1) {
+    GemmArgs b = a;
+    b.k_shares = p.shares;
+    b.beta = 0;
+    hipError_t e = dispatch(layout, epi, p.tile[0], b, s);
+    if (e != hipSuccess) return e;
+    const size_t n4 = (size_t)a.M * a.N / 4;
+    hipLaunchKernelGGL(k_shares_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a.k_part, (float*)a.C, a.M, a.N, a.ldc, p.shares, a.beta);
+    return hipGetLastError();
+  }
   if (p.parts == 1) return dispatch(layout, epi, p.tile[0], a, s);
   hipError_t e = dispatch(layout, epi, p.tile[0], column_range(layout, epi, a, 0, p.n0), s);
   if (e != hipSuccess) return e;

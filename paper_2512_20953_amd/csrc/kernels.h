@@ -48,6 +48,11 @@ struct GemmArgs {
   // TN only: the k axis may be the concatenation of n_seg pieces of seg_k rows each (K = n_seg * seg_k), piece i
   // of A starting at segA[i] and of B at segB[i] (same leading dimensions).  n_seg == 0: one piece, A and B.
   int seg_k, n_seg;
+  // TN only, optional: room for partial sums, with which launch_gemm may cut the k axis into k_shares parts (each a
+  // whole number of pieces) that run side by side; their sums are added up by a second kernel.
+  float* k_part;
+  size_t k_part_floats;
+  int k_shares;        // set by launch_gemm
   // EPI_GELU_BWD only, optional: column sums of the (bf16-rounded) output over each slab of 64 rows are written
   // to colsum_part[m / 64][n] (leading dimension ld_colsum), for the bias gradient.  Needs M % 64 == 0 (it is).
   float* colsum_part;
@@ -60,6 +65,7 @@ struct GemmArgs {
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 bool gemm_shape_ok(int M, int N, int K);
 int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout);  // columns of a wave's sub-tile, the smallest over the launches that cover the output
+size_t gemm_k_part_floats(int M, int N, int K, int n_seg);  // what k_part should hold for a weight gradient over n_seg pieces (0: it would not be used)
 bool gemm_segments_ok(int seg_k, int n_seg);  // seg_k a positive multiple of 128, 1 <= n_seg <= kMaxGemmSegments
 
 // ---- attention (d = 64 or 128, S multiple of 128) ----

@@ -7,6 +7,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -29,7 +30,7 @@ struct ActLayout {
 };
 
 struct Workspace {
-  size_t d0, d1, dmid, dbig, dsm, delta, part_n2, part_n1, part_b1, part_bqkv, rope, prof_x, prof_dy, prof_y, prof_dx, layer_ws, pend, vec_part, bytes;
+  size_t d0, d1, dmid, dbig, dsm, delta, part_n2, part_n1, part_b1, part_bqkv, rope, prof_x, prof_dy, prof_y, prof_dx, layer_ws, pend, vec_part, k_part, bytes;
 };
 
 // Output-gradient operands of one layer's four weight-gradient products, kept per (position in the group, layer)
@@ -59,7 +60,8 @@ struct ah_stage {
   // Deferred weight gradients: with group > 1 the four weight-gradient products of a layer run once per `group`
   // micro-batches, over the concatenation of their tokens, instead of once per micro-batch.
   int group;
-  bool defer_matrix[4];         // by WgradWhich: small outputs stay undeferred (see plan())
+  bool defer_matrix[4];         // by WgradWhich (see plan())
+  size_t k_part_floats;
   bool force_immediate;         // the profiler's per-layer timing runs undeferred
   PendLayout pend;
   VecPartLayout vpart;
@@ -107,6 +109,12 @@ int validate(const ah_stage_config_t* c) {
   return AH_OK;
 }
 
+// rows and columns of the four weight gradients, in the order of WgradWhich
+std::array<std::array<int, 2>, 4> wgrad_shapes(const ah_stage* s) {
+  const int Fu = (s->llama ? 2 : 1) * s->F;
+  return {{{s->F, s->h}, {s->h, Fu}, {s->hl, s->h}, {s->h, 3 * s->hl}}};
+}
+
 void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->cfg = *c;
   s->L = c->n_layers;
@@ -122,14 +130,9 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->res32 = c->residual_fp32 != 0;
   s->group = c->wgrad_group > 1 ? c->wgrad_group : 1;
   {
-    // A deferred product runs at the end of its group with a k axis G times as long.  That pays for large outputs
-    // (fewer fp32 passes over a large matrix, one prologue and epilogue).  A small output, one round of 128 x 128 tiles
-    // or less, is better taken per micro-batch: the side stream runs it beside the rest of backward, and its
-    // read-modify-write is small anyway (measured on the BERT-Large stage, whose matrices are all of that kind:
-    // 26.7 ms per step undeferred, 29.1 deferred).
-    const int Fu_ = (c->arch == AH_ARCH_LLAMA ? 2 : 1) * s->F;
-    const int mn[4][2] = {{s->F, s->h}, {s->h, Fu_}, {s->hl, s->h}, {s->h, 3 * s->hl}};  // WG_FC2, WG_FC1, WG_WO, WG_QKV
-    for (int i = 0; i < 4; i++) s->defer_matrix[i] = (long)(mn[i][0] / 128) * (mn[i][1] / 128) > 256;
+    // A deferred product runs at the end of its group with a k axis G times as long: fewer fp32 passes over the matrix,
+    // one prologue and epilogue, and for a small output enough k for shares that fill the chip.
+    for (bool& m : s->defer_matrix) m = true;
     // tuning and test aid: the choice given outright, bit i = matrix i (second MLP, first MLP, out-projection, QKV)
     if (const char* m = getenv("AH_DEFER_MATRICES"))
       for (int i = 0; i < 4; i++) s->defer_matrix[i] = (atoi(m) >> i) & 1;
@@ -220,6 +223,12 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->vpart.bytes = o;
   o = before_vec;
   w.vec_part = take(s->group > 1 ? (size_t)s->L * s->vpart.bytes : 0);
+  // partial sums of a deferred product whose k axis is shared by blocks: one product at a time uses them
+  s->k_part_floats = 0;
+  if (s->group > 1)
+    for (const auto& mn : wgrad_shapes(s))
+      s->k_part_floats = std::max(s->k_part_floats, gemm_k_part_floats(mn[0], mn[1], s->T * s->group, s->group));
+  w.k_part = take(s->k_part_floats * 4);
   w.bytes = o;
 }
 
@@ -397,6 +406,7 @@ hipError_t wgrad(ah_stage* s, int site, int layer, WgradWhich which, const Wgrad
   g.lda = M; g.ldb = N; g.ldc = N; g.M = M; g.N = N; g.K = s->T; g.beta = now ? wp.beta_now : wp.beta;
   if (!now) {
     g.seg_k = s->T; g.n_seg = wp.nseg; g.K = s->T * wp.nseg;
+    if (s->k_part_floats) { g.k_part = (float*)P(s->bufs.workspace, s->ws.k_part); g.k_part_floats = s->k_part_floats; }
     for (int i = 0; i < wp.nseg; i++) {
       const ActPtrs a = act_ptrs(s, wp.slots[i], layer);
       char* dy;

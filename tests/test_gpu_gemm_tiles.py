@@ -51,3 +51,34 @@ def test_gemm_tiles(M, N, K):
         P.gemm_nn_swiglu(A, B, U, Mo)
         _close(U, ref, K, True)
         _close(Mo, torch.nn.functional.silu(ref[:, :N // 2]) * ref[:, N // 2:], K, True)
+
+
+@pytest.mark.parametrize("arch,n_mb", [("gpt", 8), ("gpt", 11), ("llama", 7)])
+def test_group_products_with_the_k_axis_shared_by_blocks(arch, n_mb):
+    """Weight gradients of a narrow stage over groups of 8 micro-batches x 2048 tokens: 12 .. 64 tiles of 64 x 64, so
+    the k axis is cut into shares of whole micro-batches (8, 4 or 2; an incomplete group of 3 or 7 into 3 or 7).
+    Against the sums taken per micro-batch: the same up to the order of fp32 additions, y and dx bit for bit."""
+    grads, outs = [], []
+    for group in (1, 8):
+        cfg = P.StageConfig.make(arch=arch, n_layers=2, hidden=256, n_heads=4, head_dim=64, ffn=512, seq=512, mb=4, n_mb=n_mb,
+                                 max_in_flight=group, wgrad_group=group)
+        st = P.Stage(cfg)
+        g = torch.Generator(device="cuda").manual_seed(5)
+        st.params.copy_(torch.randn(st.params.shape, generator=g, device="cuda") * 0.05)
+        for repeat in range(2):                     # the second iteration adds to nothing of the first
+            st.zero_grads()
+            g.manual_seed(6)
+            ys = []
+            for m in range(n_mb):
+                x, dy = (torch.randn(2048, 256, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+                y, dx = torch.empty_like(x), torch.empty_like(x)
+                st.forward(m % group, x, y)
+                st.backward(m % group, dy, dx)
+                ys += [y, dx]
+            st.flush_grads()
+        torch.cuda.synchronize()
+        grads.append([st.grad_view(l, n).clone() for l in range(2) for n in ("wqkv", "wo", "w1", "w2")])
+        outs.append(ys)
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    for a, b in zip(*grads):
+        assert ((a - b).double().norm() / a.double().norm()).item() <= 2e-6
