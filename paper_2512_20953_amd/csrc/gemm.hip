@@ -236,12 +236,20 @@ __device__ __forceinline__ void ring_step(const char* gA, const char* gB, uint32
 namespace ksplit {
 // The pipeline of the tiles whose waves share a sub-tile and split the k axis: of the four k-steps of a 64-wide
 // k-block, wave wk takes 4 / WGK.  The partial sums meet in the epilogue's staging strips.
-// Two tiles use it, 64 x 64 with four shares and 64 x 128 with two, for outputs of fewer than 256 tiles of 128 x 128.
-// Such a launch lasts as long as one block's chain of k-blocks; these have four (two) times the blocks, and a chain
-// a quarter as long.  256 x 256 x 1024: 9.3 -> 5.5 us, 1024 x 1024 x 2048: 21.6 -> 8.8, 2048 x 1024 x 2048: 21.6 -> 13.2 (NT).
+//  64 x 64 with four shares and 64 x 128 with two are for outputs of fewer than 256 tiles of 128 x 128.  Such a launch
+//    lasts as long as one block's chain of k-blocks; these have four (two) times the blocks, and a chain a quarter as
+//    long.  256 x 256 x 1024: 9.3 -> 5.5 us, 1024 x 1024 x 2048: 21.6 -> 8.8, 2048 x 1024 x 2048: 21.6 -> 13.2 (NT).
+//  128 x 128 with four shares: every wave owns the whole tile, so a k-block costs 32 KB of fragment reads instead of
+//    the 64 KB of four 64 x 64 sub-tiles.  Beside 512 clocks of MFMA the CU's path to and from the LDS was busy ~950
+//    (reads at 128 B per clock, the 32 KB fill at 1.7 times its bytes), now ~690; what bounds it then is the rate at
+//    which the loads arrive (64 B per clock and CU).  2048 x 2048 x 8192: 76 -> 61 us (NT).  The epilogue moves four
+//    times the partial sums (3 us): at k = 2048 the two are level, and where two blocks of the 64 x 64 sub-tiles share
+//    a CU (more than 256 tiles) those are faster; in the weight gradient, whose transposing reads are half as long,
+//    there is no gain (67 against 67 us), so it is not built there.
 constexpr int BK = 64;
 template <int BM, int BN> constexpr int stage_bytes() { return (BM + BN) * 2 * BK; }
-template <int BM, int BN> constexpr int stages() { return 81920 / stage_bytes<BM, BN>(); }   // half of a CU's LDS: two blocks share a CU
+// ring depth: all of a CU's 160 KB for the 128 x 128 tile, half of it for the small ones (two blocks share a CU): 5, 3 and 5 stages
+template <int BM, int BN> constexpr int stages() { return (BM * BN < 128 * 128 ? 81920 : 163840) / stage_bytes<BM, BN>(); }
 
 // Second (or only) part of a k-block: the block's slot is free (its fragments are in registers, the barrier is
 // passed), so the loads of the stage NS ahead go there while the next stage's first fragments are read.  The two
@@ -808,9 +816,11 @@ const TileCfg kTiles[] = {
   {256, 128, 2, 2, 1, {7.1f, 14.1f}, {10.8f, 28.5f}, {12.3f, 12.7f}, {20.4f, 25.2f}},
   {128, 256, 2, 2, 1, {7.4f, 13.7f}, {12.1f, 27.4f}, {11.0f, 12.8f}, {20.5f, 25.0f}},
   {128, 128, 2, 2, 1, {4.4f, 9.0f}, {5.9f, 14.7f}, {8.2f, 8.0f}, {11.0f, 15.3f}},
+  {128, 128, 1, 1, 4, {7.5f, 7.6f}, {14.2f, 14.5f}, {0.f, 0.f}, {0.f, 0.f}},   // not built for the weight gradient (see namespace ksplit)
   {64, 128, 1, 2, 2, {3.8f, 5.7f}, {4.8f, 10.5f}, {5.6f, 6.0f}, {7.5f, 10.9f}},
   {64, 64, 1, 1, 4, {3.6f, 3.3f}, {4.3f, 6.8f}, {4.5f, 3.8f}, {5.5f, 7.3f}}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kWholeCuTile = 4;      // the tile above whose blocks take all of a CU's LDS although the launch is small
 constexpr float kLaunchGap = 2.5f;   // the part of a that later rounds of the same launch do not pay
 
 int forced_tile() {
@@ -822,7 +832,11 @@ int forced_tile() {
   return forced;
 }
 
-bool tile_fits(int i, int M, int n) { return M % kTiles[i].bm == 0 && n % kTiles[i].bn == 0; }
+// beside: other launches run at the same time (kernels.h); their blocks find no room on a CU beside kWholeCuTile's
+// (BERT-Large layer with the weight gradients on a second stream: 4.17 ms without that tile, 4.36 with it)
+bool tile_fits(int i, int M, int n, bool tn, bool beside) {
+  return M % kTiles[i].bm == 0 && n % kTiles[i].bn == 0 && !(i == kWholeCuTile && (tn || beside));
+}
 
 // time of covering an M x n output with tile i, the k axis cut into `shares` that run side by side
 float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
@@ -839,13 +853,13 @@ float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
   return us;
 }
 
-int pick_tile(int M, int N, int K, bool tn) {
+int pick_tile(int M, int N, int K, bool tn, bool beside) {
   const int forced = forced_tile();
-  if (forced >= 0 && forced < kNumTiles && tile_fits(forced, M, N)) return forced;
+  if (forced >= 0 && forced < kNumTiles && tile_fits(forced, M, N, tn, beside)) return forced;
   int best = -1;
   float best_t = 0;
   for (int i = 0; i < kNumTiles; i++) {
-    if (!tile_fits(i, M, N)) continue;
+    if (!tile_fits(i, M, N, tn, beside)) continue;
     const float t = tile_cost(i, M, N, K, tn);
     if (best < 0 || t < best_t) { best = i; best_t = t; }
   }
@@ -865,23 +879,23 @@ constexpr float kSecondLaunch = 2.f;  // us: the first launch's last tiles run a
 constexpr int kMaxShares = 16;
 float shares_cost(int M, int N, int shares) { return 4.f + (float)M * N * 4.f * (shares + 2) / 4.5e6f; }  // launch, and 4.5 TB/s
 
-Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats) {
-  Plan p = {1, {pick_tile(M, N, K, tn), -1}, N, 1};
+Plan make_plan(int M, int N, int K, bool tn, bool beside, int n_seg, size_t part_floats) {
+  Plan p = {1, {pick_tile(M, N, K, tn, beside), -1}, N, 1};
   if (p.tile[0] < 0 || forced_tile() >= 0 || getenv("AH_GEMM_NOSPLIT")) return p;
   float best = 0.96f * tile_cost(p.tile[0], M, N, K, tn);  // the model's accuracy: a second launch has to promise more
   for (int s = 2; tn && s <= kMaxShares && (size_t)M * N * s <= part_floats; s++) {
     if (n_seg > 1 ? n_seg % s : K % (128 * s)) continue;
     for (int i = 0; i < kNumTiles; i++) {
-      if (!tile_fits(i, M, N)) continue;
+      if (!tile_fits(i, M, N, tn, beside)) continue;
       const float t = tile_cost(i, M, N, K, tn, s) + shares_cost(M, N, s);
       if (t < best) { best = t; p = {1, {i, -1}, N, s}; }
     }
   }
   for (int n0 = 128; n0 < N; n0 += 128)
     for (int i = 0; i < kNumTiles; i++) {
-      if (!tile_fits(i, M, n0)) continue;
+      if (!tile_fits(i, M, n0, tn, beside)) continue;
       for (int j = 0; j < kNumTiles; j++) {
-        if (j == i || !tile_fits(j, M, N - n0)) continue;
+        if (j == i || !tile_fits(j, M, N - n0, tn, beside)) continue;
         const float t = tile_cost(i, M, n0, K, tn) + tile_cost(j, M, N - n0, K, tn) + kSecondLaunch;
         if (t < best) { best = t; p = {2, {i, j}, n0, 1}; }
       }
@@ -890,15 +904,15 @@ Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats) {
 }
 
 // make_plan is a search over a few thousand candidates: remembered per problem
-Plan cached_plan(int M, int N, int K, bool tn, int n_seg = 1, size_t part_floats = 0) {
-  struct Entry { int M, N, K; bool tn; int n_seg; size_t part_floats; Plan p; };
+Plan cached_plan(int M, int N, int K, bool tn, bool beside = false, int n_seg = 1, size_t part_floats = 0) {
+  struct Entry { int M, N, K; bool tn, beside; int n_seg; size_t part_floats; Plan p; };
   static std::mutex mu;
   static std::vector<Entry> cache;
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : cache)
-    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.n_seg == n_seg && e.part_floats == part_floats) return e.p;
-  const Plan p = make_plan(M, N, K, tn, n_seg, part_floats);
-  if (cache.size() < 4096) cache.push_back({M, N, K, tn, n_seg, part_floats, p});
+    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.beside == beside && e.n_seg == n_seg && e.part_floats == part_floats) return e.p;
+  const Plan p = make_plan(M, N, K, tn, beside, n_seg, part_floats);
+  if (cache.size() < 4096) cache.push_back({M, N, K, tn, beside, n_seg, part_floats, p});
   return p;
 }
 
@@ -916,7 +930,10 @@ hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
     case 1: return run<256, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
     case 2: return run<128, 256, 2, 2, 1, AKS, BKS, EPI>(a, s);
     case 3: return run<128, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
-    case 4: return run<64, 128, 1, 2, 2, AKS, BKS, EPI>(a, s);
+    case kWholeCuTile:
+      if constexpr (!(AKS && BKS)) return run<128, 128, 1, 1, 4, AKS, BKS, EPI>(a, s);
+      else return hipErrorInvalidValue;
+    case 5: return run<64, 128, 1, 2, 2, AKS, BKS, EPI>(a, s);
     default: return run<64, 64, 1, 1, 4, AKS, BKS, EPI>(a, s);
   }
 }
@@ -934,7 +951,7 @@ int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout) {
 
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg) {
   if (!gemm_shape_ok(M, N, K)) return 0;
-  const Plan p = cached_plan(M, N, K, true, n_seg, (size_t)M * N * kMaxShares);
+  const Plan p = cached_plan(M, N, K, true, false, n_seg, (size_t)M * N * kMaxShares);
   return p.shares > 1 ? (size_t)M * N * p.shares : 0;
 }
 
@@ -1006,7 +1023,7 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
   }
   a.k_shares = 1;
   const bool tn = layout == GEMM_TN;
-  const Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0);
+  const Plan p = cached_plan(a.M, a.N, a.K, tn, !tn && a.beside, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0);
   if (p.tile[0] < 0) return hipErrorInvalidValue;
   if (p.shares > 1) {
     GemmArgs b = a;

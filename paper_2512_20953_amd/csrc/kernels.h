@@ -45,6 +45,7 @@ struct GemmArgs {
   int M, N, K;
   int beta;
   int group, xcd_remap;  // tile rasterisation (set by launch_gemm)
+  int beside;            // other launches are expected on the device at the same time: prefer tiles that leave them room on a CU
   // TN only: the k axis may be the concatenation of n_seg pieces of seg_k rows each (K = n_seg * seg_k), piece i
   // of A starting at segA[i] and of B at segB[i] (same leading dimensions).  n_seg == 0: one piece, A and B.
   int seg_k, n_seg;

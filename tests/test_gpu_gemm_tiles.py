@@ -1,7 +1,7 @@
 """GEMM entry points at the sizes where a tile shape begins, ends or leaves a remainder, against float64 products.
 
-The launcher picks the tile by the output and k extents; the cases below reach every tile shape (64 x 64 and 64 x 128
-with the k axis split between waves, 128 x 128, the 256-wide ones), tile counts that are no multiple of the 8 XCDs,
+The launcher picks the tile by the output and k extents; the cases below reach every tile shape (64 x 64, 64 x 128 and,
+for long k, 128 x 128 with the k axis split between waves, 128 x 128, the 256-wide ones), tile counts that are no multiple of the 8 XCDs,
 and k extents from one ring fill less (k = 128 is two k-blocks, the ring holds three to five) to several.
 
 Tolerance: a bf16 output is the fp32 sum rounded once, 2^-9 of its value at most (2^-8 between neighbouring values);
@@ -15,7 +15,7 @@ import paper_2512_20953_amd as P
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(128, 128, 128), (128, 384, 256), (384, 640, 384), (256, 256, 1024), (640, 1152, 640), (1024, 1024, 512), (896, 1152, 384),
-          (1024, 2048, 128), (2048, 1024, 640), (1920, 1664, 256), (2048, 2048, 256), (1152, 4352, 128), (4096, 4096, 128)]
+          (1024, 2048, 128), (2048, 1024, 640), (1920, 1664, 256), (2048, 2048, 256), (2048, 2048, 4224), (1152, 4352, 128), (4096, 4096, 128)]
 
 
 def _close(got, ref, k, bf16):
