@@ -73,7 +73,7 @@ struct ah_stage {
   // reductions); created on first use, joined back into the caller's stream before every return.
   hipStream_t side;
   hipEvent_t sync_ev[8];
-  bool side_ready, side_off;
+  bool side_ready, side_off, side_pays;
   std::vector<hipEvent_t> ev_pool;           // pairs, in launch order
   std::vector<int> ev_site;                  // site of pair i
   std::vector<int> ev_mult;                  // micro-batches covered by the launch of pair i
@@ -133,6 +133,15 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
     // A deferred product runs at the end of its group with a k axis G times as long: fewer fp32 passes over the matrix,
     // one prologue and epilogue, and for a small output enough k for shares that fill the chip.
     for (bool& m : s->defer_matrix) m = true;
+    // Per-micro-batch products on the second stream hide the launches' tails and fill idle CUs (13B layer 3.86 -> 3.68
+    // ms, a 512-wide one over 4096 tokens 0.55 -> 0.49), but each layer then pays for eight cross-stream orderings,
+    // ~40 us of host and queue time: where a layer's products are shorter than that they cost more than they hide
+    // (two micro-batches of one layer: 0.4 GFLOP 280 against 240 us without, 2.4 GFLOP 313 / 299, 6.4 GFLOP 356 / 349,
+    // 26 GFLOP 492 / 552).
+    double gflop = 0;
+    for (const auto& mn : wgrad_shapes(s)) gflop += 2e-9 * s->T * mn[0] * mn[1];
+    const char* e = getenv("AH_SIDE_STREAM_MIN_GFLOP");  // tuning and test aid
+    s->side_pays = gflop >= (e ? atof(e) : 12.0);
     // tuning and test aid: the choice given outright, bit i = matrix i (second MLP, first MLP, out-projection, QKV)
     if (const char* m = getenv("AH_DEFER_MATRICES"))
       for (int i = 0; i < 4; i++) s->defer_matrix[i] = (atoi(m) >> i) & 1;
@@ -557,7 +566,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
 // The side stream and its events, created on the first backward pass (the device of the caller's buffers is
 // current then).  AH_NO_SIDE_STREAM in the environment keeps everything on the caller's stream (tuning aid).
 hipError_t ensure_side(ah_stage* s) {
-  if (s->side_ready || s->side_off) return hipSuccess;
+  if (s->side_ready || s->side_off || !s->side_pays) return hipSuccess;
   if (getenv("AH_NO_SIDE_STREAM")) { s->side_off = true; return hipSuccess; }
   hipError_t e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking);
   if (e != hipSuccess) return e;

@@ -82,3 +82,30 @@ def test_group_products_with_the_k_axis_shared_by_blocks(arch, n_mb):
     assert all(torch.equal(a, b) for a, b in zip(*outs))
     for a, b in zip(*grads):
         assert ((a - b).double().norm() / a.double().norm()).item() <= 2e-6
+
+
+@pytest.mark.parametrize("arch", ["gpt", "llama"])
+@pytest.mark.parametrize("recompute", [0, 1])
+def test_second_stream_by_size_changes_no_bit(arch, recompute, monkeypatch):
+    """Whether the per-micro-batch weight gradients run on the second stream is decided by their flops; a small stage
+    keeps one stream.  Forced either way: the same bits, over two iterations on the same stage."""
+    res = []
+    for gflop in ("0", "1e9"):
+        monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", gflop)   # read when the stage is created
+        cfg = P.StageConfig.make(arch=arch, n_layers=3, hidden=256, n_heads=4, head_dim=64, ffn=512, seq=256, mb=2, n_mb=2, recompute=recompute)
+        st = P.Stage(cfg)
+        g = torch.Generator(device="cuda").manual_seed(9)
+        st.params.copy_(torch.randn(st.params.shape, generator=g, device="cuda") * 0.05)
+        out = []
+        for it in range(2):
+            st.zero_grads()
+            for m in range(2):
+                x, dy = (torch.randn(512, 256, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+                y, dx = torch.empty_like(x), torch.empty_like(x)
+                st.forward(0, x, y)
+                st.backward(0, dy, dx)
+                out += [y, dx]
+            torch.cuda.synchronize()
+            out.append(st.grads.clone())
+        res.append(out)
+    assert all(torch.equal(a, b) for a, b in zip(*res))
