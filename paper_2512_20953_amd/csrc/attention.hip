@@ -17,7 +17,7 @@
 //
 // Backward is two deterministic kernels (no atomics): one block per 128
 // queries accumulates dQ over the key tiles at or before it and leaves
-// delta = rowsum(dO * O) of its queries behind; one block per 128 keys then
+// delta = rowsum(dO * O) of its queries behind, negated; one block per 128 keys then
 // accumulates dK and dV over the query tiles at or after it (causal; without
 // the mask both walk every tile of the sequence).
 #include "common.h"
@@ -37,6 +37,11 @@ constexpr int NSLOT = 2;  // ring slots of the forward and dQ kernels (two block
 // other wave's vector work (softmax, masks, conversions) fills in behind them instead of delaying them.  Used in the
 // forward kernel (8 % faster on launches of more than two blocks per CU); in the dQ kernel it cost 1-3 %.
 #define AH_PRIO(p) __builtin_amdgcn_s_setprio(p)
+
+// the next tile has landed for the whole block, and every wave is done with the one that its slot held
+#define AH_NEXT_TILE()                                \
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));    \
+  __builtin_amdgcn_s_barrier()
 
 // LDS tile [64 rows][D] bf16.  16-byte piece p of row r is stored at piece
 // swz(r, p): conflict-free both for 16-byte reads down a column of pieces and
@@ -255,9 +260,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict
   char *const K0 = ring, *const V0 = ring + TILEB, *const K1 = ring + STAGE, *const V1 = ring + STAGE + TILEB;
   issue_tile<D>(kp, off, K0, wave);
   issue_tile<D>(vp, off, V0, wave);
-#define AH_NEXT_TILE()                                \
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));    \
-  __builtin_amdgcn_s_barrier()
   AH_NEXT_TILE();
   for (int j = 0; j < nfull; j += 2) {
     const size_t o1 = (size_t)(j + 1) * step, o2 = (size_t)min(j + 2, last) * step;
@@ -272,7 +274,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict
     AH_NEXT_TILE();
     fwd_step<D, true>(kp + o1, vp + o1, off, K0, V0, K1, V1, st, last * 64, q, qw0, sc2, wave, lane);
   }
-#undef AH_NEXT_TILE
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant tail loads
 
   const float l = st.l + __shfl_xor(st.l, 32, 64);
@@ -470,9 +471,9 @@ struct DqState {
 // One key tile of 64 for the wave's 32 queries.  With head_dim 64 the LDS reads run a phase ahead of their
 // use as in dkv_tile; with head_dim 128 the 256 registers of a wave (two blocks share a CU) leave no room
 // for fragments in flight, so they are fetched where they are used and the other block covers the wait.
-template <int D>
+template <int D, bool DIAG>
 __device__ __forceinline__ void dq_tile(const char* __restrict__ cK, const char* __restrict__ cV, DqState<D>& st, int k0, int q,
-                                        bool diag, float sc2, int lane) {
+                                        float sc2, int lane) {
   constexpr int NK = D / 16, ND = D / 32;
   constexpr bool AHEAD = D == 64;
   const int hf = lane >> 5;
@@ -511,7 +512,7 @@ __device__ __forceinline__ void dq_tile(const char* __restrict__ cK, const char*
     const float nl = -st.lse2;
 #pragma unroll
     for (int r = 0; r < 16; r++) s[r] = fexp2(__builtin_fmaf(s[r], sc2, nl));
-    if (diag) {  // wave-uniform
+    if (DIAG) {
 #pragma unroll
       for (int r = 0; r < 16; r++)
         if (t * 32 + 8 * (r >> 2) + (r & 3) > lim) s[r] = 0.f;
@@ -539,14 +540,15 @@ __device__ __forceinline__ void dq_tile(const char* __restrict__ cK, const char*
   if (AHEAD) AH_SCHED_FENCE();
 }
 
-template <int D, bool CAUSAL, bool MAY_SKIP>
+// MASK as in fwd_step
+template <int D, bool MASK>
 __device__ __forceinline__ void dq_step(const bf16* gK, const bf16* gV, uint32_t* off, char* __restrict__ nK,
                                         char* __restrict__ nV, const char* __restrict__ cK, const char* __restrict__ cV,
                                         DqState<D>& st, int k0, int q, int qw0, float sc2, int wave, int lane) {
   issue_tile<D>(gK, off, nK, wave);
   issue_tile<D>(gV, off, nV, wave);
-  if (CAUSAL && MAY_SKIP && k0 > qw0 + 31) return;
-  dq_tile<D>(cK, cV, st, k0, q, CAUSAL && k0 + 63 > qw0, sc2, lane);
+  if (MASK && k0 > qw0 + 31) return;
+  dq_tile<D, MASK>(cK, cV, st, k0, q, sc2, lane);
 }
 
 template <int D, bool CAUSAL>
@@ -554,7 +556,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
                                                       const bf16* __restrict__ d_o, const float* __restrict__ lse,
                                                       float* __restrict__ delta, bf16* __restrict__ dqkv, int S, int nh,
                                                       float sc2, float scale) {
-  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB, LPS = 2 * (D / 32);  // ring slot = K tile then V tile
+  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB;  // ring slot = K tile then V tile
   __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
@@ -581,38 +583,33 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
     for (int r = 0; r < 16; r++) st.acc[dt][r] = 0.f;
   st.lse2 = lse[((size_t)b * nh + head) * S + q] * LOG2E;
   st.delta = row_delta<D>(st.dof, o + ((size_t)b * S + q) * (nh * D) + head * D, hf);
-  if (hf == 0) delta[((size_t)b * nh + head) * S + q] = st.delta;
+  if (hf == 0) delta[((size_t)b * nh + head) * S + q] = -st.delta;  // negated: what the dK/dV kernel starts dP from
 
   uint32_t off[D / 32];
 #pragma unroll
   for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
 
-  // key tiles of 64 up to and including the diagonal (all of them without the mask).  Tile t lives in ring
-  // slot t % NSLOT; the tile loaded during step j is min(j + NSLOT - 1, last): past the end the last tile is
-  // fetched again into a dead slot, which keeps the number of loads in flight uniform for the counted wait.
-  const int ntile = CAUSAL ? 2 * qb + 2 : S / 64, last = ntile - 1;
+  // tiles, ring and peeled diagonal as in the forward kernel
+  const int ntile = CAUSAL ? 2 * qb + 2 : S / 64, last = ntile - 1, nfull = CAUSAL ? ntile - 2 : ntile;
   const size_t step = (size_t)64 * ld;
-#pragma unroll
-  for (int t = 0; t < NSLOT - 1; t++) {
-    const size_t o = (size_t)min(t, last) * step;
-    issue_tile<D>(kp + o, off, ring + t * STAGE, wave);
-    issue_tile<D>(vp + o, off, ring + t * STAGE + TILEB, wave);
+  char *const K0 = ring, *const V0 = ring + TILEB, *const K1 = ring + STAGE, *const V1 = ring + STAGE + TILEB;
+  issue_tile<D>(kp, off, K0, wave);
+  issue_tile<D>(vp, off, V0, wave);
+  AH_NEXT_TILE();
+  for (int j = 0; j < nfull; j += 2) {
+    const size_t o1 = (size_t)(j + 1) * step, o2 = (size_t)min(j + 2, last) * step;
+    dq_step<D, false>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, j * 64, q, qw0, sc2, wave, lane);
+    AH_NEXT_TILE();
+    dq_step<D, false>(kp + o2, vp + o2, off, K0, V0, K1, V1, st, (j + 1) * 64, q, qw0, sc2, wave, lane);
+    AH_NEXT_TILE();
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NSLOT - 2) * LPS));
-  __builtin_amdgcn_s_barrier();
-  for (int j = 0; j < last; j++) {
-    const size_t o = (size_t)min(j + NSLOT - 1, last) * step;
-    char* fill = ring + ((j + NSLOT - 1) & (NSLOT - 1)) * STAGE;
-    const char* cur = ring + (j & (NSLOT - 1)) * STAGE;
-    dq_step<D, CAUSAL, false>(kp + o, vp + o, off, fill, fill + TILEB, cur, cur + TILEB, st, j * 64, q, qw0, sc2, wave, lane);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NSLOT - 2) * LPS));
-    __builtin_amdgcn_s_barrier();
-  }
-  {  // the last tile, peeled as in the forward kernel
-    const size_t o = (size_t)last * step;
-    char* fill = ring + ((last + NSLOT - 1) & (NSLOT - 1)) * STAGE;
-    const char* cur = ring + (last & (NSLOT - 1)) * STAGE;
-    dq_step<D, CAUSAL, true>(kp + o, vp + o, off, fill, fill + TILEB, cur, cur + TILEB, st, last * 64, q, qw0, sc2, wave, lane);
+  if (CAUSAL) {
+    const size_t o1 = (size_t)last * step;
+    int late = lane;  // opaque, so that the addresses of these two tiles are not computed and kept (spilled) before the loop
+    asm volatile("" : "+v"(late));
+    dq_step<D, true>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, (last - 1) * 64, q, qw0, sc2, wave, late);
+    AH_NEXT_TILE();
+    if (last * 64 <= qw0 + 31) dq_tile<D, true>(K1, V1, st, last * 64, q, sc2, late);
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant tail loads
 
@@ -727,7 +724,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
     for (int r = 0; r < 16; r++) st.acc[dt][r] = 0.f;
   st.lse2 = lse[((size_t)b * nh + head) * S + q] * LOG2E;
   st.delta = row_delta<D>(st.dof, o + ((size_t)b * S + q) * (nh * D) + head * D, hf);   // both key halves compute it, one writes
-  if (hf == 0 && kh == 0) delta[((size_t)b * nh + head) * S + q] = st.delta;
+  if (hf == 0 && kh == 0) delta[((size_t)b * nh + head) * S + q] = -st.delta;
 
   uint32_t off[D / 32];
 #pragma unroll
@@ -782,26 +779,32 @@ struct DkvState {
   f32x16 dk[D / 32], dv[D / 32];
 };
 
-// One query tile of 64 for the wave's 32 keys.  Every fragment comes out of LDS, which all four waves
-// share and which is the busiest unit of this kernel, so the reads are issued one phase ahead of their
-// use (scheduling fences keep the compiler from sinking them back to the point of use): the transposed
-// fragments of the second pair of products are requested while the first pair runs and while the
-// probabilities are rebuilt, the row-major fragments of the next half while the second pair runs.
-template <int D>
+// One query tile of 64 for the wave's 32 keys.  Every fragment comes out of LDS, which all the waves of a CU share and
+// which is the busiest unit of this kernel.  With head_dim 128 the state (K, V, the accumulators of dK and dV: 192
+// registers) leaves room for one wave to a SIMD only, so the reads are issued one phase ahead of their use (scheduling
+// fences keep the compiler from sinking them back): the transposed fragments of the second pair of products are
+// requested while the first pair runs and while the probabilities are rebuilt, the row-major fragments of the next half
+// while the second pair runs.  With head_dim 64 two blocks share a CU: fragments are fetched where they are used and the
+// other block's wave covers the wait (8 x 16 x 512 x 64: 48.9 -> 45.5 us for the whole backward).
+template <int D, bool DIAG>
 __device__ __forceinline__ void dkv_tile(const char* __restrict__ cQ, const char* __restrict__ cO, DkvState<D>& st,
                                          const float* __restrict__ lse_tile, const float* __restrict__ delta_tile, int q0, int key,
-                                         bool diag, float sc2, int lane) {
+                                         float sc2, int lane) {
   constexpr int NK = D / 16, ND = D / 32;
+  constexpr bool AHEAD = D == 128;
   const int hf = lane >> 5;
   const int lim = key - q0 - 4 * hf;  // query offset ql (without the 4*hf term) is masked iff ql < lim
   bf16x8 fq[NK], fo[NK];
+  auto fetch_rows = [&](int t) {
 #pragma unroll
-  for (int ks = 0; ks < NK; ks++) {
-    fq[ks] = frag_rowmajor<D>(cQ, lane & 31, ks, hf);
-    fo[ks] = frag_rowmajor<D>(cO, lane & 31, ks, hf);
-  }
-  // delta of the lane's queries (q0 + t*32 + 8g + 4hf + i), read ahead with the fragments: the product dO V^T is
-  // accumulated onto -delta, which gives dP - delta without a subtraction per element
+    for (int ks = 0; ks < NK; ks++) {
+      fq[ks] = frag_rowmajor<D>(cQ, t * 32 + (lane & 31), ks, hf);
+      fo[ks] = frag_rowmajor<D>(cO, t * 32 + (lane & 31), ks, hf);
+    }
+  };
+  if (AHEAD) fetch_rows(0);
+  // -delta of the lane's queries (q0 + t*32 + 8g + 4hf + i): the product dO V^T starts from it, which gives dP - delta
+  // without a subtraction per element
   f32x4 dl[2][4];
 #pragma unroll
   for (int t = 0; t < 2; t++)
@@ -809,65 +812,58 @@ __device__ __forceinline__ void dkv_tile(const char* __restrict__ cQ, const char
     for (int g = 0; g < 4; g++) dl[t][g] = *(const f32x4*)(delta_tile + t * 32 + 8 * g + 4 * hf);
 #pragma unroll
   for (int t = 0; t < 2; t++) {
-    AH_SCHED_FENCE();
+    if (AHEAD) AH_SCHED_FENCE();
     f32x16 s, dp;
 #pragma unroll
-    for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -dl[t][r >> 2][r & 3]; }
-    bf16x8 tq0[ND], to0[ND], tq1[ND], to1[ND];
+    for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = dl[t][r >> 2][r & 3]; }
+    bf16x8 tq[2][ND], to[2][ND];
+    auto fetch_columns = [&](int s2) {
+#pragma unroll
+      for (int dt = 0; dt < ND; dt++) {
+        to[s2][dt] = frag_transposed<D>(cO, t * 32 + 16 * s2 + 4 * hf, dt, lane);
+        tq[s2][dt] = frag_transposed<D>(cQ, t * 32 + 16 * s2 + 4 * hf, dt, lane);
+      }
+    };
+    if (!AHEAD) fetch_rows(t);
 #pragma unroll
     for (int ks = 0; ks < NK; ks++) {
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[ks], st.kf[ks], s, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[ks], st.vf[ks], dp, 0, 0, 0);
+      if (!AHEAD && (ks & 1)) AH_SCHED_FENCE();
     }
-#pragma unroll
-    for (int dt = 0; dt < ND; dt++) {
-      to0[dt] = frag_transposed<D>(cO, t * 32 + 4 * hf, dt, lane);
-      tq0[dt] = frag_transposed<D>(cQ, t * 32 + 4 * hf, dt, lane);
+    if (AHEAD) {
+      fetch_columns(0);
+      AH_SCHED_FENCE();
     }
-    AH_SCHED_FENCE();
     // lane holds queries q0 + t*32 + 8g + 4hf + i of its key
 #pragma unroll
     for (int g = 0; g < 4; g++) {
-      const int ql = t * 32 + 8 * g + 4 * hf;
-      const f32x4 l4 = *(const f32x4*)(lse_tile + ql);
+      const f32x4 l4 = *(const f32x4*)(lse_tile + t * 32 + 8 * g + 4 * hf);
 #pragma unroll
       for (int i = 0; i < 4; i++) {
         const int r = 4 * g + i;
         s[r] = fexp2(__builtin_fmaf(s[r], sc2, -l4[i] * LOG2E));
+        if (DIAG && t * 32 + 8 * g + i < lim) s[r] = 0.f;
+        dp[r] *= s[r];
       }
     }
-    if (diag) {  // wave-uniform: only tiles that straddle the diagonal pay for the mask
-#pragma unroll
-      for (int r = 0; r < 16; r++)
-        if (t * 32 + 8 * (r >> 2) + (r & 3) < lim) s[r] = 0.f;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; r++) dp[r] *= s[r];
     AH_SCHED_FENCE();
     const bf16x8 pf0 = pack8(s, 0), dsf0 = pack8(dp, 0), pf1 = pack8(s, 1), dsf1 = pack8(dp, 1);
+    if (AHEAD) fetch_columns(1);
+    else fetch_columns(0);
 #pragma unroll
     for (int dt = 0; dt < ND; dt++) {
-      to1[dt] = frag_transposed<D>(cO, t * 32 + 16 + 4 * hf, dt, lane);
-      tq1[dt] = frag_transposed<D>(cQ, t * 32 + 16 + 4 * hf, dt, lane);
-    }
-#pragma unroll
-    for (int dt = 0; dt < ND; dt++) {
-      st.dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to0[dt], pf0, st.dv[dt], 0, 0, 0);
-      st.dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq0[dt], dsf0, st.dk[dt], 0, 0, 0);
+      st.dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to[0][dt], pf0, st.dv[dt], 0, 0, 0);
+      st.dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq[0][dt], dsf0, st.dk[dt], 0, 0, 0);
     }
     AH_SCHED_FENCE();
+    if (!AHEAD) fetch_columns(1);
 #pragma unroll
     for (int dt = 0; dt < ND; dt++) {
-      st.dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to1[dt], pf1, st.dv[dt], 0, 0, 0);
-      st.dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq1[dt], dsf1, st.dk[dt], 0, 0, 0);
+      st.dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to[1][dt], pf1, st.dv[dt], 0, 0, 0);
+      st.dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq[1][dt], dsf1, st.dk[dt], 0, 0, 0);
     }
-    if (t == 0) {
-#pragma unroll
-      for (int ks = 0; ks < NK; ks++) {
-        fq[ks] = frag_rowmajor<D>(cQ, 32 + (lane & 31), ks, hf);
-        fo[ks] = frag_rowmajor<D>(cO, 32 + (lane & 31), ks, hf);
-      }
-    }
+    if (AHEAD && t == 0) fetch_rows(1);
   }
   AH_SCHED_FENCE();
 }
@@ -875,34 +871,34 @@ __device__ __forceinline__ void dkv_tile(const char* __restrict__ cQ, const char
 // ring slot of the dK/dV kernel: Q tile, dO tile, then 64 log-sum-exps, 64 deltas and 512 spare bytes
 template <int D>
 __device__ __forceinline__ void dkv_issue(const bf16* gQ, const bf16* gO, const float* gL, const float* gD, uint32_t* offq,
-                                          uint32_t* offo, char* __restrict__ slot, int wave, int lane) {
+                                          uint32_t* offo, uint32_t& offs, char* __restrict__ slot, int wave) {
   constexpr int TILEB = 64 * 2 * D;
   issue_tile<D>(gQ, offq, slot, wave);
   issue_tile<D>(gO, offo, slot + TILEB, wave);
   // one 4-byte load per lane: waves 0 and 1 bring the statistics, waves 2 and 3 repeat them into the
   // spare bytes so that every wave has the same number of loads in flight
-  const float* src = ((wave & 1) ? gD : gL) + lane;
-  __builtin_amdgcn_global_load_lds(src, AH_LDS(slot + 2 * TILEB + wave * 256), 4, 0, 0);
+  load4_to_lds((wave & 1) ? gD : gL, offs, slot + 2 * TILEB + wave * 256);
 }
 
-template <int D, bool CAUSAL, bool MAY_SKIP>
+// MASK: one of the block's first two tiles under the mask, which straddle the diagonal for two of the waves and lie
+// wholly before or wholly after the keys of the others
+template <int D, bool MASK>
 __device__ __forceinline__ void dkv_step(const bf16* gQ, const bf16* gO, const float* gL, const float* gD, uint32_t* offq,
-                                         uint32_t* offo, char* __restrict__ fill, const char* __restrict__ cur, DkvState<D>& st,
-                                         int q0, int key, int kw0, float sc2, int wave, int lane) {
+                                         uint32_t* offo, uint32_t& offs, char* __restrict__ fill, const char* __restrict__ cur,
+                                         DkvState<D>& st, int q0, int key, int kw0, float sc2, int wave, int lane) {
   constexpr int TILEB = 64 * 2 * D;
-  dkv_issue<D>(gQ, gO, gL, gD, offq, offo, fill, wave, lane);
+  dkv_issue<D>(gQ, gO, gL, gD, offq, offo, offs, fill, wave);
   const float* lse_tile = (const float*)(cur + 2 * TILEB);
-  if (CAUSAL && MAY_SKIP && q0 + 63 < kw0) return;  // every query of this tile is before every key of the wave
-  // diag: the tile straddles the diagonal of this wave's keys (wave-uniform)
-  dkv_tile<D>(cur, cur + TILEB, st, lse_tile, lse_tile + 64, q0, key, CAUSAL && q0 < kw0 + 31, sc2, lane);
+  if (MASK && q0 + 63 < kw0) return;
+  dkv_tile<D, MASK>(cur, cur + TILEB, st, lse_tile, lse_tile + 64, q0, key, sc2, lane);
 }
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
                                                        const float* __restrict__ lse, const float* __restrict__ delta,
                                                        bf16* __restrict__ dqkv, int S, int nh, float sc2, float scale) {
-  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB + 1024, LPS = 2 * (D / 32) + 1;
-  __shared__ __attribute__((aligned(1024))) char ring[4 * STAGE];
+  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB + 1024;
+  __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
   const int nbh = gridDim.x / (S / 128);
@@ -929,45 +925,39 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(const bf16* __restrict__ 
 #pragma unroll
     for (int r = 0; r < 16; r++) { st.dk[dt][r] = 0.f; st.dv[dt][r] = 0.f; }
 
-  uint32_t offq[D / 32], offo[D / 32];
+  uint32_t offq[D / 32], offo[D / 32], offs = lane * 4;  // byte offsets of the lane's loads (offs: the 4-byte statistics)
 #pragma unroll
   for (int i = 0; i < D / 32; i++) {
     offq[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
     offo[i] = tile_src_offset<D>(wave + 4 * i, lane, ldo);
   }
 
-  // query tiles of 64 from the diagonal on (from 0 without the mask).  Tile t lives in ring slot t % 4; past the
-  // end the last tile is fetched again into a dead slot (uniform number of loads in flight for the counted wait).
+  // Query tiles of 64 from the diagonal on (from 0 without the mask), an even number; ring and rounds of two as in the
+  // forward kernel, the two tiles on the diagonal peeled at the front.
   const int j0 = CAUSAL ? 2 * kb : 0, ntile = S / 64 - j0, last = ntile - 1;
   qp += (size_t)j0 * 64 * ld;
   dop += (size_t)j0 * 64 * ldo;
   lse_row += j0 * 64;
   delta_row += j0 * 64;
   const size_t stepq = (size_t)64 * ld, stepo = (size_t)64 * ldo;
-#pragma unroll
-  for (int t = 0; t < 3; t++) {
-    const int tt = min(t, last);
-    dkv_issue<D>(qp + tt * stepq, dop + tt * stepo, lse_row + tt * 64, delta_row + tt * 64, offq, offo, ring + t * STAGE, wave, lane);
+  char *const R0 = ring, *const R1 = ring + STAGE;
+#define AH_DKV_STEP(MASK, next, fill, cur, j)                                                                                    \
+  dkv_step<D, MASK>(qp + (next) * stepq, dop + (next) * stepo, lse_row + (next) * 64, delta_row + (next) * 64, offq, offo, offs, \
+                    fill, cur, st, (j0 + (j)) * 64, key, kw0, sc2, wave, lane);                                                  \
+  AH_NEXT_TILE()
+  dkv_issue<D>(qp, dop, lse_row, delta_row, offq, offo, offs, R0, wave);
+  AH_NEXT_TILE();
+  if (CAUSAL) {
+    const int n2 = min(2, last);
+    AH_DKV_STEP(true, 1, R1, R0, 0);
+    AH_DKV_STEP(true, n2, R0, R1, 1);
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LPS));
-  __builtin_amdgcn_s_barrier();
-  // Only the block's first tile can lie wholly before a wave's keys (waves 2 and 3 under the mask); it is
-  // peeled so that the loop body has a single path and the accumulators stay where the MFMAs want them.
-  {
-    const int tf = min(3, last);
-    dkv_step<D, CAUSAL, true>(qp + tf * stepq, dop + tf * stepo, lse_row + tf * 64, delta_row + tf * 64, offq, offo, ring + 3 * STAGE, ring,
-                              st, j0 * 64, key, kw0, sc2, wave, lane);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LPS));
-    __builtin_amdgcn_s_barrier();
+  for (int j = CAUSAL ? 2 : 0; j < ntile; j += 2) {
+    const int n2 = min(j + 2, last);
+    AH_DKV_STEP(false, j + 1, R1, R0, j);
+    AH_DKV_STEP(false, n2, R0, R1, j + 1);
   }
-  for (int j = 1; j < ntile; j++) {
-    const int tf = min(j + 3, last);
-    dkv_step<D, CAUSAL, false>(qp + tf * stepq, dop + tf * stepo, lse_row + tf * 64, delta_row + tf * 64, offq, offo,
-                               ring + ((j + 3) & 3) * STAGE, ring + (j & 3) * STAGE, st, (j0 + j) * 64, key, kw0, sc2, wave, lane);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LPS));
-    __builtin_amdgcn_s_barrier();
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant tail loads
+#undef AH_DKV_STEP
 
   bf16* outk = dqkv + ((size_t)b * S + key) * ld + nh * D + head * D;
   bf16* outv = outk + nh * D;
@@ -1009,7 +999,7 @@ __device__ __forceinline__ void dkv_half_tile(const char* __restrict__ cQ, const
   AH_SCHED_FENCE();
   f32x16 s, dp;
 #pragma unroll
-  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -dl[r >> 2][r & 3]; }
+  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = dl[r >> 2][r & 3]; }
   bf16x8 tq0[ND], to0[ND], tq1[ND], to1[ND];
 #pragma unroll
   for (int ks = 0; ks < NK; ks++) {
@@ -1096,7 +1086,7 @@ __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; r++) { st.dk[dt][r] = 0.f; st.dv[dt][r] = 0.f; }
 
-  uint32_t offq[D / 32], offo[D / 32];
+  uint32_t offq[D / 32], offo[D / 32], offs = lane * 4;  // byte offsets of the lane's loads (offs: the 4-byte statistics)
 #pragma unroll
   for (int i = 0; i < D / 32; i++) {
     offq[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
@@ -1114,14 +1104,14 @@ __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict_
 #pragma unroll
   for (int t = 0; t < 3; t++) {
     const int tt = min(t, last);
-    dkv_issue<D>(qp + tt * stepq, dop + tt * stepo, lse_row + tt * 64, delta_row + tt * 64, offq, offo, ring + t * STAGE, wave, lane);
+    dkv_issue<D>(qp + tt * stepq, dop + tt * stepo, lse_row + tt * 64, delta_row + tt * 64, offq, offo, offs, ring + t * STAGE, wave);
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LPS));
   __builtin_amdgcn_s_barrier();
   for (int j = 0; j < ntile; j++) {
     const int tf = min(j + 3, last);
-    dkv_issue<D>(qp + tf * stepq, dop + tf * stepo, lse_row + tf * 64, delta_row + tf * 64, offq, offo, ring + ((j + 3) & 3) * STAGE, wave,
-                 lane);
+    dkv_issue<D>(qp + tf * stepq, dop + tf * stepo, lse_row + tf * 64, delta_row + tf * 64, offq, offo, offs, ring + ((j + 3) & 3) * STAGE,
+                 wave);
     const char* cur = ring + (j & 3) * STAGE;
     const float* lse_tile = (const float*)(cur + 2 * TILEB);
     // in the block's own tile the wave's queries lie before (qh < kt), on (qh == kt) or after (qh > kt) its keys
