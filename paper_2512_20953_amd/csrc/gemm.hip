@@ -304,8 +304,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   const int wm = wmn / WGN, wn = wmn % WGN;
 
   // block -> tile: consecutive logical tiles share an XCD (blocks are dealt to the
-  // 8 XCDs round-robin), and run down groups of 8 tile-rows so that the tiles in
-  // flight on one XCD reuse the same operand panels in its L2.
+  // 8 XCDs round-robin), and run down groups of 4 tile-rows so that the 32 tiles in
+  // flight on one XCD reuse the same operand panels in its L2 (4 of A, 8 of B; 8 and 4 have the same size but took 0.5 %
+  // longer on the 7B shard's layer, 1 % on the 13B and LLaMA-style layers; 2, 3, 5, 6 and 16 rows are no better).
   // With the k axis shared by blocks (kernels.h) the shares follow each other: an XCD then works on one share's operands.
   constexpr bool KSHARES = AKS && BKS && EPI == EPI_F32_SET;
   const int shares = KSHARES ? g.k_shares : 1;
@@ -1008,7 +1009,7 @@ GemmArgs column_range(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, in
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in, hipStream_t s) {
   GemmArgs a = a_in;
   static int grp = -1, remap = -1;
-  if (grp < 0) { grp = getenv("AH_GEMM_GROUP") ? atoi(getenv("AH_GEMM_GROUP")) : 8; remap = getenv("AH_GEMM_NOREMAP") ? 0 : 1; }
+  if (grp < 0) { grp = getenv("AH_GEMM_GROUP") ? atoi(getenv("AH_GEMM_GROUP")) : 4; remap = getenv("AH_GEMM_NOREMAP") ? 0 : 1; }
   a.group = grp; a.xcd_remap = remap;
   if (!gemm_shape_ok(a.M, a.N, a.K)) return hipErrorInvalidValue;
   if (a.n_seg != 0) {  // pieces along k: weight-gradient layout only, and the pieces must add up to K
