@@ -833,10 +833,15 @@ int forced_tile() {
   return forced;
 }
 
-// beside: other launches run at the same time (kernels.h); their blocks find no room on a CU beside kWholeCuTile's
-// (BERT-Large layer with the weight gradients on a second stream: 4.17 ms without that tile, 4.36 with it)
-bool tile_fits(int i, int M, int n, bool tn, bool beside) {
-  return M % kTiles[i].bm == 0 && n % kTiles[i].bn == 0 && !(i == kWholeCuTile && (tn || beside));
+// The choice knows the problem alone, not what runs beside it on another stream: the order of a sum's terms, and so its
+// last bits, depends on the tile.  kWholeCuTile's blocks leave no room on a CU for those of a second stream, so it is
+// taken only where k is long enough for a clear gain: BERT-Large stage, k <= 4096, 23.9 ms a step with it, 23.7 without
+// (27.8 / 26.4 with a second stream); 1.3B stage, k up to 8192, 26.6 / 27.4 (29.5 / 29.2).
+constexpr int kWholeCuMinK = 5120;
+// head: a wave's columns must hold whole heads of this width (0: any; the rotary epilogue, EPI_ROPE, of forward)
+bool tile_fits(int i, int M, int n, int K, bool tn, int head) {
+  const TileCfg& t = kTiles[i];
+  return M % t.bm == 0 && n % t.bn == 0 && !(i == kWholeCuTile && (tn || (K < kWholeCuMinK && !head))) && !(head && t.bn / t.wgn % head);
 }
 
 // time of covering an M x n output with tile i, the k axis cut into `shares` that run side by side
@@ -854,13 +859,13 @@ float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
   return us;
 }
 
-int pick_tile(int M, int N, int K, bool tn, bool beside) {
+int pick_tile(int M, int N, int K, bool tn, int head) {
   const int forced = forced_tile();
-  if (forced >= 0 && forced < kNumTiles && tile_fits(forced, M, N, tn, beside)) return forced;
+  if (forced >= 0 && forced < kNumTiles && tile_fits(forced, M, N, K, tn, head)) return forced;
   int best = -1;
   float best_t = 0;
   for (int i = 0; i < kNumTiles; i++) {
-    if (!tile_fits(i, M, N, tn, beside)) continue;
+    if (!tile_fits(i, M, N, K, tn, head)) continue;
     const float t = tile_cost(i, M, N, K, tn);
     if (best < 0 || t < best_t) { best = i; best_t = t; }
   }
@@ -880,23 +885,23 @@ constexpr float kSecondLaunch = 2.f;  // us: the first launch's last tiles run a
 constexpr int kMaxShares = 16;
 float shares_cost(int M, int N, int shares) { return 4.f + (float)M * N * 4.f * (shares + 2) / 4.5e6f; }  // launch, and 4.5 TB/s
 
-Plan make_plan(int M, int N, int K, bool tn, bool beside, int n_seg, size_t part_floats) {
-  Plan p = {1, {pick_tile(M, N, K, tn, beside), -1}, N, 1};
+Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats, int head) {
+  Plan p = {1, {pick_tile(M, N, K, tn, head), -1}, N, 1};
   if (p.tile[0] < 0 || forced_tile() >= 0 || getenv("AH_GEMM_NOSPLIT")) return p;
   float best = 0.96f * tile_cost(p.tile[0], M, N, K, tn);  // the model's accuracy: a second launch has to promise more
   for (int s = 2; tn && s <= kMaxShares && (size_t)M * N * s <= part_floats; s++) {
     if (n_seg > 1 ? n_seg % s : K % (128 * s)) continue;
     for (int i = 0; i < kNumTiles; i++) {
-      if (!tile_fits(i, M, N, tn, beside)) continue;
+      if (!tile_fits(i, M, N, K, tn, head)) continue;
       const float t = tile_cost(i, M, N, K, tn, s) + shares_cost(M, N, s);
       if (t < best) { best = t; p = {1, {i, -1}, N, s}; }
     }
   }
   for (int n0 = 128; n0 < N; n0 += 128)
     for (int i = 0; i < kNumTiles; i++) {
-      if (!tile_fits(i, M, n0, tn, beside)) continue;
+      if (!tile_fits(i, M, n0, K, tn, head)) continue;
       for (int j = 0; j < kNumTiles; j++) {
-        if (j == i || !tile_fits(j, M, N - n0, tn, beside)) continue;
+        if (j == i || !tile_fits(j, M, N - n0, K, tn, head)) continue;
         const float t = tile_cost(i, M, n0, K, tn) + tile_cost(j, M, N - n0, K, tn) + kSecondLaunch;
         if (t < best) { best = t; p = {2, {i, j}, n0, 1}; }
       }
@@ -904,16 +909,23 @@ Plan make_plan(int M, int N, int K, bool tn, bool beside, int n_seg, size_t part
   return p;
 }
 
+// of a forward product, which is never cut into shares
+float plan_cost(const Plan& p, int M, int N, int K) {
+  return p.parts == 1 ? tile_cost(p.tile[0], M, N, K, false)
+                      : tile_cost(p.tile[0], M, p.n0, K, false) + tile_cost(p.tile[1], M, N - p.n0, K, false) + kSecondLaunch;
+}
+
 // make_plan is a search over a few thousand candidates: remembered per problem
-Plan cached_plan(int M, int N, int K, bool tn, bool beside = false, int n_seg = 1, size_t part_floats = 0) {
-  struct Entry { int M, N, K; bool tn, beside; int n_seg; size_t part_floats; Plan p; };
+Plan cached_plan(int M, int N, int K, bool tn, int n_seg = 1, size_t part_floats = 0, int head = 0) {
+  struct Entry { int M, N, K; bool tn; int n_seg; size_t part_floats; int head; Plan p; };
   static std::mutex mu;
   static std::vector<Entry> cache;
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : cache)
-    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.beside == beside && e.n_seg == n_seg && e.part_floats == part_floats) return e.p;
-  const Plan p = make_plan(M, N, K, tn, beside, n_seg, part_floats);
-  if (cache.size() < 4096) cache.push_back({M, N, K, tn, beside, n_seg, part_floats, p});
+    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.n_seg == n_seg && e.part_floats == part_floats && e.head == head)
+      return e.p;
+  const Plan p = make_plan(M, N, K, tn, n_seg, part_floats, head);
+  if (cache.size() < 4096) cache.push_back({M, N, K, tn, n_seg, part_floats, head, p});
   return p;
 }
 
@@ -941,18 +953,20 @@ hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout) {
-  if (!gemm_shape_ok(M, N, K)) return 0;
-  const Plan p = cached_plan(M, N, K, layout == GEMM_TN);
-  if (p.tile[0] < 0) return 0;
-  int w = kTiles[p.tile[0]].bn / kTiles[p.tile[0]].wgn;
-  if (p.parts == 2) w = std::min(w, kTiles[p.tile[1]].bn / kTiles[p.tile[1]].wgn);
-  return w;
+// The rotary kernel reads and writes the rotated columns once more (and rounds them once more); tiles whose waves hold
+// whole heads, where the output would take others, cost more than that only on the smallest outputs (128-wide heads,
+// fused against kernel, us a layer: 128 rows x 256 hidden 36.6 / 32.5, 384 x 640 46.3 / 41.5, 1024 x 1024 61.1 / 62.3,
+// 4096 x 1024 116.8 / 126.1).
+bool gemm_rope_pays(int M, int N, int K, int d, int rope_cols) {
+  if (!gemm_shape_ok(M, N, K) || d <= 0 || d % 16) return false;
+  const Plan heads = cached_plan(M, N, K, false, 1, 0, d), any = cached_plan(M, N, K, false);
+  if (heads.tile[0] < 0) return false;
+  return plan_cost(heads, M, N, K) <= plan_cost(any, M, N, K) + 3.f + (float)M * rope_cols * 4.f / 4.5e6f;
 }
 
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg) {
   if (!gemm_shape_ok(M, N, K)) return 0;
-  const Plan p = cached_plan(M, N, K, true, false, n_seg, (size_t)M * N * kMaxShares);
+  const Plan p = cached_plan(M, N, K, true, n_seg, (size_t)M * N * kMaxShares);
   return p.shares > 1 ? (size_t)M * N * p.shares : 0;
 }
 
@@ -1024,7 +1038,8 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
   }
   a.k_shares = 1;
   const bool tn = layout == GEMM_TN;
-  const Plan p = cached_plan(a.M, a.N, a.K, tn, !tn && a.beside, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0);
+  const Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0,
+                             epi == EPI_ROPE ? a.rope_d : 0);
   if (p.tile[0] < 0) return hipErrorInvalidValue;
   if (p.shares > 1) {
     GemmArgs b = a;

@@ -25,7 +25,7 @@ enum GemmEpilogue {
   EPI_SWIGLU_BWD = 9,
   // NN only, no bias: C = acc with the rotary embedding applied to columns [0, rope_cols) on the fp32 sums (heads of
   // rope_d columns, pairs (i, i + rope_d / 2), position = row % rope_S, table rope_cs[pos][i] = (cos, sin)).  Every
-  // tile's wave strip must hold whole heads: gemm_min_wave_cols(M, N, K) % rope_d == 0.
+  // tile's wave strip must hold whole heads: launch_gemm takes such tiles only.
   EPI_ROPE = 10
 };
 
@@ -45,7 +45,6 @@ struct GemmArgs {
   int M, N, K;
   int beta;
   int group, xcd_remap;  // tile rasterisation (set by launch_gemm)
-  int beside;            // other launches are expected on the device at the same time: prefer tiles that leave them room on a CU
   // TN only: the k axis may be the concatenation of n_seg pieces of seg_k rows each (K = n_seg * seg_k), piece i
   // of A starting at segA[i] and of B at segB[i] (same leading dimensions).  n_seg == 0: one piece, A and B.
   int seg_k, n_seg;
@@ -65,7 +64,7 @@ struct GemmArgs {
 // M, N, K multiples of 128, all leading dimensions multiples of 8.
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 bool gemm_shape_ok(int M, int N, int K);
-int gemm_min_wave_cols(int M, int N, int K, GemmLayout layout);  // columns of a wave's sub-tile, the smallest over the launches that cover the output
+bool gemm_rope_pays(int M, int N, int K, int rope_d, int rope_cols);  // EPI_ROPE can be had and beats EPI_BF16 and the rotary kernel
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg);  // what k_part should hold for a weight gradient over n_seg pieces (0: it would not be used)
 bool gemm_segments_ok(int seg_k, int n_seg);  // seg_k a positive multiple of 128, 1 <= n_seg <= kMaxGemmSegments
 

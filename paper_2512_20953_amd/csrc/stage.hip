@@ -146,10 +146,7 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
     if (const char* m = getenv("AH_DEFER_MATRICES"))
       for (int i = 0; i < 4; i++) s->defer_matrix[i] = (atoi(m) >> i) & 1;
   }
-  {
-    const int wc = gemm_min_wave_cols(s->T, 3 * s->hl, s->h, GEMM_NN);
-    s->rope_in_gemm = s->llama && wc > 0 && wc % s->d == 0 && !getenv("AH_ROPE_KERNEL");  // the variable: tuning aid
-  }
+  s->rope_in_gemm = s->llama && gemm_rope_pays(s->T, 3 * s->hl, s->h, s->d, 2 * s->hl) && !getenv("AH_ROPE_KERNEL");  // the variable: tuning aid
   s->eps = c->norm_eps > 0 ? c->norm_eps : (s->llama ? 1e-6f : 1e-5f);
   s->rope_base = c->rope_base > 0 ? c->rope_base : 10000.f;
   const int h = s->h, hl = s->hl, F = s->F;
@@ -352,12 +349,12 @@ ActPtrs act_ptrs(const ah_stage* s, int slot, int layer) {
   } while (0)
 
 hipError_t gemm(ah_stage* s, int site, GemmLayout lay, GemmEpilogue epi, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N,
-                int K, const void* bias, const void* aux, int ld_aux, void* C2, int beta, hipStream_t st, bool beside = false,
+                int K, const void* bias, const void* aux, int ld_aux, void* C2, int beta, hipStream_t st,
                 float* colsum_part = nullptr, int colsum_acc = 0) {
   GemmArgs g = {};
   g.colsum_part = colsum_part; g.ld_colsum = N; g.colsum_acc = colsum_acc;
   g.A = A; g.B = B; g.C = C; g.C2 = C2; g.bias = bias; g.aux = aux;
-  g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.ld_aux = ld_aux; g.M = M; g.N = N; g.K = K; g.beta = beta; g.beside = beside;
+  g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.ld_aux = ld_aux; g.M = M; g.N = N; g.K = K; g.beta = beta;
   SiteTimer t(s, site, st);
   return launch_gemm(lay, epi, g, st);
 }
@@ -496,7 +493,6 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   const int nb = norm_bwd_blocks(T), cb = colsum_blocks(T);
   const bool rms = s->llama;
   hipEvent_t* ev = s->sync_ev;
-  const bool beside = sd != st;
 #define ON_SIDE(site, expr)              \
   do {                                   \
     SiteTimer t_(s, site, sd);           \
@@ -510,14 +506,14 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   TRY(wgrad(s, SITE_FC2_WGRAD, layer, WG_FC2, wp, a.g, dy, p.g_w2, F, h, st, sd));
   if (!s->llama) {
     // du, and as a by-product of its epilogue the column sums of du per 64-row slab (for db1)
-    TRY(gemm(s, SITE_FC2_DGRAD, GEMM_NT, EPI_GELU_BWD, dy, h, p.w2, h, du, F, T, F, h, nullptr, a.u, F, nullptr, 0, st, beside, part_b1, vp.acc));
+    TRY(gemm(s, SITE_FC2_DGRAD, GEMM_NT, EPI_GELU_BWD, dy, h, p.w2, h, du, F, T, F, h, nullptr, a.u, F, nullptr, 0, st, part_b1, vp.acc));
     TRY(stream_order(st, sd, ev[1]));
     if (vp.finish) ON_SIDE(SITE_COLSUM, launch_colsum_finish(part_b1, T / 64, F, p.g_b1, beta, sd));
   } else {
     // d(gate | up) straight from the product dm = dy Wd^T: the SwiGLU backward is the GEMM's epilogue
     GemmArgs g = {};
     g.A = dy; g.B = p.w2; g.C = du; g.aux = a.u;
-    g.lda = h; g.ldb = h; g.ldc = 2 * F; g.ld_aux = 2 * F; g.swiglu_F = F; g.M = T; g.N = F; g.K = h; g.beside = beside;
+    g.lda = h; g.ldb = h; g.ldc = 2 * F; g.ld_aux = 2 * F; g.swiglu_F = F; g.M = T; g.N = F; g.K = h;
     {
       SiteTimer t(s, SITE_FC2_DGRAD, st);
       TRY(launch_gemm(GEMM_NT, EPI_SWIGLU_BWD, g, st));
@@ -525,7 +521,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     TRY(stream_order(st, sd, ev[1]));
   }
   TRY(wgrad(s, SITE_FC1_WGRAD, layer, WG_FC1, wp, a.c, du, p.g_w1, h, Fu, st, sd));
-  TRY(gemm(s, SITE_FC1_DGRAD, GEMM_NT, EPI_BF16, du, Fu, p.w1, Fu, dsm, h, T, h, Fu, nullptr, nullptr, 0, nullptr, 0, st, beside));  // dc
+  TRY(gemm(s, SITE_FC1_DGRAD, GEMM_NT, EPI_BF16, du, Fu, p.w1, Fu, dsm, h, T, h, Fu, nullptr, nullptr, 0, nullptr, 0, st));  // dc
   // The side stream is done with du.  Only attention backward may have to wait for that, and only where dqkv
   // shares du's buffer; an event nobody waits for is not recorded.
   const bool du_reused = sd != st && dqkv == du;
@@ -539,7 +535,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   }
   // output projection
   TRY(wgrad(s, SITE_WO_WGRAD, layer, WG_WO, wp, a.o, dmid, p.g_wo, hl, h, st, sd));
-  TRY(gemm(s, SITE_WO_DGRAD, GEMM_NT, EPI_BF16, dmid, h, p.wo, h, dsm, hl, T, hl, h, nullptr, nullptr, 0, nullptr, 0, st, beside));  // do
+  TRY(gemm(s, SITE_WO_DGRAD, GEMM_NT, EPI_BF16, dmid, h, p.wo, h, dsm, hl, T, hl, h, nullptr, nullptr, 0, nullptr, 0, st));  // do
   // attention (where dqkv shares its buffer with du: wait until the first MLP matrix's weight gradient has read it)
   if (du_reused) TRY(hipStreamWaitEvent(st, ev[2], 0));
   TIMED(SITE_ATTN_BWD, launch_attention_bwd(a.qkv, a.o, (const float*)a.lse, dsm, dqkv, delta, B, S, s->nh, s->d, s->causal, st));
@@ -550,7 +546,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     if (vp.finish) ON_SIDE(SITE_COLSUM, launch_colsum_finish(part_bqkv, cb, 3 * hl, p.g_bqkv, beta, sd));
   }
   TRY(wgrad(s, SITE_QKV_WGRAD, layer, WG_QKV, wp, a.a, dqkv, p.g_wqkv, h, 3 * hl, st, sd));
-  TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st, beside));  // da
+  TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st));  // da
   // first norm backward; dx = dx_mid + norm_bwd(da); column sums give d(gain), d(offset), d(bo)
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32));
   TRY(stream_order(st, sd, ev[5]));

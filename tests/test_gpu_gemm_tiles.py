@@ -15,7 +15,7 @@ import paper_2512_20953_amd as P
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(128, 128, 128), (128, 384, 256), (384, 640, 384), (256, 256, 1024), (640, 1152, 640), (1024, 1024, 512), (896, 1152, 384),
-          (1024, 2048, 128), (2048, 1024, 640), (1920, 1664, 256), (2048, 2048, 256), (2048, 2048, 4224), (1152, 4352, 128), (4096, 4096, 128)]
+          (1024, 2048, 128), (2048, 1024, 640), (1920, 1664, 256), (2048, 2048, 256), (2048, 2048, 4224), (2048, 2048, 5248), (1152, 4352, 128), (4096, 4096, 128)]
 
 
 def _close(got, ref, k, bf16):
@@ -109,3 +109,59 @@ def test_second_stream_by_size_changes_no_bit(arch, recompute, monkeypatch):
             out.append(st.grads.clone())
         res.append(out)
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+@pytest.mark.parametrize("hidden,ffn", [(2048, 8192), (2048, 4224)])
+def test_dx_depends_on_neither_streams_nor_groups(hidden, ffn, monkeypatch):
+    """2048 x 2048 input gradients over k = 4224 .. 8192, whose tile splits the k axis between its waves: with and without that stream, and with deferred weight gradients, y and dx are the same bits."""
+    res = []
+    for group, gflop in ((1, "0"), (1, "1e9"), (2, "0")):
+        monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", gflop)   # read when the stage is created
+        cfg = P.StageConfig.make(arch="gpt", n_layers=1, hidden=hidden, n_heads=16, head_dim=128, ffn=ffn, seq=2048, mb=1, n_mb=2,
+                                 max_in_flight=group, wgrad_group=group)
+        st = P.Stage(cfg)
+        g = torch.Generator(device="cuda").manual_seed(9)
+        st.params.copy_(torch.randn(st.params.shape, generator=g, device="cuda") * 0.02)
+        st.zero_grads()
+        out = []
+        for m in range(2):
+            x, dy = (torch.randn(2048, hidden, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+            y, dx = torch.empty_like(x), torch.empty_like(x)
+            st.forward(m % group, x, y)
+            st.backward(m % group, dy, dx)
+            out += [y, dx]
+        st.flush_grads()
+        torch.cuda.synchronize()
+        st.close()
+        res.append(out)
+    for other in res[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(res[0], other))
+
+
+@pytest.mark.parametrize("rows,hidden,heads", [(128, 256, 1), (384, 640, 5), (4096, 1024, 8), (8192, 512, 4), (2048, 2048, 16)])
+def test_rotary_epilogue_against_its_kernel(rows, hidden, heads, monkeypatch):
+    """128-wide heads: where it pays, the QKV product takes tiles whose waves hold whole heads although others fit the
+    output better, and rotates in its epilogue; the smallest outputs keep the separate rotary kernel.  Against that
+    kernel, which rounds q and k once more: 2^-9 of their values, and no more than that on the scores, whose size is
+    about 1 here; with the two roundings of the outputs, 2^-7 of the norm in all."""
+    res = []
+    for kernel in (False, True):
+        if kernel:
+            monkeypatch.setenv("AH_ROPE_KERNEL", "1")            # read when the stage is created
+        seq = min(rows, 2048)
+        cfg = P.StageConfig.make(arch="llama", n_layers=1, hidden=hidden, n_heads=heads, head_dim=128, ffn=512, seq=seq, mb=rows // seq, n_mb=1)
+        st = P.Stage(cfg)
+        g = torch.Generator(device="cuda").manual_seed(3)
+        st.params.copy_(torch.randn(st.params.shape, generator=g, device="cuda") * hidden ** -0.5)
+        for name in ("ln1_g", "ln2_g"):
+            st.param_view(0, name).fill_(1.0)
+        x, dy = (torch.randn(rows, hidden, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+        y, dx = torch.empty_like(x), torch.empty_like(x)
+        st.zero_grads()
+        st.forward(0, x, y)
+        st.backward(0, dy, dx)
+        torch.cuda.synchronize()
+        res.append([t.double() for t in (y, dx, st.grad_view(0, "wqkv"))])
+        st.close()
+    for a, b in zip(*res):
+        assert torch.isfinite(a).all() and ((a - b).norm() / b.norm()).item() <= 2.0 ** -7
