@@ -98,6 +98,7 @@ def _load():
     L.ah_gemm_nn_swiglu.argtypes = [vp, vp, vp, vp, i, i, i, vp]
     L.ah_gemm_tn.argtypes = [vp, vp, vp, i, i, i, i, vp]
     L.ah_gemm_tn_segmented.argtypes = [C.POINTER(vp), C.POINTER(vp), i, vp, i, i, i, i, vp]
+    L.ah_gemm_plan.argtypes = [i, i, i, i, i, C.c_uint64, C.POINTER(C.c_int32)]
     L.ah_attention_fwd.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
     L.ah_attention_bwd.argtypes = [vp, vp, vp, vp, vp, vp, i, i, i, i, i, vp]
     L.ah_attention_bwd_static.argtypes = [vp, vp, vp, vp, vp, i, i, i, i, i, vp]
@@ -247,6 +248,14 @@ def gemm_tn_segmented(A_list, B_list, Cout, beta, stream=None):
     pa = (C.c_void_p * n)(*[a.data_ptr() for a in A_list])
     pb = (C.c_void_p * n)(*[b.data_ptr() for b in B_list])
     _check(lib.ah_gemm_tn_segmented(pa, pb, n, _ptr(Cout), M, B_list[0].shape[1], seg_k, int(beta), _stream(stream)))
+
+
+def gemm_plan(layout, M, N, K, n_seg=1, part_floats=0):
+    """How the library covers a product ("nn", "nt", "tn"): (parts of the k axis between blocks,
+    [(columns, tile rows, tile columns, waves along k) per launch])."""
+    o = (C.c_int32 * 10)()
+    _check(lib.ah_gemm_plan(("nn", "nt", "tn").index(layout), M, N, K, n_seg, part_floats, o))
+    return o[1], [tuple(o[2 + 4 * l:6 + 4 * l]) for l in range(o[0])]
 
 
 def attention_fwd(qkv, o, lse, B, S, nh, d, causal=True, stream=None):

@@ -66,3 +66,20 @@ extern "C" int ah_gemm_tn_segmented(const void* const* A_seg, const void* const*
   g.lda = M; g.ldb = N; g.ldc = N; g.M = M; g.N = N; g.K = seg_k * n_seg; g.beta = beta;
   return hip_status(launch_gemm(GEMM_TN, EPI_F32_ACC, g, (hipStream_t)stream), "ah_gemm_tn_segmented");
 }
+
+extern "C" int ah_gemm_plan(int layout, int M, int N, int K, int n_seg, uint64_t part_floats, int32_t out[10]) {
+  if (!out || layout < GEMM_NN || layout > GEMM_TN || n_seg < 1 || n_seg > kMaxGemmSegments)
+    return set_error(AH_EINVAL, "ah_gemm_plan: bad argument");
+  GemmPlanInfo p;
+  if (K % n_seg || !gemm_segments_ok(K / n_seg, n_seg) || !gemm_plan((GemmLayout)layout, M, N, K, n_seg, part_floats, 0, &p)) return set_error(AH_EUNSUPPORTED, "ah_gemm_plan: %s", kShapeMsg);
+  out[0] = p.launches;
+  out[1] = p.shares;
+  for (int i = 0; i < 2; i++) {
+    const bool there = i < p.launches;
+    out[2 + 4 * i] = there ? p.cols[i] : 0;
+    out[3 + 4 * i] = p.bm[i];
+    out[4 + 4 * i] = p.bn[i];
+    out[5 + 4 * i] = p.wgk[i];
+  }
+  return AH_OK;
+}

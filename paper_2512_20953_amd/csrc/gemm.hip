@@ -805,21 +805,28 @@ bool gemm_segments_ok(int seg_k, int n_seg) {
 namespace {
 
 // Tile choice.  The chip's 256 CUs take the tiles of a launch in rounds, one or (where half the LDS suffices) two to
-// a CU; the time of a round is a + b K.  Both are measured, in us with K in units of 1024: 256 and 512 tiles of each
-// kind, K = 256 .. 16384, the weights read from HBM, replayed back to back, so that a includes the gap between
-// launches.  fwd is for the products with a k-contiguous operand (mean of NN and NT), tn for the weight gradient.
-// A round that leaves CUs idle is shorter (the board is limited by power, the caches by what all CUs ask of them):
-// 160 tiles of 256 x 256 take 0.78 and 64 of them 0.70 of the time of 256.
-struct Rate { float a, b; };
+// a CU; the time of a full round is a + b K, that of one of which only the share `fill` of the slots is taken is
+// 1 - f (1 - fill) times that (the board is limited by power, the caches by what all CUs ask of them).  Measured, in us
+// with K in units of 1024: 256 and 512 tiles of each kind, K = 256 .. 16384, the weights read from HBM, replayed back to
+// back, so that a includes the gap between launches.  fwd is for the products with a k-contiguous operand (mean of NN and
+// NT), tn for the weight gradient.
+// f: 64 and 160 tiles of 256 x 256 take 0.70 and 0.78 of the time of 256 (f = 0.40, 0.59; 0.47 and 0.57 over 54 products
+// of 64 .. 127 and 128 .. 191 tiles, 0.49 and 0.60 in the weight gradient).  With 0.35 there too, 130 .. 192 such tiles
+// lost to 520 .. 768 of 128 x 128: 2560 x 3840 x 1536 (NT) 39.1 us against 32.8, 4096 x 3072 x 1024 with cold operands
+// 38.0 / 30.5.
+// tn of the two small tiles: fitted to 1500 weight gradients of K = 128 .. 32768, scaled like the other tiles' rows
+// (those over-estimate by 8 %).  The line through K >= 256 alone was 10-35 % short at K = 128 .. 512, where these tiles then
+// displaced 128 x 128: 3200 x 896 x 128 8.6 us against 7.3.
+struct Rate { float a, b, f; };
 struct TileCfg { int bm, bn, wgm, wgn, wgk; Rate fwd1, fwd2, tn1, tn2; };  // one, two tiles to a CU
 const TileCfg kTiles[] = {
-  {256, 256, 2, 2, 1, {11.5f, 23.1f}, {21.8f, 44.9f}, {16.3f, 23.3f}, {33.5f, 45.4f}},
-  {256, 128, 2, 2, 1, {7.1f, 14.1f}, {10.8f, 28.5f}, {12.3f, 12.7f}, {20.4f, 25.2f}},
-  {128, 256, 2, 2, 1, {7.4f, 13.7f}, {12.1f, 27.4f}, {11.0f, 12.8f}, {20.5f, 25.0f}},
-  {128, 128, 2, 2, 1, {4.4f, 9.0f}, {5.9f, 14.7f}, {8.2f, 8.0f}, {11.0f, 15.3f}},
-  {128, 128, 1, 1, 4, {7.5f, 7.6f}, {14.2f, 14.5f}, {0.f, 0.f}, {0.f, 0.f}},   // not built for the weight gradient (see namespace ksplit)
-  {64, 128, 1, 2, 2, {3.8f, 5.7f}, {4.8f, 10.5f}, {5.6f, 6.0f}, {7.5f, 10.9f}},
-  {64, 64, 1, 1, 4, {3.6f, 3.3f}, {4.3f, 6.8f}, {4.5f, 3.8f}, {5.5f, 7.3f}}};
+  {256, 256, 2, 2, 1, {11.5f, 23.1f, .45f}, {21.8f, 44.9f, .35f}, {16.3f, 23.3f, .50f}, {33.5f, 45.4f, .35f}},
+  {256, 128, 2, 2, 1, {7.1f, 14.1f, .35f}, {10.8f, 28.5f, .35f}, {12.3f, 12.7f, .35f}, {20.4f, 25.2f, .35f}},
+  {128, 256, 2, 2, 1, {7.4f, 13.7f, .35f}, {12.1f, 27.4f, .35f}, {11.0f, 12.8f, .35f}, {20.5f, 25.0f, .35f}},
+  {128, 128, 2, 2, 1, {4.4f, 9.0f, .35f}, {5.9f, 14.7f, .35f}, {8.2f, 8.0f, .35f}, {11.0f, 15.3f, .35f}},
+  {128, 128, 1, 1, 4, {7.5f, 7.6f, .35f}, {14.2f, 14.5f, .35f}, {}, {}},   // not built for the weight gradient (see namespace ksplit)
+  {64, 128, 1, 2, 2, {3.8f, 5.7f, .35f}, {4.8f, 10.5f, .35f}, {6.6f, 5.6f, .23f}, {8.7f, 10.1f, .14f}},
+  {64, 64, 1, 1, 4, {3.6f, 3.3f, .35f}, {4.3f, 6.8f, .35f}, {5.7f, 3.5f, .15f}, {6.6f, 6.4f, .03f}}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kWholeCuTile = 4;      // the tile above whose blocks take all of a CU's LDS although the launch is small
 constexpr float kLaunchGap = 2.5f;   // the part of a that later rounds of the same launch do not pay
@@ -854,7 +861,7 @@ float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
   if (rest > 0) {
     const Rate& r = rest > 256 ? r2 : r1;
     const float fill = (float)rest / (rest > 256 ? 512 : 256);
-    us += (r.a + r.b * k) * (0.65f + 0.35f * fill) - kLaunchGap;
+    us += (r.a + r.b * k) * (1.f - r.f * (1.f - fill)) - kLaunchGap;
   }
   return us;
 }
@@ -962,6 +969,21 @@ bool gemm_rope_pays(int M, int N, int K, int d, int rope_cols) {
   const Plan heads = cached_plan(M, N, K, false, 1, 0, d), any = cached_plan(M, N, K, false);
   if (heads.tile[0] < 0) return false;
   return plan_cost(heads, M, N, K) <= plan_cost(any, M, N, K) + 3.f + (float)M * rope_cols * 4.f / 4.5e6f;
+}
+
+bool gemm_plan(GemmLayout layout, int M, int N, int K, int n_seg, size_t part_floats, int head, GemmPlanInfo* out) {
+  if (!gemm_shape_ok(M, N, K)) return false;
+  const bool tn = layout == GEMM_TN;
+  const Plan p = cached_plan(M, N, K, tn, tn ? n_seg : 1, tn ? part_floats : 0, head);
+  if (p.tile[0] < 0) return false;
+  *out = {p.parts, p.shares, {p.n0, N - p.n0}, {}, {}, {}};
+  for (int i = 0; i < p.parts; i++) {
+    const TileCfg& t = kTiles[p.tile[i]];
+    out->bm[i] = t.bm;
+    out->bn[i] = t.bn;
+    out->wgk[i] = t.wgk;
+  }
+  return true;
 }
 
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg) {

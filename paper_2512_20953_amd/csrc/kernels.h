@@ -66,6 +66,10 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, h
 bool gemm_shape_ok(int M, int N, int K);
 bool gemm_rope_pays(int M, int N, int K, int rope_d, int rope_cols);  // EPI_ROPE can be had and beats EPI_BF16 and the rotary kernel
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg);  // what k_part should hold for a weight gradient over n_seg pieces (0: it would not be used)
+// The launches that launch_gemm covers an output with: column ranges of cols[i], tiles of bm x bn whose waves take wgk
+// shares of each k-block, the k axis cut into `shares` parts between blocks.  head: EPI_ROPE's head width (else 0).
+struct GemmPlanInfo { int launches, shares, cols[2], bm[2], bn[2], wgk[2]; };
+bool gemm_plan(GemmLayout layout, int M, int N, int K, int n_seg, size_t part_floats, int head, GemmPlanInfo* out);
 bool gemm_segments_ok(int seg_k, int n_seg);  // seg_k a positive multiple of 128, 1 <= n_seg <= kMaxGemmSegments
 
 // ---- attention (d = 64 or 128, S multiple of 128) ----

@@ -1,0 +1,45 @@
+"""The launcher's choice of tiles (host arithmetic: no GPU)."""
+import random
+
+import pytest
+
+import paper_2512_20953_amd as P
+
+
+@pytest.mark.parametrize("layout,M,N,K,tile", [
+    # weight gradients over few tokens: the 128 x 128 tile, whose fixed cost is below that of two rounds' worth of
+    # small ones (measured at 3200 x 896 x 128: 7.3 us against 8.6 for 64 x 128)
+    ("tn", 3200, 896, 128, (128, 128)), ("tn", 7936, 384, 128, (128, 128)), ("tn", 1152, 2176, 128, (128, 128)),
+    ("tn", 256, 11520, 128, (128, 128)), ("tn", 2176, 1792, 128, (128, 128)),
+    # 130 .. 192 tiles of 256 x 256 on 256 CUs against 520 .. 768 of 128 x 128 (2560 x 3840 x 1536: 36 us against 39)
+    ("nn", 2560, 3840, 1536, (256, 256)), ("nt", 2560, 3840, 1536, (256, 256)), ("nt", 6656, 1280, 1920, (256, 256)),
+    ("nn", 2560, 3328, 1664, (256, 256)), ("nn", 4864, 1792, 1536, (256, 256)), ("nn", 2048, 4608, 1536, (256, 256)),
+    ("nn", 4096, 3072, 1024, (256, 256)),
+])
+def test_the_measured_faster_tile_is_taken(layout, M, N, K, tile):
+    shares, launches = P.gemm_plan(layout, M, N, K)
+    assert shares == 1 and [l[1:3] for l in launches] == [tile]
+
+
+def test_plans_cover_the_output():
+    rng = random.Random(3)
+    size = lambda hi: 128 * max(1, round(2 ** rng.uniform(0, hi)))
+    for _ in range(1500):
+        layout = rng.choice(["nn", "nt", "tn"])
+        n_seg = rng.randint(1, 16) if layout == "tn" else 1
+        M, N, K = size(6), size(6), size(5) * n_seg
+        part = M * N * rng.choice([0, 2, 5, 16]) if layout == "tn" else 0
+        shares, launches = P.gemm_plan(layout, M, N, K, n_seg, part)
+        assert sum(l[0] for l in launches) == N
+        for cols, bm, bn, _ in launches:
+            assert cols > 0 and M % bm == 0 and cols % bn == 0
+        if shares > 1:       # whole pieces, or whole pairs of k-blocks of one piece; the partial sums have room
+            assert len(launches) == 1 and M * N * shares <= part
+            assert n_seg % shares == 0 if n_seg > 1 else K % (128 * shares) == 0
+
+
+def test_bad_plan_arguments_are_refused():
+    for bad, status in ((("nn", 100, 128, 128), 5), (("tn", 128, 128, 128, 0), 1), (("tn", 128, 128, 128, 17), 1), (("tn", 128, 128, 384, 2), 5)):
+        with pytest.raises(P.AhError) as e:
+            P.gemm_plan(*bad)
+        assert e.value.status == status
