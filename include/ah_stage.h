@@ -252,9 +252,9 @@ int ah_gemm_tn_segmented(const void* const* A_seg, const void* const* B_seg, int
 /* How the library covers an M x N product over K (layout 0: nn, 1: nt, 2: tn over n_seg pieces, with room for
  * part_floats partial sums as a stage's deferred weight gradients have; else n_seg 1 and 0): host arithmetic, for
  * tests and tuning.  out[0] launches (1 or 2, side by side over columns), out[1] parts of the k axis between blocks;
- * then for each of two launches (zeros where there is one) its columns, tile rows, tile columns, and the waves of a
- * block that share a tile along k. */
-int ah_gemm_plan(int layout, int M, int N, int K, int n_seg, uint64_t part_floats, int32_t out[10]);
+ * then for each of two launches (zeros where there is one) its columns, the rows and columns of a tile, the waves of a
+ * block that share a tile along k, and the rows of tiles that blocks walk together. */
+int ah_gemm_plan(int layout, int M, int N, int K, int n_seg, uint64_t part_floats, int32_t out[12]);
 /* Attention over packed qkv[B*S, 3*nh*d] (bf16, [Q|K|V], head-major): o[B*S, nh*d] bf16, lse[B, nh, S] fp32.
  * causal != 0: query i attends to keys 0..i of its sequence; causal == 0: to all S keys. */
 int ah_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int nh, int d, int causal, void* hip_stream);

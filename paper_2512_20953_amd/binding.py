@@ -252,10 +252,10 @@ def gemm_tn_segmented(A_list, B_list, Cout, beta, stream=None):
 
 def gemm_plan(layout, M, N, K, n_seg=1, part_floats=0):
     """How the library covers a product ("nn", "nt", "tn"): (parts of the k axis between blocks,
-    [(columns, tile rows, tile columns, waves along k) per launch])."""
-    o = (C.c_int32 * 10)()
+    [(columns, rows of a tile, columns of a tile, waves along k, tile rows walked together) per launch])."""
+    o = (C.c_int32 * 12)()
     _check(lib.ah_gemm_plan(("nn", "nt", "tn").index(layout), M, N, K, n_seg, part_floats, o))
-    return o[1], [tuple(o[2 + 4 * l:6 + 4 * l]) for l in range(o[0])]
+    return o[1], [tuple(o[2 + 5 * l:7 + 5 * l]) for l in range(o[0])]
 
 
 def attention_fwd(qkv, o, lse, B, S, nh, d, causal=True, stream=None):

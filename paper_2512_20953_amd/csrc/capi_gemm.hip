@@ -67,7 +67,7 @@ extern "C" int ah_gemm_tn_segmented(const void* const* A_seg, const void* const*
   return hip_status(launch_gemm(GEMM_TN, EPI_F32_ACC, g, (hipStream_t)stream), "ah_gemm_tn_segmented");
 }
 
-extern "C" int ah_gemm_plan(int layout, int M, int N, int K, int n_seg, uint64_t part_floats, int32_t out[10]) {
+extern "C" int ah_gemm_plan(int layout, int M, int N, int K, int n_seg, uint64_t part_floats, int32_t out[12]) {
   if (!out || layout < GEMM_NN || layout > GEMM_TN || n_seg < 1 || n_seg > kMaxGemmSegments)
     return set_error(AH_EINVAL, "ah_gemm_plan: bad argument");
   GemmPlanInfo p;
@@ -76,10 +76,11 @@ extern "C" int ah_gemm_plan(int layout, int M, int N, int K, int n_seg, uint64_t
   out[1] = p.shares;
   for (int i = 0; i < 2; i++) {
     const bool there = i < p.launches;
-    out[2 + 4 * i] = there ? p.cols[i] : 0;
-    out[3 + 4 * i] = p.bm[i];
-    out[4 + 4 * i] = p.bn[i];
-    out[5 + 4 * i] = p.wgk[i];
+    out[2 + 5 * i] = there ? p.cols[i] : 0;
+    out[3 + 5 * i] = p.bm[i];
+    out[4 + 5 * i] = p.bn[i];
+    out[5 + 5 * i] = p.wgk[i];
+    out[6 + 5 * i] = p.raster[i];
   }
   return AH_OK;
 }

@@ -304,9 +304,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   const int wm = wmn / WGN, wn = wmn % WGN;
 
   // block -> tile: consecutive logical tiles share an XCD (blocks are dealt to the
-  // 8 XCDs round-robin), and run down groups of 4 tile-rows so that the 32 tiles in
-  // flight on one XCD reuse the same operand panels in its L2 (4 of A, 8 of B; 8 and 4 have the same size but took 0.5 %
-  // longer on the 7B shard's layer, 1 % on the 13B and LLaMA-style layers; 2, 3, 5, 6 and 16 rows are no better).
+  // 8 XCDs round-robin), and run down groups of about 4 tile-rows (raster_rows) so that the 32 tiles in
+  // flight on one XCD reuse the same operand panels in its L2.
   // With the k axis shared by blocks (kernels.h) the shares follow each other: an XCD then works on one share's operands.
   constexpr bool KSHARES = AKS && BKS && EPI == EPI_F32_SET;
   const int shares = KSHARES ? g.k_shares : 1;
@@ -936,8 +935,21 @@ Plan cached_plan(int M, int N, int K, bool tn, int n_seg = 1, size_t part_floats
   return p;
 }
 
+// Tile rows per raster group.  Four: the 32 tiles an XCD has in flight then read 4 panels of A and 8 of B (8 and 4 have the
+// same size but took 0.5 % longer on the 7B shard's layer, 1 % on the 13B and LLaMA-style layers; 2, 3, 5, 6 and 16 rows
+// are no better there).  A last group of one or two rows would read the whole of B for itself: where that is a fair part
+// of the output, the rows are spread evenly instead (forward and input gradients, geometric means over 18 .. 188 products
+// against groups of four: 5 rows 0.965, 6 0.975, 9 0.978, 10 0.983; 640 x 4096 x 1152 14.8 -> 12.5 us, 1152 x 4096 x 1280 22.4 -> 20.2.  Weight gradients
+// 0.990 .. 1.002; 7 and 11 rows 0.998 .. 1.004, 13 and more 0.993 .. 1.03, so those keep groups of four).
+int raster_rows(int tiles_m) {
+  if (tiles_m >= 12 || tiles_m % 4 == 0 || tiles_m % 4 == 3) return 4;
+  const int groups = std::max(tiles_m / 4, 1);
+  return (tiles_m + groups - 1) / groups;
+}
+
 template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
-hipError_t run(const GemmArgs& a, hipStream_t s) {
+hipError_t run(GemmArgs a, hipStream_t s) {
+  if (a.group <= 0) a.group = raster_rows(a.M / BM);
   dim3 grid((a.M / BM) * (a.N / BN) * (AKS && BKS && EPI == EPI_F32_SET ? a.k_shares : 1));
   hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI>), grid, dim3(64 * WGM * WGN * WGK), 0, s, a);
   return hipGetLastError();
@@ -976,12 +988,13 @@ bool gemm_plan(GemmLayout layout, int M, int N, int K, int n_seg, size_t part_fl
   const bool tn = layout == GEMM_TN;
   const Plan p = cached_plan(M, N, K, tn, tn ? n_seg : 1, tn ? part_floats : 0, head);
   if (p.tile[0] < 0) return false;
-  *out = {p.parts, p.shares, {p.n0, N - p.n0}, {}, {}, {}};
+  *out = {p.parts, p.shares, {p.n0, N - p.n0}, {}, {}, {}, {}};
   for (int i = 0; i < p.parts; i++) {
     const TileCfg& t = kTiles[p.tile[i]];
     out->bm[i] = t.bm;
     out->bn[i] = t.bn;
     out->wgk[i] = t.wgk;
+    out->raster[i] = raster_rows(M / t.bm);
   }
   return true;
 }
@@ -1045,7 +1058,7 @@ GemmArgs column_range(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, in
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in, hipStream_t s) {
   GemmArgs a = a_in;
   static int grp = -1, remap = -1;
-  if (grp < 0) { grp = getenv("AH_GEMM_GROUP") ? atoi(getenv("AH_GEMM_GROUP")) : 4; remap = getenv("AH_GEMM_NOREMAP") ? 0 : 1; }
+  if (grp < 0) { grp = getenv("AH_GEMM_GROUP") ? atoi(getenv("AH_GEMM_GROUP")) : 0; remap = getenv("AH_GEMM_NOREMAP") ? 0 : 1; }
   a.group = grp; a.xcd_remap = remap;
   if (!gemm_shape_ok(a.M, a.N, a.K)) return hipErrorInvalidValue;
   if (a.n_seg != 0) {  // pieces along k: weight-gradient layout only, and the pieces must add up to K

@@ -44,7 +44,7 @@ struct GemmArgs {
   int rope_S, rope_d, rope_cols;
   int M, N, K;
   int beta;
-  int group, xcd_remap;  // tile rasterisation (set by launch_gemm)
+  int group, xcd_remap;  // tile rasterisation (set by launch_gemm; group 0: by the tile rows of the launch)
   // TN only: the k axis may be the concatenation of n_seg pieces of seg_k rows each (K = n_seg * seg_k), piece i
   // of A starting at segA[i] and of B at segB[i] (same leading dimensions).  n_seg == 0: one piece, A and B.
   int seg_k, n_seg;
@@ -67,8 +67,9 @@ bool gemm_shape_ok(int M, int N, int K);
 bool gemm_rope_pays(int M, int N, int K, int rope_d, int rope_cols);  // EPI_ROPE can be had and beats EPI_BF16 and the rotary kernel
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg);  // what k_part should hold for a weight gradient over n_seg pieces (0: it would not be used)
 // The launches that launch_gemm covers an output with: column ranges of cols[i], tiles of bm x bn whose waves take wgk
-// shares of each k-block, the k axis cut into `shares` parts between blocks.  head: EPI_ROPE's head width (else 0).
-struct GemmPlanInfo { int launches, shares, cols[2], bm[2], bn[2], wgk[2]; };
+// shares of each k-block, walked in groups of `raster` tile rows, the k axis cut into `shares` parts between blocks.
+// head: EPI_ROPE's head width (else 0).
+struct GemmPlanInfo { int launches, shares, cols[2], bm[2], bn[2], wgk[2], raster[2]; };
 bool gemm_plan(GemmLayout layout, int M, int N, int K, int n_seg, size_t part_floats, int head, GemmPlanInfo* out);
 bool gemm_segments_ok(int seg_k, int n_seg);  // seg_k a positive multiple of 128, 1 <= n_seg <= kMaxGemmSegments
 

@@ -31,7 +31,7 @@ def test_plans_cover_the_output():
         part = M * N * rng.choice([0, 2, 5, 16]) if layout == "tn" else 0
         shares, launches = P.gemm_plan(layout, M, N, K, n_seg, part)
         assert sum(l[0] for l in launches) == N
-        for cols, bm, bn, _ in launches:
+        for cols, bm, bn, _, _ in launches:
             assert cols > 0 and M % bm == 0 and cols % bn == 0
         if shares > 1:       # whole pieces, or whole pairs of k-blocks of one piece; the partial sums have room
             assert len(launches) == 1 and M * N * shares <= part
@@ -43,3 +43,15 @@ def test_bad_plan_arguments_are_refused():
         with pytest.raises(P.AhError) as e:
             P.gemm_plan(*bad)
         assert e.value.status == status
+
+
+@pytest.mark.parametrize("layout,M,N,K", [("nn", 640, 4096, 1152), ("nt", 768, 4096, 1152), ("nn", 1152, 4096, 1280), ("nt", 1280, 3712, 128),
+                                          ("nn", 896, 4096, 1152), ("nn", 1024, 4096, 1152), ("nn", 1664, 4096, 1152)])
+def test_no_raster_group_of_one_or_two_rows_in_small_outputs(layout, M, N, K):
+    """Such a group reads the whole second operand for itself; groups hold about four rows and at most six."""
+    _, launches = P.gemm_plan(layout, M, N, K)
+    for _, bm, _, _, group in launches:
+        rows = M // bm
+        assert 4 <= group <= 6
+        if rows < 12:
+            assert rows % group == 0 or rows % group >= 3, (rows, group)
