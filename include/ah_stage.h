@@ -178,6 +178,10 @@ int ah_stage_forward(ah_stage_t* st, int slot, const void* x, void* y, void* hip
  * sums. */
 int ah_stage_backward(ah_stage_t* st, int slot, const void* dy, void* dx, void* hip_stream);
 
+/* How many streams ah_stage_backward enqueues on: 1 (the caller's), or 2 where the products of single micro-batches run
+ * beside it on a stream of the library's own (decided by sizes when the stage is created; host arithmetic, for tests). */
+int ah_stage_backward_streams(const ah_stage_t* st, int* n_streams);
+
 /* Closes an incomplete group of the gradient accumulation over micro-batches (Section III-A; see wgrad_group).
  * Takes the gradients of the micro-batches whose backward has run but
  * whose group is incomplete (wgrad_group > 1 and a micro-batch count that is

@@ -81,6 +81,7 @@ def _load():
     L.ah_stage_param_layout.argtypes = [vp, i, i, C.POINTER(C.c_uint64), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
     L.ah_stage_forward.argtypes = [vp, i, vp, vp, vp]
     L.ah_stage_backward.argtypes = [vp, i, vp, vp, vp]
+    L.ah_stage_backward_streams.argtypes = [vp, C.POINTER(i)]
     L.ah_stage_grads.argtypes = [vp, C.POINTER(vp), C.POINTER(C.c_uint64)]
     L.ah_stage_zero_grads.argtypes = [vp, vp]
     L.ah_stage_flush_grads.argtypes = [vp, vp]
@@ -194,6 +195,11 @@ class Stage:
 
     def flush_grads(self, stream=None):
         _check(lib.ah_stage_flush_grads(self._h, _stream(stream)))
+
+    def backward_streams(self):
+        n = C.c_int()
+        _check(lib.ah_stage_backward_streams(self._h, C.byref(n)))
+        return n.value
 
     def grads_ptr(self):
         p, n = C.c_void_p(), C.c_uint64()

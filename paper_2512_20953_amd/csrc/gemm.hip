@@ -915,10 +915,10 @@ Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats, int 
   return p;
 }
 
-// of a forward product, which is never cut into shares
-float plan_cost(const Plan& p, int M, int N, int K) {
-  return p.parts == 1 ? tile_cost(p.tile[0], M, N, K, false)
-                      : tile_cost(p.tile[0], M, p.n0, K, false) + tile_cost(p.tile[1], M, N - p.n0, K, false) + kSecondLaunch;
+float plan_cost(const Plan& p, int M, int N, int K, bool tn) {
+  if (p.shares > 1) return tile_cost(p.tile[0], M, N, K, tn, p.shares) + shares_cost(M, N, p.shares);
+  return p.parts == 1 ? tile_cost(p.tile[0], M, N, K, tn)
+                      : tile_cost(p.tile[0], M, p.n0, K, tn) + tile_cost(p.tile[1], M, N - p.n0, K, tn) + kSecondLaunch;
 }
 
 // make_plan is a search over a few thousand candidates: remembered per problem
@@ -980,7 +980,7 @@ bool gemm_rope_pays(int M, int N, int K, int d, int rope_cols) {
   if (!gemm_shape_ok(M, N, K) || d <= 0 || d % 16) return false;
   const Plan heads = cached_plan(M, N, K, false, 1, 0, d), any = cached_plan(M, N, K, false);
   if (heads.tile[0] < 0) return false;
-  return plan_cost(heads, M, N, K) <= plan_cost(any, M, N, K) + 3.f + (float)M * rope_cols * 4.f / 4.5e6f;
+  return plan_cost(heads, M, N, K, false) <= plan_cost(any, M, N, K, false) + 3.f + (float)M * rope_cols * 4.f / 4.5e6f;
 }
 
 bool gemm_plan(GemmLayout layout, int M, int N, int K, int n_seg, size_t part_floats, int head, GemmPlanInfo* out) {
@@ -997,6 +997,22 @@ bool gemm_plan(GemmLayout layout, int M, int N, int K, int n_seg, size_t part_fl
     out->raster[i] = raster_rows(M / t.bm);
   }
   return true;
+}
+
+GemmTime gemm_wgrad_time(int M, int N, int K, int n_seg, size_t part_floats) {
+  if (!gemm_shape_ok(M, N, K)) return {};
+  const Plan p = cached_plan(M, N, K, true, n_seg, part_floats);
+  if (p.tile[0] < 0) return {};
+  GemmTime t = {plan_cost(p, M, N, K, true), 0.f, 0.f};
+  for (int i = 0; i < p.parts; i++) {
+    const TileCfg& c = kTiles[p.tile[i]];
+    const int n = p.parts == 1 ? N : i ? N - p.n0 : p.n0;
+    const long tiles = (long)(M / c.bm) * (n / c.bn) * p.shares, rounds = (tiles + 255) / 256;
+    const float us = t.us * n / N;
+    if (c.bm * c.bn <= 128 * 128) t.room_us += us;    // (the 128 x 128 tile with four k shares is not built for this product)
+    else t.idle_us += us * (1.f - (float)tiles / (256 * rounds));
+  }
+  return t;
 }
 
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg) {

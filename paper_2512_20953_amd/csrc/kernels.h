@@ -65,6 +65,10 @@ struct GemmArgs {
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 bool gemm_shape_ok(int M, int N, int K);
 bool gemm_rope_pays(int M, int N, int K, int rope_d, int rope_cols);  // EPI_ROPE can be had and beats EPI_BF16 and the rotary kernel
+// A weight gradient's time by the launcher's model; of it, that of launches whose blocks leave room for others on their
+// CUs, and of the other launches the share of the CUs that stays idle.
+struct GemmTime { float us, room_us, idle_us; };
+GemmTime gemm_wgrad_time(int M, int N, int K, int n_seg, size_t part_floats);
 size_t gemm_k_part_floats(int M, int N, int K, int n_seg);  // what k_part should hold for a weight gradient over n_seg pieces (0: it would not be used)
 // The launches that launch_gemm covers an output with: column ranges of cols[i], tiles of bm x bn whose waves take wgk
 // shares of each k-block, walked in groups of `raster` tile rows, the k axis cut into `shares` parts between blocks.

@@ -60,8 +60,8 @@ struct ah_stage {
   // Deferred weight gradients: with group > 1 the four weight-gradient products of a layer run once per `group`
   // micro-batches, over the concatenation of their tokens, instead of once per micro-batch.
   int group;
-  bool defer_matrix[4];         // by WgradWhich (see plan())
-  size_t k_part_floats;
+  bool defer;                   // whether the products wait for their group (see wgrads_wait)
+  size_t k_part_floats;         // room for the partial sums of a product whose k axis is shared by blocks
   bool force_immediate;         // the profiler's per-layer timing runs undeferred
   PendLayout pend;
   VecPartLayout vpart;
@@ -73,7 +73,7 @@ struct ah_stage {
   // reductions); created on first use, joined back into the caller's stream before every return.
   hipStream_t side;
   hipEvent_t sync_ev[8];
-  bool side_ready, side_off, side_pays;
+  bool side_ready, side_pays;
   std::vector<hipEvent_t> ev_pool;           // pairs, in launch order
   std::vector<int> ev_site;                  // site of pair i
   std::vector<int> ev_mult;                  // micro-batches covered by the launch of pair i
@@ -115,6 +115,33 @@ std::array<std::array<int, 2>, 4> wgrad_shapes(const ah_stage* s) {
   return {{{s->F, s->h}, {s->h, Fu}, {s->hl, s->h}, {s->h, 3 * s->hl}}};
 }
 
+// Whether a group's weight-gradient products are deferred to its end.  There they have a k axis G times as long: fewer
+// fp32 passes over the matrices, one prologue and epilogue, and for a small output enough k for shares that fill the chip.
+// Taken per micro-batch on the second stream they fill what the main chain leaves of the chip instead: by the model's
+// times, about three quarters of launches whose blocks leave room on their CUs and the idle CUs' share of the others, for
+// 40 us of cross-stream orderings.  Small groups of middle-sized products gain more from that.  The three numbers are
+// fitted to 17 stages at groups of 2 .. 16 and hold on 14 others (us per micro-batch and layer, per micro-batch / deferred):
+// 1280-wide, 3072 tokens: G = 2 515 / 568, G = 4 519 / 553, G = 8 521 / 517; BERT-Large: 513 / 542, 513 / 513, 514 / 493;
+// 768-wide BERT: 390 / 428, 389 / 397, 382 / 382; 2048-wide GPT: 889 / 853, 895 / 831, 898 / 823; 512-wide: 193 / 174,
+// 184 / 160, 185 / 156.  Of 117 pairs of stage and group the choice is more than 2 % off the better one in nine, 4.4 % at
+// most.  From groups of five on deferring is level or better, with exceptions of up to 4 % (1536-wide LLaMA-style, 4096
+// tokens, G = 8 993 / 1033) that the model does not see.  Deferring some matrices and not others was slower than the better
+// of the two on 16 of 17 stages.
+bool wgrads_wait(const ah_stage* s) {
+  if (s->group <= 1) return false;
+  if (const char* e = getenv("AH_DEFER_WGRADS")) return atoi(e) != 0;  // tuning and test aid
+  if (s->group > 4 || !s->side_pays) return true;
+  float at_once = 0.f, hidden = -40.f, deferred = 0.f;
+  for (const auto& mn : wgrad_shapes(s)) {
+    const GemmTime t = gemm_wgrad_time(mn[0], mn[1], s->T, 1, 0);
+    at_once += t.us;
+    hidden += 0.75f * t.room_us + t.idle_us;
+    const int K = s->T * s->group;
+    deferred += gemm_wgrad_time(mn[0], mn[1], K, s->group, gemm_k_part_floats(mn[0], mn[1], K, s->group)).us / s->group;
+  }
+  return deferred <= at_once - hidden;
+}
+
 void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->cfg = *c;
   s->L = c->n_layers;
@@ -130,9 +157,6 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->res32 = c->residual_fp32 != 0;
   s->group = c->wgrad_group > 1 ? c->wgrad_group : 1;
   {
-    // A deferred product runs at the end of its group with a k axis G times as long: fewer fp32 passes over the matrix,
-    // one prologue and epilogue, and for a small output enough k for shares that fill the chip.
-    for (bool& m : s->defer_matrix) m = true;
     // Per-micro-batch products on the second stream hide the launches' tails and fill idle CUs (13B layer 3.86 -> 3.68
     // ms, a 512-wide one over 4096 tokens 0.55 -> 0.49), but each layer then pays for eight cross-stream orderings,
     // ~40 us of host and queue time: where a layer's products are shorter than that they cost more than they hide
@@ -140,11 +164,9 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
     // 26 GFLOP 492 / 552).
     double gflop = 0;
     for (const auto& mn : wgrad_shapes(s)) gflop += 2e-9 * s->T * mn[0] * mn[1];
-    const char* e = getenv("AH_SIDE_STREAM_MIN_GFLOP");  // tuning and test aid
-    s->side_pays = gflop >= (e ? atof(e) : 12.0);
-    // tuning and test aid: the choice given outright, bit i = matrix i (second MLP, first MLP, out-projection, QKV)
-    if (const char* m = getenv("AH_DEFER_MATRICES"))
-      for (int i = 0; i < 4; i++) s->defer_matrix[i] = (atoi(m) >> i) & 1;
+    const char* e = getenv("AH_SIDE_STREAM_MIN_GFLOP");  // tuning and test aid; AH_NO_SIDE_STREAM keeps everything on the caller's stream
+    s->side_pays = gflop >= (e ? atof(e) : 12.0) && !getenv("AH_NO_SIDE_STREAM");
+    s->defer = wgrads_wait(s);
   }
   s->rope_in_gemm = s->llama && gemm_rope_pays(s->T, 3 * s->hl, s->h, s->d, 2 * s->hl) && !getenv("AH_ROPE_KERNEL");  // the variable: tuning aid
   s->eps = c->norm_eps > 0 ? c->norm_eps : (s->llama ? 1e-6f : 1e-5f);
@@ -231,7 +253,7 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
   w.vec_part = take(s->group > 1 ? (size_t)s->L * s->vpart.bytes : 0);
   // partial sums of a deferred product whose k axis is shared by blocks: one product at a time uses them
   s->k_part_floats = 0;
-  if (s->group > 1)
+  if (s->defer)
     for (const auto& mn : wgrad_shapes(s))
       s->k_part_floats = std::max(s->k_part_floats, gemm_k_part_floats(mn[0], mn[1], s->T * s->group, s->group));
   w.k_part = take(s->k_part_floats * 4);
@@ -373,7 +395,7 @@ BwdBufs pend_bufs(const ah_stage* s, int pos, int layer, char** dy_out) {
 //   nseg <  0: leaves them to a later call;
 //   nseg >  0: takes them over the nseg micro-batches in slots[] (group positions 0 .. nseg - 1), whose token
 //              axes are concatenated inside the product.
-// Matrices that are never deferred (defer_matrix) are taken now whatever nseg says, with beta_now.
+// Where products do not wait for their group (ah_stage::defer) they are taken now whatever nseg says, with beta_now.
 struct WgradPlan { int nseg; int slots[kMaxGemmSegments]; int beta, beta_now; };
 
 enum WgradWhich { WG_FC2, WG_FC1, WG_WO, WG_QKV };
@@ -404,8 +426,8 @@ hipError_t finish_vectors(ah_stage* s, int layer, const VecPlan& vp, hipStream_t
 // products on the side stream).
 hipError_t wgrad(ah_stage* s, int site, int layer, WgradWhich which, const WgradPlan& wp, const void* act, const void* dY, float* C,
                  int M, int N, hipStream_t st, hipStream_t sd) {
-  const bool now = wp.nseg == 0 || !s->defer_matrix[which];
-  if (now && !act) return hipSuccess;  // a flush: this matrix was taken with each micro-batch
+  const bool now = wp.nseg == 0 || !s->defer;
+  if (now && !act) return hipSuccess;  // a flush: the products were taken with each micro-batch
   if (!now && wp.nseg < 0) return hipSuccess;
   GemmArgs g = {};
   g.A = act; g.B = dY; g.C = C;
@@ -559,11 +581,14 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   return hipSuccess;
 }
 
-// The side stream and its events, created on the first backward pass (the device of the caller's buffers is
-// current then).  AH_NO_SIDE_STREAM in the environment keeps everything on the caller's stream (tuning aid).
+// Whether backward uses the side stream.  With the products deferred only the small reductions would be left for it, and
+// beside the main chain they cost more than they hide (75.4 vs 75.1 ms per step): everything stays on the caller's stream.
+bool two_streams(const ah_stage* s, bool in_group) { return s->side_pays && !(in_group && s->defer); }
+
+// The side stream and its events, created on the first backward pass that uses them (the device of the caller's buffers
+// is current then).
 hipError_t ensure_side(ah_stage* s) {
-  if (s->side_ready || s->side_off || !s->side_pays) return hipSuccess;
-  if (getenv("AH_NO_SIDE_STREAM")) { s->side_off = true; return hipSuccess; }
+  if (s->side_ready) return hipSuccess;
   hipError_t e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking);
   if (e != hipSuccess) return e;
   for (auto& v : s->sync_ev) {
@@ -639,7 +664,7 @@ hipError_t flush_wgrads(ah_stage* s, hipStream_t st) {
 // Backward of one micro-batch.  Undeferred, every layer takes its weight gradients at once.  Deferred
 // (group > 1), the micro-batch's output-gradient operands are written into the pending block of its position in
 // the group; the last micro-batch of a group takes the products for the whole group, layer by layer as its own
-// backward passes each layer (so they overlap the rest of backward on the side stream), and frees the group's slots.
+// backward passes each layer (on the same stream: see wgrad), and frees the group's slots.
 hipError_t stage_backward(ah_stage* s, int slot, const void* dy, void* dx, hipStream_t st, hipEvent_t* ev) {
   const int beta = s->overwrite_grads ? 0 : 1;
   char* wsb = (char*)s->bufs.workspace;
@@ -655,13 +680,10 @@ hipError_t stage_backward(ah_stage* s, int slot, const void* dy, void* dx, hipSt
     wp.slots[pos] = slot;
   }
   const void* cur = dy;
-  TRY(ensure_side(s));
-  // per-site timing wants one kernel at a time: a trace keeps everything on the caller's stream
-  const bool streams_ok = s->side_ready && !s->tracing;
-  // With every matrix deferred only the small reductions would be left for the side stream, and beside the main
-  // chain they cost more than they hide (75.4 vs 75.1 ms per step): everything stays on the caller's stream then.
-  const bool all_deferred = deferred && s->defer_matrix[0] && s->defer_matrix[1] && s->defer_matrix[2] && s->defer_matrix[3];
-  const hipStream_t sd = (streams_ok && !all_deferred) ? s->side : st;
+  // (a trace keeps everything on the caller's stream: per-site timing wants one kernel at a time)
+  const bool two = two_streams(s, deferred) && !s->tracing;
+  if (two) TRY(ensure_side(s));
+  const hipStream_t sd = two ? s->side : st;
   if (deferred) {  // the caller may reuse dy once this call's work has run: keep a copy for the deferred product
     char* keep;
     (void)pend_bufs(s, pos, s->L - 1, &keep);
@@ -756,7 +778,6 @@ extern "C" int ah_stage_create(const ah_stage_config_t* cfg, const ah_stage_buff
   s->rope_ready = false;
   s->side = nullptr;
   s->side_ready = false;
-  s->side_off = false;
   s->tracing = false;
   s->ev_used = 0;
   *out = s;
@@ -804,6 +825,12 @@ extern "C" int ah_stage_backward(ah_stage_t* st, int slot, const void* dy, void*
   if (st->busy[slot] != 1) return set_error(AH_ESTATE, "ah_stage_backward: slot %d holds no forward pass awaiting backward", slot);
   if (int rc = refuse_capture_of_groups(st, (hipStream_t)stream, "ah_stage_backward")) return rc;
   return hip_status(stage_backward(st, slot, dy, dx, (hipStream_t)stream, nullptr), "ah_stage_backward");
+}
+
+extern "C" int ah_stage_backward_streams(const ah_stage_t* st, int* n_streams) {
+  if (!st || !n_streams) return set_error(AH_EINVAL, "ah_stage_backward_streams: NULL argument");
+  *n_streams = two_streams(st, st->group > 1) ? 2 : 1;
+  return AH_OK;
 }
 
 extern "C" int ah_stage_flush_grads(ah_stage_t* st, void* stream) {

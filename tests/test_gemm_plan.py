@@ -1,9 +1,11 @@
-"""The launcher's choice of tiles (host arithmetic: no GPU)."""
+"""The launcher's choice of tiles, and a stage's of when to take its weight gradients (host arithmetic: no GPU)."""
+import ctypes
 import random
 
 import pytest
 
 import paper_2512_20953_amd as P
+from paper_2512_20953_amd.binding import _Buffers, lib
 
 
 @pytest.mark.parametrize("layout,M,N,K,tile", [
@@ -55,3 +57,26 @@ def test_no_raster_group_of_one_or_two_rows_in_small_outputs(layout, M, N, K):
         assert 4 <= group <= 6
         if rows < 12:
             assert rows % group == 0 or rows % group >= 3, (rows, group)
+
+
+@pytest.mark.parametrize("arch,hidden,heads,head_dim,ffn,seq,mb,group,deferred", [
+    # measured, us per micro-batch and layer, products taken at once / deferred to the end of the group
+    ("gpt", 1280, 10, 128, 3840, 1024, 3, 3, False),     # 518 / 563
+    ("bert", 768, 12, 64, 3072, 512, 8, 3, False),       # 391 / 403
+    ("bert", 1024, 16, 64, 4096, 512, 8, 3, False),      # 513 / 531
+    ("gpt", 768, 6, 128, 3072, 2048, 2, 4, False),       # 446 / 462
+    ("gpt", 512, 8, 64, 2048, 512, 4, 3, True),          # 190 / 165
+    ("bert", 1024, 16, 64, 4096, 512, 8, 8, True),       # 514 / 493
+    ("gpt", 1280, 10, 128, 3840, 1024, 3, 12, True),     # 522 / 503
+    ("gpt", 256, 4, 64, 1024, 128, 2, 2, True),          # too small for a second stream
+])
+def test_small_groups_of_middle_sizes_take_their_products_at_once(arch, hidden, heads, head_dim, ffn, seq, mb, group, deferred):
+    """Taken at once, the products of a stage this large run on a second stream; deferred, everything is on one."""
+    cfg = P.StageConfig.make(arch=arch, n_layers=1, hidden=hidden, n_heads=heads, head_dim=head_dim, ffn=ffn, seq=seq, mb=mb, n_mb=group,
+                             max_in_flight=group, wgrad_group=group)
+    h, n = ctypes.c_void_p(), ctypes.c_int()      # the handle is host metadata only, no device access
+    assert lib.ah_stage_create(ctypes.byref(cfg), ctypes.byref(_Buffers(256, 512, 768, 1024)), ctypes.byref(h)) == 0
+    assert lib.ah_stage_backward_streams(h, ctypes.byref(n)) == 0
+    assert n.value == (1 if deferred else 2)
+    assert lib.ah_stage_backward_streams(h, None) == 1 and lib.ah_stage_backward_streams(None, ctypes.byref(n)) == 1
+    assert lib.ah_stage_destroy(h) == 0

@@ -82,7 +82,7 @@ def test_recompute_is_bit_identical(name):
     assert torch.equal(outs[0][2], outs[1][2])
 
 
-@pytest.mark.parametrize("defer", ["by_size", "all", "all_but_out_projection", "mlp_second_and_out_projection"])
+@pytest.mark.parametrize("defer", ["by_size", "deferred", "at_once"])
 @pytest.mark.parametrize("name,n_mb,group", [("tiny", 4, 2), ("tiny", 5, 3), ("gpt_d128_tp2", 3, 3), ("llama_small", 3, 2),
                                              ("bert_tiny", 2, 16), ("gpt_odd", 3, 2)])
 def test_deferred_weight_gradients(name, n_mb, group, defer, monkeypatch):
@@ -90,18 +90,18 @@ def test_deferred_weight_gradients(name, n_mb, group, defer, monkeypatch):
     that needs the flush, a group larger than the iteration): against the oracle at the usual gates, and
     against the undeferred run: y and dx bit for bit (their path is the same), the gradients up to fp32
     summation order (a group's sums are formed in the accumulators and in shared partial sums before they
-    reach the gradient buffer).  Which matrices wait for the group is the library's choice by output size; at
-    these reduced sizes that choice defers none of them (only the vector gradients are grouped), so the other
-    variants force it: every matrix deferred (products over pieces of the k axis taken from the slots and the
-    pending blocks, everything on the caller's stream), and two mixtures (deferred and per-micro-batch products
-    side by side, the second stream in use; the first is what the library picks for the 2048-wide stage)."""
-    mask = {"by_size": None, "all": 15, "all_but_out_projection": 11, "mlp_second_and_out_projection": 5}[defer]
+    reach the gradient buffer).  Whether a group's products wait for its end is the library's choice by size (at these
+    sizes they do); either way is forced too: deferred, products over pieces of the k axis taken from the slots and the
+    pending blocks, everything on the caller's stream; at once, only the vector gradients are grouped and the products
+    run per micro-batch on the second stream."""
     w = dict(SI.WORKLOADS[name] if name in SI.WORKLOADS else REDUCED[name], n_mb=n_mb)
-    monkeypatch.delenv("AH_DEFER_MATRICES", raising=False)
+    monkeypatch.delenv("AH_DEFER_WGRADS", raising=False)
     st0, ys0, dxs0 = _run_case(w, n_mb)
-    if mask is not None:
-        monkeypatch.setenv("AH_DEFER_MATRICES", str(mask))   # read when the stage is created
+    if defer != "by_size":                                   # both read when the stage is created
+        monkeypatch.setenv("AH_DEFER_WGRADS", "1" if defer == "deferred" else "0")
+        monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", "0")
     st1, ys1, dxs1 = _run_case(w, n_mb, wgrad_group=group)
+    assert st1.backward_streams() == (2 if defer == "at_once" else 1)
     assert all(np.array_equal(a, b) for a, b in zip(ys0 + dxs0, ys1 + dxs1))
     for l in range(w["n_layers"]):
         for pname in SI.draw_layer_params(w, l):
