@@ -1,6 +1,7 @@
 """One training step of a tiny stage captured into a HIP graph and replayed against eager steps (run as a child
 process by tests/test_gpu_stage_parity.py, so that a fault inside the graph launch cannot take the test session down).
 Usage: python -m tests.graph_replay_case <wgrad_group>"""
+import os
 import sys
 
 import torch
@@ -11,12 +12,14 @@ from tests import gpu_util as U
 
 
 def main(group):
+    os.environ["AH_SIDE_STREAM_MIN_GFLOP"] = "0"    # a stage this small keeps one stream otherwise; read when it is created
     w = dict(SI.WORKLOADS["tiny"], n_mb=4)
     gcfg, _ = U.make_cfgs(w, max_in_flight=2, wgrad_group=group)
     params = [SI.draw_layer_params(w, l, perturb_vectors=True) for l in range(w["n_layers"])]
     xs = [SI.draw_activation(w, "x", m) for m in range(4)]
     dys = [SI.draw_activation(w, "dy", m) for m in range(4)]
     st = P.Stage(gcfg)
+    assert st.backward_streams() == (1 if group > 1 else 2)
     U.load_params(st, params)
     xd, dyd = [U.to_dev(x) for x in xs], [U.to_dev(d) for d in dys]
     y, dx = [torch.empty_like(t) for t in xd], [torch.empty_like(t) for t in xd]
@@ -30,7 +33,7 @@ def main(group):
         st.flush_grads(s)
 
     with torch.cuda.stream(s):
-        step()                      # also creates the library's own stream and events, outside the capture
+        step()                      # also creates the library's own stream and events, outside the capture, which records the forks and joins
         torch.cuda.synchronize()
         want = (st.grads.clone(), [t.clone() for t in y + dx])
         g = torch.cuda.CUDAGraph()

@@ -69,6 +69,8 @@ def test_no_raster_group_of_one_or_two_rows_in_small_outputs(layout, M, N, K):
     ("bert", 1024, 16, 64, 4096, 512, 8, 8, True),       # 514 / 493
     ("gpt", 1280, 10, 128, 3840, 1024, 3, 12, True),     # 522 / 503
     ("gpt", 256, 4, 64, 1024, 128, 2, 2, True),          # too small for a second stream
+    ("gpt", 256, 4, 64, 1024, 128, 2, 1, True),          # the same without groups
+    ("gpt", 512, 8, 64, 2048, 1024, 4, 1, False),        # 26 GFLOP
 ])
 def test_small_groups_of_middle_sizes_take_their_products_at_once(arch, hidden, heads, head_dim, ffn, seq, mb, group, deferred):
     """Taken at once, the products of a stage this large run on a second stream; deferred, everything is on one."""

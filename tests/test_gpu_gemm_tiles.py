@@ -94,6 +94,7 @@ def test_second_stream_by_size_changes_no_bit(arch, recompute, monkeypatch):
         monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", gflop)   # read when the stage is created
         cfg = P.StageConfig.make(arch=arch, n_layers=3, hidden=256, n_heads=4, head_dim=64, ffn=512, seq=256, mb=2, n_mb=2, recompute=recompute)
         st = P.Stage(cfg)
+        assert st.backward_streams() == (2 if gflop == "0" else 1)
         g = torch.Generator(device="cuda").manual_seed(9)
         st.params.copy_(torch.randn(st.params.shape, generator=g, device="cuda") * 0.05)
         out = []
@@ -113,13 +114,16 @@ def test_second_stream_by_size_changes_no_bit(arch, recompute, monkeypatch):
 
 @pytest.mark.parametrize("hidden,ffn", [(2048, 8192), (2048, 4224)])
 def test_dx_depends_on_neither_streams_nor_groups(hidden, ffn, monkeypatch):
-    """2048 x 2048 input gradients over k = 4224 .. 8192, whose tile splits the k axis between its waves: with and without that stream, and with deferred weight gradients, y and dx are the same bits."""
+    """2048 x 2048 input gradients over k = 4224 .. 8192 (the longer ones' tile splits the k axis between its waves): with
+    and without the second stream, and with the weight gradients of a group deferred or not, y and dx are the same bits."""
     res = []
-    for group, gflop in ((1, "0"), (1, "1e9"), (2, "0")):
-        monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", gflop)   # read when the stage is created
+    for group, gflop, defer, streams in ((1, "0", "1", 2), (1, "1e9", "1", 1), (2, "0", "1", 1), (2, "0", "0", 2)):
+        monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", gflop)   # both read when the stage is created
+        monkeypatch.setenv("AH_DEFER_WGRADS", defer)
         cfg = P.StageConfig.make(arch="gpt", n_layers=1, hidden=hidden, n_heads=16, head_dim=128, ffn=ffn, seq=2048, mb=1, n_mb=2,
                                  max_in_flight=group, wgrad_group=group)
         st = P.Stage(cfg)
+        assert st.backward_streams() == streams
         g = torch.Generator(device="cuda").manual_seed(9)
         st.params.copy_(torch.randn(st.params.shape, generator=g, device="cuda") * 0.02)
         st.zero_grads()

@@ -308,7 +308,9 @@ def test_bidirectional_stage_is_permutation_equivariant_and_differs_from_causal(
 @pytest.mark.parametrize("name", ["tiny", "llama_small"])
 def test_second_stream_changes_no_bit(name, monkeypatch):
     """Backward puts weight gradients and reductions on a stream of its own; with that switched off (everything on
-    the caller's stream) the outputs and every gradient must be bit-identical, also with recompute."""
+    the caller's stream) the outputs and every gradient must be bit-identical, also with recompute.  (Stages this small
+    keep one stream unless told otherwise.)"""
+    monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", "0")        # both read when the stage is created
     w = SI.WORKLOADS[name] if name in SI.WORKLOADS else REDUCED[name]
     outs = []
     for off in (False, True):
@@ -320,6 +322,7 @@ def test_second_stream_changes_no_bit(name, monkeypatch):
             gcfg, _ = U.make_cfgs(w, recompute=rc)
             params, xs, dys = _inputs(w)
             st = P.Stage(gcfg)
+            assert st.backward_streams() == (1 if off else 2)
             U.load_params(st, params)
             ys, dxs = U.run_gpu(st, xs, dys)
             ys2, dxs2 = U.run_gpu(st, xs, dys)          # a second iteration on the same stage (streams already exist)
@@ -331,16 +334,19 @@ def test_second_stream_changes_no_bit(name, monkeypatch):
 
 
 @pytest.mark.parametrize("name,group", [("gpt_d128_tp2", 0), ("gpt_d128_tp2", 2), ("llama_res32", 0)])
-def test_forward_beside_backward_changes_no_bit(name, group):
+def test_forward_beside_backward_changes_no_bit(name, group, monkeypatch):
     """Micro-batches are independent until their gradients meet (Section III-A): without recompute the forward of
     micro-batch m + 1 may run on a second stream beside the backward of micro-batch m.  Outputs, input gradients and
     the accumulated gradients must equal those of the serial order F0 B0 F1 B1 ... bit for bit.  Two slots; with
-    wgrad_group 2 a slot is free again only after the backward that closes its group, so that forward follows it."""
+    wgrad_group 2 a slot is free again only after the backward that closes its group, so that forward follows it.  With
+    per-micro-batch gradients the library's own second stream runs as well."""
+    monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", "0")        # read when the stage is created
     w = REDUCED[name]
     K = 5
     gcfg, _ = U.make_cfgs(w, max_in_flight=2, recompute=0, wgrad_group=group)
     params, xs, dys = _inputs(w, n_mb=K)
     st = P.Stage(gcfg)
+    assert st.backward_streams() == (1 if group else 2)
     U.load_params(st, params)
     ys, dxs = U.run_gpu(st, xs, dys)
     g_serial = st.grads.clone()
