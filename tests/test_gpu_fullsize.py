@@ -24,12 +24,12 @@ def _bf16_normal(rng, shape, std):
 
 @pytest.mark.parametrize("layout,M,N,K", [
     ("nn", 4096, 8192, 4096),   # first MLP matrix forward
-    ("nn", 4096, 6144, 4096),   # QKV forward: two launches over column ranges with different tiles
-    ("nt", 4096, 2048, 4096),   # out-projection input gradient (256x128 tiles)
+    ("nn", 4096, 6144, 4096),   # QKV forward: two launches over column ranges, 128 x 256 and 256 x 256 tiles
+    ("nt", 4096, 2048, 4096),   # out-projection input gradient (128 x 256 tiles)
     ("nt", 4096, 4096, 8192),   # first MLP matrix input gradient
     ("tn", 8192, 4096, 4096),   # second MLP matrix weight gradient
     ("tn", 2048, 4096, 4096),   # out-projection weight gradient
-    ("tn", 4096, 6144, 4096),   # QKV weight gradient: covered by two launches (256x128 tiles over 2048 columns, 256x256 over 4096)
+    ("tn", 4096, 6144, 4096),   # QKV weight gradient: 768 tiles of 128 x 256
 ])
 def test_gemm_at_benchmark_shapes_sampled_entries(layout, M, N, K):
     rng = np.random.default_rng(7)
@@ -71,9 +71,9 @@ def test_gemm_at_benchmark_shapes_sampled_entries(layout, M, N, K):
 
 @pytest.mark.parametrize("M,F,K", [
     (4096, 4096, 1024),   # 512 tiles of 256 x 256: a wave pairs 64 gate columns with their 64 up columns
-    (2048, 2048, 512),    # 256 x 128 tiles: 32 + 32 columns per wave
-    (4096, 3072, 512),    # 6144 tile columns: two launches over column ranges with different tile shapes
-    (384, 640, 128),      # 128 x 128 tiles, odd multiples
+    (2048, 2048, 512),    # 512 tiles of 128 x 128: 32 + 32 columns per wave
+    (4096, 3072, 512),    # 1536 tiles of 128 x 128 (two launches, 256 x 128 and 128 x 256: test_gpu_gemm_tiles.py)
+    (384, 640, 128),      # 64 x 64 tiles, odd multiples of 128
 ])
 def test_gemm_with_fused_swiglu_sampled_entries(M, F, K):
     """gate | up product and silu(gate) * up from its epilogue, against float64 on sampled rows (all columns)."""
@@ -222,8 +222,7 @@ def test_full_depth_stage_against_the_oracle(name, threaded_oracle, capsys):
     if w["recompute"]:
         return
     # The same micro-batches in the launch configuration bench.py times: the weight-gradient products deferred over the
-    # group of micro-batches (one product per matrix over their concatenated tokens; for gpt1p3b the library keeps the
-    # small out-projection product per micro-batch beside the deferred ones), against the same oracle results.
+    # group of micro-batches (one product per matrix over their concatenated tokens), against the same oracle results.
     st.close()
     del st, taps
     torch.cuda.empty_cache()
