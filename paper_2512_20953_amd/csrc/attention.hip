@@ -123,7 +123,7 @@ struct FwdState {
 constexpr float RESCALE_SLACK = 8.f;
 
 // One key tile of 64 for the wave's 32 queries.  LDS reads are issued a phase ahead of their use (see
-// dkv_tile); the mask costs vector work only on tiles that straddle the diagonal (diag is wave-uniform).
+// dkv_tile).  DIAG: the tile straddles the diagonal; the code of other tiles has no mask in it.
 template <int D, bool DIAG>
 __device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char* __restrict__ cV, FwdState<D>& st, int k0,
                                          int q, float sc2, int lane) {
@@ -1093,8 +1093,9 @@ __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict_
     offo[i] = tile_src_offset<D>(wave + 4 * i, lane, ldo);
   }
 
-  // query tiles of 64 from the one that holds the block's own positions on (from 0 without the mask); ring and
-  // counted waits as in attn_dkv_kernel
+  // Query tiles of 64 from the one that holds the block's own positions on (from 0 without the mask).  Tile t lives in ring
+  // slot t % 4; loads run three tiles ahead and are waited for by count, past the end the last tile is fetched again into a
+  // dead slot (a uniform number of loads in flight)
   const int j0 = CAUSAL ? kb : 0, ntile = S / 64 - j0, last = ntile - 1;
   qp += (size_t)j0 * 64 * ld;
   dop += (size_t)j0 * 64 * ldo;

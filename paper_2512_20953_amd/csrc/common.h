@@ -14,17 +14,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define AH_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
-// 16 bytes per lane, global memory straight into LDS: lane i of the wave lands
-// at lds_base + 16*i (lds_base must be wave-uniform).
-__device__ __forceinline__ void load16_to_lds(const void* gsrc, void* lds_base) {
-  __builtin_amdgcn_global_load_lds(gsrc, AH_LDS(lds_base), 16, 0, 0);
-}
-
-// The same from a wave-uniform base plus a 32-bit byte offset per lane: the instruction has a form for just that (base
-// in scalar registers).  The compiler only sees it if the widening of the offset stays beside the load: for a
+// 16 bytes per lane, global memory straight into LDS: lane i of the wave lands at lds_base + 16*i (lds_base must be
+// wave-uniform).  The source is a wave-uniform base plus a 32-bit byte offset per lane: the instruction has a form for
+// just that (base in scalar registers).  The compiler only sees it if the widening of the offset stays beside the load: for a
 // loop-invariant offset it hoists the widening and then spends two vector registers and a 64-bit add per load, and
 // the load itself issues more slowly.  The empty statement makes the offset look rewritten each time (no instruction).
-// GEMM loop, 256 x 256 tiles: 4096 x 4096 x 8192 NT 198.9 -> 191.1 us, TN 203.5 -> 195.3; 4096 x 8192 x 4096 NN
+// GEMM loop, 256 x 256 tiles, against an address per lane: 4096 x 4096 x 8192 NT 198.9 -> 191.1 us, TN 203.5 -> 195.3; 4096 x 8192 x 4096 NN
 // 201.3 -> 192.3 (same bits).
 __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t& off, void* lds_base) {
   asm("" : "+v"(off));

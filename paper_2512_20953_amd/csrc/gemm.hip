@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
         }
         if (EPI == EPI_ROPE && rot) {
           // rotary embedding on the fp32 sums: the pair of column c of a head is c +- d/2, d/16 pieces away in the
-          // same strip row (a wave's strip holds whole heads: WN % d == 0, checked by the caller)
+          // same strip row (a wave's strip holds whole heads: WN % d == 0, see tile_fits)
           const auto pp = strip_piece(row, rope_pcp);
           const f32x4 plo = pp.lo, phi = pp.hi;
           const float pv[8] = {plo[0], plo[1], plo[2], plo[3], phi[0], phi[1], phi[2], phi[3]};
@@ -841,8 +841,13 @@ int forced_tile() {
 
 // The choice knows the problem alone, not what runs beside it on another stream: the order of a sum's terms, and so its
 // last bits, depends on the tile.  kWholeCuTile's blocks leave no room on a CU for those of a second stream, so it is
-// taken only where k is long enough for a clear gain: BERT-Large stage, k <= 4096, 23.9 ms a step with it, 23.7 without
-// (27.8 / 26.4 with a second stream); 1.3B stage, k up to 8192, 26.6 / 27.4 (29.5 / 29.2).
+// taken only from a k on where the gain is clear.  Stage times with the line elsewhere, against 5120 (G: micro-batches
+// per group; with G = 1 the second stream runs): at 3584, 1280-wide stage (k = 3840) 1.06 at G = 1, 1.02 at G = 2 and 3,
+// BERT-Large (k = 4096) 1.01 at G = 1, 0.98 at G = 8; at 2048, 768-wide BERT (k = 3072) 1.00 at G = 1, 0.98 at G = 3;
+// at 6400, 1536-wide stage (k = 6144) 0.97 at G = 1, 1.015 at G = 3, 1.026 at G = 5, LLaMA-style 2048-wide (k = 5504
+// and 6144) 1.00; without the tile, the latter 1.03 at G = 1 and 3, 2048-wide GPT (k = 6144 and 8192) 0.98 at G = 1, 1.015 from
+// G = 2 on.  Single products gain below the line too (1408 x 1536 x 4096 NT 39.0 us, 27.7 with this tile): what they
+// lose is the price of one choice for all callers.
 constexpr int kWholeCuMinK = 5120;
 // head: a wave's columns must hold whole heads of this width (0: any; the rotary epilogue, EPI_ROPE, of forward)
 bool tile_fits(int i, int M, int n, int K, bool tn, int head) {

@@ -160,8 +160,9 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
     // Per-micro-batch products on the second stream hide the launches' tails and fill idle CUs (13B layer 3.86 -> 3.68
     // ms, a 512-wide one over 4096 tokens 0.55 -> 0.49), but each layer then pays for eight cross-stream orderings,
     // ~40 us of host and queue time: where a layer's products are shorter than that they cost more than they hide
-    // (two micro-batches of one layer: 0.4 GFLOP 280 against 240 us without, 2.4 GFLOP 313 / 299, 6.4 GFLOP 356 / 349,
-    // 26 GFLOP 492 / 552).
+    // (two micro-batches of one layer: 0.4 GFLOP 280 against 240 us without, 2.4 GFLOP 313 / 299, 6.4 GFLOP 412 / 340,
+    // 12.9 GFLOP 380 .. 436 / 390, 14.5 GFLOP 432 / 438 and, LLaMA-style, 444 / 414, 19.3 GFLOP 478 / 498, 26 GFLOP 470 / 490: level
+    // somewhere between 12 and 19).
     double gflop = 0;
     for (const auto& mn : wgrad_shapes(s)) gflop += 2e-9 * s->T * mn[0] * mn[1];
     const char* e = getenv("AH_SIDE_STREAM_MIN_GFLOP");  // tuning and test aid; AH_NO_SIDE_STREAM keeps everything on the caller's stream
