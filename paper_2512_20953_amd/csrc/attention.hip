@@ -44,12 +44,15 @@ constexpr int NSLOT = 2;  // ring slots of the forward and dQ kernels (two block
   __builtin_amdgcn_s_barrier()
 
 // LDS tile [64 rows][D] bf16.  16-byte piece p of row r is stored at piece
-// swz(r, p): conflict-free both for 16-byte reads down a column of pieces and
-// for the transposing reads of 4 rows x 64 bytes.
+// swz(r, p): conflict-free both for 16-byte reads down a column of pieces (16 rows
+// at a time must hit 16 different pieces of the 256 bytes that the banks span) and
+// for the transposing reads of 4 rows x 64 bytes.  With D = 64 the banks hold two
+// rows: rows 2i and 2i + 1 share a permutation, the eight values of i have eight
+// different ones, and the low bit of i moves a piece to the other 64 bytes.
 template <int D>
 __device__ __forceinline__ int swz(int r, int p) {
   if (D == 128) return p ^ ((r & 3) << 2) ^ ((r >> 2) & 3);
-  return p ^ (r & 7);
+  return p ^ ((r << 1) & 4) ^ ((r >> 2) & 3);
 }
 
 template <int D>
