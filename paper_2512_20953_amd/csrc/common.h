@@ -25,10 +25,6 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t& off, v
   asm("" : "+v"(off));
   __builtin_amdgcn_global_load_lds((const char*)base + off, AH_LDS(lds_base), 16, 0, 0);
 }
-__device__ __forceinline__ void load4_to_lds(const void* base, uint32_t& off, void* lds_base) {  // 4 bytes per lane, lane i at lds_base + 4 * i
-  asm("" : "+v"(off));
-  __builtin_amdgcn_global_load_lds((const char*)base + off, AH_LDS(lds_base), 4, 0, 0);
-}
 
 // Transposing LDS read: within each group of 16 lanes, lane j supplies the
 // address of 4 consecutive 16-bit elements; lane i receives element (i % 4) of
