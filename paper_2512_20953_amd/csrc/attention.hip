@@ -72,10 +72,6 @@ __device__ __forceinline__ uint32_t tile_src_offset(int chunk, int lane, int ld)
 // flight.  Nothing is returned to a register; the kernels wait for these loads by count before they pass a barrier.  M0 (the
 // LDS address) is set in the same statement, and nothing else in this file uses it.  Against the builtin, forward / backward:
 // 2 x 16 x 2048 x 128 causal 51.1 / 163.2 -> 49.7 / 160.2 us, 2 x 16 x 2048 x 64 causal 29.5 / 86.4 -> 28.7 / 83.0 (same bits).
-__device__ __forceinline__ uint32_t lds_offset(const void* p) { return (uint32_t)(uintptr_t)AH_LDS(p); }
-__device__ __forceinline__ void load16(const void* base, uint32_t off, void* lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory");
-}
 __device__ __forceinline__ void load4(const void* base, uint32_t off, void* lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory");
 }
@@ -83,7 +79,7 @@ __device__ __forceinline__ void load4(const void* base, uint32_t off, void* lds)
 template <int D>
 __device__ __forceinline__ void issue_tile(const bf16* __restrict__ g, const uint32_t* off, char* lds, int wave) {
 #pragma unroll
-  for (int i = 0; i < D / 32; i++) load16(g, off[i], lds + (wave + 4 * i) * 1024);
+  for (int i = 0; i < D / 32; i++) load16_to_lds_uncounted(g, off[i], lds + (wave + 4 * i) * 1024);
 }
 
 // 8 consecutive head-dim values (k-step ks, half hf) of row r

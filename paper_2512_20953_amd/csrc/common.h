@@ -26,6 +26,14 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t& off, v
   __builtin_amdgcn_global_load_lds((const char*)base + off, AH_LDS(lds_base), 16, 0, 0);
 }
 
+// The same as an assembly statement: the compiler neither waits for it nor orders LDS reads after it (that is the kernel's
+// business: a wait by count, and a compiler fence), and does not take it for an access that may return out of order
+// with LDS reads.  M0 is set in the same statement: no load16_to_lds may follow in the kernel.
+__device__ __forceinline__ uint32_t lds_offset(const void* p) { return (uint32_t)(uintptr_t)AH_LDS(p); }
+__device__ __forceinline__ void load16_to_lds_uncounted(const void* base, uint32_t off, void* lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory");
+}
+
 // Transposing LDS read: within each group of 16 lanes, lane j supplies the
 // address of 4 consecutive 16-bit elements; lane i receives element (i % 4) of
 // the data addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4.  With lane j
@@ -46,16 +54,17 @@ __device__ __forceinline__ bf16 f2bf(float v) { return (bf16)v; }  // round to n
 // tanh-form GeLU written through the logistic function: with z = kappa (u + 0.044715 u^3),
 // 0.5 (1 + tanh z) = sigma(2 z), so gelu(u) = u sigma(2z) and
 // gelu'(u) = sigma(2z) (1 + 2 u (1 - sigma(2z)) kappa (1 + 0.134145 u^2)).
-// sigma uses the hardware exp2 and reciprocal (1 ulp each); exp2 overflow gives sigma = 0 exactly.
-#define AH_KAPPA 0.7978845608028654f
-__device__ __forceinline__ float sigmoid2z(float u) {
-  const float z2 = (2.0f * AH_KAPPA) * __builtin_fmaf(0.044715f * u * u, u, u);
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z2));
+// sigma uses the hardware exp2 and reciprocal (1 ulp each); exp2 overflow gives sigma = 0 exactly.  The constants are
+// multiplied out: these run once per element in GEMM epilogues, whose length the vector instructions bound.
+__device__ __forceinline__ float sigmoid2z(float u, float uu) {   // uu = u * u
+  constexpr float c1 = -2.0 * 1.4426950408889634 * 0.7978845608028654, c3 = c1 * 0.044715;   // exp2(c1 u + c3 u^3) = exp(-2 z)
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(u * __builtin_fmaf(c3, uu, c1)));
 }
-__device__ __forceinline__ float gelu_f(float u) { return u * sigmoid2z(u); }
+__device__ __forceinline__ float gelu_f(float u) { return u * sigmoid2z(u, u * u); }
 __device__ __forceinline__ float gelu_grad_f(float u) {
-  const float s = sigmoid2z(u);
-  return s * __builtin_fmaf(2.0f * u * (1.0f - s), AH_KAPPA * __builtin_fmaf(0.134145f, u * u, 1.0f), 1.0f);
+  constexpr float d1 = 2.0 * 0.7978845608028654, d3 = d1 * 0.134145;
+  const float uu = u * u, s = sigmoid2z(u, uu);
+  return __builtin_fmaf(s * (1.0f - s), u * __builtin_fmaf(d3, uu, d1), s);
 }
 
 // silu(x) = x sigma(x) through the hardware exp2 and reciprocal

@@ -553,6 +553,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   const bool has_bias = (EPI == EPI_BF16 || EPI == EPI_GELU || RESID) && bias != nullptr;
   constexpr int PPR = WN / 8;                       // 8-column pieces per strip row
   constexpr int NIT = RPW * PPR / 64;               // pieces per lane per strip
+  // ROLLED: the pieces of a strip are taken in a loop that is not unrolled.  Straight-line code runs once per launch and tile,
+  // at the rate at which instructions arrive from a cold cache: the GeLU epilogues of a 256 x 256 tile had 27 and 42 KB of
+  // it, now 10 and 14.  4096 x 4096 x 1024: forward 47.0 -> 42.0 us (half of the difference to the plain epilogue); input
+  // gradient 51.7 -> 49.3.  Plain and residual epilogues (10 .. 15 KB) gain nothing from it, the rotary one loses 2 %.
+  // AUX_LDS: the second operand's pieces then wait in LDS, two strips' worth per wave (each lane reads back what it asked
+  // for), instead of in registers, which a loop cannot index (loaded piece by piece in the loop: 57.6 us).
+  constexpr bool AUX_LDS = !SPLIT && EPI == EPI_GELU_BWD;
+  constexpr bool ROLLED = !SPLIT && (EPI == EPI_GELU || EPI == EPI_GELU_BWD);
+  constexpr int UNROLL = ROLLED ? 1 : NIT;
+  char* const aux_lds = ring + NW * SR * ROWB + wave * (2 * NIT * 1024);
+  static_assert(!AUX_LDS || NW * (SR * ROWB + 2 * NIT * 1024) <= RING, "two strips of the second operand must fit behind the staging strips");
   auto strip_piece = [&](int row, int piece) {      // 4 + 4 consecutive columns of a row, the partial sums added up
     const char* p = strip_rd + row * ROWB + piece * 32;
     f32x4 lo = *(const f32x4*)p, hi = *(const f32x4*)(p + 16);
@@ -600,6 +611,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       dcs_c[2 * q4] = e[0]; dcs_s[2 * q4] = e[1]; dcs_c[2 * q4 + 1] = e[2]; dcs_s[2 * q4 + 1] = e[3];
     }
   }
+  const uint32_t aux_off = AUX_LDS ? (uint32_t)(row0 * g.ld_aux + n) * 2u : 0;
+  auto fetch_aux = [&](int tm) {
+    const bf16* p = aux + (size_t)(m0 + wm * WM + tm * 32) * g.ld_aux;
+#pragma unroll
+    for (int it = 0; it < NIT; it++) load16_to_lds_uncounted(p + (size_t)it * (64 / PPR) * g.ld_aux, aux_off, aux_lds + ((tm & 1) * NIT + it) * 1024);
+  };
+  if constexpr (AUX_LDS) fetch_aux(0);
 #pragma unroll
   for (int tm = 0; tm < TM; tm += SR / 32) {
     const int mbase = m0 + wm * WM + tm * 32 + wk * RPW + row0;
@@ -612,11 +630,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       }
     }
     // operands of the epilogue that come from memory: issue their loads before the strip round trip
-    bf16x8 ax[NIT], ax2[EPI == EPI_SWIGLU_BWD ? NIT : 1];
+    bf16x8 ax[AUX_LDS ? 1 : NIT], ax2[EPI == EPI_SWIGLU_BWD ? NIT : 1];
     f32x4 old0[NIT], old1[NIT];
-    if (EPI == EPI_RESID || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) {
+    if constexpr (AUX_LDS) {
+      if (tm + 1 < TM) fetch_aux(tm + 1);
+    } else if (EPI == EPI_RESID || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) {
 #pragma unroll
-      for (int it = 0; it < NIT; it++) ax[it] = *(const bf16x8*)(aux + (size_t)(mbase + it * (64 / PPR)) * g.ld_aux + n);
+      for (int it = 0; it < NIT; it++) ax[AUX_LDS ? 0 : it] = *(const bf16x8*)(aux + (size_t)(mbase + it * (64 / PPR)) * g.ld_aux + n);
     }
     if (EPI == EPI_SWIGLU_BWD) {  // aux = gate | up: the up columns sit swiglu_F further
 #pragma unroll
@@ -644,10 +664,19 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     if constexpr (SPLIT) {
       __syncthreads();
     } else {
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+      if constexpr (AUX_LDS) {
+        // this strip's pieces have landed: behind them there are the next strip's NIT loads (but for the last strip) and at
+        // least NIT stores of the strip before (but for the first)
+        if (tm > 0 && tm + 1 < TM) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * NIT));
+        else if (tm > 0 || TM > 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(NIT));
+        else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+      } else {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+      }
       __builtin_amdgcn_wave_barrier();
+      if (AUX_LDS) asm volatile("" ::: "memory");
     }
-#pragma unroll
+#pragma unroll UNROLL
     for (int it = 0; it < NIT; it++) {
       const int row = row0 + it * (64 / PPR);
       const auto pc = strip_piece(row, cp);
@@ -693,8 +722,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
           for (int i = 0; i < 4; i++) { v[i] += old0[it][i]; v[4 + i] += old1[it][i]; }
         }
         if (EPI == EPI_GELU_BWD) {
+          const bf16x8 u8 = AUX_LDS ? *(const bf16x8*)(aux_lds + ((tm & 1) * NIT + it) * 1024 + lane * 16) : ax[AUX_LDS ? 0 : it];
 #pragma unroll
-          for (int i = 0; i < 8; i++) v[i] *= gelu_grad_f(bf2f(ax[it][i]));
+          for (int i = 0; i < 8; i++) v[i] *= gelu_grad_f(bf2f(u8[i]));
         }
         bf16x8 o;
         if (EPI == EPI_SWIGLU_BWD) {
