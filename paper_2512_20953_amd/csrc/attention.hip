@@ -23,6 +23,7 @@
 #include "common.h"
 #include "kernels.h"
 #include <cstdlib>
+#include <type_traits>
 
 namespace ah {
 namespace {
@@ -130,6 +131,31 @@ struct FwdState {
   bf16x8 qf[D / 16];
   f32x16 oacc[D / 32];
   float m, l;
+  __device__ __forceinline__ void load(const bf16* __restrict__ qrow, int hf) {
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) qf[ks] = *(const bf16x8*)(qrow + ks * 16 + hf * 8);
+#pragma unroll
+    for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) oacc[dt][r] = 0.f;
+    m = -INFINITY;
+    l = 0.f;
+  }
+  // the query's output row and log-sum-exp
+  __device__ __forceinline__ void store(bf16* __restrict__ orow, float* __restrict__ lse, int hf) {
+    const float sum = l + __shfl_xor(l, 32, 64);
+    const float inv = 1.f / sum;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        bf16x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = f2bf(oacc[dt][4 * g + i] * inv);
+        *(bf16x4*)(orow + dt * 32 + 8 * g + 4 * hf) = v;
+      }
+    if (hf == 0) *lse = (m + __log2f(sum)) * LN2;
+  }
 };
 
 // The running maximum is only raised when a new score exceeds it by more than this many powers of two:
@@ -138,11 +164,14 @@ struct FwdState {
 // largest block of vector arithmetic in the loop -- runs on the first tile only in practice.
 constexpr float RESCALE_SLACK = 8.f;
 
+// ---- without the mask, head_dim 64: one tile after the other.  Three waves share a SIMD and all of them run to the end, so
+// that they cover each other's waits; the steps below, whose first scores and last product stand alone, are level on long
+// sequences there and lose on short ones (8 x 16 x 512: 17.2 against 18.0 us in a stage).
 // One key tile of 64 for the wave's 32 queries.  LDS reads are issued a phase ahead of their use (see
-// dkv_tile).  DIAG: the tile straddles the diagonal; the code of other tiles has no mask in it.
-template <int D, bool DIAG>
-__device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char* __restrict__ cV, FwdState<D>& st, int k0,
-                                         int q, float sc2, int lane) {
+// dkv_tile).
+template <int D>
+__device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char* __restrict__ cV, FwdState<D>& st, float sc2,
+                                         int lane) {
   constexpr int NK = D / 16, ND = D / 32;
   const int hf = lane >> 5;
   bf16x8 fk0[NK], fk1[NK];
@@ -167,15 +196,6 @@ __device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char
     for (int dt = 0; dt < ND; dt++) v0[s2][dt] = frag_transposed<D>(cV, 16 * s2 + 4 * hf, dt, lane);
   AH_PRIO(0);
   AH_SCHED_FENCE();
-  if (DIAG) {
-    // element r of half t is key k0 + t*32 + 8*(r/4) + 4*hf + r%4: masked iff that exceeds q
-    const int lim = q - k0 - 4 * hf;
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      if (8 * (r >> 2) + (r & 3) > lim) s0[r] = -INFINITY;
-      if (32 + 8 * (r >> 2) + (r & 3) > lim) s1[r] = -INFINITY;
-    }
-  }
   float mx = fmaxf(s0[0], s1[0]);
 #pragma unroll
   for (int r = 1; r < 16; r++) mx = fmaxf(fmaxf(mx, s0[r]), s1[r]);  // one three-way maximum each
@@ -221,23 +241,189 @@ __device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char
   AH_SCHED_FENCE();
 }
 
-// MASK: the tile is one of the block's last two under the mask, which straddle the diagonal for two of the waves and lie
-// wholly before or wholly after the queries of the others
-template <int D, bool MASK>
-__device__ __forceinline__ void fwd_step(const bf16* gK, const bf16* gV, uint32_t* off, char* __restrict__ nK,
-                                         char* __restrict__ nV, const char* __restrict__ cK, const char* __restrict__ cV,
-                                         FwdState<D>& st, int k0, int q, int qw0, float sc2, int wave, int lane) {
-  issue_tile<D>(gK, off, nK, wave);
-  issue_tile<D>(gV, off, nV, wave);
-  if (MASK && k0 > qw0 + 31) return;
-  fwd_tile<D, MASK>(cK, cV, st, k0, q, sc2, lane);
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_fwd_plain_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
+                                                             int S, int nh, float sc2) {
+  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB;  // ring slot = K tile then V tile
+  __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
+  const int lane = threadIdx.x & 63, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
+  const int nbh = gridDim.x / (S / 128);
+  const int bh = blockIdx.x % nbh, qb = blockIdx.x / nbh;
+  const int b = bh / nh, head = bh % nh;
+  const int ld = 3 * nh * D;
+  const bf16* qp = qkv + (size_t)b * S * ld + head * D;
+  const bf16* kp = qp + nh * D;
+  const bf16* vp = qp + 2 * nh * D;
+  const int q = qb * 128 + wave * 32 + (lane & 31);
+
+  FwdState<D> st;
+  st.load(qp + (size_t)q * ld, hf);
+  uint32_t off[D / 32];
+#pragma unroll
+  for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
+
+  // Tile t lives in ring slot t % 2 and is loaded during step t - 1 (the last step loads the last tile again, into a dead
+  // slot).  Two tiles per round (S / 64 is even), so that every LDS address is a constant away from a loop-invariant one.
+  const int ntile = S / 64, last = ntile - 1;
+  const size_t step = (size_t)64 * ld;
+  char *const K0 = ring, *const V0 = ring + TILEB, *const K1 = ring + STAGE, *const V1 = ring + STAGE + TILEB;
+  issue_tile<D>(kp, off, K0, wave);
+  issue_tile<D>(vp, off, V0, wave);
+  AH_NEXT_TILE();
+  for (int j = 0; j < ntile; j += 2) {
+    const size_t o1 = (size_t)(j + 1) * step, o2 = (size_t)min(j + 2, last) * step;
+    issue_tile<D>(kp + o1, off, K1, wave);
+    issue_tile<D>(vp + o1, off, V1, wave);
+    fwd_tile<D>(K0, V0, st, sc2, lane);
+    AH_NEXT_TILE();
+    issue_tile<D>(kp + o2, off, K0, wave);
+    issue_tile<D>(vp + o2, off, V0, wave);
+    fwd_tile<D>(K1, V1, st, sc2, lane);
+    AH_NEXT_TILE();
+  }
+  st.store(o + ((size_t)b * S + q) * (nh * D) + head * D, lse + ((size_t)b * nh + head) * S + q, hf);
+}
+
+// Byte offsets of a lane's fragments in a tile: row[ks] as frag_rowmajor, lo[dt] and hi[dt] as frag_transposed, for rows that
+// start at a multiple of 16 (the permutation depends on the row's low four bits only), so that every other fragment is a
+// compile-time distance away.
+template <int D>
+struct LaneOffs {
+  int row[D / 16], lo[D / 32], hi[D / 32];
+  __device__ __forceinline__ LaneOffs(int lane) {
+    const int r = lane & 31, hf = lane >> 5, rt = 4 * hf + ((lane & 15) >> 2);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) row[ks] = r * (2 * D) + swz<D>(r, 2 * ks + hf) * 16;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; dt++) {
+      const int c = dt * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
+      lo[dt] = rt * (2 * D) + swz<D>(rt, c >> 3) * 16 + (c & 7) * 2;
+      hi[dt] = (rt + 8) * (2 * D) + swz<D>(rt + 8, c >> 3) * 16 + (c & 7) * 2;
+    }
+  }
+  __device__ __forceinline__ bf16x8 rows(const char* t, int rb, int ks) const { return *(const bf16x8*)(t + row[ks] + rb * (2 * D)); }
+  __device__ __forceinline__ bf16x8 cols(const char* t, int rb, int dt) const {
+    return cat4(lds_read_tr4(t + lo[dt] + rb * (2 * D)), lds_read_tr4(t + hi[dt] + rb * (2 * D)));
+  }
+};
+
+// f(integral_constant<int, I>) for I .. N - 1, unrolled
+template <int I, int N, class F>
+__device__ __forceinline__ void unrolled(const F& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<I + 1, N>(f);
+  }
+}
+
+// scores of one key tile: s0, s1 = K Q^T
+template <int D>
+__device__ __forceinline__ void fwd_scores(const char* cK, const LaneOffs<D>& lo, const bf16x8 (&qf)[D / 16], f32x16& s0, f32x16& s1) {
+#pragma unroll
+  for (int r = 0; r < 16; r++) { s0[r] = 0.f; s1[r] = 0.f; }
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) {
+    s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cK, 0, ks), qf[ks], s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cK, 32, ks), qf[ks], s1, 0, 0, 0);
+  }
+}
+
+template <bool DIAG>
+__device__ __forceinline__ float fwd_max(f32x16& s0, f32x16& s1, int lim) {
+  if (DIAG) {
+    // element r of half t is key k0 + t*32 + 8*(r/4) + 4*hf + r%4: masked iff that exceeds q (lim = q - k0 - 4 hf)
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+      if (8 * (r >> 2) + (r & 3) > lim) s0[r] = -INFINITY;
+      if (32 + 8 * (r >> 2) + (r & 3) > lim) s1[r] = -INFINITY;
+    }
+  }
+  float mx = fmaxf(s0[0], s1[0]);
+#pragma unroll
+  for (int r = 1; r < 16; r++) mx = fmaxf(fmaxf(mx, s0[r]), s1[r]);  // one three-way maximum each
+  return half_max(mx);
+}
+
+// ---- otherwise: a pipeline of steps.  A step takes the softmax of tile j (its scores in s0, s1, their maximum in mx), its product
+// with V, and the scores of tile j + 1 (NEXT).  One probability (multiply-add, exponential, sum, half a conversion) fits under
+// one matrix instruction (32 clocks; both units busy, 17 ns against 17 and 9 alone), so the step is a fixed sequence of
+// slots: an LDS fragment requested AHEAD slots before its use, one matrix instruction, its share of the probabilities
+// (all 32 before the products that need them), and the maximum of the new scores under the last products.  The fences
+// keep the sequence as written.  A wave that is left alone on its SIMD, as the causal mask leaves the ones with the most
+// keys, no longer does one thing at a time; with two, what is left to bound it is the CU's path from the LDS (320 KB of
+// fragments and tiles a step at head_dim 128).  Against one phase after the other: 2 x 16 x 2048 x 128 causal 51.0 -> 46.3 us, without
+// the mask 72.6 -> 69.8, 1 x 32 x 4096 x 128 causal 143.3 -> 138.3, 2 x 16 x 2048 x 64 causal 30.4 -> 27.9.  AHEAD 2 .. 7 and a raised
+// issue priority change nothing; 64 queries per wave and one wave per SIMD (half the fragments) take 85 us for 69.8.
+template <int D, bool NEXT, bool DIAG>
+__device__ __forceinline__ void fwd_pipe(const char* nK, const char* cV, FwdState<D>& st, f32x16& s0, f32x16& s1, float& mx,
+                                         const LaneOffs<D>& lo, int lim, float sc2) {
+  constexpr int NK = D / 16, ND = D / 32;
+  const float mxs = mx * sc2;
+  if (__any(mxs > st.m + RESCALE_SLACK)) {  // wave-uniform branch
+    const float m_new = fmaxf(st.m, mxs);
+    const float alpha = fexp2(st.m - m_new);
+    st.m = m_new;
+    st.l *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < ND; dt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) st.oacc[dt][r] *= alpha;
+  }
+  const float nm = -st.m;
+  constexpr int N1 = NEXT ? 2 * NK : 0, N2 = N1 + 2 * ND, NS = N2 + 2 * ND;  // slots: scores, then the halves of the product with V
+  constexpr int SE = NEXT ? NS - ND - 2 : 0;                                 // slots over which the exponentials are spread
+  static_assert(!NEXT || (15 * SE / 32 < N1 && 23 * SE / 32 < N2 && 31 * SE / 32 < NS - ND), "probabilities precede their products");
+  constexpr int AHEAD = 4;                                                   // fragments requested before their use
+  f32x16 t0, t1;
+  bf16x8 fr[NS], pf[4];
+  float ls[2] = {0.f, 0.f};
+  auto fetch = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < N1) fr[i] = lo.rows(nK, 32 * (i & 1), i >> 1);
+    else if constexpr (i < NS) fr[i] = lo.cols(cV, 16 * ((i - N1) / ND), (i - N1) % ND);
+  };
+  auto element = [&](auto ic) {
+    constexpr int e = decltype(ic)::value, r = e & 15;
+    f32x16& s = e < 16 ? s0 : s1;
+    s[r] = fexp2(__builtin_fmaf(s[r], sc2, nm));
+    ls[e & 1] += s[r];
+    if constexpr ((e & 7) == 7) pf[e >> 3] = pack8(s, (e >> 3) & 1);
+  };
+  if (NEXT) {
+#pragma unroll
+    for (int r = 0; r < 16; r++) { t0[r] = 0.f; t1[r] = 0.f; }
+  } else {
+    unrolled<0, 32>(element);
+  }
+  unrolled<0, AHEAD>(fetch);
+  unrolled<0, NS>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    AH_SCHED_FENCE();
+    fetch(std::integral_constant<int, i + AHEAD>{});
+    if constexpr (i < N1) {
+      f32x16& t = i & 1 ? t1 : t0;
+      t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], st.qf[i >> 1], t, 0, 0, 0);
+    } else {
+      constexpr int dt = (i - N1) % ND;
+      st.oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], pf[(i - N1) / ND], st.oacc[dt], 0, 0, 0);
+    }
+    AH_SCHED_FENCE();
+    if constexpr (i < SE) unrolled<i * 32 / SE, (i + 1) * 32 / SE>(element);
+    if constexpr (NEXT && i == NS - ND) mx = fwd_max<DIAG>(t0, t1, lim);
+  });
+  st.l += ls[0] + ls[1];
+  if (NEXT) {
+    s0 = t0;
+    s1 = t1;
+  }
 }
 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
                                                        int S, int nh, float sc2) {
-  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB;  // ring slot = K tile then V tile
-  __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
+  constexpr int TILEB = 64 * 2 * D;
+  __shared__ __attribute__((aligned(1024))) char ring[4 * TILEB];  // two K tiles, two V tiles
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
   const int nbh = gridDim.x / (S / 128);
@@ -250,61 +436,67 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict
   const bf16* vp = qp + 2 * nh * D;
   const int qw0 = qb * 128 + wave * 32, q = qw0 + (lane & 31);
 
-  FwdState<D> st;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) st.qf[ks] = *(const bf16x8*)(qp + (size_t)q * ld + ks * 16 + hf * 8);
-#pragma unroll
-  for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) st.oacc[dt][r] = 0.f;
-  st.m = -INFINITY;
-  st.l = 0.f;
-
   uint32_t off[D / 32];
 #pragma unroll
   for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
 
-  // Key tiles of 64 up to and including the diagonal (all of them without the mask), an even number.  Tile t lives in
-  // ring slot t % 2 and is loaded during step t - 1 (the last step loads the last tile again, into a dead slot).  The
-  // loop takes two tiles per round, so that every LDS address is a constant away from a loop-invariant one, and the
-  // two tiles on the diagonal are peeled, so that the other tiles' code has no mask in it (as a condition inside the
-  // loop the compiler turns it into 64 compares and selects per tile).  Vector instructions per tile, exponentials
-  // apart: 249 -> 107.  2 x 16 x 2048 x 128 causal 57.6 -> 52.6 us, without the mask 76.3 -> 72.8; 1 x 32 x 4096 x 128
-  // causal 153.7 -> 148.6; 8 x 16 x 512 x 64 without the mask 15.5 -> 14.8 (same bits).
+  // Key tiles of 64 up to and including the diagonal (all of them without the mask), an even number.  K tile t lives in K slot
+  // t % 2 and V tile t in V slot t % 2; step j reads K tile j + 1 and V tile j, while K tile j + 2 and V tile j + 1 arrive.  The
+  // loop takes two steps per round, so that every LDS address is a constant away from a loop-invariant one; the steps
+  // whose scores straddle the diagonal are peeled, so that the others have no mask in them.
   const int ntile = CAUSAL ? 2 * qb + 2 : S / 64, last = ntile - 1, nfull = CAUSAL ? ntile - 2 : ntile;
   const size_t step = (size_t)64 * ld;
-  char *const K0 = ring, *const V0 = ring + TILEB, *const K1 = ring + STAGE, *const V1 = ring + STAGE + TILEB;
+  char *const K0 = ring, *const K1 = ring + TILEB, *const V0 = ring + 2 * TILEB, *const V1 = ring + 3 * TILEB;
   issue_tile<D>(kp, off, K0, wave);
   issue_tile<D>(vp, off, V0, wave);
-  AH_NEXT_TILE();
-  for (int j = 0; j < nfull; j += 2) {
-    const size_t o1 = (size_t)(j + 1) * step, o2 = (size_t)min(j + 2, last) * step;
-    fwd_step<D, false>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, j * 64, q, qw0, sc2, wave, lane);
-    AH_NEXT_TILE();
-    fwd_step<D, false>(kp + o2, vp + o2, off, K0, V0, K1, V1, st, (j + 1) * 64, q, qw0, sc2, wave, lane);
-    AH_NEXT_TILE();
-  }
-  if (CAUSAL) {
-    const size_t o1 = (size_t)last * step;
-    fwd_step<D, true>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, (last - 1) * 64, q, qw0, sc2, wave, lane);
-    AH_NEXT_TILE();
-    fwd_step<D, true>(kp + o1, vp + o1, off, K0, V0, K1, V1, st, last * 64, q, qw0, sc2, wave, lane);
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant tail loads
+  issue_tile<D>(kp + step, off, K1, wave);
 
-  const float l = st.l + __shfl_xor(st.l, 32, 64);
-  const float inv = 1.f / l;
-  bf16* op = o + ((size_t)b * S + q) * (nh * D) + head * D;
-#pragma unroll
-  for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      bf16x4 v;
-#pragma unroll
-      for (int i = 0; i < 4; i++) v[i] = f2bf(st.oacc[dt][4 * g + i] * inv);
-      *(bf16x4*)(op + dt * 32 + 8 * g + 4 * hf) = v;
+  FwdState<D> st;
+  st.load(qp + (size_t)q * ld, hf);
+  const LaneOffs<D> lo(lane);
+  f32x16 s0, s1;
+  float mx;
+  const int lim = q - 4 * hf;
+  AH_NEXT_TILE();
+  fwd_scores<D>(K0, lo, st.qf, s0, s1);
+  if (CAUSAL && nfull == 0) mx = fwd_max<true>(s0, s1, lim);
+  else mx = fwd_max<false>(s0, s1, lim);
+  AH_NEXT_TILE();
+  int j = 0;
+#define AH_FWD_LOADS(cK, nV)                                             \
+  issue_tile<D>(kp + (size_t)min(j + 2, last) * step, off, cK, wave);    \
+  issue_tile<D>(vp + (size_t)(j + 1) * step, off, nV, wave)
+  for (; j < nfull - 2; ) {
+    AH_FWD_LOADS(K0, V1);
+    fwd_pipe<D, true, false>(K1, V0, st, s0, s1, mx, lo, 0, sc2);
+    AH_NEXT_TILE();
+    j++;
+    AH_FWD_LOADS(K1, V0);
+    fwd_pipe<D, true, false>(K0, V1, st, s0, s1, mx, lo, 0, sc2);
+    AH_NEXT_TILE();
+    j++;
+  }
+  if (nfull > 0) {
+    AH_FWD_LOADS(K0, V1);
+    fwd_pipe<D, true, false>(K1, V0, st, s0, s1, mx, lo, 0, sc2);
+    AH_NEXT_TILE();
+    j++;
+    if (CAUSAL) {
+      AH_FWD_LOADS(K1, V0);
+      fwd_pipe<D, true, true>(K0, V1, st, s0, s1, mx, lo, lim - (last - 1) * 64, sc2);
+      AH_NEXT_TILE();
+      j++;
     }
-  if (hf == 0) lse[((size_t)b * nh + head) * S + q] = (st.m + __log2f(l)) * LN2;
+  }
+  if (CAUSAL) {  // j == last - 1, an even tile
+    issue_tile<D>(vp + (size_t)last * step, off, V1, wave);
+    fwd_pipe<D, true, true>(K1, V0, st, s0, s1, mx, lo, lim - last * 64, sc2);
+    AH_NEXT_TILE();
+  }
+  // (under the mask the first two waves see no key of the last tile: its scores are all masked)
+  if (!CAUSAL || wave >= 2) fwd_pipe<D, false, false>(K0, V1, st, s0, s1, mx, lo, 0, sc2);
+#undef AH_FWD_LOADS
+  st.store(o + ((size_t)b * S + q) * (nh * D) + head * D, lse + ((size_t)b * nh + head) * S + q, hf);
 }
 
 // =========================================================================== forward for launches that cannot fill the chip
@@ -393,14 +585,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd64_kernel(const bf16* __restri
   const int qw0 = qb * 64 + qt * 32, q = qw0 + (lane & 31);
 
   FwdState<D> st;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) st.qf[ks] = *(const bf16x8*)(qp + (size_t)q * ld + ks * 16 + hf * 8);
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) st.oacc[dt][r] = 0.f;
-  st.m = -INFINITY;
-  st.l = 0.f;
+  st.load(qp + (size_t)q * ld, hf);
 
   uint32_t off[D / 32];
 #pragma unroll
@@ -1182,6 +1367,8 @@ template <int D, bool CAUSAL>
 static void launch_fwd_t(dim3 grid, hipStream_t s, const void* qkv, void* o, float* lse, int S, int nh, float sc2) {
   if ((int)grid.x <= small_grid_blocks())  // at most one 128-query block per CU: 64-query blocks with the keys split between wave pairs
     hipLaunchKernelGGL((attn_fwd64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, S, nh, sc2);
+  else if constexpr (D == 64 && !CAUSAL)
+    hipLaunchKernelGGL((attn_fwd_plain_kernel<D>), grid, dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, S, nh, sc2);
   else
     hipLaunchKernelGGL((attn_fwd_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, S, nh, sc2);
 }
