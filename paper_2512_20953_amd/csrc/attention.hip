@@ -113,6 +113,31 @@ __device__ __forceinline__ float half_max(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// A wave's result of 32 rows x D, val(dt, r) being the element of row lane % 32 and column dt * 32 + 8 (r / 4) + 4 (lane / 32) + r % 4,
+// to 32 rows of the output.  It passes through a strip of LDS of the wave's own and leaves as whole rows, 16 bytes a lane: stored
+// straight from the registers, an instruction writes 16 bytes to each of 32 rows (dK and dV of 128 keys: 4.5 us, now 1.45).
+template <int D> constexpr int strip_bytes() { return 32 * 2 * D; }
+template <int D, class F>
+__device__ __forceinline__ void store_rows(const F& val, char* strip, bf16* __restrict__ dst, size_t ld, int lane) {
+  constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;   // bytes of a row, 16-byte pieces of a row, rows per store
+  auto at = [](int row, int piece) { return row * RB + ((piece ^ (D == 128 ? row : row >> 1)) & (PPR - 1)) * 16; };
+  const int base = at(lane & 31, 0) + 8 * (lane >> 5);
+#pragma unroll
+  for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+      bf16x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; i++) v[i] = f2bf(val(dt, 4 * g + i));
+      *(bf16x4*)(strip + (base ^ ((4 * dt + g) * 16))) = v;
+    }
+  __builtin_amdgcn_wave_barrier();
+  const int row = lane / PPR, piece = lane % PPR;
+#pragma unroll
+  for (int it = 0; it < 32 / RPI; it++) *(bf16x8*)(dst + (size_t)(row + it * RPI) * ld + piece * 8) = *(const bf16x8*)(strip + at(row + it * RPI, piece));
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Query block of a thread block under the causal mask (block qb walks 2*qb + 2 key tiles).  A launch that
@@ -141,20 +166,12 @@ struct FwdState {
     m = -INFINITY;
     l = 0.f;
   }
-  // the query's output row and log-sum-exp
-  __device__ __forceinline__ void store(bf16* __restrict__ orow, float* __restrict__ lse, int hf) {
+  // the output rows of the wave's 32 queries (orow: the first) and the query's log-sum-exp
+  __device__ __forceinline__ void store(char* strip, bf16* __restrict__ orow, size_t ldo, float* __restrict__ lse, int lane) const {
     const float sum = l + __shfl_xor(l, 32, 64);
     const float inv = 1.f / sum;
-#pragma unroll
-    for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        bf16x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; i++) v[i] = f2bf(oacc[dt][4 * g + i] * inv);
-        *(bf16x4*)(orow + dt * 32 + 8 * g + 4 * hf) = v;
-      }
-    if (hf == 0) *lse = (m + __log2f(sum)) * LN2;
+    store_rows<D>([&](int dt, int r) { return oacc[dt][r] * inv; }, strip, orow, ldo, lane);
+    if (lane < 32) *lse = (m + __log2f(sum)) * LN2;
   }
 };
 
@@ -243,19 +260,19 @@ __device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char
 
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_fwd_plain_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
-                                                             int S, int nh, float sc2) {
+                                                             int B, int S, int nh, float sc2) {
   constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB;  // ring slot = K tile then V tile
   __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
-  const int nbh = gridDim.x / (S / 128);
-  const int bh = blockIdx.x % nbh, qb = blockIdx.x / nbh;
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int qb = blockIdx.x / nbh, bh = blockIdx.x - qb * nbh;
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
   const bf16* vp = qp + 2 * nh * D;
-  const int q = qb * 128 + wave * 32 + (lane & 31);
+  const int qw0 = qb * 128 + wave * 32, q = qw0 + (lane & 31);
 
   FwdState<D> st;
   st.load(qp + (size_t)q * ld, hf);
@@ -282,7 +299,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_plain_kernel(const bf16* __re
     fwd_tile<D>(K1, V1, st, sc2, lane);
     AH_NEXT_TILE();
   }
-  st.store(o + ((size_t)b * S + q) * (nh * D) + head * D, lse + ((size_t)b * nh + head) * S + q, hf);
+  st.store(ring + wave * strip_bytes<D>(), o + ((size_t)b * S + qw0) * (nh * D) + head * D, nh * D, lse + ((size_t)b * nh + head) * S + q, lane);
 }
 
 // Byte offsets of a lane's fragments in a tile: row[ks] as frag_rowmajor, lo[dt] and hi[dt] as frag_transposed, for rows that
@@ -421,15 +438,15 @@ __device__ __forceinline__ void fwd_pipe(const char* nK, const char* cV, FwdStat
 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
-                                                       int S, int nh, float sc2) {
+                                                       int B, int S, int nh, float sc2) {
   constexpr int TILEB = 64 * 2 * D;
   __shared__ __attribute__((aligned(1024))) char ring[4 * TILEB];  // two K tiles, two V tiles
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
-  const int nbh = gridDim.x / (S / 128);
-  const int bh = blockIdx.x % nbh;
-  const int qb = CAUSAL ? causal_query_block(blockIdx.x / nbh, S / 128) : blockIdx.x / nbh;
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int qb = CAUSAL ? causal_query_block(rank, S / 128) : rank;
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
@@ -496,7 +513,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict
   // (under the mask the first two waves see no key of the last tile: its scores are all masked)
   if (!CAUSAL || wave >= 2) fwd_pipe<D, false, false>(K0, V1, st, s0, s1, mx, lo, 0, sc2);
 #undef AH_FWD_LOADS
-  st.store(o + ((size_t)b * S + q) * (nh * D) + head * D, lse + ((size_t)b * nh + head) * S + q, hf);
+  st.store(ring + wave * strip_bytes<D>(), o + ((size_t)b * S + qw0) * (nh * D) + head * D, nh * D, lse + ((size_t)b * nh + head) * S + q, lane);
 }
 
 // =========================================================================== forward for launches that cannot fill the chip
@@ -566,7 +583,7 @@ __device__ __forceinline__ void fwd_half_tile(const char* __restrict__ cK, const
 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_fwd64_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o, float* __restrict__ lse,
-                                                         int S, int nh, float sc2) {
+                                                         int B, int S, int nh, float sc2) {
   constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB, ND = D / 32;
   __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
   static_assert(2 * (ND * 16 + 2) * 64 * 4 <= NSLOT * STAGE, "the partial results of two waves fit in the ring");
@@ -574,10 +591,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd64_kernel(const bf16* __restri
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qt = wave & 1, kh = wave >> 1;
   const int nq = S / 64;
-  const int nbh = gridDim.x / nq;
-  const int bh = blockIdx.x % nbh;
-  const int qb = CAUSAL ? causal_query_block(blockIdx.x / nbh, nq) : blockIdx.x / nbh;
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int qb = CAUSAL ? causal_query_block(rank, nq) : rank;
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
@@ -753,16 +770,16 @@ __device__ __forceinline__ void dq_step(const bf16* gK, const bf16* gV, uint32_t
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                       const bf16* __restrict__ d_o, const float* __restrict__ lse,
-                                                      float* __restrict__ delta, bf16* __restrict__ dqkv, int S, int nh,
+                                                      float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int nh,
                                                       float sc2, float scale) {
   constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB;  // ring slot = K tile then V tile
   __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
-  const int nbh = gridDim.x / (S / 128);
-  const int bh = blockIdx.x % nbh;
-  const int qb = CAUSAL ? causal_query_block(blockIdx.x / nbh, S / 128) : blockIdx.x / nbh;
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int qb = CAUSAL ? causal_query_block(rank, S / 128) : rank;
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
@@ -812,16 +829,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant tail loads
 
-  bf16* out = dqkv + ((size_t)b * S + q) * ld + head * D;
-#pragma unroll
-  for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      bf16x4 v;
-#pragma unroll
-      for (int i = 0; i < 4; i++) v[i] = f2bf(st.acc[dt][4 * g + i] * scale);
-      *(bf16x4*)(out + dt * 32 + 8 * g + 4 * hf) = v;
-    }
+  // (the other waves may still read the second ring slot; the strips lie in the first)
+  store_rows<D>([&](int dt, int r) { return st.acc[dt][r] * scale; }, ring + wave * strip_bytes<D>(), dqkv + ((size_t)b * S + qw0) * ld + head * D, ld, lane);
 }
 
 // =========================================================================== backward: dQ for launches that cannot fill the chip
@@ -891,19 +900,19 @@ __device__ __forceinline__ void dq_half_tile(const char* __restrict__ cK, const 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                         const bf16* __restrict__ d_o, const float* __restrict__ lse,
-                                                        float* __restrict__ delta, bf16* __restrict__ dqkv, int S, int nh,
+                                                        float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int nh,
                                                         float sc2, float scale) {
   constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB, ND = D / 32;
   __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
-  static_assert(2 * ND * 16 * 64 * 4 <= NSLOT * STAGE, "the partial results of two waves fit in the ring");
+  static_assert(2 * ND * 16 * 64 * 4 + 2 * strip_bytes<D>() <= NSLOT * STAGE, "the partial results and output strips of two waves fit in the ring");
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qt = wave & 1, kh = wave >> 1;
   const int nq = S / 64;
-  const int nbh = gridDim.x / nq;
-  const int bh = blockIdx.x % nbh;
-  const int qb = CAUSAL ? causal_query_block(blockIdx.x / nbh, nq) : blockIdx.x / nbh;
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int qb = CAUSAL ? causal_query_block(rank, nq) : rank;
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
@@ -954,19 +963,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
   }
   __syncthreads();
   if (kh == 1) return;
-  bf16* out = dqkv + ((size_t)b * S + q) * ld + head * D;
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      bf16x4 v;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int r = 4 * g + i;
-        v[i] = f2bf((st.acc[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale);
-      }
-      *(bf16x4*)(out + dt * 32 + 8 * g + 4 * hf) = v;
-    }
+  store_rows<D>([&](int dt, int r) { return (st.acc[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale; }, ring + NSLOT * STAGE - (2 - qt) * strip_bytes<D>(),
+                dqkv + ((size_t)b * S + qw0) * ld + head * D, ld, lane);
 }
 
 // =========================================================================== backward: dK, dV (one block per 128 keys)
@@ -989,7 +987,7 @@ __device__ __forceinline__ void dkv_step(const char* cur, int t, const char* nxt
                                          const LaneOffs<D>& lo, int lim, float sc2, int hf) {
   constexpr int NK = D / 16, ND = D / 32, TILEB = 64 * 2 * D;
   constexpr int N1 = 2 * NK, NS = N1 + 4 * ND;   // slots: S and dP by turns, then dV and dK by turns
-  constexpr int SE = NS - 2 * ND - 1 < N1 ? NS - 2 * ND - 1 : N1;  // slots over which the 16 probabilities are spread
+  constexpr int SE = NS - 2 * ND - 2;            // slots over which the 16 probabilities are spread
   static_assert(15 * SE / 16 < NS - 2 * ND && 7 * SE / 16 < N1, "probabilities precede their products");
   constexpr int AHEAD = 5;
   const float* stat = (const float*)(cur + 2 * TILEB) + t + 4 * hf;        // log-sum-exps; 64 further on the -deltas
@@ -1052,15 +1050,15 @@ __device__ __forceinline__ void dkv_issue(const bf16* gQ, const bf16* gO, const 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
                                                        const float* __restrict__ lse, const float* __restrict__ delta,
-                                                       bf16* __restrict__ dqkv, int S, int nh, float sc2, float scale) {
+                                                       bf16* __restrict__ dqkv, int B, int S, int nh, float sc2, float scale) {
   constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB + 1024;
   __shared__ __attribute__((aligned(1024))) char ring[3 * STAGE];
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
-  const int nbh = gridDim.x / (S / 128);
-  const int bh = blockIdx.x % nbh;
-  const int kb = blockIdx.x / nbh;  // key block 0 sees every query tile: heaviest first
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int kb = rank;  // key block 0 sees every query tile: heaviest first
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D, ldo = nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
@@ -1132,21 +1130,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_dkv_kernel(const bf
   for (; j < ntile; j++) { AH_DKV_TILE(false) }
 #undef AH_DKV_TILE
 
-  bf16* outk = dqkv + ((size_t)b * S + key) * ld + nh * D + head * D;
-  bf16* outv = outk + nh * D;
-#pragma unroll
-  for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      bf16x4 a, c;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        a[i] = f2bf(st.dk[dt][4 * g + i] * scale);
-        c[i] = f2bf(st.dv[dt][4 * g + i]);
-      }
-      *(bf16x4*)(outk + dt * 32 + 8 * g + 4 * hf) = a;
-      *(bf16x4*)(outv + dt * 32 + 8 * g + 4 * hf) = c;
-    }
+  char* strip = ring + wave * strip_bytes<D>();
+  bf16* out = dqkv + ((size_t)b * S + kw0) * ld + nh * D + head * D;
+  store_rows<D>([&](int dt, int r) { return st.dk[dt][r] * scale; }, strip, out, ld, lane);
+  store_rows<D>([&](int dt, int r) { return st.dv[dt][r]; }, strip, out + nh * D, ld, lane);
 }
 
 // =========================================================================== backward: dK, dV for launches that cannot fill the chip
@@ -1227,18 +1214,18 @@ __device__ __forceinline__ void dkv_half_tile(const char* __restrict__ cQ, const
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
-                                                         bf16* __restrict__ dqkv, int S, int nh, float sc2, float scale) {
+                                                         bf16* __restrict__ dqkv, int B, int S, int nh, float sc2, float scale) {
   constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB + 1024, LPS = 2 * (D / 32) + 1, ND = D / 32;
   __shared__ __attribute__((aligned(1024))) char ring[4 * STAGE];
-  static_assert(2 * 2 * ND * 16 * 64 * 4 <= 4 * STAGE, "the partial results of two waves fit in the ring");
+  static_assert(2 * 2 * ND * 16 * 64 * 4 + 2 * strip_bytes<D>() <= 4 * STAGE, "the partial results and output strips of two waves fit in the ring");
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kt = wave & 1, qh = wave >> 1;
   const int nkb = S / 64;
-  const int nbh = gridDim.x / nkb;
-  const int bh = blockIdx.x % nbh;
-  const int kb = blockIdx.x / nbh;  // key block 0 sees every query tile: heaviest first
-  const int b = bh / nh, head = bh % nh;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int kb = rank;  // key block 0 sees every query tile: heaviest first
+  const int b = bh / nh, head = bh - b * nh;
   const int ld = 3 * nh * D, ldo = nh * D;
   const bf16* qp = qkv + (size_t)b * S * ld + head * D;
   const bf16* kp = qp + nh * D;
@@ -1308,22 +1295,10 @@ __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict_
   }
   __syncthreads();
   if (qh == 1) return;
-  bf16* outk = dqkv + ((size_t)b * S + key) * ld + nh * D + head * D;
-  bf16* outv = outk + nh * D;
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      bf16x4 a, c;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int r = 4 * g + i;
-        a[i] = f2bf((st.dk[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale);
-        c[i] = f2bf(st.dv[dt][r] + mg[((ND + dt) * 16 + r) * 64 + lane]);
-      }
-      *(bf16x4*)(outk + dt * 32 + 8 * g + 4 * hf) = a;
-      *(bf16x4*)(outv + dt * 32 + 8 * g + 4 * hf) = c;
-    }
+  char* strip = ring + 4 * STAGE - (2 - kt) * strip_bytes<D>();
+  bf16* out = dqkv + ((size_t)b * S + kw0) * ld + nh * D + head * D;
+  store_rows<D>([&](int dt, int r) { return (st.dk[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale; }, strip, out, ld, lane);
+  store_rows<D>([&](int dt, int r) { return st.dv[dt][r] + mg[((ND + dt) * 16 + r) * 64 + lane]; }, strip, out + nh * D, ld, lane);
 }
 
 }  // namespace
@@ -1340,13 +1315,13 @@ static int small_grid_blocks() {
 static bool attn_shape_ok(int B, int S, int nh, int d) { return B > 0 && nh > 0 && S > 0 && S % 128 == 0 && (d == 64 || d == 128); }
 
 template <int D, bool CAUSAL>
-static void launch_fwd_t(dim3 grid, hipStream_t s, const void* qkv, void* o, float* lse, int S, int nh, float sc2) {
+static void launch_fwd_t(dim3 grid, hipStream_t s, const void* qkv, void* o, float* lse, int B, int S, int nh, float sc2) {
   if ((int)grid.x <= small_grid_blocks())  // at most one 128-query block per CU: 64-query blocks with the keys split between wave pairs
-    hipLaunchKernelGGL((attn_fwd64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, S, nh, sc2);
+    hipLaunchKernelGGL((attn_fwd64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, B, S, nh, sc2);
   else if constexpr (D == 64 && !CAUSAL)
-    hipLaunchKernelGGL((attn_fwd_plain_kernel<D>), grid, dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, S, nh, sc2);
+    hipLaunchKernelGGL((attn_fwd_plain_kernel<D>), grid, dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, B, S, nh, sc2);
   else
-    hipLaunchKernelGGL((attn_fwd_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, S, nh, sc2);
+    hipLaunchKernelGGL((attn_fwd_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (bf16*)o, lse, B, S, nh, sc2);
 }
 
 hipError_t launch_attention_fwd(const void* qkv, void* o, float* lse, int B, int S, int nh, int d, bool causal, hipStream_t s) {
@@ -1354,11 +1329,11 @@ hipError_t launch_attention_fwd(const void* qkv, void* o, float* lse, int B, int
   const float sc2 = LOG2E / sqrtf((float)d);
   const dim3 grid(B * nh * (S / 128));
   if (d == 128) {
-    if (causal) launch_fwd_t<128, true>(grid, s, qkv, o, lse, S, nh, sc2);
-    else launch_fwd_t<128, false>(grid, s, qkv, o, lse, S, nh, sc2);
+    if (causal) launch_fwd_t<128, true>(grid, s, qkv, o, lse, B, S, nh, sc2);
+    else launch_fwd_t<128, false>(grid, s, qkv, o, lse, B, S, nh, sc2);
   } else {
-    if (causal) launch_fwd_t<64, true>(grid, s, qkv, o, lse, S, nh, sc2);
-    else launch_fwd_t<64, false>(grid, s, qkv, o, lse, S, nh, sc2);
+    if (causal) launch_fwd_t<64, true>(grid, s, qkv, o, lse, B, S, nh, sc2);
+    else launch_fwd_t<64, false>(grid, s, qkv, o, lse, B, S, nh, sc2);
   }
   return hipGetLastError();
 }
@@ -1366,19 +1341,19 @@ hipError_t launch_attention_fwd(const void* qkv, void* o, float* lse, int B, int
 // dQ first: it leaves the row sums delta = rowsum(dO * O) of its queries behind for the dK/dV kernel
 template <int D, bool CAUSAL>
 static void launch_bwd_t(dim3 grid, hipStream_t s, const void* qkv, const void* o, const float* lse, const void* d_o,
-                         void* dqkv, float* delta, int S, int nh, float sc2, float scale) {
+                         void* dqkv, float* delta, int B, int S, int nh, float sc2, float scale) {
   if ((int)grid.x <= small_grid_blocks())  // at most one 128-query block per CU: 64-query blocks with the keys split between wave pairs
     hipLaunchKernelGGL((attn_dq64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse,
-                       delta, (bf16*)dqkv, S, nh, sc2, scale);
+                       delta, (bf16*)dqkv, B, S, nh, sc2, scale);
   else
     hipLaunchKernelGGL((attn_dq_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse, delta,
-                       (bf16*)dqkv, S, nh, sc2, scale);
+                       (bf16*)dqkv, B, S, nh, sc2, scale);
   if ((int)grid.x <= small_grid_blocks())  // at most one 128-key block per CU: 64-key blocks with the queries split between wave pairs
     hipLaunchKernelGGL((attn_dkv64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (const bf16*)d_o, lse, delta,
-                       (bf16*)dqkv, S, nh, sc2, scale);
+                       (bf16*)dqkv, B, S, nh, sc2, scale);
   else
     hipLaunchKernelGGL((attn_dkv_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)d_o, lse, delta, (bf16*)dqkv,
-                       S, nh, sc2, scale);
+                       B, S, nh, sc2, scale);
 }
 
 hipError_t launch_attention_bwd(const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
@@ -1387,11 +1362,11 @@ hipError_t launch_attention_bwd(const void* qkv, const void* o, const float* lse
   const float scale = 1.f / sqrtf((float)d), sc2 = LOG2E * scale;
   const dim3 grid(B * nh * (S / 128));
   if (d == 128) {
-    if (causal) launch_bwd_t<128, true>(grid, s, qkv, o, lse, d_o, dqkv, delta, S, nh, sc2, scale);
-    else launch_bwd_t<128, false>(grid, s, qkv, o, lse, d_o, dqkv, delta, S, nh, sc2, scale);
+    if (causal) launch_bwd_t<128, true>(grid, s, qkv, o, lse, d_o, dqkv, delta, B, S, nh, sc2, scale);
+    else launch_bwd_t<128, false>(grid, s, qkv, o, lse, d_o, dqkv, delta, B, S, nh, sc2, scale);
   } else {
-    if (causal) launch_bwd_t<64, true>(grid, s, qkv, o, lse, d_o, dqkv, delta, S, nh, sc2, scale);
-    else launch_bwd_t<64, false>(grid, s, qkv, o, lse, d_o, dqkv, delta, S, nh, sc2, scale);
+    if (causal) launch_bwd_t<64, true>(grid, s, qkv, o, lse, d_o, dqkv, delta, B, S, nh, sc2, scale);
+    else launch_bwd_t<64, false>(grid, s, qkv, o, lse, d_o, dqkv, delta, B, S, nh, sc2, scale);
   }
   return hipGetLastError();
 }
