@@ -83,6 +83,13 @@ __device__ __forceinline__ void issue_tile(const bf16* __restrict__ g, const uin
   for (int i = 0; i < D / 32; i++) load16_to_lds_uncounted(g, off[i], lds + (wave + 4 * i) * 1024);
 }
 
+// 32 rows
+template <int D>
+__device__ __forceinline__ void issue_half(const bf16* __restrict__ g, const uint32_t* off, char* lds, int wave) {
+#pragma unroll
+  for (int i = 0; i < D / 64; i++) load16_to_lds_uncounted(g, off[i], lds + (wave + 4 * i) * 1024);
+}
+
 // 8 consecutive head-dim values (k-step ks, half hf) of row r
 template <int D>
 __device__ __forceinline__ bf16x8 frag_rowmajor(const char* __restrict__ t, int r, int ks, int hf) {
@@ -682,49 +689,173 @@ struct DqState {
   bf16x8 qf[D / 16], dof[D / 16];
   f32x16 acc[D / 32];
   float lse2, delta;
+  // token: the query's row of o and d_o; row: its place in lse and delta
+  __device__ __forceinline__ void load(const bf16* __restrict__ qrow, const bf16* __restrict__ o, const bf16* __restrict__ d_o,
+                                       const float* __restrict__ lse, float* __restrict__ dlt, size_t token, size_t row, int head, int nh,
+                                       int hf, bool keep) {
+    const size_t at = token * (nh * D) + head * D;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) {
+      qf[ks] = *(const bf16x8*)(qrow + ks * 16 + hf * 8);
+      dof[ks] = *(const bf16x8*)(d_o + at + ks * 16 + hf * 8);
+    }
+#pragma unroll
+    for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[dt][r] = 0.f;
+    lse2 = lse[row] * LOG2E;
+    delta = row_delta<D>(dof, o + at, hf);
+    if (hf == 0 && keep) dlt[row] = -delta;  // negated: what the dK/dV kernel starts dP from
+  }
 };
 
-// One key tile of 64 for the wave's 32 queries.  With head_dim 64 the LDS reads run a phase ahead of their
-// use as in dkv_tile; with head_dim 128 the 256 registers of a wave (two blocks share a CU) leave no room
-// for fragments in flight, so they are fetched where they are used and the other block covers the wait.
+// ---- head_dim 128: a pipeline of steps over 32 keys, in slots as in the forward kernel (the 256 registers of a wave leave no room for
+// 64): 2 x 16 x 2048 causal 79.7 -> 70.2 us, without the mask 99.9 -> 96.9 (one tile of 64 keys after the other, its fragments
+// fetched where they were used).
+// One step: dS of the keys whose scores S and dP - delta are in s, dp (K
+// rows at cK), its product with K, and S and dP - delta of the next 32 keys (rows at nK, nV).
+template <int D, bool MASK>
+__device__ __forceinline__ void dq_step(const char* cK, const char* nK, const char* nV, DqState<D>& st, f32x16& s, f32x16& dp,
+                                        const LaneOffs<D>& lo, int lim, float sc2) {
+  constexpr int NK = D / 16, ND = D / 32;
+  constexpr int N1 = 2 * NK, NS = N1 + 2 * ND;   // slots: S and dP by turns, then dQ
+  constexpr int SE = NS - ND - 2;                // slots over which the 16 elements are spread
+  static_assert(15 * SE / 16 < NS - ND && 7 * SE / 16 < N1, "dS precedes its product");
+  constexpr int AHEAD = 4;
+  f32x16 ns, ndp;
+#pragma unroll
+  for (int r = 0; r < 16; r++) { ns[r] = 0.f; ndp[r] = -st.delta; }   // the product dO V^T lands on -delta: dP - delta for free
+  bf16x8 fr[NS], dsf[2];
+  auto fetch = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < N1) fr[i] = lo.rows(i & 1 ? nV : nK, 0, i >> 1);
+    else if constexpr (i < NS) fr[i] = lo.cols(cK, 16 * ((i - N1) / ND), (i - N1) % ND);
+  };
+  auto element = [&](auto ic) {   // key 8 (r / 4) + 4 hf + r % 4 of the 32, the lane's query: masked iff beyond lim = q - first key - 4 hf
+    constexpr int r = decltype(ic)::value;
+    s[r] = fexp2(__builtin_fmaf(s[r], sc2, -st.lse2));
+    if (MASK && 8 * (r >> 2) + (r & 3) > lim) s[r] = 0.f;
+    s[r] *= dp[r];
+    if constexpr ((r & 7) == 7) dsf[r >> 3] = pack8(s, r >> 3);
+  };
+  unrolled<0, AHEAD>(fetch);
+  unrolled<0, NS>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    AH_SCHED_FENCE();
+    fetch(std::integral_constant<int, i + AHEAD>{});
+    if constexpr (i >= N1) st.acc[(i - N1) % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], dsf[(i - N1) / ND], st.acc[(i - N1) % ND], 0, 0, 0);
+    else if constexpr (i & 1) ndp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], st.dof[i >> 1], ndp, 0, 0, 0);
+    else ns = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], st.qf[i >> 1], ns, 0, 0, 0);
+    AH_SCHED_FENCE();
+    if constexpr (i < SE) unrolled<i * 16 / SE, (i + 1) * 16 / SE>(element);
+  });
+  s = ns;
+  dp = ndp;
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
+                                                      const bf16* __restrict__ d_o, const float* __restrict__ lse,
+                                                      float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int nh,
+                                                      float sc2, float scale) {
+  constexpr int HALF = 32 * 2 * D;                                 // bytes of 32 rows
+  __shared__ __attribute__((aligned(1024))) char ring[10 * HALF];  // six halves of K tiles, four of V tiles
+  const int lane = threadIdx.x & 63, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: LDS bases stay scalar
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int qb = CAUSAL ? causal_query_block(rank, S / 128) : rank;
+  const int b = bh / nh, head = bh - b * nh;
+  const int ld = 3 * nh * D;
+  const bf16* qp = qkv + (size_t)b * S * ld + head * D;
+  const bf16* kp = qp + nh * D;
+  const bf16* vp = qp + 2 * nh * D;
+  const int qw0 = qb * 128 + wave * 32, q = qw0 + (lane & 31);
+
+  DqState<D> st;
+  st.load(qp + (size_t)q * ld, o, d_o, lse, delta, (size_t)b * S + q, ((size_t)b * nh + head) * S + q, head, nh, hf, true);
+
+  uint32_t off[D / 64];
+#pragma unroll
+  for (int i = 0; i < D / 64; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
+
+  // Keys by 32 up to and including the diagonal (all of them without the mask), two steps per round.  Keys 32 h .. are in K
+  // slot h % 6 and V slot h % 4: step h reads the columns of K half h and the rows of halves h + 1, so a round needs four halves
+  // of K (three of V) while the two after those arrive.  (Past the end the last half is fetched again, into slots whose scores
+  // nobody uses.)
+  const int nround = CAUSAL ? 2 * qb + 2 : S / 64, lasth = 2 * nround - 1;
+  auto load = [&](int h) {
+    const size_t row = (size_t)min(h, lasth) * 32 * ld;
+    issue_half<D>(kp + row, off, ring + (h % 6) * HALF, wave);
+    issue_half<D>(vp + row, off, ring + (6 + (h & 3)) * HALF, wave);
+  };
+  // (opaque to the compiler, which otherwise keeps every lane's address of every slot)
+  auto slot_k = [&](int h) { int x = (h % 6) * HALF; asm("" : "+s"(x)); return (const char*)ring + x; };
+  auto slot_v = [&](int h) { int x = (6 + (h & 3)) * HALF; asm("" : "+s"(x)); return (const char*)ring + x; };
+  load(0);
+  load(1);
+  load(2);
+  const LaneOffs<D> lo(lane);
+  f32x16 s, dp;
+#pragma unroll
+  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -st.delta; }
+  AH_NEXT_TILE();
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(slot_k(0), 0, ks), st.qf[ks], s, 0, 0, 0);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(slot_v(0), 0, ks), st.dof[ks], dp, 0, 0, 0);
+  }
+  const int lim = q - 4 * hf;
+#define AH_DQ_ROUND(MASK)                                                                                               \
+  load(h + 3);                                                                                                          \
+  load(h + 4);                                                                                                          \
+  dq_step<D, MASK>(slot_k(h), slot_k(h + 1), slot_v(h + 1), st, s, dp, lo, lim - 32 * h, sc2);                          \
+  dq_step<D, MASK>(slot_k(h + 1), slot_k(h + 2), slot_v(h + 2), st, s, dp, lo, lim - 32 * h - 32, sc2);                 \
+  AH_NEXT_TILE()
+  int h = 0;
+#pragma unroll 1
+  for (; h < (CAUSAL ? 4 * qb : lasth); h += 2) { AH_DQ_ROUND(false); }
+  if (CAUSAL) {  // the keys of the block's own queries
+#pragma unroll 1
+    for (; h < lasth; h += 2) { AH_DQ_ROUND(true); }
+  }
+#undef AH_DQ_ROUND
+
+  store_rows<D>([&](int dt, int r) { return st.acc[dt][r] * scale; }, ring + wave * strip_bytes<D>(), dqkv + ((size_t)b * S + qw0) * ld + head * D, ld, lane);
+}
+
+// ---- head_dim 64: one tile of 64 keys after the other, LDS reads a phase ahead of their use.  Three waves fit a SIMD this way (168
+// registers; the steps above take 181) and do better than two that overlap their own phases: 8 x 16 x 512 20.3 against
+// 21.6 us, 2 x 16 x 2048 causal 35.2 / 38.1, 1 x 32 x 4096 causal 5 % more for the whole backward.
 template <int D, bool DIAG>
 __device__ __forceinline__ void dq_tile(const char* __restrict__ cK, const char* __restrict__ cV, DqState<D>& st, int k0, int q,
                                         float sc2, int lane) {
   constexpr int NK = D / 16, ND = D / 32;
-  constexpr bool AHEAD = D == 64;
   const int hf = lane >> 5;
   const int lim = q - k0 - 4 * hf;  // element r of half t is masked iff t*32 + 8*(r/4) + r%4 > lim
   bf16x8 fk[NK], fv[NK];
-  if (AHEAD) {
 #pragma unroll
-    for (int ks = 0; ks < NK; ks++) {
-      fk[ks] = frag_rowmajor<D>(cK, lane & 31, ks, hf);
-      fv[ks] = frag_rowmajor<D>(cV, lane & 31, ks, hf);
-    }
+  for (int ks = 0; ks < NK; ks++) {
+    fk[ks] = frag_rowmajor<D>(cK, lane & 31, ks, hf);
+    fv[ks] = frag_rowmajor<D>(cV, lane & 31, ks, hf);
   }
 #pragma unroll
   for (int t = 0; t < 2; t++) {
-    if (AHEAD) AH_SCHED_FENCE();
+    AH_SCHED_FENCE();
     f32x16 s, dp;
 #pragma unroll
     for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -st.delta; }   // the product dO V^T lands on -delta: dP - delta for free
     bf16x8 kt[2][ND];
 #pragma unroll
     for (int ks = 0; ks < NK; ks++) {
-      if (!AHEAD) {
-        fk[ks] = frag_rowmajor<D>(cK, t * 32 + (lane & 31), ks, hf);
-        fv[ks] = frag_rowmajor<D>(cV, t * 32 + (lane & 31), ks, hf);
-      }
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[ks], st.qf[ks], s, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[ks], st.dof[ks], dp, 0, 0, 0);
     }
-    if (AHEAD) {
 #pragma unroll
-      for (int s2 = 0; s2 < 2; s2++)
+    for (int s2 = 0; s2 < 2; s2++)
 #pragma unroll
-        for (int dt = 0; dt < ND; dt++) kt[s2][dt] = frag_transposed<D>(cK, t * 32 + 16 * s2 + 4 * hf, dt, lane);
-      AH_SCHED_FENCE();
-    }
+      for (int dt = 0; dt < ND; dt++) kt[s2][dt] = frag_transposed<D>(cK, t * 32 + 16 * s2 + 4 * hf, dt, lane);
+    AH_SCHED_FENCE();
     const float nl = -st.lse2;
 #pragma unroll
     for (int r = 0; r < 16; r++) s[r] = fexp2(__builtin_fmaf(s[r], sc2, nl));
@@ -735,30 +866,27 @@ __device__ __forceinline__ void dq_tile(const char* __restrict__ cK, const char*
     }
 #pragma unroll
     for (int r = 0; r < 16; r++) s[r] *= dp[r];  // dS^T
-    if (AHEAD && t == 0) {
+    if (t == 0) {
 #pragma unroll
       for (int ks = 0; ks < NK; ks++) {
         fk[ks] = frag_rowmajor<D>(cK, 32 + (lane & 31), ks, hf);
         fv[ks] = frag_rowmajor<D>(cV, 32 + (lane & 31), ks, hf);
       }
     }
-    if (AHEAD) AH_SCHED_FENCE();
+    AH_SCHED_FENCE();
 #pragma unroll
     for (int s2 = 0; s2 < 2; s2++) {
       const bf16x8 dsf = pack8(s, s2);
 #pragma unroll
-      for (int dt = 0; dt < ND; dt++) {
-        if (!AHEAD) kt[s2][dt] = frag_transposed<D>(cK, t * 32 + 16 * s2 + 4 * hf, dt, lane);
-        st.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[s2][dt], dsf, st.acc[dt], 0, 0, 0);
-      }
+      for (int dt = 0; dt < ND; dt++) st.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[s2][dt], dsf, st.acc[dt], 0, 0, 0);
     }
   }
-  if (AHEAD) AH_SCHED_FENCE();
+  AH_SCHED_FENCE();
 }
 
 // MASK as in fwd_step
 template <int D, bool MASK>
-__device__ __forceinline__ void dq_step(const bf16* gK, const bf16* gV, uint32_t* off, char* __restrict__ nK,
+__device__ __forceinline__ void dq_tile_step(const bf16* gK, const bf16* gV, uint32_t* off, char* __restrict__ nK,
                                         char* __restrict__ nV, const char* __restrict__ cK, const char* __restrict__ cV,
                                         DqState<D>& st, int k0, int q, int qw0, float sc2, int wave, int lane) {
   issue_tile<D>(gK, off, nK, wave);
@@ -768,7 +896,7 @@ __device__ __forceinline__ void dq_step(const bf16* gK, const bf16* gV, uint32_t
 }
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
+__global__ __launch_bounds__(256, 2) void attn_dq_plain_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                       const bf16* __restrict__ d_o, const float* __restrict__ lse,
                                                       float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int nh,
                                                       float sc2, float scale) {
@@ -787,19 +915,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
   const int qw0 = qb * 128 + wave * 32, q = qw0 + (lane & 31);
 
   DqState<D> st;
-  const bf16* dop = d_o + ((size_t)b * S + q) * (nh * D) + head * D;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) {
-    st.qf[ks] = *(const bf16x8*)(qp + (size_t)q * ld + ks * 16 + hf * 8);
-    st.dof[ks] = *(const bf16x8*)(dop + ks * 16 + hf * 8);
-  }
-#pragma unroll
-  for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) st.acc[dt][r] = 0.f;
-  st.lse2 = lse[((size_t)b * nh + head) * S + q] * LOG2E;
-  st.delta = row_delta<D>(st.dof, o + ((size_t)b * S + q) * (nh * D) + head * D, hf);
-  if (hf == 0) delta[((size_t)b * nh + head) * S + q] = -st.delta;  // negated: what the dK/dV kernel starts dP from
+  st.load(qp + (size_t)q * ld, o, d_o, lse, delta, (size_t)b * S + q, ((size_t)b * nh + head) * S + q, head, nh, hf, true);
 
   uint32_t off[D / 32];
 #pragma unroll
@@ -814,16 +930,16 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
   AH_NEXT_TILE();
   for (int j = 0; j < nfull; j += 2) {
     const size_t o1 = (size_t)(j + 1) * step, o2 = (size_t)min(j + 2, last) * step;
-    dq_step<D, false>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, j * 64, q, qw0, sc2, wave, lane);
+    dq_tile_step<D, false>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, j * 64, q, qw0, sc2, wave, lane);
     AH_NEXT_TILE();
-    dq_step<D, false>(kp + o2, vp + o2, off, K0, V0, K1, V1, st, (j + 1) * 64, q, qw0, sc2, wave, lane);
+    dq_tile_step<D, false>(kp + o2, vp + o2, off, K0, V0, K1, V1, st, (j + 1) * 64, q, qw0, sc2, wave, lane);
     AH_NEXT_TILE();
   }
   if (CAUSAL) {
     const size_t o1 = (size_t)last * step;
     int late = lane;  // opaque, so that the addresses of these two tiles are not computed and kept (spilled) before the loop
     asm volatile("" : "+v"(late));
-    dq_step<D, true>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, (last - 1) * 64, q, qw0, sc2, wave, late);
+    dq_tile_step<D, true>(kp + o1, vp + o1, off, K1, V1, K0, V0, st, (last - 1) * 64, q, qw0, sc2, wave, late);
     AH_NEXT_TILE();
     if (last * 64 <= qw0 + 31) dq_tile<D, true>(K1, V1, st, last * 64, q, sc2, late);
   }
@@ -919,20 +1035,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
   const bf16* vp = qp + 2 * nh * D;
   const int qw0 = qb * 64 + qt * 32, q = qw0 + (lane & 31);
 
-  DqState<D> st;
-  const bf16* dop = d_o + ((size_t)b * S + q) * (nh * D) + head * D;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) {
-    st.qf[ks] = *(const bf16x8*)(qp + (size_t)q * ld + ks * 16 + hf * 8);
-    st.dof[ks] = *(const bf16x8*)(dop + ks * 16 + hf * 8);
-  }
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) st.acc[dt][r] = 0.f;
-  st.lse2 = lse[((size_t)b * nh + head) * S + q] * LOG2E;
-  st.delta = row_delta<D>(st.dof, o + ((size_t)b * S + q) * (nh * D) + head * D, hf);   // both key halves compute it, one writes
-  if (hf == 0 && kh == 0) delta[((size_t)b * nh + head) * S + q] = -st.delta;
+  DqState<D> st;   // (both key halves' waves take delta, one writes it)
+  st.load(qp + (size_t)q * ld, o, d_o, lse, delta, (size_t)b * S + q, ((size_t)b * nh + head) * S + q, head, nh, hf, kh == 0);
 
   uint32_t off[D / 32];
 #pragma unroll
@@ -1345,6 +1449,9 @@ static void launch_bwd_t(dim3 grid, hipStream_t s, const void* qkv, const void* 
   if ((int)grid.x <= small_grid_blocks())  // at most one 128-query block per CU: 64-query blocks with the keys split between wave pairs
     hipLaunchKernelGGL((attn_dq64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse,
                        delta, (bf16*)dqkv, B, S, nh, sc2, scale);
+  else if constexpr (D == 64)
+    hipLaunchKernelGGL((attn_dq_plain_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse, delta,
+                       (bf16*)dqkv, B, S, nh, sc2, scale);
   else
     hipLaunchKernelGGL((attn_dq_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse, delta,
                        (bf16*)dqkv, B, S, nh, sc2, scale);
