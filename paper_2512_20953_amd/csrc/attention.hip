@@ -22,6 +22,7 @@
 // the mask both walk every tile of the sequence).
 #include "common.h"
 #include "kernels.h"
+#include <cfloat>
 #include <cstdlib>
 #include <type_traits>
 
@@ -529,39 +530,38 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict
 // owns queries 32 * (w & 1) .. + 31 and, of every 64-key tile, the keys 32 * (w >> 1) .. + 31.  There are twice as
 // many blocks (two per CU, heavy ones paired with light ones) and every wave walks half the keys of its queries;
 // the two partial results per query (running maximum, sum and output accumulator) meet in LDS at the end.
+// The steps are those of the 128-row kernels, here and in both backward kernels: 1 x 16 x 2048 x 128 causal, forward / dQ / dK,dV, 34.4 /
+// 42.6 / 60.9 us one phase after the other, 32.7 / 41.0 / 57.0 now; 1 x 16 x 1024 x 64 causal 11.7 / 13.1 / 16.8 and 11.0 / 13.4 / 15.3.
 template <int D>
-__device__ __forceinline__ void fwd_half_tile(const char* __restrict__ cK, const char* __restrict__ cV, FwdState<D>& st, int kbase,
-                                              int kh, int q, bool diag, float sc2, int lane) {
-  constexpr int NK = D / 16, ND = D / 32;
-  const int hf = lane >> 5;
-  bf16x8 fk[NK];
-#pragma unroll
-  for (int ks = 0; ks < NK; ks++) fk[ks] = frag_rowmajor<D>(cK, 32 * kh + (lane & 31), ks, hf);
-  AH_SCHED_FENCE();
-  f32x16 s;
+__device__ __forceinline__ void fwd_half_scores(const char* cK, const LaneOffs<D>& lo, const bf16x8 (&qf)[D / 16], f32x16& s) {
 #pragma unroll
   for (int r = 0; r < 16; r++) s[r] = 0.f;
 #pragma unroll
-  for (int ks = 0; ks < NK; ks++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[ks], st.qf[ks], s, 0, 0, 0);
-  bf16x8 v[2][ND];
-#pragma unroll
-  for (int s2 = 0; s2 < 2; s2++)
-#pragma unroll
-    for (int dt = 0; dt < ND; dt++) v[s2][dt] = frag_transposed<D>(cV, 32 * kh + 16 * s2 + 4 * hf, dt, lane);
-  AH_SCHED_FENCE();
-  if (diag) {
-    // element r is key kbase + 8*(r/4) + 4*hf + r%4: masked iff that exceeds q
-    const int lim = q - kbase - 4 * hf;
+  for (int ks = 0; ks < D / 16; ks++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cK, 0, ks), qf[ks], s, 0, 0, 0);
+}
+
+// maximum over 32 keys; under the mask (lim = q - first key - 4 hf) of those the query sees
+template <bool DIAG>
+__device__ __forceinline__ float fwd_half_max(f32x16& s, int lim) {
+  if (DIAG) {
 #pragma unroll
     for (int r = 0; r < 16; r++)
       if (8 * (r >> 2) + (r & 3) > lim) s[r] = -INFINITY;
   }
-  float mx = s[0];
+  float mx = fmaxf(s[0], s[1]);
 #pragma unroll
-  for (int r = 1; r < 16; r++) mx = fmaxf(mx, s[r]);
-  mx = half_max(mx) * sc2;
-  if (__any(mx > st.m + RESCALE_SLACK)) {  // wave-uniform branch
-    const float m_new = fmaxf(st.m, mx);
+  for (int r = 2; r < 16; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);  // one three-way maximum each
+  return half_max(mx);
+}
+
+// One step of the pipeline (see fwd_pipe) over 32 keys
+template <int D, bool NEXT, bool DIAG>
+__device__ __forceinline__ void fwd_half_step(const char* nK, const char* cV, FwdState<D>& st, f32x16& s, float& mx, const LaneOffs<D>& lo,
+                                              int lim, float sc2) {
+  constexpr int NK = D / 16, ND = D / 32;
+  const float mxs = mx * sc2;
+  if (__any(mxs > st.m + RESCALE_SLACK)) {  // wave-uniform branch
+    const float m_new = fmaxf(st.m, mxs);
     const float alpha = fexp2(st.m - m_new);
     st.m = m_new;
     st.l *= alpha;
@@ -571,21 +571,43 @@ __device__ __forceinline__ void fwd_half_tile(const char* __restrict__ cK, const
       for (int r = 0; r < 16; r++) st.oacc[dt][r] *= alpha;
   }
   const float nm = -st.m;
+  constexpr int N1 = NEXT ? NK : 0, NS = N1 + 2 * ND;   // slots: scores, then the product with V
+  constexpr int SE = NEXT ? N1 + ND - 1 : 0;            // slots over which the 16 probabilities are spread
+  static_assert(!NEXT || (7 * SE / 16 < N1 && 15 * SE / 16 < N1 + ND), "probabilities precede their products");
+  constexpr int AHEAD = 4;
+  f32x16 t;
+  bf16x8 fr[NS], pf[2];
   float ls = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; r++) {
+  auto fetch = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < N1) fr[i] = lo.rows(nK, 0, i);
+    else if constexpr (i < NS) fr[i] = lo.cols(cV, 16 * ((i - N1) / ND), (i - N1) % ND);
+  };
+  auto element = [&](auto ic) {
+    constexpr int r = decltype(ic)::value;
     s[r] = fexp2(__builtin_fmaf(s[r], sc2, nm));
     ls += s[r];
+    if constexpr ((r & 7) == 7) pf[r >> 3] = pack8(s, r >> 3);
+  };
+  if (NEXT) {
+#pragma unroll
+    for (int r = 0; r < 16; r++) t[r] = 0.f;
+  } else {
+    unrolled<0, 16>(element);
   }
+  unrolled<0, AHEAD>(fetch);
+  unrolled<0, NS>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    AH_SCHED_FENCE();
+    fetch(std::integral_constant<int, i + AHEAD>{});
+    if constexpr (i < N1) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], st.qf[i], t, 0, 0, 0);
+    else st.oacc[(i - N1) % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], pf[(i - N1) / ND], st.oacc[(i - N1) % ND], 0, 0, 0);
+    AH_SCHED_FENCE();
+    if constexpr (i < SE) unrolled<i * 16 / SE, (i + 1) * 16 / SE>(element);
+    if constexpr (NEXT && i == NS - ND) mx = fwd_half_max<DIAG>(t, lim);
+  });
   st.l += ls;
-  AH_SCHED_FENCE();
-#pragma unroll
-  for (int s2 = 0; s2 < 2; s2++) {
-    const bf16x8 pf = pack8(s, s2);
-#pragma unroll
-    for (int dt = 0; dt < ND; dt++) st.oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[s2][dt], pf, st.oacc[dt], 0, 0, 0);
-  }
-  AH_SCHED_FENCE();
+  if (NEXT) s = t;
 }
 
 template <int D, bool CAUSAL>
@@ -615,24 +637,39 @@ __global__ __launch_bounds__(256, 2) void attn_fwd64_kernel(const bf16* __restri
 #pragma unroll
   for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
 
-  // key tiles of 64 up to and including the one that holds the block's own keys; tile t lives in ring slot t % 2
-  // and is fetched during step t - 1 (past the end the last tile again, into a slot nobody reads)
-  const int ntile = CAUSAL ? qb + 1 : nq, last = ntile - 1;
+  // Key tiles of 64 up to and including the one that holds the block's own keys, one step of the pipeline each (the wave's half of
+  // it).  K tile t lives in K slot t % 2 and V tile t in V slot t % 2; step j reads K tile j + 1 and V tile j, while K tile
+  // j + 2 and V tile j + 1 arrive.
+  st.m = -FLT_MAX;   // finite: in the block's own tile a wave may see no key at all
+  const int ntile = CAUSAL ? qb + 1 : nq, last = ntile - 1, k0 = 32 * kh;
   const size_t step = (size_t)64 * ld;
-  issue_tile<D>(kp, off, ring, wave);
-  issue_tile<D>(vp, off, ring + TILEB, wave);
-  AH_LANDED(0);
-  for (int j = 0; j < ntile; j++) {
-    const size_t o2 = (size_t)min(j + 1, last) * step;
-    char* fill = ring + ((j + 1) & 1) * STAGE;
-    const char* cur = ring + (j & 1) * STAGE;
-    issue_tile<D>(kp + o2, off, fill, wave);
-    issue_tile<D>(vp + o2, off, fill + TILEB, wave);
-    // In the block's own tile the wave's keys lie before (kh < qt), on (kh == qt) or after (kh > qt) its queries.
-    const bool own = CAUSAL && j == last;
-    if (!(own && kh > qt)) fwd_half_tile<D>(cur, cur + TILEB, st, j * 64 + 32 * kh, kh, q, own && kh == qt, sc2, lane);
-    AH_LANDED(0);
-  }
+  auto load_k = [&](int t) { issue_tile<D>(kp + (size_t)min(t, last) * step, off, ring + (t & 1) * TILEB, wave); };
+  auto load_v = [&](int t) { issue_tile<D>(vp + (size_t)min(t, last) * step, off, ring + (2 + (t & 1)) * TILEB, wave); };
+  auto slot_k = [&](int t) { int x = (t & 1) * TILEB; asm("" : "+s"(x)); return (const char*)ring + x + k0 * (2 * D); };
+  auto slot_v = [&](int t) { int x = (2 + (t & 1)) * TILEB; asm("" : "+s"(x)); return (const char*)ring + x + k0 * (2 * D); };
+  load_k(0);
+  load_v(0);
+  load_k(1);
+  const LaneOffs<D> lo(lane);
+  f32x16 s;
+  const int lim = q - k0 - 4 * hf;
+  AH_NEXT_TILE();
+  fwd_half_scores<D>(slot_k(0), lo, st.qf, s);
+  float mx = CAUSAL && last == 0 ? fwd_half_max<true>(s, lim) : fwd_half_max<false>(s, 0);
+  AH_NEXT_TILE();   // the first K tile's slot is loaded next
+  int j = 0;
+#define AH_FWD_STEP(MASK, limit)                                                              \
+  load_k(j + 2);                                                                              \
+  load_v(j + 1);                                                                              \
+  fwd_half_step<D, true, MASK>(slot_k(j + 1), slot_v(j), st, s, mx, lo, limit, sc2);          \
+  AH_NEXT_TILE();                                                                             \
+  j++
+#pragma unroll 1
+  while (j < (CAUSAL ? last - 1 : last)) { AH_FWD_STEP(false, 0); }
+  if (CAUSAL && last > 0) { AH_FWD_STEP(true, lim - last * 64); }
+#undef AH_FWD_STEP
+  fwd_half_step<D, false, false>(slot_k(last), slot_v(last), st, s, mx, lo, 0, sc2);
+  __syncthreads();
 
   // merge: the waves of the second key half leave (m, l, O) in LDS, lane by lane; the others fold them in
   float* mg = (float*)ring + (size_t)qt * (ND * 16 + 2) * 64;
@@ -753,6 +790,18 @@ __device__ __forceinline__ void dq_step(const char* cK, const char* nK, const ch
   dp = ndp;
 }
 
+// S and dP - delta of the first 32 keys of a pipeline
+template <int D>
+__device__ __forceinline__ void dq_scores(const char* cK, const char* cV, const DqState<D>& st, f32x16& s, f32x16& dp, const LaneOffs<D>& lo) {
+#pragma unroll
+  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -st.delta; }
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cK, 0, ks), st.qf[ks], s, 0, 0, 0);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cV, 0, ks), st.dof[ks], dp, 0, 0, 0);
+  }
+}
+
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                       const bf16* __restrict__ d_o, const float* __restrict__ lse,
@@ -797,14 +846,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
   load(2);
   const LaneOffs<D> lo(lane);
   f32x16 s, dp;
-#pragma unroll
-  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -st.delta; }
   AH_NEXT_TILE();
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) {
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(slot_k(0), 0, ks), st.qf[ks], s, 0, 0, 0);
-    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(slot_v(0), 0, ks), st.dof[ks], dp, 0, 0, 0);
-  }
+  dq_scores<D>(slot_k(0), slot_v(0), st, s, dp, lo);
   const int lim = q - 4 * hf;
 #define AH_DQ_ROUND(MASK)                                                                                               \
   load(h + 3);                                                                                                          \
@@ -952,75 +995,14 @@ __global__ __launch_bounds__(256, 2) void attn_dq_plain_kernel(const bf16* __res
 // =========================================================================== backward: dQ for launches that cannot fill the chip
 // The split of attn_fwd64_kernel applied to dQ: 64 queries per block, wave w owns queries 32 * (w & 1) .. + 31 and
 // keys 32 * (w >> 1) .. + 31 of every 64-key tile; the two partial dQ per query are added in LDS at the end.
-template <int D>
-__device__ __forceinline__ void dq_half_tile(const char* __restrict__ cK, const char* __restrict__ cV, DqState<D>& st, int kbase,
-                                             int kh, int q, bool diag, float sc2, int lane) {
-  constexpr int NK = D / 16, ND = D / 32;
-  const int hf = lane >> 5;
-  // with head_dim 128 the 256 registers of a wave (two blocks share a CU) leave no room for all fragments at once:
-  // they are fetched where they are used and the other block covers the wait
-  constexpr bool AHEAD = D == 64;
-  bf16x8 fk[NK], fv[NK];
-  if (AHEAD) {
-#pragma unroll
-    for (int ks = 0; ks < NK; ks++) {
-      fk[ks] = frag_rowmajor<D>(cK, 32 * kh + (lane & 31), ks, hf);
-      fv[ks] = frag_rowmajor<D>(cV, 32 * kh + (lane & 31), ks, hf);
-    }
-    AH_SCHED_FENCE();
-  }
-  f32x16 s, dp;
-#pragma unroll
-  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -st.delta; }   // dP - delta for free
-#pragma unroll
-  for (int ks = 0; ks < NK; ks++) {
-    if (!AHEAD) {
-      fk[ks] = frag_rowmajor<D>(cK, 32 * kh + (lane & 31), ks, hf);
-      fv[ks] = frag_rowmajor<D>(cV, 32 * kh + (lane & 31), ks, hf);
-    }
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[ks], st.qf[ks], s, 0, 0, 0);
-    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[ks], st.dof[ks], dp, 0, 0, 0);
-  }
-  bf16x8 kt[2][ND];
-  if (AHEAD) {
-#pragma unroll
-    for (int s2 = 0; s2 < 2; s2++)
-#pragma unroll
-      for (int dt = 0; dt < ND; dt++) kt[s2][dt] = frag_transposed<D>(cK, 32 * kh + 16 * s2 + 4 * hf, dt, lane);
-    AH_SCHED_FENCE();
-  }
-  const float nl = -st.lse2;
-#pragma unroll
-  for (int r = 0; r < 16; r++) s[r] = fexp2(__builtin_fmaf(s[r], sc2, nl));
-  if (diag) {  // wave-uniform; element r is key kbase + 8*(r/4) + 4*hf + r%4
-    const int lim = q - kbase - 4 * hf;
-#pragma unroll
-    for (int r = 0; r < 16; r++)
-      if (8 * (r >> 2) + (r & 3) > lim) s[r] = 0.f;
-  }
-#pragma unroll
-  for (int r = 0; r < 16; r++) s[r] *= dp[r];  // dS^T
-  if (AHEAD) AH_SCHED_FENCE();
-#pragma unroll
-  for (int s2 = 0; s2 < 2; s2++) {
-    const bf16x8 dsf = pack8(s, s2);
-#pragma unroll
-    for (int dt = 0; dt < ND; dt++) {
-      if (!AHEAD) kt[s2][dt] = frag_transposed<D>(cK, 32 * kh + 16 * s2 + 4 * hf, dt, lane);
-      st.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[s2][dt], dsf, st.acc[dt], 0, 0, 0);
-    }
-  }
-  if (AHEAD) AH_SCHED_FENCE();
-}
-
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
                                                         const bf16* __restrict__ d_o, const float* __restrict__ lse,
                                                         float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int nh,
                                                         float sc2, float scale) {
-  constexpr int TILEB = 64 * 2 * D, STAGE = 2 * TILEB, ND = D / 32;
-  __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];
-  static_assert(2 * ND * 16 * 64 * 4 + 2 * strip_bytes<D>() <= NSLOT * STAGE, "the partial results and output strips of two waves fit in the ring");
+  constexpr int TILEB = 64 * 2 * D, ND = D / 32;
+  __shared__ __attribute__((aligned(1024))) char ring[5 * TILEB];   // three K tiles, two V tiles
+  static_assert(2 * ND * 16 * 64 * 4 + 2 * strip_bytes<D>() <= 5 * TILEB, "the partial results and output strips of two waves fit in the ring");
   const int lane = threadIdx.x & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qt = wave & 1, kh = wave >> 1;
@@ -1042,21 +1024,33 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
 #pragma unroll
   for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
 
-  const int ntile = CAUSAL ? qb + 1 : nq, last = ntile - 1;
-  const size_t step = (size_t)64 * ld;
-  issue_tile<D>(kp, off, ring, wave);
-  issue_tile<D>(vp, off, ring + TILEB, wave);
-  AH_LANDED(0);
-  for (int j = 0; j < ntile; j++) {
-    const size_t o2 = (size_t)min(j + 1, last) * step;
-    char* fill = ring + ((j + 1) & 1) * STAGE;
-    const char* cur = ring + (j & 1) * STAGE;
-    issue_tile<D>(kp + o2, off, fill, wave);
-    issue_tile<D>(vp + o2, off, fill + TILEB, wave);
-    const bool own = CAUSAL && j == last;
-    if (!(own && kh > qt)) dq_half_tile<D>(cur, cur + TILEB, st, j * 64 + 32 * kh, kh, q, own && kh == qt, sc2, lane);
-    AH_LANDED(0);
+  // One step of the pipeline per key tile (the wave's half of it).  K tile t lives in K slot t % 3 and V tile t in V slot t % 2: step j
+  // reads the columns of K tile j and the rows of tiles j + 1, while tiles j + 2 arrive (past the end the last one again)
+  const int ntile = CAUSAL ? qb + 1 : nq, last = ntile - 1, k0 = 32 * kh;
+  auto load = [&](int t) {
+    const size_t row = (size_t)min(t, last) * 64 * ld;
+    issue_tile<D>(kp + row, off, ring + (t % 3) * TILEB, wave);
+    issue_tile<D>(vp + row, off, ring + (3 + (t & 1)) * TILEB, wave);
+  };
+  auto slot_k = [&](int t) { int x = (t % 3) * TILEB; asm("" : "+s"(x)); return (const char*)ring + x + k0 * (2 * D); };
+  auto slot_v = [&](int t) { int x = (3 + (t & 1)) * TILEB; asm("" : "+s"(x)); return (const char*)ring + x + k0 * (2 * D); };
+  load(0);
+  load(1);
+  const LaneOffs<D> lo(lane);
+  f32x16 s, dp;
+  AH_NEXT_TILE();
+  dq_scores<D>(slot_k(0), slot_v(0), st, s, dp, lo);
+  AH_NEXT_TILE();   // the first V tile's slot is loaded next
+#pragma unroll 1
+  for (int j = 0; j < last; j++) {
+    load(j + 2);
+    dq_step<D, false>(slot_k(j), slot_k(j + 1), slot_v(j + 1), st, s, dp, lo, 0, sc2);
+    AH_NEXT_TILE();
   }
+  // the last tile, under the mask that of the block's own queries (for a wave whose keys all lie after its queries, all masked; its
+  // next scores are nobody's)
+  dq_step<D, CAUSAL>(slot_k(last), slot_k(last), slot_v(last), st, s, dp, lo, q - 64 * last - k0 - 4 * hf, sc2);
+  __syncthreads();
 
   float* mg = (float*)ring + (size_t)qt * ND * 16 * 64;
   if (kh == 1) {
@@ -1067,7 +1061,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
   }
   __syncthreads();
   if (kh == 1) return;
-  store_rows<D>([&](int dt, int r) { return (st.acc[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale; }, ring + NSLOT * STAGE - (2 - qt) * strip_bytes<D>(),
+  store_rows<D>([&](int dt, int r) { return (st.acc[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale; }, ring + 5 * TILEB - (2 - qt) * strip_bytes<D>(),
                 dqkv + ((size_t)b * S + qw0) * ld + head * D, ld, lane);
 }
 
@@ -1139,6 +1133,20 @@ __device__ __forceinline__ void dkv_step(const char* cur, int t, const char* nxt
   dp = ndp;
 }
 
+// S and dP - delta of the first 32 queries of a pipeline: rows t .. of the tile at cur
+template <int D>
+__device__ __forceinline__ void dkv_scores(const char* cur, int t, const DkvState<D>& st, f32x16& s, f32x16& dp, const LaneOffs<D>& lo, int hf) {
+  constexpr int TILEB = 64 * 2 * D;
+  const float* nstat = (const float*)(cur + 2 * TILEB) + 64 + t + 4 * hf;
+#pragma unroll
+  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = nstat[8 * (r >> 2) + (r & 3)]; }
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cur + t * (2 * D), 0, ks), st.kf[ks], s, 0, 0, 0);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cur + TILEB + t * (2 * D), 0, ks), st.vf[ks], dp, 0, 0, 0);
+  }
+}
+
 // ring slot of the dK/dV kernel: Q tile, dO tile, then 64 log-sum-exps, 64 deltas and 512 spare bytes
 template <int D>
 __device__ __forceinline__ void dkv_issue(const bf16* gQ, const bf16* gO, const float* gL, const float* gD, uint32_t* offq,
@@ -1208,16 +1216,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_dkv_kernel(const bf
   load(1, nxt);
   f32x16 s, dp;
   AH_NEXT_TILE();
-  {
-    const float* nstat = (const float*)(cur + 2 * TILEB) + 64 + 4 * hf;
-#pragma unroll
-    for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = nstat[8 * (r >> 2) + (r & 3)]; }
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cur, 0, ks), st.kf[ks], s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo.rows(cur + TILEB, 0, ks), st.vf[ks], dp, 0, 0, 0);
-    }
-  }
+  dkv_scores<D>(cur, 0, st, s, dp, lo, hf);
   const int lim = key - j0 * 64 - 4 * hf;   // under the mask the lane's key sees no query before lim
 #define AH_DKV_TILE(MASK)                                                             \
   load(j + 2, fill);                                                                  \
@@ -1244,77 +1243,6 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_dkv_kernel(const bf
 // 64 keys per block instead of 128 (twice the blocks, dispatched heaviest first, so that the CUs even out): wave w
 // owns keys 32 * (w & 1) .. + 31 of the block and, of every 64-query tile, the queries 32 * (w >> 1) .. + 31; the two
 // partial dK, dV per key are added in LDS at the end.
-template <int D>
-__device__ __forceinline__ void dkv_half_tile(const char* __restrict__ cQ, const char* __restrict__ cO, DkvState<D>& st,
-                                              const float* __restrict__ lse_tile, const float* __restrict__ delta_tile, int q0, int key,
-                                              int t, bool diag, float sc2, int lane) {
-  constexpr int NK = D / 16, ND = D / 32;
-  const int hf = lane >> 5;
-  const int lim = key - q0 - 4 * hf;  // query offset ql (without the 4*hf term) is masked iff ql < lim
-  bf16x8 fq[NK], fo[NK];
-#pragma unroll
-  for (int ks = 0; ks < NK; ks++) {
-    fq[ks] = frag_rowmajor<D>(cQ, 32 * t + (lane & 31), ks, hf);
-    fo[ks] = frag_rowmajor<D>(cO, 32 * t + (lane & 31), ks, hf);
-  }
-  f32x4 dl[4];   // delta of the lane's queries: dO V^T is accumulated onto -delta
-#pragma unroll
-  for (int g = 0; g < 4; g++) dl[g] = *(const f32x4*)(delta_tile + t * 32 + 8 * g + 4 * hf);
-  AH_SCHED_FENCE();
-  f32x16 s, dp;
-#pragma unroll
-  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = dl[r >> 2][r & 3]; }
-  bf16x8 tq0[ND], to0[ND], tq1[ND], to1[ND];
-#pragma unroll
-  for (int ks = 0; ks < NK; ks++) {
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[ks], st.kf[ks], s, 0, 0, 0);
-    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[ks], st.vf[ks], dp, 0, 0, 0);
-  }
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++) {
-    to0[dt] = frag_transposed<D>(cO, t * 32 + 4 * hf, dt, lane);
-    tq0[dt] = frag_transposed<D>(cQ, t * 32 + 4 * hf, dt, lane);
-  }
-  AH_SCHED_FENCE();
-  // lane holds queries q0 + t*32 + 8g + 4hf + i of its key
-#pragma unroll
-  for (int g = 0; g < 4; g++) {
-    const int ql = t * 32 + 8 * g + 4 * hf;
-    const f32x4 l4 = *(const f32x4*)(lse_tile + ql);
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int r = 4 * g + i;
-      s[r] = fexp2(__builtin_fmaf(s[r], sc2, -l4[i] * LOG2E));
-    }
-  }
-  if (diag) {  // wave-uniform
-#pragma unroll
-    for (int r = 0; r < 16; r++)
-      if (t * 32 + 8 * (r >> 2) + (r & 3) < lim) s[r] = 0.f;
-  }
-#pragma unroll
-  for (int r = 0; r < 16; r++) dp[r] *= s[r];
-  AH_SCHED_FENCE();
-  const bf16x8 pf0 = pack8(s, 0), dsf0 = pack8(dp, 0), pf1 = pack8(s, 1), dsf1 = pack8(dp, 1);
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++) {
-    to1[dt] = frag_transposed<D>(cO, t * 32 + 16 + 4 * hf, dt, lane);
-    tq1[dt] = frag_transposed<D>(cQ, t * 32 + 16 + 4 * hf, dt, lane);
-  }
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++) {
-    st.dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to0[dt], pf0, st.dv[dt], 0, 0, 0);
-    st.dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq0[dt], dsf0, st.dk[dt], 0, 0, 0);
-  }
-  AH_SCHED_FENCE();
-#pragma unroll
-  for (int dt = 0; dt < ND; dt++) {
-    st.dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to1[dt], pf1, st.dv[dt], 0, 0, 0);
-    st.dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq1[dt], dsf1, st.dk[dt], 0, 0, 0);
-  }
-  AH_SCHED_FENCE();
-}
-
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
@@ -1357,32 +1285,38 @@ __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict_
     offo[i] = tile_src_offset<D>(wave + 4 * i, lane, ldo);
   }
 
-  // Query tiles of 64 from the one that holds the block's own positions on (from 0 without the mask).  Tile t lives in ring
-  // slot t % 4; loads run three tiles ahead and are waited for by count, past the end the last tile is fetched again into a
-  // dead slot (a uniform number of loads in flight)
+  // Query tiles of 64 from the one that holds the block's own positions on (from 0 without the mask), one step of the pipeline
+  // each (the wave's half of it).  Tile t lives in ring slot t % 4; loads run three tiles ahead and are waited for by count, past
+  // the end the last tile is fetched again (a uniform number of loads in flight)
   const int j0 = CAUSAL ? kb : 0, ntile = S / 64 - j0, last = ntile - 1;
   qp += (size_t)j0 * 64 * ld;
   dop += (size_t)j0 * 64 * ldo;
   lse_row += j0 * 64;
   delta_row += j0 * 64;
-  const size_t stepq = (size_t)64 * ld, stepo = (size_t)64 * ldo;
-#pragma unroll
-  for (int t = 0; t < 3; t++) {
-    const int tt = min(t, last);
-    dkv_issue<D>(qp + tt * stepq, dop + tt * stepo, lse_row + tt * 64, delta_row + tt * 64, offq, offo, offs, ring + t * STAGE, wave);
-  }
-  AH_LANDED(2 * LPS);
-  for (int j = 0; j < ntile; j++) {
-    const int tf = min(j + 3, last);
-    dkv_issue<D>(qp + tf * stepq, dop + tf * stepo, lse_row + tf * 64, delta_row + tf * 64, offq, offo, offs, ring + ((j + 3) & 3) * STAGE,
-                 wave);
-    const char* cur = ring + (j & 3) * STAGE;
-    const float* lse_tile = (const float*)(cur + 2 * TILEB);
-    // in the block's own tile the wave's queries lie before (qh < kt), on (qh == kt) or after (qh > kt) its keys
-    const bool own = CAUSAL && j == 0;
-    if (!(own && qh < kt))
-      dkv_half_tile<D>(cur, cur + TILEB, st, lse_tile, lse_tile + 64, (j0 + j) * 64, key, qh, own && qh == kt, sc2, lane);
-    AH_LANDED(2 * LPS);
+  auto load = [&](int t) {
+    char* slot = ring + (t & 3) * STAGE;
+    t = min(t, last);
+    dkv_issue<D>(qp + (size_t)t * 64 * ld, dop + (size_t)t * 64 * ldo, lse_row + t * 64, delta_row + t * 64, offq, offo, offs, slot, wave);
+  };
+  load(0);
+  load(1);
+  load(2);
+  const LaneOffs<D> lo(lane);
+  f32x16 s, dp;
+  const int t0 = 32 * qh;
+  AH_LANDED(LPS);   // tiles 0 and 1
+  dkv_scores<D>(ring, t0, st, s, dp, lo, hf);
+  auto slot = [&](int t) { int x = (t & 3) * STAGE; asm("" : "+s"(x)); return (const char*)ring + x; };
+  const int lim = key - j0 * 64 - t0 - 4 * hf;
+  // (in the block's own tile the wave's queries may all lie before its keys: masked like the others)
+  load(3);
+  dkv_step<D, CAUSAL>(slot(0), t0, slot(1), t0, st, s, dp, lo, lim, sc2, hf);
+  AH_LANDED(LPS);
+#pragma unroll 1
+  for (int j = 1; j < ntile; j++) {
+    load(j + 3);
+    dkv_step<D, false>(slot(j), t0, slot(j + 1), t0, st, s, dp, lo, 0, sc2, hf);
+    AH_LANDED(LPS);
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));  // drain the redundant tail loads
   __syncthreads();
