@@ -93,10 +93,26 @@ hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const voi
 hipError_t launch_norm_bwd(bool rms, const void* da, const void* x, const float* stats, const void* gamma,
                            const void* dres, void* dx, float* part, int T, int h, hipStream_t s, int acc = 0, bool x_f32 = false);
 int norm_bwd_blocks(int T);
-// g[c] = beta * g[c] + sum_b part[b][c]
-hipError_t launch_colsum_finish(const float* part, int nblk, int n, float* g, int beta, hipStream_t s);
-// the three partial arrays a norm backward leaves in `part` -> three gradient vectors in one launch
-hipError_t launch_colsum_finish3(const float* part, int nblk, int n, float* g0, float* g1, float* g2, int beta, hipStream_t s);
+// g[c] = beta * g[c] + sum_b part[b][c] for the vectors of a list (n a multiple of 64), in one launch
+struct FoldList {
+  static constexpr int kMax = 8;   // a layer's vector gradients
+  const float* part[kMax];
+  float* g[kMax];
+  int n[kMax], nblk[kMax], first[kMax + 1], count;   // first: block of the launch at which a vector begins
+  void add(const float* p, int blocks, int width, float* out) {
+    if (count == 0) first[0] = 0;
+    part[count] = p; nblk[count] = blocks; n[count] = width; g[count] = out;
+    first[count + 1] = first[count] + width / 64;
+    count++;
+  }
+  // the three arrays that a norm backward leaves in `p`
+  void add3(const float* p, int blocks, int width, float* g0, float* g1, float* g2) {
+    add(p, blocks, width, g0);
+    add(p + (size_t)blocks * width, blocks, width, g1);
+    add(p + (size_t)2 * blocks * width, blocks, width, g2);
+  }
+};
+hipError_t launch_fold(const FoldList& a, int beta, hipStream_t s);
 // partial column sums of a bf16 matrix [T, n] -> part[nblk][n] (acc != 0: added to what is there)
 hipError_t launch_colsum_partial(const void* m, int T, int n, int ld, float* part, hipStream_t s, int acc = 0);
 int colsum_blocks(int T);

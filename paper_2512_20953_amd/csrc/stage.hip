@@ -417,8 +417,17 @@ VecPlan vec_plan(const ah_stage* s, int layer, bool deferred, int pos, bool clos
           pos > 0 ? 1 : 0, closes, beta_group};
 }
 
-// Folds one layer's partial sums into its vector gradients (the four reductions that end a layer's backward).
-hipError_t finish_vectors(ah_stage* s, int layer, const VecPlan& vp, hipStream_t st);
+// One layer's partial sums as entries of a list to be folded into its vector gradients, by the kernel that left them.
+void add_b1(const ah_stage* s, const LayerPtrs& p, const VecPlan& vp, FoldList& f) { f.add(vp.b1, s->T / 64, s->F, p.g_b1); }
+void add_bqkv(const ah_stage* s, const LayerPtrs& p, const VecPlan& vp, FoldList& f) { f.add(vp.bqkv, colsum_blocks(s->T), 3 * s->hl, p.g_bqkv); }
+void add_n2(const ah_stage* s, const LayerPtrs& p, const VecPlan& vp, FoldList& f) {
+  if (s->llama) f.add(vp.n2, norm_bwd_blocks(s->T), s->h, p.g_ln2_g);
+  else f.add3(vp.n2, norm_bwd_blocks(s->T), s->h, p.g_ln2_g, p.g_ln2_b, p.g_b2);
+}
+void add_n1(const ah_stage* s, const LayerPtrs& p, const VecPlan& vp, FoldList& f) {
+  if (s->llama) f.add(vp.n1, norm_bwd_blocks(s->T), s->h, p.g_ln1_g);
+  else f.add3(vp.n1, norm_bwd_blocks(s->T), s->h, p.g_ln1_g, p.g_ln1_b, p.g_bo);
+}
 
 // One weight-gradient product C[M, N] (+)= sum over the plan's micro-batches of act^T dY.
 // A product over one micro-batch goes to `sd` (the side stream: beside the rest of backward it hides its tail and
@@ -511,9 +520,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   char* wsb = (char*)s->bufs.workspace;
   char *dmid = bb.dmid, *du = bb.du, *dqkv = bb.dqkv, *dsm = wsb + s->ws.dsm;
   float *part_n2 = vp.n2, *part_n1 = vp.n1, *part_b1 = vp.b1, *part_bqkv = vp.bqkv;
-  const int beta = vp.beta;
   float* delta = (float*)(wsb + s->ws.delta);
-  const int nb = norm_bwd_blocks(T), cb = colsum_blocks(T);
   const bool rms = s->llama;
   hipEvent_t* ev = s->sync_ev;
 #define ON_SIDE(site, expr)              \
@@ -524,6 +531,20 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     if (e_ != hipSuccess) return e_;     \
   } while (0)
 
+  // Vector gradients whose partial sums are complete: on the side stream they are folded as they come, on one stream together
+  // at the layer's end (a launch instead of four)
+  FoldList folds = {};
+#define FOLD(add)                                                       \
+  do {                                                                  \
+    if (vp.finish) {                                                    \
+      add(s, p, vp, folds);                                             \
+      if (sd != st) {                                                   \
+        ON_SIDE(SITE_COLSUM, launch_fold(folds, vp.beta, sd));          \
+        folds.count = 0;                                                \
+      }                                                                 \
+    }                                                                   \
+  } while (0)
+
   // second MLP matrix: dW2 += g^T dy ; input gradient of the activation
   TRY(stream_order(st, sd, ev[0]));  // dy is complete
   TRY(wgrad(s, SITE_FC2_WGRAD, layer, WG_FC2, wp, a.g, dy, p.g_w2, F, h, st, sd));
@@ -531,7 +552,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     // du, and as a by-product of its epilogue the column sums of du per 64-row slab (for db1)
     TRY(gemm(s, SITE_FC2_DGRAD, GEMM_NT, EPI_GELU_BWD, dy, h, p.w2, h, du, F, T, F, h, nullptr, a.u, F, nullptr, 0, st, part_b1, vp.acc));
     TRY(stream_order(st, sd, ev[1]));
-    if (vp.finish) ON_SIDE(SITE_COLSUM, launch_colsum_finish(part_b1, T / 64, F, p.g_b1, beta, sd));
+    FOLD(add_b1);
   } else {
     // d(gate | up) straight from the product dm = dy Wd^T: the SwiGLU backward is the GEMM's epilogue
     GemmArgs g = {};
@@ -552,10 +573,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   // second norm backward; dx_mid = dy + norm_bwd(dc); column sums give d(gain), d(offset), d(b2)
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_mid, (const float*)a.stats2, p.ln2_g, dy, dmid, part_n2, T, h, st, vp.acc, s->res32));
   TRY(stream_order(st, sd, ev[3]));
-  if (vp.finish) {
-    if (rms) ON_SIDE(SITE_COLSUM, launch_colsum_finish(part_n2, nb, h, p.g_ln2_g, beta, sd));
-    else ON_SIDE(SITE_COLSUM, launch_colsum_finish3(part_n2, nb, h, p.g_ln2_g, p.g_ln2_b, p.g_b2, beta, sd));
-  }
+  FOLD(add_n2);
   // output projection
   TRY(wgrad(s, SITE_WO_WGRAD, layer, WG_WO, wp, a.o, dmid, p.g_wo, hl, h, st, sd));
   TRY(gemm(s, SITE_WO_DGRAD, GEMM_NT, EPI_BF16, dmid, h, p.wo, h, dsm, hl, T, hl, h, nullptr, nullptr, 0, nullptr, 0, st));  // do
@@ -566,18 +584,17 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   TRY(stream_order(st, sd, ev[4]));
   if (!s->llama) {
     ON_SIDE(SITE_COLSUM, launch_colsum_partial(dqkv, T, 3 * hl, 3 * hl, part_bqkv, sd, vp.acc));
-    if (vp.finish) ON_SIDE(SITE_COLSUM, launch_colsum_finish(part_bqkv, cb, 3 * hl, p.g_bqkv, beta, sd));
+    FOLD(add_bqkv);
   }
   TRY(wgrad(s, SITE_QKV_WGRAD, layer, WG_QKV, wp, a.a, dqkv, p.g_wqkv, h, 3 * hl, st, sd));
   TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st));  // da
   // first norm backward; dx = dx_mid + norm_bwd(da); column sums give d(gain), d(offset), d(bo)
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32));
   TRY(stream_order(st, sd, ev[5]));
-  if (vp.finish) {
-    if (rms) ON_SIDE(SITE_COLSUM, launch_colsum_finish(part_n1, nb, h, p.g_ln1_g, beta, sd));
-    else ON_SIDE(SITE_COLSUM, launch_colsum_finish3(part_n1, nb, h, p.g_ln1_g, p.g_ln1_b, p.g_bo, beta, sd));
-  }
+  FOLD(add_n1);
+  if (sd == st) ON_SIDE(SITE_COLSUM, launch_fold(folds, vp.beta, sd));   // one launch for the layer
   TRY(stream_order(sd, st, ev[6]));  // join
+#undef FOLD
 #undef ON_SIDE
   return hipSuccess;
 }
@@ -623,18 +640,17 @@ hipError_t stage_forward(ah_stage* s, int slot, const void* x, void* y, hipStrea
   return hipSuccess;
 }
 
+// Folds one layer's partial sums into its vector gradients.
 hipError_t finish_vectors(ah_stage* s, int layer, const VecPlan& vp, hipStream_t st) {
   const LayerPtrs p = layer_ptrs(s, layer);
-  const int T = s->T, h = s->h, hl = s->hl, F = s->F, nb = norm_bwd_blocks(T), cb = colsum_blocks(T);
-  if (s->llama) {
-    TIMED(SITE_COLSUM, launch_colsum_finish(vp.n2, nb, h, p.g_ln2_g, vp.beta, st));
-    TIMED(SITE_COLSUM, launch_colsum_finish(vp.n1, nb, h, p.g_ln1_g, vp.beta, st));
-  } else {
-    TIMED(SITE_COLSUM, launch_colsum_finish(vp.b1, T / 64, F, p.g_b1, vp.beta, st));
-    TIMED(SITE_COLSUM, launch_colsum_finish3(vp.n2, nb, h, p.g_ln2_g, p.g_ln2_b, p.g_b2, vp.beta, st));
-    TIMED(SITE_COLSUM, launch_colsum_finish(vp.bqkv, cb, 3 * hl, p.g_bqkv, vp.beta, st));
-    TIMED(SITE_COLSUM, launch_colsum_finish3(vp.n1, nb, h, p.g_ln1_g, p.g_ln1_b, p.g_bo, vp.beta, st));
+  FoldList f = {};
+  add_n2(s, p, vp, f);
+  add_n1(s, p, vp, f);
+  if (!s->llama) {
+    add_b1(s, p, vp, f);
+    add_bqkv(s, p, vp, f);
   }
+  TIMED(SITE_COLSUM, launch_fold(f, vp.beta, st));
   return hipSuccess;
 }
 
