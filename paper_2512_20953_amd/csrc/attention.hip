@@ -848,6 +848,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
   f32x16 s, dp;
   AH_NEXT_TILE();
   dq_scores<D>(slot_k(0), slot_v(0), st, s, dp, lo);
+  AH_NEXT_TILE();   // every wave has read V half 0, whose slot the first round fills
   const int lim = q - 4 * hf;
 #define AH_DQ_ROUND(MASK)                                                                                               \
   load(h + 3);                                                                                                          \
