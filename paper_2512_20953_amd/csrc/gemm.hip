@@ -282,8 +282,9 @@ __device__ __forceinline__ void first_step(const char* __restrict__ cur, int ks,
 
 }  // namespace ksplit
 
+// One tile of a product: block `block` of the (M / BM) (N / BN) k_shares that cover it.
 template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN * WGK;
   static_assert(NW == 4, "four waves per block");
   constexpr bool SPLIT = WGK > 1;                // which pipeline
@@ -311,8 +312,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   const int shares = KSHARES ? g.k_shares : 1;
   const int tiles_m = g.M / BM, tiles_n = g.N / BN, out_tiles = tiles_m * tiles_n, ntiles = out_tiles * shares;
   // (Where the count is not a multiple of 8 the first ntiles % 8 XCDs take one tile more.)
-  int logical = blockIdx.x;
-  if (g.xcd_remap) logical = (blockIdx.x & 7) * (ntiles >> 3) + min((int)(blockIdx.x & 7), ntiles & 7) + (blockIdx.x >> 3);
+  int logical = block;
+  if (g.xcd_remap) logical = (block & 7) * (ntiles >> 3) + min(block & 7, ntiles & 7) + (block >> 3);
   const int share = KSHARES ? logical / out_tiles : 0;
   if (KSHARES) logical -= share * out_tiles;
   const int GROUP = g.group;
@@ -810,6 +811,21 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   }
 }
 
+template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
+__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
+  gemm_tile<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI>(g, blockIdx.x);
+}
+
+// Several weight gradients over the same k axis in one launch, the blocks of one product after those of another (a block's
+// XCD follows its number, so a product's tiles keep to the raster of a launch of its own, from another XCD on).
+struct GemmGroup { int count, first[kMaxGemmGroup + 1]; GemmArgs p[kMaxGemmGroup]; };
+template <int BM, int BN, int WGM, int WGN, int WGK, int EPI>
+__global__ __launch_bounds__(256) void gemm_group_kernel(GemmGroup gg) {
+  int i = 0;
+  while (i + 1 < gg.count && (int)blockIdx.x >= gg.first[i + 1]) i++;
+  gemm_tile<BM, BN, WGM, WGN, WGK, true, true, EPI>(gg.p[i], blockIdx.x - gg.first[i]);
+}
+
 // C[m, n] = beta C[m, n] + sum over the k shares of part[share][m, n], in the order of the shares.  Bound by memory:
 // every partial sum is read once; four columns per lane.
 __global__ __launch_bounds__(256) void k_shares_kernel(const float* __restrict__ part, float* __restrict__ C, int M, int N, int ldc, int shares, int beta) {
@@ -885,11 +901,11 @@ bool tile_fits(int i, int M, int n, int K, bool tn, int head) {
   return M % t.bm == 0 && n % t.bn == 0 && !(i == kWholeCuTile && (tn || (K < kWholeCuMinK && !head))) && !(head && t.bn / t.wgn % head);
 }
 
-// time of covering an M x n output with tile i, the k axis cut into `shares` that run side by side
-float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
+// time of a launch of `tiles` tiles of kind i over K
+float launch_cost(int i, long tiles, float K, bool tn) {
   const TileCfg& t = kTiles[i];
-  const long tiles = (long)(M / t.bm) * (n / t.bn) * shares, full = tiles / 512, rest = tiles % 512;
-  const float k = K / 1024.f / shares;
+  const long full = tiles / 512, rest = tiles % 512;
+  const float k = K / 1024.f;
   const Rate &r1 = tn ? t.tn1 : t.fwd1, &r2 = tn ? t.tn2 : t.fwd2;
   float us = full * (r2.a + r2.b * k - kLaunchGap) + kLaunchGap;
   if (rest > 0) {
@@ -898,6 +914,11 @@ float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
     us += (r.a + r.b * k) * (1.f - r.f * (1.f - fill)) - kLaunchGap;
   }
   return us;
+}
+
+// time of covering an M x n output with tile i, the k axis cut into `shares` that run side by side
+float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
+  return launch_cost(i, (long)(M / kTiles[i].bm) * (n / kTiles[i].bn) * shares, (float)K / shares, tn);
 }
 
 int pick_tile(int M, int N, int K, bool tn, int head) {
@@ -1106,16 +1127,18 @@ GemmArgs column_range(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, in
 
 }  // namespace
 
-hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in, hipStream_t s) {
-  GemmArgs a = a_in;
+namespace {
+
+// Checks a problem and sets what the kernels expect beside it.
+bool complete(GemmLayout layout, GemmArgs& a) {
   static int grp = -1, remap = -1;
   if (grp < 0) { grp = getenv("AH_GEMM_GROUP") ? atoi(getenv("AH_GEMM_GROUP")) : 0; remap = getenv("AH_GEMM_NOREMAP") ? 0 : 1; }
   a.group = grp; a.xcd_remap = remap;
-  if (!gemm_shape_ok(a.M, a.N, a.K)) return hipErrorInvalidValue;
+  if (!gemm_shape_ok(a.M, a.N, a.K)) return false;
   if (a.n_seg != 0) {  // pieces along k: weight-gradient layout only, and the pieces must add up to K
-    if (layout != GEMM_TN || !gemm_segments_ok(a.seg_k, a.n_seg) || (long)a.seg_k * a.n_seg != a.K) return hipErrorInvalidValue;
+    if (layout != GEMM_TN || !gemm_segments_ok(a.seg_k, a.n_seg) || (long)a.seg_k * a.n_seg != a.K) return false;
     for (int i = 0; i < a.n_seg; i++)
-      if (!a.segA[i] || !a.segB[i]) return hipErrorInvalidValue;
+      if (!a.segA[i] || !a.segB[i]) return false;
     a.A = a.segA[0];
     a.B = a.segB[0];
   } else {
@@ -1123,6 +1146,78 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
     a.segB[0] = a.B;
   }
   a.k_shares = 1;
+  return true;
+}
+
+template <int BM, int BN, int WGM, int WGN, int WGK>
+hipError_t run_group(const GemmArgs* p, int n, hipStream_t s) {
+  GemmGroup gg;
+  gg.count = n;
+  gg.first[0] = 0;
+  for (int i = 0; i < n; i++) {
+    gg.p[i] = p[i];
+    if (gg.p[i].group <= 0) gg.p[i].group = raster_rows(p[i].M / BM);
+    gg.first[i + 1] = gg.first[i] + (p[i].M / BM) * (p[i].N / BN);
+  }
+  const dim3 grid(gg.first[n]), block(64 * WGM * WGN * WGK);
+  if (p[0].beta) hipLaunchKernelGGL((gemm_group_kernel<BM, BN, WGM, WGN, WGK, EPI_F32_ACC>), grid, block, 0, s, gg);
+  else hipLaunchKernelGGL((gemm_group_kernel<BM, BN, WGM, WGN, WGK, EPI_F32_SET>), grid, block, 0, s, gg);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// The tile is one for all products: they share the k axis, so their tiles take the same time, and a launch of all of them
+// is priced like one of a single product with as many.  A layer's four products together fill whole rounds where each by
+// itself leaves CUs idle (BERT-Large: 16, 48, 64 and 64 tiles of 256 x 256), and small ones pay for one launch.  Stage steps, one by
+// one / together: smallest 353.0 / 322.6 us, 5-head stage (pairs) 254.7 / 236.7, BERT-Large layer 3744 / 3651, 1.3B 6387 / 6274, 7B
+// shard 17608 / 17453; over 40 random stages with groups of 2 .. 8 0.956 (geometric mean, worst 1.002), over 40 with pairs 0.903
+// (0.978).
+int gemm_group_tile(const GemmShape* p, int n, int K, int n_seg, size_t part_floats) {
+  if (n < 2 || n > kMaxGemmGroup || forced_tile() >= 0 || getenv("AH_GEMM_SEPARATE")) return -1;  // (the variable: tuning and test aid)
+  float separate = 0.f;
+  for (int i = 0; i < n; i++) {
+    if (!gemm_shape_ok(p[i].M, p[i].N, K)) return -1;
+    separate += plan_cost(cached_plan(p[i].M, p[i].N, K, true, n_seg, part_floats), p[i].M, p[i].N, K, true);
+  }
+  int best = -1;
+  float best_t = separate;
+  for (int t = 0; t < kNumTiles; t++) {
+    long tiles = 0;
+    bool fits = true;
+    for (int i = 0; i < n; i++) {
+      fits = fits && tile_fits(t, p[i].M, p[i].N, K, true, 0);
+      tiles += (long)(p[i].M / kTiles[t].bm) * (p[i].N / kTiles[t].bn);
+    }
+    if (!fits) continue;
+    const float us = launch_cost(t, tiles, K, true);
+    if (us < best_t) { best = t; best_t = us; }
+  }
+  return best;
+}
+
+hipError_t launch_gemm_group(int tile, const GemmArgs* p_in, int n, hipStream_t s) {
+  if (n < 1 || n > kMaxGemmGroup) return hipErrorInvalidValue;
+  GemmArgs p[kMaxGemmGroup];
+  for (int i = 0; i < n; i++) {
+    p[i] = p_in[i];
+    if (!complete(GEMM_TN, p[i]) || p[i].K != p[0].K || p[i].beta != p[0].beta || tile < 0 || tile >= kNumTiles ||
+        !tile_fits(tile, p[i].M, p[i].N, p[i].K, true, 0))
+      return hipErrorInvalidValue;
+  }
+  switch (tile) {
+    case 0: return run_group<256, 256, 2, 2, 1>(p, n, s);
+    case 1: return run_group<256, 128, 2, 2, 1>(p, n, s);
+    case 2: return run_group<128, 256, 2, 2, 1>(p, n, s);
+    case 3: return run_group<128, 128, 2, 2, 1>(p, n, s);
+    case 5: return run_group<64, 128, 1, 2, 2>(p, n, s);
+    default: return run_group<64, 64, 1, 1, 4>(p, n, s);
+  }
+}
+
+hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in, hipStream_t s) {
+  GemmArgs a = a_in;
+  if (!complete(layout, a)) return hipErrorInvalidValue;
   const bool tn = layout == GEMM_TN;
   const Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0,
                              epi == EPI_ROPE ? a.rope_d : 0);

@@ -64,6 +64,12 @@ struct GemmArgs {
 // M, N, K multiples of 128, all leading dimensions multiples of 8.
 hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 bool gemm_shape_ok(int M, int N, int K);
+// Weight gradients (GEMM_TN, EPI_F32_ACC) of the same K, pieces and beta in one launch.  gemm_group_tile: the tile to launch
+// them with, or -1 where launches of their own are expected to be faster; it depends on the shapes alone.
+constexpr int kMaxGemmGroup = 4;   // a layer's matrices
+struct GemmShape { int M, N; };
+int gemm_group_tile(const GemmShape* p, int n, int K, int n_seg, size_t part_floats);
+hipError_t launch_gemm_group(int tile, const GemmArgs* p, int n, hipStream_t s);
 bool gemm_rope_pays(int M, int N, int K, int rope_d, int rope_cols);  // EPI_ROPE can be had and beats EPI_BF16 and the rotary kernel
 // A weight gradient's time by the launcher's model; of it, that of launches whose blocks leave room for others on their
 // CUs, and of the other launches the share of the CUs that stays idle.

@@ -73,7 +73,7 @@ struct ah_stage {
   // reductions); created on first use, joined back into the caller's stream before every return.
   hipStream_t side;
   hipEvent_t sync_ev[8];
-  bool side_ready, side_pays;
+  bool side_ready, side_pays, pair_wgrads;
   std::vector<hipEvent_t> ev_pool;           // pairs, in launch order
   std::vector<int> ev_site;                  // site of pair i
   std::vector<int> ev_mult;                  // micro-batches covered by the launch of pair i
@@ -166,6 +166,9 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
     double gflop = 0;
     for (const auto& mn : wgrad_shapes(s)) gflop += 2e-9 * s->T * mn[0] * mn[1];
     const char* e = getenv("AH_SIDE_STREAM_MIN_GFLOP");  // tuning and test aid; AH_NO_SIDE_STREAM keeps everything on the caller's stream
+    // (pairs by size alone, wherever they run: the tile of a pair decides on the last bits.  Above the line the first product of a pair
+    // would no longer run beside its input gradient)
+    s->pair_wgrads = gflop < 12.0;
     s->side_pays = gflop >= (e ? atof(e) : 12.0) && !getenv("AH_NO_SIDE_STREAM");
     s->defer = wgrads_wait(s);
   }
@@ -286,12 +289,12 @@ __global__ void fill_pattern_kernel(__bf16* p, size_t n, uint32_t seed) {
 enum Site {
   SITE_QKV_FWD, SITE_WO_FWD, SITE_FC1_FWD, SITE_FC2_FWD, SITE_FC2_WGRAD, SITE_FC2_DGRAD, SITE_FC1_WGRAD, SITE_FC1_DGRAD,
   SITE_WO_WGRAD, SITE_WO_DGRAD, SITE_QKV_WGRAD, SITE_QKV_DGRAD, SITE_ATTN_FWD, SITE_ATTN_BWD, SITE_NORM_FWD, SITE_NORM_BWD,
-  SITE_COLSUM, SITE_ROPE, SITE_COUNT
+  SITE_COLSUM, SITE_ROPE, SITE_MLP_WGRAD, SITE_ATTN_WGRAD, SITE_LAYER_WGRAD, SITE_COUNT
 };
 const char* const kSiteNames[SITE_COUNT] = {
   "gemm_nn.qkv_fwd", "gemm_nn.wo_fwd", "gemm_nn.fc1_fwd", "gemm_nn.fc2_fwd", "gemm_tn.fc2_wgrad", "gemm_nt.fc2_dgrad",
   "gemm_tn.fc1_wgrad", "gemm_nt.fc1_dgrad", "gemm_tn.wo_wgrad", "gemm_nt.wo_dgrad", "gemm_tn.qkv_wgrad", "gemm_nt.qkv_dgrad",
-  "attention_fwd", "attention_bwd", "norm_fwd", "norm_bwd", "colsum", "rope"};
+  "attention_fwd", "attention_bwd", "norm_fwd", "norm_bwd", "colsum", "rope", "gemm_tn.mlp_wgrads", "gemm_tn.attn_wgrads", "gemm_tn.layer_wgrads"};
 
 // brackets the launches issued while it lives with an event pair when tracing
 struct SiteTimer {
@@ -429,17 +432,19 @@ void add_n1(const ah_stage* s, const LayerPtrs& p, const VecPlan& vp, FoldList& 
   else f.add3(vp.n1, norm_bwd_blocks(s->T), s->h, p.g_ln1_g, p.g_ln1_b, p.g_bo);
 }
 
-// One weight-gradient product C[M, N] (+)= sum over the plan's micro-batches of act^T dY.
-// A product over one micro-batch goes to `sd` (the side stream: beside the rest of backward it hides its tail and
-// the launch gaps); a product over a whole group goes to `st`: it fills the chip for milliseconds, and next to it the
-// kernels of the main chain only slow down (gpt7b_tp2, G = 8: 76.1 ms per step this way, 77.9 with the group's
-// products on the side stream).
-hipError_t wgrad(ah_stage* s, int site, int layer, WgradWhich which, const WgradPlan& wp, const void* act, const void* dY, float* C,
-                 int M, int N, hipStream_t st, hipStream_t sd) {
+// The weight-gradient products C[M, N] (+)= sum over the plan's micro-batches of act^T dY that are to run next, together
+// where that pays.
+struct WgradList { GemmArgs g[kMaxGemmGroup]; int site[kMaxGemmGroup]; int count; };
+
+// Adds one product, unless the plan leaves it to a later call.
+void add_wgrad(const ah_stage* s, WgradList& list, int site, int layer, WgradWhich which, const WgradPlan& wp, const void* act,
+               const void* dY, float* C, int M, int N) {
   const bool now = wp.nseg == 0 || !s->defer;
-  if (now && !act) return hipSuccess;  // a flush: the products were taken with each micro-batch
-  if (!now && wp.nseg < 0) return hipSuccess;
-  GemmArgs g = {};
+  if (now && !act) return;  // a flush: the products were taken with each micro-batch
+  if (!now && wp.nseg < 0) return;
+  GemmArgs& g = list.g[list.count];
+  list.site[list.count++] = site;
+  g = {};
   g.A = act; g.B = dY; g.C = C;
   g.lda = M; g.ldb = N; g.ldc = N; g.M = M; g.N = N; g.K = s->T; g.beta = now ? wp.beta_now : wp.beta;
   if (!now) {
@@ -453,9 +458,27 @@ hipError_t wgrad(ah_stage* s, int site, int layer, WgradWhich which, const Wgrad
       g.segB[i] = which == WG_FC2 ? dy : which == WG_FC1 ? b.du : which == WG_WO ? b.dmid : b.dqkv;
     }
   }
-  hipStream_t run_on = now ? sd : st;
-  SiteTimer t(s, site, run_on, now ? 1 : wp.nseg);
-  return launch_gemm(GEMM_TN, EPI_F32_ACC, g, run_on);
+}
+
+// Launches the list on st and empties it; as one launch (traced as `together`) where the launcher expects that to be faster.
+hipError_t launch_wgrads(ah_stage* s, WgradList& list, int together, hipStream_t st) {
+  const int n = list.count;
+  list.count = 0;
+  if (n == 0) return hipSuccess;
+  const int mult = std::max(list.g[0].n_seg, 1);
+  GemmShape shape[kMaxGemmGroup];
+  for (int i = 0; i < n; i++) shape[i] = {list.g[i].M, list.g[i].N};
+  const int tile = gemm_group_tile(shape, n, list.g[0].K, mult, list.g[0].k_part ? list.g[0].k_part_floats : 0);
+  if (tile >= 0) {
+    SiteTimer t(s, together, st, mult);
+    return launch_gemm_group(tile, list.g, n, st);
+  }
+  for (int i = 0; i < n; i++) {
+    SiteTimer t(s, list.site[i], st, mult);
+    hipError_t e = launch_gemm(GEMM_TN, EPI_F32_ACC, list.g[i], st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // One layer forward.  y == nullptr: stop after the activations backward needs
@@ -545,9 +568,19 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     }                                                                   \
   } while (0)
 
+  // Weight gradients.  A group's run on st (they fill the chip for milliseconds, and next to them the kernels of the main chain
+  // only slow down: gpt7b_tp2, G = 8: 76.1 ms per step this way, 77.9 on the side stream), all four of the layer when its
+  // chain is through: their operands stay in the group's pending blocks.  Those of one micro-batch run on sd, beside the rest of
+  // backward, each as soon as its operands are there; small ones in pairs, as du's buffer is used again.
+  const bool now = wp.nseg == 0 || !s->defer;
+  WgradList wl = {};
+  auto wgrad = [&](int site, WgradWhich which, const void* act, const void* dY, float* C, int M, int N, bool pair_ends, int together) {
+    add_wgrad(s, wl, site, layer, which, wp, act, dY, C, M, N);
+    return now && (pair_ends || !s->pair_wgrads) ? launch_wgrads(s, wl, together, sd) : hipSuccess;
+  };
   // second MLP matrix: dW2 += g^T dy ; input gradient of the activation
   TRY(stream_order(st, sd, ev[0]));  // dy is complete
-  TRY(wgrad(s, SITE_FC2_WGRAD, layer, WG_FC2, wp, a.g, dy, p.g_w2, F, h, st, sd));
+  TRY(wgrad(SITE_FC2_WGRAD, WG_FC2, a.g, dy, p.g_w2, F, h, false, SITE_MLP_WGRAD));
   if (!s->llama) {
     // du, and as a by-product of its epilogue the column sums of du per 64-row slab (for db1)
     TRY(gemm(s, SITE_FC2_DGRAD, GEMM_NT, EPI_GELU_BWD, dy, h, p.w2, h, du, F, T, F, h, nullptr, a.u, F, nullptr, 0, st, part_b1, vp.acc));
@@ -564,7 +597,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     }
     TRY(stream_order(st, sd, ev[1]));
   }
-  TRY(wgrad(s, SITE_FC1_WGRAD, layer, WG_FC1, wp, a.c, du, p.g_w1, h, Fu, st, sd));
+  TRY(wgrad(SITE_FC1_WGRAD, WG_FC1, a.c, du, p.g_w1, h, Fu, true, SITE_MLP_WGRAD));
   TRY(gemm(s, SITE_FC1_DGRAD, GEMM_NT, EPI_BF16, du, Fu, p.w1, Fu, dsm, h, T, h, Fu, nullptr, nullptr, 0, nullptr, 0, st));  // dc
   // The side stream is done with du.  Only attention backward may have to wait for that, and only where dqkv
   // shares du's buffer; an event nobody waits for is not recorded.
@@ -575,7 +608,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   TRY(stream_order(st, sd, ev[3]));
   FOLD(add_n2);
   // output projection
-  TRY(wgrad(s, SITE_WO_WGRAD, layer, WG_WO, wp, a.o, dmid, p.g_wo, hl, h, st, sd));
+  TRY(wgrad(SITE_WO_WGRAD, WG_WO, a.o, dmid, p.g_wo, hl, h, false, SITE_ATTN_WGRAD));
   TRY(gemm(s, SITE_WO_DGRAD, GEMM_NT, EPI_BF16, dmid, h, p.wo, h, dsm, hl, T, hl, h, nullptr, nullptr, 0, nullptr, 0, st));  // do
   // attention (where dqkv shares its buffer with du: wait until the first MLP matrix's weight gradient has read it)
   if (du_reused) TRY(hipStreamWaitEvent(st, ev[2], 0));
@@ -586,13 +619,14 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     ON_SIDE(SITE_COLSUM, launch_colsum_partial(dqkv, T, 3 * hl, 3 * hl, part_bqkv, sd, vp.acc));
     FOLD(add_bqkv);
   }
-  TRY(wgrad(s, SITE_QKV_WGRAD, layer, WG_QKV, wp, a.a, dqkv, p.g_wqkv, h, 3 * hl, st, sd));
+  TRY(wgrad(SITE_QKV_WGRAD, WG_QKV, a.a, dqkv, p.g_wqkv, h, 3 * hl, true, SITE_ATTN_WGRAD));
   TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st));  // da
   // first norm backward; dx = dx_mid + norm_bwd(da); column sums give d(gain), d(offset), d(bo)
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32));
   TRY(stream_order(st, sd, ev[5]));
   FOLD(add_n1);
   if (sd == st) ON_SIDE(SITE_COLSUM, launch_fold(folds, vp.beta, sd));   // one launch for the layer
+  TRY(launch_wgrads(s, wl, SITE_LAYER_WGRAD, st));   // a group's
   TRY(stream_order(sd, st, ev[6]));  // join
 #undef FOLD
 #undef ON_SIDE
@@ -666,10 +700,12 @@ hipError_t flush_wgrads(ah_stage* s, hipStream_t st) {
   const int h = s->h, hl = s->hl, F = s->F, Fu = s->llama ? 2 * F : F;
   for (int l = s->L - 1; l >= 0; l--) {
     const LayerPtrs p = layer_ptrs(s, l);
-    TRY(wgrad(s, SITE_FC2_WGRAD, l, WG_FC2, wp, nullptr, nullptr, p.g_w2, F, h, st, st));
-    TRY(wgrad(s, SITE_FC1_WGRAD, l, WG_FC1, wp, nullptr, nullptr, p.g_w1, h, Fu, st, st));
-    TRY(wgrad(s, SITE_WO_WGRAD, l, WG_WO, wp, nullptr, nullptr, p.g_wo, hl, h, st, st));
-    TRY(wgrad(s, SITE_QKV_WGRAD, l, WG_QKV, wp, nullptr, nullptr, p.g_wqkv, h, 3 * hl, st, st));
+    WgradList wl = {};
+    add_wgrad(s, wl, SITE_FC2_WGRAD, l, WG_FC2, wp, nullptr, nullptr, p.g_w2, F, h);
+    add_wgrad(s, wl, SITE_FC1_WGRAD, l, WG_FC1, wp, nullptr, nullptr, p.g_w1, h, Fu);
+    add_wgrad(s, wl, SITE_WO_WGRAD, l, WG_WO, wp, nullptr, nullptr, p.g_wo, hl, h);
+    add_wgrad(s, wl, SITE_QKV_WGRAD, l, WG_QKV, wp, nullptr, nullptr, p.g_wqkv, h, 3 * hl);
+    TRY(launch_wgrads(s, wl, SITE_LAYER_WGRAD, st));
     TRY(finish_vectors(s, l, vec_plan(s, l, true, n, true, 0, wp.beta), st));
   }
   for (int i = 0; i < n; i++) s->busy[s->pend_slots[i]] = 0;
@@ -996,6 +1032,9 @@ extern "C" int ah_stage_trace_end(ah_stage_t* st, ah_trace_entry_t* out, int cap
   flops[SITE_FC2_FWD] = flops[SITE_FC2_WGRAD] = flops[SITE_FC2_DGRAD] = 2 * T * F * h;
   flops[SITE_ATTN_FWD] = attn;
   flops[SITE_ATTN_BWD] = 2 * attn;
+  flops[SITE_MLP_WGRAD] = flops[SITE_FC1_WGRAD] + flops[SITE_FC2_WGRAD];
+  flops[SITE_ATTN_WGRAD] = flops[SITE_WO_WGRAD] + flops[SITE_QKV_WGRAD];
+  flops[SITE_LAYER_WGRAD] = flops[SITE_MLP_WGRAD] + flops[SITE_ATTN_WGRAD];
   bytes[SITE_NORM_FWD] = 4 * T * h + 8 * T;
   bytes[SITE_NORM_BWD] = 8 * T * h + 8 * T;
   bytes[SITE_ROPE] = 2 * (2 * T * 2 * hl);
