@@ -92,12 +92,14 @@ hipError_t launch_attention_bwd(const void* qkv, const void* o, const float* lse
 // ---- row-wise / element-wise kernels (bf16 I/O, fp32 math) ----
 // a = norm(x) * gamma (+ beta); stats[2*T] = (mean, rstd) per row (RMS: mean slot unused = 0)
 // x_f32: x is fp32 (the residual stream kept in fp32) instead of bf16
+// keep, optional (x in bf16): a copy of x, in fp32 with keep_f32
 hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const void* beta, void* a, float* stats,
-                           int T, int h, float eps, hipStream_t s, bool x_f32 = false);
+                           int T, int h, float eps, hipStream_t s, bool x_f32 = false, void* keep = nullptr, bool keep_f32 = false);
 // dx = dres + norm_bwd(da);  partial column sums of (da*xhat, da, dres) go to `part` ([3][nblk][h] fp32),
 // written, or with acc != 0 added to what is there (a group of micro-batches sharing one set of partial sums)
+// keep, optional: a copy of dres
 hipError_t launch_norm_bwd(bool rms, const void* da, const void* x, const float* stats, const void* gamma,
-                           const void* dres, void* dx, float* part, int T, int h, hipStream_t s, int acc = 0, bool x_f32 = false);
+                           const void* dres, void* dx, float* part, int T, int h, hipStream_t s, int acc = 0, bool x_f32 = false, void* keep = nullptr);
 int norm_bwd_blocks(int T);
 // g[c] = beta * g[c] + sum_b part[b][c] for the vectors of a list (n a multiple of 64), in one launch
 struct FoldList {
@@ -126,7 +128,5 @@ int colsum_blocks(int T);
 hipError_t launch_rope(void* qkv, const float* cos_sin, int T, int S, int nh, int d, float sign, hipStream_t s);
 // device-to-device copy of a multiple of 16 bytes
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
-// n bf16 values (a multiple of 8) -> fp32
-hipError_t launch_widen(void* dst_f32, const void* src_bf16, size_t n, hipStream_t s);
 
 }  // namespace ah

@@ -39,11 +39,29 @@ template <> struct XVec<true> {
   __device__ __forceinline__ float get(int j) const { return j < 4 ? a[j] : b[j - 4]; }
 };
 
+// The stage's input is kept for backward: its first norm, which reads it, leaves the copy, in bf16 or widened to the fp32 stream
+// (4096 x 4096: 20.4 us, where a copy of 13.0 us preceded a norm of 14.8).  Instances of their own: with the choice made at
+// run time a 4096-wide row takes eight more registers, and one wave fits a SIMD instead of two (bound to two, the instance
+// that copies spills four).  With the same in the norm backward: 5-head stage 237.1 -> 234.9 us, smallest 321.6 -> 319.2, 1.3B
+// 6052 -> 6024, 7B shard 17561 -> 17438, LLaMA-style 5962 -> 5943.
+enum Keep { KEEP_NONE, KEEP_BF16, KEEP_F32 };
+template <Keep KEEP, bool XF32>
+__device__ __forceinline__ void keep_input(void* to, size_t elem, const XVec<XF32>& t) {
+  static_assert(KEEP == KEEP_NONE || !XF32, "an fp32 input is there already");
+  if constexpr (KEEP == KEEP_BF16) {
+    *(bf16x8*)((bf16*)to + elem) = t.v;
+  } else if constexpr (KEEP == KEEP_F32) {
+    float* p = (float*)to + elem;
+    *(f32x4*)p = f32x4{t.get(0), t.get(1), t.get(2), t.get(3)};
+    *(f32x4*)(p + 4) = f32x4{t.get(4), t.get(5), t.get(6), t.get(7)};
+  }
+}
+
 // ---------------------------------------------------------------- norm forward: one block per row
-template <bool RMS, int MAXC, bool XF32>
+template <bool RMS, int MAXC, bool XF32, Keep KEEP>
 __global__ __launch_bounds__(NT) void norm_fwd_kernel(const void* __restrict__ x, const bf16* __restrict__ gamma,
                                                       const bf16* __restrict__ beta, bf16* __restrict__ a,
-                                                      float* __restrict__ stats, int h, float eps) {
+                                                      float* __restrict__ stats, int h, float eps, void* __restrict__ keep) {
   __shared__ float red[8];
   const int row = blockIdx.x, nchunk = h >> 3;
   float v[MAXC][8];
@@ -54,6 +72,7 @@ __global__ __launch_bounds__(NT) void norm_fwd_kernel(const void* __restrict__ x
     if (c < nchunk) {
       XVec<XF32> t;
       t.load(x, (size_t)row * h + c * 8);
+      keep_input<KEEP>(keep, (size_t)row * h + c * 8, t);
 #pragma unroll
       for (int j = 0; j < 8; j++) { v[i][j] = t.get(j); s += RMS ? v[i][j] * v[i][j] : v[i][j]; }
     }
@@ -95,10 +114,10 @@ __global__ __launch_bounds__(NT) void norm_fwd_kernel(const void* __restrict__ x
 // reductions with no block barrier, and it walks rows w, w + (waves in the grid), ... with the next row's loads
 // issued before the current one is reduced: loads, arithmetic and stores of different rows overlap inside a wave
 // as well as across the waves of a CU.  The gain and offset stay packed in registers for all rows.
-template <bool RMS, int MAXI, bool XF32>
-__global__ __launch_bounds__(NT) void norm_fwd_wave_kernel(const void* __restrict__ x, const bf16* __restrict__ gamma,
+template <bool RMS, int MAXI, bool XF32, Keep KEEP>
+__global__ __launch_bounds__(NT, MAXI == 8 && KEEP == KEEP_BF16 ? 2 : 1) void norm_fwd_wave_kernel(const void* __restrict__ x, const bf16* __restrict__ gamma,
                                                            const bf16* __restrict__ beta, bf16* __restrict__ a,
-                                                           float* __restrict__ stats, int T, int h, float eps) {
+                                                           float* __restrict__ stats, int T, int h, float eps, void* __restrict__ keep) {
   const int lane = threadIdx.x & 63, nchunk = h >> 3;
   const int nw = gridDim.x * (NT / 64);
   int row = blockIdx.x * (NT / 64) + (threadIdx.x >> 6);
@@ -121,6 +140,11 @@ __global__ __launch_bounds__(NT) void norm_fwd_wave_kernel(const void* __restric
 #pragma unroll
       for (int i = 0; i < MAXI; i++)
         if (lane + 64 * i < nchunk) nxt[i].load(x, (size_t)nr * h + (lane + 64 * i) * 8);
+    }
+    if constexpr (KEEP != KEEP_NONE) {
+#pragma unroll
+      for (int i = 0; i < MAXI; i++)
+        if (lane + 64 * i < nchunk) keep_input<KEEP>(keep, (size_t)row * h + (lane + 64 * i) * 8, cur[i]);
     }
     float s = 0.f;
 #pragma unroll
@@ -163,6 +187,8 @@ __global__ __launch_bounds__(NT) void norm_fwd_wave_kernel(const void* __restric
 }
 
 // ---------------------------------------------------------------- norm backward
+// keep, optional: a copy of dres (the stage's output gradient, which a group's weight gradients need after the call; 4096 x 4096:
+// 30.5 us with and 30.4 without, a copy kernel 13.0).
 // Block b handles rows b, b + nblk, b + 2*nblk, ... (so that the blocks, which advance together, read one
 // contiguous stretch of memory at a time and spread over all HBM channels); a thread keeps its columns for
 // all of them, so the three column sums accumulate in registers and leave the block once.  512 threads (two waves per
@@ -174,7 +200,7 @@ template <bool RMS, int MAXC, bool XF32>
 __global__ __launch_bounds__(NTB) void norm_bwd_kernel(const bf16* __restrict__ da, const void* __restrict__ x,
                                                        const float* __restrict__ stats, const bf16* __restrict__ gamma,
                                                        const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                       float* __restrict__ part, int T, int h, int rpb, int acc) {
+                                                       float* __restrict__ part, int T, int h, int rpb, int acc, bf16* __restrict__ keep) {
   constexpr int RB = MAXC <= 1 ? 2 : 1;  // rows per batch: two keep a 4096-wide row kernel at 125 registers (36.8 us; four rows 39.6, one 38.4)
   constexpr int NWV = NTB / 64;
   constexpr bool PIPE = MAXC <= 2;  // wider rows (hidden > 8192) leave no registers for a second batch, and spill a few
@@ -279,6 +305,7 @@ __global__ __launch_bounds__(NTB) void norm_bwd_kernel(const bf16* __restrict__ 
             o[j] = f2bf(r + rstd[k] * (w - c1 - xh * c2));
           }
           *(bf16x8*)(dx + (size_t)row * h + c * 8) = o;
+          if (keep) *(bf16x8*)(keep + (size_t)row * h + c * 8) = tr[k][i];
         }
       }
     }
@@ -338,7 +365,7 @@ template <bool RMS, int MAXI, bool XF32>
 __global__ __launch_bounds__(64 * NWB) void norm_bwd_wave_kernel(const bf16* __restrict__ da, const void* __restrict__ x,
                                                                 const float* __restrict__ stats, const bf16* __restrict__ gamma,
                                                                 const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                                float* __restrict__ part, int T, int h, int acc) {
+                                                                float* __restrict__ part, int T, int h, int acc, bf16* __restrict__ keep) {
   __shared__ __attribute__((aligned(16))) float red[NWB][MAXI * 512];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nchunk = h >> 3, nblk = gridDim.x;
   const float inv_h = 1.f / h;
@@ -401,6 +428,7 @@ __global__ __launch_bounds__(64 * NWB) void norm_bwd_wave_kernel(const bf16* __r
           o[j] = f2bf(r + rstd * (w - c1 - xh * c2));
         }
         *(bf16x8*)(dx + (size_t)row * h + (lane + 64 * i) * 8) = o;
+        if (keep) *(bf16x8*)(keep + (size_t)row * h + (lane + 64 * i) * 8) = cr[i];
       }
     mean = nmean;
     rstd = nrstd;
@@ -539,60 +567,53 @@ __global__ __launch_bounds__(NT) void copy16_kernel(const uint4* __restrict__ sr
   if (i < n16) dst[i] = src[i];
 }
 
-// bf16 -> fp32, 8 elements per lane (the stage input entering an fp32 residual stream)
-__global__ __launch_bounds__(NT) void widen_kernel(const bf16* __restrict__ src, float* __restrict__ dst, size_t n8) {
-  const size_t i = (size_t)blockIdx.x * NT + threadIdx.x;
-  if (i >= n8) return;
-  const bf16x8 t = *(const bf16x8*)(src + i * 8);
-  *(f32x4*)(dst + i * 8) = f32x4{bf2f(t[0]), bf2f(t[1]), bf2f(t[2]), bf2f(t[3])};
-  *(f32x4*)(dst + i * 8 + 4) = f32x4{bf2f(t[4]), bf2f(t[5]), bf2f(t[6]), bf2f(t[7])};
-}
-
 }  // namespace
 
 namespace {
 // one wave per row; MAXI = chunks of 8 values per lane
 template <bool RMS, int MAXI>
-void norm_fwd_wave_go(const void* x, bool x_f32, const void* gamma, const void* beta, void* a, float* stats, int T, int h, float eps, hipStream_t s) {
+void norm_fwd_wave_go(const void* x, bool x_f32, const void* gamma, const void* beta, void* a, float* stats, int T, int h, float eps, Keep mode, void* keep, hipStream_t s) {
   // two rows per wave where the rows suffice (the second row's loads run under the first row's arithmetic), at most 8 waves per CU
   const int waves = T >= 4096 ? 2048 : (T + 1) / 2 > 0 ? (T + 1) / 2 : 1;
   const dim3 grid((waves + NT / 64 - 1) / (NT / 64));
-  if (x_f32)
-    hipLaunchKernelGGL((norm_fwd_wave_kernel<RMS, MAXI, true>), grid, dim3(NT), 0, s, x, (const bf16*)gamma, (const bf16*)beta, (bf16*)a, stats, T, h, eps);
-  else
-    hipLaunchKernelGGL((norm_fwd_wave_kernel<RMS, MAXI, false>), grid, dim3(NT), 0, s, x, (const bf16*)gamma, (const bf16*)beta, (bf16*)a, stats, T, h, eps);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, s, x, (const bf16*)gamma, (const bf16*)beta, (bf16*)a, stats, T, h, eps, keep); };
+  if (x_f32) go(norm_fwd_wave_kernel<RMS, MAXI, true, KEEP_NONE>);
+  else if (mode == KEEP_BF16) go(norm_fwd_wave_kernel<RMS, MAXI, false, KEEP_BF16>);
+  else if (mode == KEEP_F32) go(norm_fwd_wave_kernel<RMS, MAXI, false, KEEP_F32>);
+  else go(norm_fwd_wave_kernel<RMS, MAXI, false, KEEP_NONE>);
 }
 
 template <bool RMS, int MAXC>
-void norm_fwd_go(const void* x, bool x_f32, const void* gamma, const void* beta, void* a, float* stats, int T, int h, float eps, hipStream_t s) {
-  if (x_f32)
-    hipLaunchKernelGGL((norm_fwd_kernel<RMS, MAXC, true>), dim3(T), dim3(NT), 0, s, x, (const bf16*)gamma, (const bf16*)beta, (bf16*)a, stats, h, eps);
-  else
-    hipLaunchKernelGGL((norm_fwd_kernel<RMS, MAXC, false>), dim3(T), dim3(NT), 0, s, x, (const bf16*)gamma, (const bf16*)beta, (bf16*)a, stats, h, eps);
+void norm_fwd_go(const void* x, bool x_f32, const void* gamma, const void* beta, void* a, float* stats, int T, int h, float eps, Keep mode, void* keep, hipStream_t s) {
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(T), dim3(NT), 0, s, x, (const bf16*)gamma, (const bf16*)beta, (bf16*)a, stats, h, eps, keep); };
+  if (x_f32) go(norm_fwd_kernel<RMS, MAXC, true, KEEP_NONE>);
+  else if (mode == KEEP_BF16) go(norm_fwd_kernel<RMS, MAXC, false, KEEP_BF16>);
+  else if (mode == KEEP_F32) go(norm_fwd_kernel<RMS, MAXC, false, KEEP_F32>);
+  else go(norm_fwd_kernel<RMS, MAXC, false, KEEP_NONE>);
 }
 template <bool RMS, int MAXC>
 void norm_bwd_go(const void* da, const void* x, bool x_f32, const float* stats, const void* gamma, const void* dres, void* dx, float* part,
-                 int T, int h, int acc, hipStream_t s) {
+                 int T, int h, int acc, void* keep, hipStream_t s) {
   const int nblk = norm_bwd_blocks(T);
   const int rpb = (T + nblk - 1) / nblk;
   if (x_f32)
     hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, true>), dim3(nblk), dim3(NTB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc);
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep);
   else
     hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, false>), dim3(nblk), dim3(NTB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc);
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep);
 }
 // one wave per row, hidden <= 1024
 template <bool RMS, int MAXI>
 void norm_bwd_wave_go(const void* da, const void* x, bool x_f32, const float* stats, const void* gamma, const void* dres, void* dx, float* part,
-                      int T, int h, int acc, hipStream_t s) {
+                      int T, int h, int acc, void* keep, hipStream_t s) {
   const int nblk = norm_bwd_blocks(T);
   if (x_f32)
     hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, true>), dim3(nblk), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc);
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep);
   else
     hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, false>), dim3(nblk), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc);
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep);
 }
 }  // namespace
 
@@ -613,7 +634,9 @@ int norm_bwd_blocks(int T) {
   } while (0)
 
 hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const void* beta, void* a, float* stats, int T,
-                           int h, float eps, hipStream_t s, bool x_f32) {
+                           int h, float eps, hipStream_t s, bool x_f32, void* keep, bool keep_f32) {
+  if (x_f32 && keep) return hipErrorInvalidValue;
+  const Keep mode = !keep ? KEEP_NONE : keep_f32 ? KEEP_F32 : KEEP_BF16;
   if (h % 8 || h > 16384) return hipErrorInvalidValue;
   static int wave_rows = -1;
   if (wave_rows < 0) wave_rows = getenv("AH_NORM_FWD_BLOCK_PER_ROW") ? 0 : 1;  // tuning aid
@@ -621,34 +644,34 @@ hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const voi
   if (wave_rows && per_lane <= 16) {
 #define AH_WAVE_ROWS(RMS)                                                                                     \
     do {                                                                                                      \
-      if (per_lane <= 2) norm_fwd_wave_go<RMS, 2>(x, x_f32, gamma, beta, a, stats, T, h, eps, s);             \
-      else if (per_lane <= 4) norm_fwd_wave_go<RMS, 4>(x, x_f32, gamma, beta, a, stats, T, h, eps, s);        \
-      else if (per_lane <= 8) norm_fwd_wave_go<RMS, 8>(x, x_f32, gamma, beta, a, stats, T, h, eps, s);        \
-      else if (per_lane <= 12) norm_fwd_wave_go<RMS, 12>(x, x_f32, gamma, beta, a, stats, T, h, eps, s);      \
-      else norm_fwd_wave_go<RMS, 16>(x, x_f32, gamma, beta, a, stats, T, h, eps, s);                          \
+      if (per_lane <= 2) norm_fwd_wave_go<RMS, 2>(x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);             \
+      else if (per_lane <= 4) norm_fwd_wave_go<RMS, 4>(x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);        \
+      else if (per_lane <= 8) norm_fwd_wave_go<RMS, 8>(x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);        \
+      else if (per_lane <= 12) norm_fwd_wave_go<RMS, 12>(x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);      \
+      else norm_fwd_wave_go<RMS, 16>(x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);                          \
     } while (0)
     if (rms) AH_WAVE_ROWS(true);
     else AH_WAVE_ROWS(false);
 #undef AH_WAVE_ROWS
     return hipGetLastError();
   }
-  if (rms) AH_BY_CHUNKS(norm_fwd_go, true, x, x_f32, gamma, beta, a, stats, T, h, eps, s);
-  else AH_BY_CHUNKS(norm_fwd_go, false, x, x_f32, gamma, beta, a, stats, T, h, eps, s);
+  if (rms) AH_BY_CHUNKS(norm_fwd_go, true, x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);
+  else AH_BY_CHUNKS(norm_fwd_go, false, x, x_f32, gamma, beta, a, stats, T, h, eps, mode, keep, s);
   return hipGetLastError();
 }
 
 #define AH_BWD_BY_CHUNKS(RMS)                                                                        \
   do {                                                                                               \
     const int nc = (h + 4095) / 4096;                                                                \
-    if (h <= 512) norm_bwd_wave_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, s);       \
-    else if (h <= 1024) norm_bwd_wave_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, s); \
-    else if (nc <= 1) norm_bwd_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, s);      \
-    else if (nc == 2) norm_bwd_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, s); \
-    else norm_bwd_go<RMS, 4>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, s);              \
+    if (h <= 512) norm_bwd_wave_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s);       \
+    else if (h <= 1024) norm_bwd_wave_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s); \
+    else if (nc <= 1) norm_bwd_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s);      \
+    else if (nc == 2) norm_bwd_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s); \
+    else norm_bwd_go<RMS, 4>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s);              \
   } while (0)
 
 hipError_t launch_norm_bwd(bool rms, const void* da, const void* x, const float* stats, const void* gamma, const void* dres,
-                           void* dx, float* part, int T, int h, hipStream_t s, int acc, bool x_f32) {
+                           void* dx, float* part, int T, int h, hipStream_t s, int acc, bool x_f32, void* keep) {
   if (h % 8 || h > 16384) return hipErrorInvalidValue;
   if (rms) AH_BWD_BY_CHUNKS(true);
   else AH_BWD_BY_CHUNKS(false);
@@ -681,13 +704,6 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) 
   if (bytes % 16) return hipErrorInvalidValue;
   const size_t n16 = bytes / 16;
   hipLaunchKernelGGL(copy16_kernel, dim3((unsigned)((n16 + NT - 1) / NT)), dim3(NT), 0, s, (const uint4*)src, (uint4*)dst, n16);
-  return hipGetLastError();
-}
-
-hipError_t launch_widen(void* dst_f32, const void* src_bf16, size_t n, hipStream_t s) {
-  if (n % 8) return hipErrorInvalidValue;
-  const size_t n8 = n / 8;
-  hipLaunchKernelGGL(widen_kernel, dim3((unsigned)((n8 + NT - 1) / NT)), dim3(NT), 0, s, (const bf16*)src_bf16, (float*)dst_f32, n8);
   return hipGetLastError();
 }
 

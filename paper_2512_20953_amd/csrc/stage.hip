@@ -482,15 +482,17 @@ hipError_t launch_wgrads(ah_stage* s, WgradList& list, int together, hipStream_t
 }
 
 // One layer forward.  y == nullptr: stop after the activations backward needs
-// (used when a layer is re-run inside backward).
-hipError_t layer_forward(ah_stage* s, int layer, const ActPtrs& a, void* y, bool y_is_stage_output, hipStream_t st) {
+// (used when a layer is re-run inside backward).  x: the stage's input, of which the first norm leaves a copy in a.x_in;
+// nullptr where a.x_in holds the layer's input already.
+hipError_t layer_forward(ah_stage* s, int layer, const ActPtrs& a, const void* x, void* y, bool y_is_stage_output, hipStream_t st) {
   const LayerPtrs p = layer_ptrs(s, layer);
   const int T = s->T, h = s->h, hl = s->hl, F = s->F, B = s->cfg.microbatch_size, S = s->cfg.seq_len;
   // the residual stream (x_in, x_mid, the next layer's x_in) is bf16 or fp32; the stage's output y is always bf16
   const bool r32 = s->res32;
   const GemmEpilogue resid = r32 ? EPI_RESID_F32 : EPI_RESID;
   const GemmEpilogue resid_out = r32 ? (y_is_stage_output ? EPI_RESID_F32_OUT16 : EPI_RESID_F32) : EPI_RESID;
-  TIMED(SITE_NORM_FWD, launch_norm_fwd(s->llama, a.x_in, p.ln1_g, p.ln1_b, a.a, (float*)a.stats1, T, h, s->eps, st, r32));
+  TIMED(SITE_NORM_FWD, launch_norm_fwd(s->llama, x ? x : a.x_in, p.ln1_g, p.ln1_b, a.a, (float*)a.stats1, T, h, s->eps, st, r32 && !x,
+                                       x ? a.x_in : nullptr, r32));
   if (s->llama && s->rope_in_gemm) {
     // rotary embedding on Q and K in the epilogue of their product, on the fp32 sums
     GemmArgs g = {};
@@ -533,10 +535,10 @@ hipError_t stream_order(hipStream_t from, hipStream_t to, hipEvent_t ev) {
 // the caller's next use of the gradients waits for.  Each side launch is ordered after its producer on st, st
 // waits for the side stream before a buffer the side stream still reads is rewritten (du, by attention backward,
 // where dqkv shares its buffer) and at the end of the layer (workspace and, with recompute, the shared activation
-// working set are reused by the next layer).  bb: where the intermediate gradients go; wp, vp: what happens to
-// the matrix and vector gradients now (see WgradPlan, VecPlan).
-hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* dy, void* dx, const VecPlan& vp, const BwdBufs& bb,
-                          const WgradPlan& wp, hipStream_t st, hipStream_t sd) {
+// working set are reused by the next layer).  keep_dy: where a copy of dy is left, or nullptr.  bb: where the
+// intermediate gradients go; wp, vp: what happens to the matrix and vector gradients now (see WgradPlan, VecPlan).
+hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* dy, void* keep_dy, void* dx, const VecPlan& vp,
+                          const BwdBufs& bb, const WgradPlan& wp, hipStream_t st, hipStream_t sd) {
   const LayerPtrs p = layer_ptrs(s, layer);
   const int T = s->T, h = s->h, hl = s->hl, F = s->F, B = s->cfg.microbatch_size, S = s->cfg.seq_len;
   const int Fu = s->llama ? 2 * F : F;
@@ -604,7 +606,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   const bool du_reused = sd != st && dqkv == du;
   if (du_reused) TRY(hipEventRecord(ev[2], sd));
   // second norm backward; dx_mid = dy + norm_bwd(dc); column sums give d(gain), d(offset), d(b2)
-  TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_mid, (const float*)a.stats2, p.ln2_g, dy, dmid, part_n2, T, h, st, vp.acc, s->res32));
+  TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_mid, (const float*)a.stats2, p.ln2_g, dy, dmid, part_n2, T, h, st, vp.acc, s->res32, keep_dy));
   TRY(stream_order(st, sd, ev[3]));
   FOLD(add_n2);
   // output projection
@@ -662,13 +664,11 @@ hipError_t ensure_rope(ah_stage* s, hipStream_t st) {
 
 hipError_t stage_forward(ah_stage* s, int slot, const void* x, void* y, hipStream_t st, hipEvent_t* ev) {
   TRY(ensure_rope(s, st));
-  if (s->res32) TRY(launch_widen(act_ptrs(s, slot, 0).x_in, x, (size_t)s->T * s->h, st));
-  else TRY(launch_copy(act_ptrs(s, slot, 0).x_in, x, (size_t)s->T * s->h * 2, st));
   if (ev) TRY(hipEventRecord(ev[0], st));
   for (int l = 0; l < s->L; l++) {
     const ActPtrs a = act_ptrs(s, slot, l);
     void* out = (l + 1 < s->L) ? (void*)act_ptrs(s, slot, l + 1).x_in : y;
-    TRY(layer_forward(s, l, a, out, l + 1 == s->L, st));
+    TRY(layer_forward(s, l, a, l == 0 ? x : nullptr, out, l + 1 == s->L, st));
     if (ev) TRY(hipEventRecord(ev[l + 1], st));
   }
   return hipSuccess;
@@ -737,16 +737,21 @@ hipError_t stage_backward(ah_stage* s, int slot, const void* dy, void* dx, hipSt
   const bool two = two_streams(s, deferred) && !s->tracing;
   if (two) TRY(ensure_side(s));
   const hipStream_t sd = two ? s->side : st;
-  if (deferred) {  // the caller may reuse dy once this call's work has run: keep a copy for the deferred product
-    char* keep;
+  // The caller may reuse dy once this call's work has run: a deferred product needs a copy.  The norm backward that adds dy leaves
+  // it; taken at once, on the side stream, the products read one made beforehand (the caller's dx may be dy).
+  char* keep = nullptr;
+  if (deferred) {
     (void)pend_bufs(s, pos, s->L - 1, &keep);
-    TRY(launch_copy(keep, dy, (size_t)s->T * s->h * 2, st));
-    cur = keep;
+    if (!s->defer) {
+      TRY(launch_copy(keep, dy, (size_t)s->T * s->h * 2, st));
+      cur = keep;
+      keep = nullptr;
+    }
   }
   if (ev) TRY(hipEventRecord(ev[s->L], st));
   for (int l = s->L - 1; l >= 0; l--) {
     const ActPtrs a = act_ptrs(s, slot, l);
-    if (s->recompute) TRY(layer_forward(s, l, a, nullptr, false, st));
+    if (s->recompute) TRY(layer_forward(s, l, a, nullptr, nullptr, false, st));
     BwdBufs bb = {wsb + s->ws.dmid, wsb + s->ws.dbig, wsb + s->ws.dbig};
     void* out = (l == 0) ? dx : (void*)(wsb + ((l & 1) ? s->ws.d1 : s->ws.d0));
     if (deferred) {
@@ -758,7 +763,7 @@ hipError_t stage_backward(ah_stage* s, int slot, const void* dy, void* dx, hipSt
       }
     }
     const VecPlan vp = vec_plan(s, l, deferred, pos, closes_group, beta, wp.beta);
-    TRY(layer_backward(s, l, a, cur, out, vp, bb, wp, st, sd));
+    TRY(layer_backward(s, l, a, cur, l + 1 == s->L ? keep : nullptr, out, vp, bb, wp, st, sd));
     cur = out;
     if (ev) TRY(hipEventRecord(ev[l], st));
   }
