@@ -197,7 +197,7 @@ def main():
         elif s["bytes_per_launch"] > 0:
             s["gbs"] = s["bytes_per_launch"] / (avg * 1e-3) / 1e9
     # The dominant kernel: call sites that launch the same kernel instantiation on the same shape are one
-    # entry (the weight-gradient GEMMs of the two MLP matrices are: same tile, layout, epilogue and flops).
+    # entry (the weight-gradient GEMMs of the two MLP matrices are, where they are launches of their own).
     groups = {}
     for s in sites:
         if s["flops_per_launch"] <= 0:
@@ -215,19 +215,23 @@ def main():
     # shape (it records the hash of csrc/gemm.hip); otherwise null.
     traffic, traffic_source = None, None
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic_%s.md" % args.workload)
-    is_mlp_wgrad = any(n.startswith("gemm_tn.fc") for n in dom["names"])
-    if os.path.exists(tpath) and is_mlp_wgrad:
+    # the weight gradients behind a call site: one matrix, or those that share a launch
+    h_, hl_, F_ = w["hidden"], w["n_heads"] // w["tp"] * w["head_dim"], w["ffn"] // w["tp"]
+    wgrads = {"fc2": (F_, h_), "fc1": (h_, (2 if w["arch"] == "llama" else 1) * F_), "wo": (hl_, h_), "qkv": (h_, 3 * hl_)}
+    together = {"mlp_wgrads": ("fc2", "fc1"), "attn_wgrads": ("wo", "qkv"), "layer_wgrads": tuple(wgrads)}
+    layout, _, site = dom["names"][0].partition(".")
+    matrices = [wgrads[m] for m in together.get(site, (site[:-len("_wgrad")],))] if layout == "gemm_tn" else []
+    if os.path.exists(tpath) and matrices:
         import hashlib
         sha = hashlib.sha256(open(os.path.join(ROOT, "paper_2512_20953_amd", "csrc", "gemm.hip"), "rb").read()).hexdigest()[:16]
-        meta = dict(l.split(":", 1) for l in open(tpath) if l.startswith(("traffic_bytes_per_launch:", "wgrad_group:", "gemm_hip_sha256:")))
-        if int(meta.get("wgrad_group", -1)) == G and meta.get("gemm_hip_sha256", "").strip() == sha:
+        meta = dict(l.split(":", 1) for l in open(tpath) if l.startswith(("traffic_bytes_per_launch:", "wgrad_group:", "site:", "gemm_hip_sha256:")))
+        if meta.get("site", "").strip() in dom["names"] and int(meta.get("wgrad_group", -1)) == G and meta.get("gemm_hip_sha256", "").strip() == sha:
             traffic = float(meta["traffic_bytes_per_launch"])
             traffic_source = "profiles/hbm_traffic_%s.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, csrc/gemm.hip %s)" % (args.workload, sha)
     # algorithmic bytes of one launch of the dominant kernel: each bf16 operand once, the fp32 result written once
     algorithmic_bytes = None
-    if is_mlp_wgrad:
-        Tk, h_, F_ = T * G, w["hidden"], (2 if w["arch"] == "llama" else 1) * (w["ffn"] // w["tp"])
-        algorithmic_bytes = 2.0 * Tk * (h_ + F_) + 4.0 * h_ * F_ * (1 if G == K else 2)
+    if matrices:
+        algorithmic_bytes = sum(2.0 * T * G * (m + n) + 4.0 * m * n * (1 if G == K else 2) for m, n in matrices)
     roofline = {"bound": "mfma", "scope": "dominant kernel (largest total time in the step)", "kernel": "+".join(dom["names"]),
                 "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic, "traffic_source": traffic_source,
