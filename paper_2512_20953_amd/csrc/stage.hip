@@ -166,8 +166,10 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
     double gflop = 0;
     for (const auto& mn : wgrad_shapes(s)) gflop += 2e-9 * s->T * mn[0] * mn[1];
     const char* e = getenv("AH_SIDE_STREAM_MIN_GFLOP");  // tuning and test aid; AH_NO_SIDE_STREAM keeps everything on the caller's stream
-    // (pairs by size alone, wherever they run: the tile of a pair decides on the last bits.  Above the line the first product of a pair
-    // would no longer run beside its input gradient)
+    // Pairs by size alone, wherever they run: the tile of a pair decides on the last bits.  The line is that of the second stream,
+    // where the first product of a pair no longer runs beside its input gradient.  With pairs above it, against products by themselves
+    // (two micro-batches of one layer): 26 GFLOP 1.000, 40 .. 41 0.995 and 1.011, 53 .. 67 0.998 .. 1.000, 70 1.048, 103 1.015, 116
+    // 1.007, 155 0.985, 206 0.975, 232 1.051.
     s->pair_wgrads = gflop < 12.0;
     s->side_pays = gflop >= (e ? atof(e) : 12.0) && !getenv("AH_NO_SIDE_STREAM");
     s->defer = wgrads_wait(s);
