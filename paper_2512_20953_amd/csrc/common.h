@@ -64,7 +64,7 @@ __device__ __forceinline__ float gelu_f(float u) { return u * sigmoid2z(u, u * u
 __device__ __forceinline__ float gelu_grad_f(float u) {
   constexpr float d1 = 2.0 * 0.7978845608028654, d3 = d1 * 0.134145;
   const float uu = u * u, s = sigmoid2z(u, uu);
-  return __builtin_fmaf(s * (1.0f - s), u * __builtin_fmaf(d3, uu, d1), s);
+  return __builtin_fmaf(s * (1.0f - s) * u, __builtin_fmaf(d3, uu, d1), s);   // (u first: s (1 - s) is 0 long before u^3 overflows, from 1e13 on)
 }
 
 // silu(x) = x sigma(x) through the hardware exp2 and reciprocal
