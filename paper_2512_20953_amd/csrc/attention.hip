@@ -668,7 +668,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd64_kernel(const bf16* __restri
   while (j < (CAUSAL ? last - 1 : last)) { AH_FWD_STEP(false, 0); }
   if (CAUSAL && last > 0) { AH_FWD_STEP(true, lim - last * 64); }
 #undef AH_FWD_STEP
-  fwd_half_step<D, false, false>(slot_k(last), slot_v(last), st, s, mx, lo, 0, sc2);
+  // (a wave that sees no key of the block's own tile skips it: see the 128-row dK/dV kernel)
+  if (!CAUSAL || qt >= kh) fwd_half_step<D, false, false>(slot_k(last), slot_v(last), st, s, mx, lo, 0, sc2);
   __syncthreads();
 
   // merge: the waves of the second key half leave (m, l, O) in LDS, lane by lane; the others fold them in
@@ -853,9 +854,11 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
 #define AH_DQ_ROUND(MASK)                                                                                               \
   load(h + 3);                                                                                                          \
   load(h + 4);                                                                                                          \
-  dq_step<D, MASK>(slot_k(h), slot_k(h + 1), slot_v(h + 1), st, s, dp, lo, lim - 32 * h, sc2);                          \
-  dq_step<D, MASK>(slot_k(h + 1), slot_k(h + 2), slot_v(h + 2), st, s, dp, lo, lim - 32 * h - 32, sc2);                 \
+  if (!MASK || h <= own) dq_step<D, MASK>(slot_k(h), slot_k(h + 1), slot_v(h + 1), st, s, dp, lo, lim - 32 * h, sc2);   \
+  if (!MASK || h < own)                                                                                                 \
+    dq_step<D, MASK>(slot_k(h + 1), slot_k(h + 2), slot_v(h + 2), st, s, dp, lo, lim - 32 * h - 32, sc2);               \
   AH_NEXT_TILE()
+  const int own = 4 * qb + wave;   // the half with the wave's own positions; those after it are skipped (see the dK/dV kernel)
   int h = 0;
 #pragma unroll 1
   for (; h < (CAUSAL ? 4 * qb : lasth); h += 2) { AH_DQ_ROUND(false); }
@@ -1048,9 +1051,9 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
     dq_step<D, false>(slot_k(j), slot_k(j + 1), slot_v(j + 1), st, s, dp, lo, 0, sc2);
     AH_NEXT_TILE();
   }
-  // the last tile, under the mask that of the block's own queries (for a wave whose keys all lie after its queries, all masked; its
-  // next scores are nobody's)
-  dq_step<D, CAUSAL>(slot_k(last), slot_k(last), slot_v(last), st, s, dp, lo, q - 64 * last - k0 - 4 * hf, sc2);
+  // the last tile, under the mask that of the block's own queries (a wave whose keys all lie after its queries skips it: see
+  // the 128-row dK/dV kernel; the next scores are nobody's)
+  if (!CAUSAL || qt >= kh) dq_step<D, CAUSAL>(slot_k(last), slot_k(last), slot_v(last), st, s, dp, lo, q - 64 * last - k0 - 4 * hf, sc2);
   __syncthreads();
 
   float* mg = (float*)ring + (size_t)qt * ND * 16 * 64;
@@ -1217,22 +1220,36 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_dkv_kernel(const bf
   load(1, nxt);
   f32x16 s, dp;
   AH_NEXT_TILE();
-  dkv_scores<D>(cur, 0, st, s, dp, lo, hf);
   const int lim = key - j0 * 64 - 4 * hf;   // under the mask the lane's key sees no query before lim
+#define AH_DKV_STEPS(MASK)                                                            \
+  dkv_step<D, MASK>(cur, 0, cur, 32, st, s, dp, lo, lim - j * 64, sc2, hf);           \
+  dkv_step<D, MASK>(cur, 32, nxt, 0, st, s, dp, lo, lim - j * 64 - 32, sc2, hf)
+#define AH_DKV_NEXT()                                                                 \
+  AH_NEXT_TILE();                                                                     \
+  { char* const c = cur; cur = nxt; nxt = fill; fill = c; }                           \
+  j++
 #define AH_DKV_TILE(MASK)                                                             \
   load(j + 2, fill);                                                                  \
-  dkv_step<D, MASK>(cur, 0, cur, 32, st, s, dp, lo, lim - j * 64, sc2, hf);           \
-  dkv_step<D, MASK>(cur, 32, nxt, 0, st, s, dp, lo, lim - j * 64 - 32, sc2, hf);      \
-  AH_NEXT_TILE();                                                                     \
-  { char* const c = cur; cur = nxt; nxt = fill; fill = c; }
+  AH_DKV_STEPS(MASK);                                                                 \
+  AH_DKV_NEXT()
   int j = 0;
-  if (CAUSAL) {  // the first two tiles straddle the diagonal for two of the waves and lie wholly before it or after it for the others
-#pragma unroll 1
-    for (; j < 2; j++) { AH_DKV_TILE(true) }
+  if (CAUSAL) {
+    // The block's own positions.  The first of their two tiles holds only queries before the keys of the last two waves, which
+    // skip it: a probability of zero times what is not finite would reach their results.  (By steps of 32 queries, the
+    // accumulators move out of the ordinary registers: 67.9 -> 70.6 us for the whole backward at 16 x 20 x 256 x 128.)
+    load(2, fill);
+    dkv_scores<D>(wave < 2 ? cur : nxt, 0, st, s, dp, lo, hf);
+    if (wave < 2) { AH_DKV_STEPS(true); }
+    AH_DKV_NEXT();
+    AH_DKV_TILE(true);
+  } else {
+    dkv_scores<D>(cur, 0, st, s, dp, lo, hf);
   }
 #pragma unroll 1
-  for (; j < ntile; j++) { AH_DKV_TILE(false) }
+  while (j < ntile) { AH_DKV_TILE(false); }
 #undef AH_DKV_TILE
+#undef AH_DKV_NEXT
+#undef AH_DKV_STEPS
 
   char* strip = ring + wave * strip_bytes<D>();
   bf16* out = dqkv + ((size_t)b * S + kw0) * ld + nh * D + head * D;
@@ -1306,12 +1323,12 @@ __global__ __launch_bounds__(256) void attn_dkv64_kernel(const bf16* __restrict_
   f32x16 s, dp;
   const int t0 = 32 * qh;
   AH_LANDED(LPS);   // tiles 0 and 1
-  dkv_scores<D>(ring, t0, st, s, dp, lo, hf);
+  const bool skip = CAUSAL && qh < kt;   // the wave's queries of the block's own tile all lie before its keys (see the 128-row kernel)
+  dkv_scores<D>(skip ? ring + STAGE : ring, t0, st, s, dp, lo, hf);
   auto slot = [&](int t) { int x = (t & 3) * STAGE; asm("" : "+s"(x)); return (const char*)ring + x; };
   const int lim = key - j0 * 64 - t0 - 4 * hf;
-  // (in the block's own tile the wave's queries may all lie before its keys: masked like the others)
   load(3);
-  dkv_step<D, CAUSAL>(slot(0), t0, slot(1), t0, st, s, dp, lo, lim, sc2, hf);
+  if (!skip) dkv_step<D, CAUSAL>(slot(0), t0, slot(1), t0, st, s, dp, lo, lim, sc2, hf);
   AH_LANDED(LPS);
 #pragma unroll 1
   for (int j = 1; j < ntile; j++) {
