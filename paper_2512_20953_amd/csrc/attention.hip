@@ -530,8 +530,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(const bf16* __restrict
 // owns queries 32 * (w & 1) .. + 31 and, of every 64-key tile, the keys 32 * (w >> 1) .. + 31.  There are twice as
 // many blocks (two per CU, heavy ones paired with light ones) and every wave walks half the keys of its queries;
 // the two partial results per query (running maximum, sum and output accumulator) meet in LDS at the end.
-// The steps are those of the 128-row kernels, here and in both backward kernels: 1 x 16 x 2048 x 128 causal, forward / dQ / dK,dV, 34.4 /
-// 42.6 / 60.9 us one phase after the other, 32.7 / 41.0 / 57.0 now; 1 x 16 x 1024 x 64 causal 11.7 / 13.1 / 16.8 and 11.0 / 13.4 / 15.3.
+// The steps are those of the 128-row kernels, here and in the backward kernels but dQ at head_dim 64: 1 x 16 x 2048 x 128 causal, forward / dQ
+// / dK,dV, 34.4 / 42.6 / 60.9 us one phase after the other, 32.7 / 41.0 / 57.0 now; 1 x 16 x 1024 x 64 causal, forward / dK,dV, 11.7 / 16.8
+// and 11.0 / 15.3.
 template <int D>
 __device__ __forceinline__ void fwd_half_scores(const char* cK, const LaneOffs<D>& lo, const bf16x8 (&qf)[D / 16], f32x16& s) {
 #pragma unroll
@@ -1069,6 +1070,114 @@ __global__ __launch_bounds__(256, 2) void attn_dq64_kernel(const bf16* __restric
                 dqkv + ((size_t)b * S + qw0) * ld + head * D, ld, lane);
 }
 
+// ---- head_dim 64: one tile after the other, as in the 128-row kernel of this width (168 registers, the steps take 184).  The whole backward,
+// in steps / this way: 1 x 16 x 1024 causal 26.9 / 26.2 us, without the mask 27.1 / 26.4, 1 x 8 x 4096 causal 91.4 / 89.1, 4 x
+// 16 x 512 28.6 / 28.1, 1 x 16 x 256 causal 13.1 / 12.9 (same bits).
+__device__ __forceinline__ void dq_half_tile(const char* __restrict__ cK, const char* __restrict__ cV, DqState<64>& st, int kh, int lim,
+                                             bool diag, float sc2, int lane) {
+  constexpr int D = 64, NK = D / 16, ND = D / 32;
+  const int hf = lane >> 5;
+  bf16x8 fk[NK], fv[NK];
+#pragma unroll
+  for (int ks = 0; ks < NK; ks++) {
+    fk[ks] = frag_rowmajor<D>(cK, 32 * kh + (lane & 31), ks, hf);
+    fv[ks] = frag_rowmajor<D>(cV, 32 * kh + (lane & 31), ks, hf);
+  }
+  AH_SCHED_FENCE();
+  f32x16 s, dp;
+#pragma unroll
+  for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = -st.delta; }   // dP - delta for free
+#pragma unroll
+  for (int ks = 0; ks < NK; ks++) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[ks], st.qf[ks], s, 0, 0, 0);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[ks], st.dof[ks], dp, 0, 0, 0);
+  }
+  bf16x8 kt[2][ND];
+#pragma unroll
+  for (int s2 = 0; s2 < 2; s2++)
+#pragma unroll
+    for (int dt = 0; dt < ND; dt++) kt[s2][dt] = frag_transposed<D>(cK, 32 * kh + 16 * s2 + 4 * hf, dt, lane);
+  AH_SCHED_FENCE();
+  const float nl = -st.lse2;
+#pragma unroll
+  for (int r = 0; r < 16; r++) s[r] = fexp2(__builtin_fmaf(s[r], sc2, nl));
+  if (diag) {  // wave-uniform; element r is masked iff 8 * (r / 4) + r % 4 > lim
+#pragma unroll
+    for (int r = 0; r < 16; r++)
+      if (8 * (r >> 2) + (r & 3) > lim) s[r] = 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; r++) s[r] *= dp[r];  // dS^T
+  AH_SCHED_FENCE();
+#pragma unroll
+  for (int s2 = 0; s2 < 2; s2++) {
+    const bf16x8 dsf = pack8(s, s2);
+#pragma unroll
+    for (int dt = 0; dt < ND; dt++) st.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[s2][dt], dsf, st.acc[dt], 0, 0, 0);
+  }
+  AH_SCHED_FENCE();
+}
+
+template <bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void attn_dq64_plain_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ o,
+                                                        const bf16* __restrict__ d_o, const float* __restrict__ lse,
+                                                        float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int nh,
+                                                        float sc2, float scale) {
+  constexpr int D = 64, TILEB = 64 * 2 * D, STAGE = 2 * TILEB, ND = D / 32;
+  __shared__ __attribute__((aligned(1024))) char ring[NSLOT * STAGE];   // ring slot = K tile then V tile
+  static_assert(2 * ND * 16 * 64 * 4 + 2 * strip_bytes<D>() <= NSLOT * STAGE, "the partial results and output strips of two waves fit in the ring");
+  const int lane = threadIdx.x & 63, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qt = wave & 1, kh = wave >> 1;
+  const int nq = S / 64;
+  const int nbh = B * nh;
+  const int rank = blockIdx.x / nbh, bh = blockIdx.x - rank * nbh;   // all heads of one block of rows, then the next
+  const int qb = CAUSAL ? causal_query_block(rank, nq) : rank;
+  const int b = bh / nh, head = bh - b * nh;
+  const int ld = 3 * nh * D;
+  const bf16* qp = qkv + (size_t)b * S * ld + head * D;
+  const bf16* kp = qp + nh * D;
+  const bf16* vp = qp + 2 * nh * D;
+  const int qw0 = qb * 64 + qt * 32, q = qw0 + (lane & 31);
+
+  DqState<D> st;   // (both key halves' waves take delta, one writes it)
+  st.load(qp + (size_t)q * ld, o, d_o, lse, delta, (size_t)b * S + q, ((size_t)b * nh + head) * S + q, head, nh, hf, kh == 0);
+
+  uint32_t off[D / 32];
+#pragma unroll
+  for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
+
+  // tile t lives in ring slot t % 2 and is loaded during tile t - 1 (the last one again during the last, into a dead slot)
+  const int ntile = CAUSAL ? qb + 1 : nq, last = ntile - 1;
+  const size_t step = (size_t)64 * ld;
+  issue_tile<D>(kp, off, ring, wave);
+  issue_tile<D>(vp, off, ring + TILEB, wave);
+  AH_NEXT_TILE();
+  for (int j = 0; j < ntile; j++) {
+    const size_t o2 = (size_t)min(j + 1, last) * step;
+    char* fill = ring + ((j + 1) & 1) * STAGE;
+    const char* cur = ring + (j & 1) * STAGE;
+    issue_tile<D>(kp + o2, off, fill, wave);
+    issue_tile<D>(vp + o2, off, fill + TILEB, wave);
+    // in the block's own tile the wave's keys lie before (kh < qt), on (kh == qt) or after (kh > qt: skipped) its queries
+    const bool own = CAUSAL && j == last;
+    if (!(own && kh > qt)) dq_half_tile(cur, cur + TILEB, st, kh, q - j * 64 - 32 * kh - 4 * hf, own && kh == qt, sc2, lane);
+    AH_NEXT_TILE();
+  }
+
+  float* mg = (float*)ring + (size_t)qt * ND * 16 * 64;
+  if (kh == 1) {
+#pragma unroll
+    for (int dt = 0; dt < ND; dt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) mg[(dt * 16 + r) * 64 + lane] = st.acc[dt][r];
+  }
+  __syncthreads();
+  if (kh == 1) return;
+  store_rows<D>([&](int dt, int r) { return (st.acc[dt][r] + mg[(dt * 16 + r) * 64 + lane]) * scale; }, ring + NSLOT * STAGE - (2 - qt) * strip_bytes<D>(),
+                dqkv + ((size_t)b * S + qw0) * ld + head * D, ld, lane);
+}
+
 // =========================================================================== backward: dK, dV (one block per 128 keys)
 template <int D>
 struct DkvState {
@@ -1398,21 +1507,23 @@ hipError_t launch_attention_fwd(const void* qkv, void* o, float* lse, int B, int
 template <int D, bool CAUSAL>
 static void launch_bwd_t(dim3 grid, hipStream_t s, const void* qkv, const void* o, const float* lse, const void* d_o,
                          void* dqkv, float* delta, int B, int S, int nh, float sc2, float scale) {
-  if ((int)grid.x <= small_grid_blocks())  // at most one 128-query block per CU: 64-query blocks with the keys split between wave pairs
-    hipLaunchKernelGGL((attn_dq64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse,
-                       delta, (bf16*)dqkv, B, S, nh, sc2, scale);
-  else if constexpr (D == 64)
-    hipLaunchKernelGGL((attn_dq_plain_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse, delta,
-                       (bf16*)dqkv, B, S, nh, sc2, scale);
-  else
-    hipLaunchKernelGGL((attn_dq_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse, delta,
-                       (bf16*)dqkv, B, S, nh, sc2, scale);
-  if ((int)grid.x <= small_grid_blocks())  // at most one 128-key block per CU: 64-key blocks with the queries split between wave pairs
-    hipLaunchKernelGGL((attn_dkv64_kernel<D, CAUSAL>), dim3(2 * grid.x), dim3(256), 0, s, (const bf16*)qkv, (const bf16*)d_o, lse, delta,
-                       (bf16*)dqkv, B, S, nh, sc2, scale);
-  else
-    hipLaunchKernelGGL((attn_dkv_kernel<D, CAUSAL>), grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)d_o, lse, delta, (bf16*)dqkv,
-                       B, S, nh, sc2, scale);
+  const bool small = (int)grid.x <= small_grid_blocks();  // at most one 128-row block per CU: 64-row blocks, each split between wave pairs
+  if (small) grid.x *= 2;
+  auto dq = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)o, (const bf16*)d_o, lse, delta, (bf16*)dqkv, B, S, nh, sc2, scale);
+  };
+  if constexpr (D == 64) {
+    if (small) dq(attn_dq64_plain_kernel<CAUSAL>);
+    else dq(attn_dq_plain_kernel<D, CAUSAL>);
+  } else {
+    if (small) dq(attn_dq64_kernel<D, CAUSAL>);
+    else dq(attn_dq_kernel<D, CAUSAL>);
+  }
+  auto dkv = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, (const bf16*)qkv, (const bf16*)d_o, lse, delta, (bf16*)dqkv, B, S, nh, sc2, scale);
+  };
+  if (small) dkv(attn_dkv64_kernel<D, CAUSAL>);
+  else dkv(attn_dkv_kernel<D, CAUSAL>);
 }
 
 hipError_t launch_attention_bwd(const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
