@@ -72,10 +72,10 @@ __device__ __forceinline__ uint32_t tile_src_offset(int chunk, int lane, int ld)
 // The loads into LDS as assembly: for the builtin the compiler assumes an access that may return out of order with LDS
 // reads, and waits for all of a wave's LDS reads (lgkmcnt(0)) before the first use of any of them while such a load is in
 // flight.  Nothing is returned to a register; the kernels wait for these loads by count before they pass a barrier.  M0 (the
-// LDS address) is set in the same statement, and nothing else in this file uses it.  Against the builtin, forward / backward:
+// LDS address) is set in the same statement and named as overwritten.  Against the builtin, forward / backward:
 // 2 x 16 x 2048 x 128 causal 51.1 / 163.2 -> 49.7 / 160.2 us, 2 x 16 x 2048 x 64 causal 29.5 / 86.4 -> 28.7 / 83.0 (same bits).
 __device__ __forceinline__ void load4(const void* base, uint32_t off, void* lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory", "m0");
 }
 
 template <int D>

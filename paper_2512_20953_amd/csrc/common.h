@@ -28,10 +28,10 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t& off, v
 
 // The same as an assembly statement: the compiler neither waits for it nor orders LDS reads after it (that is the kernel's
 // business: a wait by count, and a compiler fence), and does not take it for an access that may return out of order
-// with LDS reads.  M0 is set in the same statement: no load16_to_lds may follow in the kernel.
+// with LDS reads.  M0 is set in the same statement and named as overwritten.
 __device__ __forceinline__ uint32_t lds_offset(const void* p) { return (uint32_t)(uintptr_t)AH_LDS(p); }
 __device__ __forceinline__ void load16_to_lds_uncounted(const void* base, uint32_t off, void* lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_offset(lds)), "v"(off), "s"(base) : "memory", "m0");
 }
 
 // Transposing LDS read: within each group of 16 lanes, lane j supplies the
