@@ -225,7 +225,7 @@ typedef struct {
   int64_t launches;         /* event pairs recorded for this site */
   double total_ms;          /* sum of their durations */
   double flops_per_launch;  /* algorithmic flops of one launch (0 for bandwidth-bound sites) */
-  double bytes_per_launch;  /* algorithmic HBM bytes of one launch (0 for the MFMA-bound sites) */
+  double bytes_per_launch;  /* algorithmic HBM bytes of one launch, averaged over the launches of the site (0 for the MFMA-bound sites) */
 } ah_trace_entry_t;
 int ah_stage_trace_begin(ah_stage_t* st);
 int ah_stage_trace_end(ah_stage_t* st, ah_trace_entry_t* out, int capacity, int* n_out);

@@ -78,6 +78,7 @@ struct ah_stage {
   std::vector<int> ev_site;                  // site of pair i
   std::vector<int> ev_mult;                  // micro-batches covered by the launch of pair i
   size_t ev_used;
+  long kept_fwd, kept_bwd;                   // traced norm launches that left a copy behind
 };
 
 namespace {
@@ -493,6 +494,7 @@ hipError_t layer_forward(ah_stage* s, int layer, const ActPtrs& a, const void* x
   const bool r32 = s->res32;
   const GemmEpilogue resid = r32 ? EPI_RESID_F32 : EPI_RESID;
   const GemmEpilogue resid_out = r32 ? (y_is_stage_output ? EPI_RESID_F32_OUT16 : EPI_RESID_F32) : EPI_RESID;
+  if (x && s->tracing) s->kept_fwd++;
   TIMED(SITE_NORM_FWD, launch_norm_fwd(s->llama, x ? x : a.x_in, p.ln1_g, p.ln1_b, a.a, (float*)a.stats1, T, h, s->eps, st, r32 && !x,
                                        x ? a.x_in : nullptr, r32));
   if (s->llama && s->rope_in_gemm) {
@@ -608,6 +610,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   const bool du_reused = sd != st && dqkv == du;
   if (du_reused) TRY(hipEventRecord(ev[2], sd));
   // second norm backward; dx_mid = dy + norm_bwd(dc); column sums give d(gain), d(offset), d(b2)
+  if (keep_dy && s->tracing) s->kept_bwd++;
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_mid, (const float*)a.stats2, p.ln2_g, dy, dmid, part_n2, T, h, st, vp.acc, s->res32, keep_dy));
   TRY(stream_order(st, sd, ev[3]));
   FOLD(add_n2);
@@ -629,7 +632,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32));
   TRY(stream_order(st, sd, ev[5]));
   FOLD(add_n1);
-  if (sd == st) ON_SIDE(SITE_COLSUM, launch_fold(folds, vp.beta, sd));   // one launch for the layer
+  if (sd == st && folds.count > 0) ON_SIDE(SITE_COLSUM, launch_fold(folds, vp.beta, sd));   // one launch for the layer
   TRY(launch_wgrads(s, wl, SITE_LAYER_WGRAD, st));   // a group's
   TRY(stream_order(sd, st, ev[6]));  // join
 #undef FOLD
@@ -1007,6 +1010,7 @@ extern "C" int ah_stage_trace_begin(ah_stage_t* st) {
   if (!st) return set_error(AH_EINVAL, "ah_stage_trace_begin: NULL argument");
   st->tracing = true;
   st->ev_used = 0;
+  st->kept_fwd = st->kept_bwd = 0;
   return AH_OK;
 }
 
@@ -1042,8 +1046,11 @@ extern "C" int ah_stage_trace_end(ah_stage_t* st, ah_trace_entry_t* out, int cap
   flops[SITE_MLP_WGRAD] = flops[SITE_FC1_WGRAD] + flops[SITE_FC2_WGRAD];
   flops[SITE_ATTN_WGRAD] = flops[SITE_WO_WGRAD] + flops[SITE_QKV_WGRAD];
   flops[SITE_LAYER_WGRAD] = flops[SITE_MLP_WGRAD] + flops[SITE_ATTN_WGRAD];
-  bytes[SITE_NORM_FWD] = 4 * T * h + 8 * T;
-  bytes[SITE_NORM_BWD] = 8 * T * h + 8 * T;
+  // (a copy that a norm leaves of the stage's input or output gradient: 2 bytes an element more, also where the input is bf16 and the
+  // copy, like every other norm's input, fp32)
+  const double stream = st->res32 ? 4 : 2;
+  bytes[SITE_NORM_FWD] = (stream + 2) * T * h + 8 * T + 2 * T * h * st->kept_fwd / std::max(launches[SITE_NORM_FWD], 1L);
+  bytes[SITE_NORM_BWD] = (stream + 6) * T * h + 8 * T + 2 * T * h * st->kept_bwd / std::max(launches[SITE_NORM_BWD], 1L);
   bytes[SITE_ROPE] = 2 * (2 * T * 2 * hl);
   int n = 0;
   for (int sidx = 0; sidx < SITE_COUNT && n < capacity; sidx++) {
