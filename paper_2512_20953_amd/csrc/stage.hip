@@ -143,6 +143,30 @@ bool wgrads_wait(const ah_stage* s) {
   return deferred <= at_once - hidden;
 }
 
+// Room for the partial sums of a deferred product whose k axis is shared by blocks (one product at a time uses them): what the largest
+// plan takes of a group, full or not, whose products are launched one by one.  A group in one launch needs none, which with
+// the full group's plan as the limit is known before the room is: less room only makes products by themselves slower.
+// (BERT-Large, G = 8: 64 MiB for the full group's plan, which never runs.)
+size_t shares_room(const ah_stage* s) {
+  GemmShape shape[kMaxGemmGroup];
+  size_t limit = 0, room = 0;
+  int n = 0;
+  for (const auto& mn : wgrad_shapes(s)) {
+    shape[n++] = {mn[0], mn[1]};
+    limit = std::max(limit, gemm_k_part_floats(mn[0], mn[1], s->T * s->group, s->group));
+  }
+  for (int segs = 1; limit && segs <= s->group; segs++) {
+    const int K = s->T * segs;
+    if (gemm_group_tile(shape, n, K, segs, limit) >= 0) continue;
+    for (int i = 0; i < n; i++) {
+      GemmPlanInfo p;
+      if (gemm_plan(GEMM_TN, shape[i].M, shape[i].N, K, segs, limit, 0, &p) && p.shares > 1)
+        room = std::max(room, (size_t)shape[i].M * shape[i].N * p.shares);
+    }
+  }
+  return room;
+}
+
 void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->cfg = *c;
   s->L = c->n_layers;
@@ -258,11 +282,7 @@ void plan(ah_stage* s, const ah_stage_config_t* c) {
   s->vpart.bytes = o;
   o = before_vec;
   w.vec_part = take(s->group > 1 ? (size_t)s->L * s->vpart.bytes : 0);
-  // partial sums of a deferred product whose k axis is shared by blocks: one product at a time uses them
-  s->k_part_floats = 0;
-  if (s->defer)
-    for (const auto& mn : wgrad_shapes(s))
-      s->k_part_floats = std::max(s->k_part_floats, gemm_k_part_floats(mn[0], mn[1], s->T * s->group, s->group));
+  s->k_part_floats = s->defer ? shares_room(s) : 0;
   w.k_part = take(s->k_part_floats * 4);
   w.bytes = o;
 }
