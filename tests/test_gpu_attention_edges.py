@@ -3,9 +3,14 @@ one), two, an odd number, a few rounds; over more than 256 blocks of 128 rows, a
 
 Tolerances.  Output: probabilities and result are rounded to bf16 once each, 2^-9 / sqrt(3) = 1.1e-3 of a row's norm per
 rounding; 4e-3.  Log-sum-exp: fp32 sums and the hardware's exponential, 1e-6 of values below 10; 1e-4.  Gradients, by blocks
-of 32 rows (one wave's): P, dS and the result are rounded, 2e-3 together, and delta_i comes from the rounded output, an error of
-2^-9 |do_i| |o_i| / sqrt(3) in each dS of the row, which for a query with two or three keys is a sizeable part of the
-row (0.18 seen for one row) but below 0.18 / sqrt(32) = 0.03 of its block; 0.06.  A wrong row has error 1, its block 1 / sqrt(32) = 0.18."""
+of 32 rows (one wave's): P, dS and the result are rounded, 2e-3 together, and for dQ and dK delta_i comes from the rounded output, an
+error of 2^-9 |do_i| |o_i| / sqrt(3) in each dS of the row: small beside a dS of many keys (3.3e-3 measured for every block;
+1e-2 allowed), but for a query with two or three keys a sizeable part of the row (0.18 seen for one row), which is below 0.18 /
+sqrt(32) = 0.03 of its block; 0.06 for the first block of the masked dQ and dK.  A wrong row has error 1, its block 1 / sqrt(32) = 0.18.
+
+Rows leave through LDS in pieces of 8 elements, and one of them is lost in a block's norm: each against the block's root mean
+square.  The largest of a block's few hundred pieces is within about six times the block's error (2.7e-2 measured); 0.1, and 0.5
+where a row may be off by 0.18 (a row of few keys is up to twice its block's average).  A wrong piece has error 1.4."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +24,15 @@ pytestmark = pytest.mark.gpu
 
 def _blocks(got, ref, rows=32):
     d, r = ((t.reshape(-1, rows * t.shape[-1]) ** 2).sum(1) for t in (got - ref, ref))
-    return float(np.sqrt((d / np.maximum(r, U.FLOOR ** 2 * r.mean())).max()))
+    return np.sqrt(d / np.maximum(r, U.FLOOR ** 2 * r.mean()))
+
+
+def _pieces(got, ref, rows=32):
+    """The worst piece of each block."""
+    n = rows * ref.shape[-1]
+    rms = np.sqrt((ref.reshape(-1, n) ** 2).mean(1))
+    d = np.sqrt(((got - ref).reshape(-1, n // 8, 8) ** 2).mean(2)).max(1)
+    return d / np.maximum(rms, U.FLOOR * np.sqrt((ref ** 2).mean()))
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -46,6 +59,11 @@ def test_attention_edges(B, S, nh, d, causal):
         m = s.max(1)
         assert np.abs(lse[b, j].cpu().numpy() - (m + np.log(np.exp(s - m[:, None]).sum(1)))).max() <= 1e-4
         q, k, v, do = (t[None, None] for t in (q, k, v, head(d_o)))
-        assert _blocks(head(o), R.attention_fwd(q, k, v, causal)[0, 0]) <= 4e-3, (b, j)
+        ref = R.attention_fwd(q, k, v, causal)[0, 0]
+        assert _blocks(head(o), ref).max() <= 4e-3 and _pieces(head(o), ref).max() <= 0.1, (b, j)
         for blk, ref in enumerate(R.attention_bwd(q, k, v, do, causal)):
-            assert _blocks(head(dqkv, blk), ref[0, 0]) <= 0.06, (b, j, blk)
+            eb, ep = (f(head(dqkv, blk), ref[0, 0]) for f in (_blocks, _pieces))
+            if causal and blk < 2:
+                assert eb[0] <= 0.06 and ep[0] <= 0.5, (b, j, blk)
+                eb, ep = eb[1:], ep[1:]
+            assert (eb <= 1e-2).all() and (ep <= 0.1).all(), (b, j, blk)

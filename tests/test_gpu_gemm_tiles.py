@@ -112,7 +112,9 @@ SHARES = [
 
 @pytest.mark.parametrize("arch,hidden,head_dim,ffn,seq,mb,n_mb,group,expect", SHARES)
 def test_group_products_with_the_k_axis_shared_by_blocks(arch, hidden, head_dim, ffn, seq, mb, n_mb, group, expect, monkeypatch):
-    """Deferred weight gradients whose outputs have fewer tiles than the chip has CUs: the k axis is cut into shares.
+    """Deferred weight gradients whose outputs have fewer tiles than the chip has CUs: launched one by one, their k axis is cut into
+    shares (`expect`).  Most of these groups go out as one launch instead; the same cases with AH_GEMM_SEPARATE set, where the
+    shares run, are in test_gpu_grouped_wgrads.py.
     Against the sums taken per micro-batch: the same up to the order of fp32 additions (2e-6 of the norm over the 32768
     tokens of the full-size comparison; a sum's rounding errors grow with the square root of its length), y and dx bit for bit."""
     monkeypatch.setenv("AH_DEFER_WGRADS", "1")
