@@ -31,13 +31,14 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
-constexpr int NSLOT = 2;  // ring slots of the forward and dQ kernels (two blocks share a CU)
+constexpr int NSLOT = 2;  // ring slots of the kernels that take one tile after the other, and of the 64-row forward kernel
 
 // nothing is scheduled across this point
 #define AH_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 // Issue priority of the wave among the waves of its SIMD: raised for the runs of matrix instructions, so that the
-// other wave's vector work (softmax, masks, conversions) fills in behind them instead of delaying them.  Used in the
-// forward kernel (8 % faster on launches of more than two blocks per CU); in the dQ kernel it cost 1-3 %.
+// other waves' vector work (softmax, masks, conversions) fills in behind them instead of delaying them.  Used by the unmasked
+// 64-wide forward kernel, with / without: 8 x 16 x 512 12.6 / 13.4 us, 2 x 16 x 2048 38.2 / 40.6, 1 x 9 x 4096 56.7 / 68.2, 1 x 32 x 4096
+// 141.5 / 145.5, 16 x 16 x 512 24.8 / 24.1; the kernels that run in slots gain nothing from it.
 #define AH_PRIO(p) __builtin_amdgcn_s_setprio(p)
 
 // All but the last n of the wave's loads have landed, for the whole block, and every wave is done with its LDS reads.  The
@@ -192,8 +193,7 @@ constexpr float RESCALE_SLACK = 8.f;
 // ---- without the mask, head_dim 64: one tile after the other.  Three waves share a SIMD and all of them run to the end, so
 // that they cover each other's waits; the steps below, whose first scores and last product stand alone, are level on long
 // sequences there and lose on short ones (8 x 16 x 512: 17.2 against 18.0 us in a stage).
-// One key tile of 64 for the wave's 32 queries.  LDS reads are issued a phase ahead of their use (see
-// dkv_tile).
+// One key tile of 64 for the wave's 32 queries.  LDS reads are issued a phase ahead of their use.
 template <int D>
 __device__ __forceinline__ void fwd_tile(const char* __restrict__ cK, const char* __restrict__ cV, FwdState<D>& st, float sc2,
                                          int lane) {
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd64_kernel(const bf16* __restri
   if (kh == 1) return;
   const float m2 = mg[(ND * 16) * 64 + lane], l2 = mg[(ND * 16 + 1) * 64 + lane];
   const float m = fmaxf(st.m, m2);
-  const float a1 = fexp2(st.m - m), a2 = fexp2(m2 - m);  // m2 = -inf (nothing visible in that half) gives a2 = 0
+  const float a1 = fexp2(st.m - m), a2 = fexp2(m2 - m);  // m2 = -FLT_MAX (nothing visible in that half) gives a2 = 0
   const float lsum = a1 * st.l + a2 * l2;
   const float l = lsum + __shfl_xor(lsum, 32, 64);
   const float inv = 1.f / l;
@@ -831,9 +831,9 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(const bf16* __restrict_
   for (int i = 0; i < D / 64; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
 
   // Keys by 32 up to and including the diagonal (all of them without the mask), two steps per round.  Keys 32 h .. are in K
-  // slot h % 6 and V slot h % 4: step h reads the columns of K half h and the rows of halves h + 1, so a round needs four halves
-  // of K (three of V) while the two after those arrive.  (Past the end the last half is fetched again, into slots whose scores
-  // nobody uses.)
+  // slot h % 6 and V slot h % 4: step h reads the columns of K half h and the rows of halves h + 1, so a round reads three halves
+  // of K and two of V while the two after those arrive.  (Five K slots would do; either way two blocks share a CU.  Past the end the
+  // last half is fetched again, into slots whose scores nobody uses.)
   const int nround = CAUSAL ? 2 * qb + 2 : S / 64, lasth = 2 * nround - 1;
   auto load = [&](int h) {
     const size_t row = (size_t)min(h, lasth) * 32 * ld;
@@ -932,7 +932,7 @@ __device__ __forceinline__ void dq_tile(const char* __restrict__ cK, const char*
   AH_SCHED_FENCE();
 }
 
-// MASK as in fwd_step
+// MASK: the tile straddles the diagonal for some of the waves and lies behind it for others, which skip it
 template <int D, bool MASK>
 __device__ __forceinline__ void dq_tile_step(const bf16* gK, const bf16* gV, uint32_t* off, char* __restrict__ nK,
                                         char* __restrict__ nV, const char* __restrict__ cK, const char* __restrict__ cV,
@@ -969,7 +969,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_plain_kernel(const bf16* __res
 #pragma unroll
   for (int i = 0; i < D / 32; i++) off[i] = tile_src_offset<D>(wave + 4 * i, lane, ld);
 
-  // tiles, ring and peeled diagonal as in the forward kernel
+  // Tile t lives in ring slot t % 2 and is loaded during step t - 1, two steps per round (the number of tiles is even); under the mask
+  // the two tiles with the block's own positions are peeled, so that the others have no mask in them
   const int ntile = CAUSAL ? 2 * qb + 2 : S / 64, last = ntile - 1, nfull = CAUSAL ? ntile - 2 : ntile;
   const size_t step = (size_t)64 * ld;
   char *const K0 = ring, *const V0 = ring + TILEB, *const K1 = ring + STAGE, *const V1 = ring + STAGE + TILEB;

@@ -120,14 +120,15 @@ std::array<std::array<int, 2>, 4> wgrad_shapes(const ah_stage* s) {
 // fp32 passes over the matrices, one prologue and epilogue, and for a small output enough k for shares that fill the chip.
 // Taken per micro-batch on the second stream they fill what the main chain leaves of the chip instead: by the model's
 // times, about three quarters of launches whose blocks leave room on their CUs and the idle CUs' share of the others, for
-// 40 us of cross-stream orderings.  Small groups of middle-sized products gain more from that.  The three numbers are
-// fitted to 17 stages at groups of 2 .. 16 and hold on 14 others (us per micro-batch and layer, per micro-batch / deferred):
-// 1280-wide, 3072 tokens: G = 2 515 / 568, G = 4 519 / 553, G = 8 521 / 517; BERT-Large: 513 / 542, 513 / 513, 514 / 493;
-// 768-wide BERT: 390 / 428, 389 / 397, 382 / 382; 2048-wide GPT: 889 / 853, 895 / 831, 898 / 823; 512-wide: 193 / 174,
-// 184 / 160, 185 / 156.  Of 117 pairs of stage and group the choice is more than 2 % off the better one in nine, 4.4 % at
-// most.  From groups of five on deferring is level or better, with exceptions of up to 4 % (1536-wide LLaMA-style, 4096
-// tokens, G = 8 993 / 1033) that the model does not see.  Deferring some matrices and not others was slower than the better
-// of the two on 16 of 17 stages.
+// 40 us of cross-stream orderings.  The three numbers are fitted to 17 stages at groups of 2 .. 16 whose four products were
+// launches of their own, and the deferred side is still priced as those; most groups now go out as one launch, which is
+// cheaper than that.  So the rule takes products at once where deferring them is the faster form (us per micro-batch and layer,
+// at once / deferred, at G = 2, 3, 4: 1280-wide, 3072 tokens, 511 / 498, 511 / 495, 509 / 489; BERT-Large 491 / 459, 490 / 456, 491 / 454;
+// 768-wide BERT 383 / 360, 382 / 359, 381 / 359; 1024-wide GPT, 2048 tokens, 343 / 316, 345 / 312, 343 / 309): of 48 pairs of stage and
+// group up to 4, 21 are 2 .. 11 % off the better one, all of them on this side.  Where it defers, that is the better form or within
+// 2 % (2048-wide GPT 856 / 795, 854 / 784, 854 / 779; 512-wide 175 / 139, 175 / 145, 175 / 145; 1536-wide LLaMA-style, 4096 tokens, G = 4
+// 876 / 889), and from groups of five on it always does (G = 8: 2560-wide 1194 / 1156, BERT-Large 489 / 454, the LLaMA-style one 876 / 887).
+// Deferring some matrices and not others was slower than the better of the two on 16 of 17 stages.
 bool wgrads_wait(const ah_stage* s) {
   if (s->group <= 1) return false;
   if (const char* e = getenv("AH_DEFER_WGRADS")) return atoi(e) != 0;  // tuning and test aid
