@@ -131,7 +131,8 @@ typedef struct {
 typedef struct {
   uint32_t struct_size;  /* sizeof(ah_stage_profile_t), checked */
   int32_t n_layers;      /* capacity of fwd_ms / bwd_ms; must be >= the stage's n_layers */
-  float* fwd_ms;         /* host arrays supplied by the caller: median time of one micro-batch per layer */
+  float* fwd_ms;         /* host arrays supplied by the caller: median time of one micro-batch per layer (the first one's with the copy
+                          * of the stage's input, which its norm leaves for backward) */
   float* bwd_ms;
   float stage_fwd_ms, stage_bwd_ms;  /* whole stage, one micro-batch (median) */
   float iteration_ms;                /* K x (forward + backward), grads restarted at micro-batch 0 (median) */
