@@ -1,4 +1,4 @@
-// bf16 GEMM for gfx950: MFMA 32x32x16, fp32 accumulators, tiles staged through
+// bf16 GEMM for gfx950: MFMA 16x16x32 (32x32x16 in the smallest tiles), fp32 accumulators, tiles staged through
 // LDS by direct global->LDS loads (16 B per lane) through a ring of operand tiles.
 //
 // Three operand layouts cover the linear layers of a decoder layer (the GEMM is
@@ -10,8 +10,8 @@
 // with the transposing 8-byte LDS read, so no transposed copy is ever made.
 //
 // Work split: 256 threads = 4 waves in a 2 x 2 grid; each wave owns a
-// (BM/2) x (BN/2) sub-tile as 32 x 32 MFMA blocks (in the smallest tiles the
-// waves share a sub-tile and split the k axis).  The MFMA is issued with the
+// (BM/2) x (BN/2) sub-tile as 16 x 16 MFMA blocks (in the smallest tiles the
+// waves share a sub-tile of 32 x 32 blocks and split the k axis).  The MFMA is issued with the
 // operands swapped (D = B^T A^T) so that a lane ends up with 4 consecutive
 // columns of one output row: 8-byte bf16 or 16-byte fp32 accesses in the epilogue.
 #include "common.h"
@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace ah {
@@ -37,8 +38,10 @@ namespace ah {
 //    groups for the fragment reads.  With BK = 64 a loader instruction fetches 8 rows x 128 B: full cache lines
 //    (64-byte row pieces, as BK = 32 gives, cost the memory pipeline twice the requests and showed up as ~10 % of
 //    MFMA utilisation where an operand is k-contiguous).
-//  k-strided tile: [BK k][W cols]; row = 2W bytes; the 64-byte granule g of row k is stored at granule g ^ (k & 3)
-//    (W = 64, two granules: g ^ (k >> 1 & 1)): the 4 rows x 64 B that half a wave fetches in one transposing read cover all banks once.
+//  k-strided tile: [BK k][W cols]; row = 2W bytes.  Half a wave must cover all banks once in a transposing read.  For fragments
+//    of 16 columns x 32 k it fetches 8 rows (k .. k + 3 and k + 8 .. k + 11) x 32 B: the 32-byte granule g of row k is stored at
+//    granule g ^ (k & 3 | (k >> 1) & 4).  For those of 32 columns x 16 k (the smallest tiles) 4 rows x 64 B: the 64-byte granule g of row
+//    k at g ^ (k & 3) (W = 64, two granules: g ^ (k >> 1 & 1)).
 // A k-strided tile may gather its columns from two column ranges of the matrix (`gw` > 0: tile columns in groups of
 // gw, even groups from columns c, odd groups from columns F + c): the fused gate|up product of the SwiGLU block then
 // has a gate column and its up column in the same wave's accumulators.
@@ -49,7 +52,14 @@ __device__ __forceinline__ int granule_swizzle(int k) {  // a 64-wide row has tw
   return W >= 128 ? k & 3 : (k >> 1) & 1;
 }
 
-template <int BK, int W, bool KS>
+template <int W>
+__device__ __forceinline__ int granule32_swizzle(int k) {  // of 32-byte granules
+  static_assert(W >= 128, "a row spans all banks");
+  return (k & 3) | ((k >> 1) & 4);
+}
+
+// K16: the tile's fragments are 32 columns x 16 k
+template <int BK, int W, bool KS, bool K16 = false>
 __device__ __forceinline__ uint32_t loader_src_offset(int chunk, int lane, int ld, int gw = 0, int F = 0) {  // in bytes
   const int pos = chunk * 1024 + lane * 16;
   if (!KS) {
@@ -61,7 +71,9 @@ __device__ __forceinline__ uint32_t loader_src_offset(int chunk, int lane, int l
   } else {
     constexpr int RB = W * 2;
     const int k = pos / RB, q = (pos % RB) >> 4;
-    const int p = q ^ (granule_swizzle<W>(k) << 2);
+    int p;
+    if constexpr (K16) p = q ^ (granule_swizzle<W>(k) << 2);
+    else p = q ^ (granule32_swizzle<W>(k) << 1);
     int col = p * 8;
     if (gw > 0) col = ((col / gw) & 1) * F + (col / (2 * gw)) * gw + col % gw;
     return (uint32_t)(k * ld + col) * 2u;
@@ -95,6 +107,40 @@ __device__ __forceinline__ bf16x8 read_frag(const char* __restrict__ lds, int ba
     return cat4(lo, hi);
   }
 }
+
+// fragment (8 k-values for row/col = lane % 16 of a 16-wide block) for k-step ks (32 k each)
+template <int BK, int W, bool KS>
+__device__ __forceinline__ bf16x8 read_frag32(const char* __restrict__ lds, int base, int blk, int ks, int lane) {
+  if (!KS) {
+    constexpr int PR = BK / 8;
+    constexpr int SH = BK == 64 ? 1 : 2;
+    const int r = base + blk * 16 + (lane & 15);
+    const int p = ks * 4 + (lane >> 4);
+    const int q = p ^ ((r >> SH) & (PR - 1));
+    return *(const bf16x8*)(lds + r * (2 * BK) + q * 16);
+  } else {
+    constexpr int RB = W * 2;
+    const int k = ks * 32 + (lane >> 4) * 8 + ((lane & 15) >> 2);
+    const int c = base + blk * 16 + 4 * (lane & 3);
+    const int a0 = k * RB + (((c >> 4) ^ granule32_swizzle<W>(k)) << 5) + ((c * 2) & 31);
+    bf16x4 lo = lds_read_tr4(lds + a0);
+    bf16x4 hi = lds_read_tr4(lds + a0 + 4 * RB);
+    return cat4(lo, hi);
+  }
+}
+
+// Fragments of one 32-wide k-step for the wave's sub-tile.
+template <int BK, int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
+struct Frags32 {
+  static constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16;
+  bf16x8 a[TM], b[TN];
+  __device__ __forceinline__ void load(const char* __restrict__ cA, const char* __restrict__ cB, int ks, int wm, int wn, int lane) {
+#pragma unroll
+    for (int t = 0; t < TM; t++) a[t] = read_frag32<BK, BM, AKS>(cA, wm * (BM / WGM), t, ks, lane);
+#pragma unroll
+    for (int t = 0; t < TN; t++) b[t] = read_frag32<BK, BN, BKS>(cB, wn * (BN / WGN), t, ks, lane);
+  }
+};
 
 // Fragments of one 16-wide k-step for the wave's sub-tile.
 template <int BK, int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
@@ -135,65 +181,81 @@ __device__ __forceinline__ void mma_step(const Frags<BK, BM, BN, WGM, WGN, AKS, 
       acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[tn], f.a[tm], acc[tm][tn], 0, 0, 0);
 }
 
+// The 16 x 16 x 32 instruction does the flops of the 32 x 32 x 16 one at less power, which is what bounds a loop that keeps the matrix
+// pipelines busy: register-resident on random operands 2.06 against 1.78 PFLOP/s (2.44 both on zeros).  In the loops below, with
+// the same bytes through LDS: 8192^3 NT 847 -> 811 us, 2048 x 5120 x 20480 394 -> 372, 2048^3 (128 x 128 tiles) 23.2 -> 20.5.
+// As assembly, because the compiler's form has a destination of its own: with all 256 accumulation registers taken it
+// moves 12 .. 60 of 64 accumulators to other registers and back in every k-step.  What the compiler then does not know of is
+// kept here: an accumulator is used again one k-step (16 or more matrix instructions) later, and read 16 wait states
+// after the loops (gemm_tile); operands come from LDS reads, which it does wait for.
+__device__ __forceinline__ void mma16(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
+
+// One 32-wide k-step as a fixed sequence of slots: a matrix instruction on the fragments f each, and before it what falls on the slot
+// of the NV loads (load(i)) and of the reads of the next step's fragments fn, which take the first three quarters.
+template <int BK, int BM, int BN, int WGM, int WGN, bool AKS, bool BKS, int NV, class L>
+__device__ __forceinline__ void k_step(const L& load, const char* __restrict__ nA, const char* __restrict__ nB, int ks,
+                                       const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f, Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& fn,
+                                       f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16], int wm, int wn, int lane) {
+  constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16, NM = TM * TN, NF = TM + TN, SPAN = NM * 3 / 4;
+#pragma unroll
+  for (int i = 0; i < NM; i++) {
+#pragma unroll
+    for (int v = i * NV / NM; v < (i + 1) * NV / NM; v++) load(v);
+#pragma unroll
+    for (int r = i * NF / SPAN; r < (i + 1) * NF / SPAN && r < NF; r++) {
+      if (r < TN) fn.b[r] = read_frag32<BK, BN, BKS>(nB, wn * (BN / WGN), r, ks, lane);
+      else fn.a[r - TN] = read_frag32<BK, BM, AKS>(nA, wm * (BM / WGM), r - TN, ks, lane);
+    }
+    mma16(acc[i / TN][i % TN], f.a[i / TN], f.b[i % TN]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 namespace k64 {
 constexpr int BK = 64;  // k-extent of one operand tile in LDS (128 bytes per row of a k-contiguous operand: whole cache lines)
 constexpr int NB = 5;   // operand tiles in the LDS ring (A and B tiles alternate): 2.5 k-blocks of 64
 
 // The pipeline.  Operand tiles of 64 k are numbered A_0, B_0, A_1, B_1, ...; tile n lives in ring buffer n % 5.
-// A k-block (A_j, B_j) is four k-steps of 16; fragments are double-buffered in registers (f0, f1), the fragments
-// of a k-step being read from LDS under the MFMAs of the step before.  Each half of a k-block starts the loads of
-// one tile three tiles ahead, into the buffer of a tile of the previous k-block.  That buffer is free: the one
-// barrier per k-block (before the first fragments of the next k-block are read) is preceded by a wait for the
-// wave's own LDS reads, and after it no wave reads the finished k-block again.  The same wait counts the wave's
-// own loads down to the one tile issued last, so the next k-block has landed for the whole block.
+// A k-block (A_j, B_j) is two k-steps of 32; fragments are double-buffered in registers (f0, f1), the fragments
+// of a k-step being read from LDS under the MFMAs of the step before.  So all fragments of k-block j are in registers at its
+// middle: there the one barrier per k-block frees its two buffers, and, after a wait that counts the wave's own loads down to the
+// one tile issued last, says that k-block j+1 has landed for the whole block.  The second half of a k-block and the first half of
+// the next one each start the loads of one tile into the buffers so freed.
 // (In the code below the tile sequence is F_0, S_0, F_1, ...: F is A or B, see b_first.)
 // The two halves are separate functions so that within each the buffer written is not one of the buffers read:
 // the restrict qualifiers then tell the compiler that LDS reads never wait for the loads in flight.
 
-// Which operand's tiles take the even numbers matters: an even tile is requested 2.5 half-blocks before its
-// first use, an odd one 1.5.  The weights (B of the forward and input-gradient products) stream from HBM while
+// Which operand's tiles take the even numbers matters: an even tile is requested 1.5 k-blocks before the wait for it, an odd one 1.  The weights (B of the forward and input-gradient products) stream from HBM while
 // the activations were just written and mostly sit in the caches, so there B goes first.
 template <bool AKS>
 constexpr bool b_first() { return !AKS; }
 
-// k-steps 0 and 1 of k-block j; on entry f0 holds the fragments of k-step 0.  Starts the loads of the odd tile
-// of k-block j+1.
+// First k-step of k-block j (f0 holds its fragments): starts the loads of the even tile of k-block j+2 and reads the
+// fragments of the second one.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
-__device__ __forceinline__ void half_even(const char* gS, uint32_t* offS, char* __restrict__ fill, const char* __restrict__ cA,
-                                          const char* __restrict__ cB, Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f0,
-                                          Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f1, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32],
+__device__ __forceinline__ void half_even(const char* gF, uint32_t* offF, char* __restrict__ fill, const char* __restrict__ cA,
+                                          const char* __restrict__ cB, const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f0,
+                                          Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f1, f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16],
                                           int wave, int wm, int wn, int lane) {
-  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN;
-  constexpr int NR = TM * (AKS ? 2 : 1) + TN * (BKS ? 2 : 1), NM = TM * TN;
-  constexpr int WS = b_first<AKS>() ? BM : BN;  // the odd tiles are A tiles when B goes first
-  issue_tile_loads<BK, WS, NW>(gS, offS, fill, wave);
-  f1.load(cA, cB, 1, wm, wn, lane);
-  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f0, acc);
-  interleave<0, NM, NR, WS / 8 / NW>();
-  f0.load(cA, cB, 2, wm, wn, lane);
-  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f1, acc);
-  interleave<0, NM, NR, 0>();
+  constexpr int NW = WGM * WGN, WF = b_first<AKS>() ? BN : BM;
+  k_step<BK, BM, BN, WGM, WGN, AKS, BKS, WF / 8 / NW>([&](int i) { load16_to_lds(gF, offF[i], fill + (wave + NW * i) * 1024); }, cA, cB, 1, f0, f1,
+                                                      acc, wm, wn, lane);
 }
 
-// k-steps 2 and 3 of k-block j; on entry f0 holds the fragments of k-step 2.  Starts the loads of the even tile
-// of k-block j+2, waits for k-block j+1 (nA, nB) and leaves its first fragments in f0.
+// Second k-step of k-block j: waits for k-block j+1 (nA, nB), starts the loads of the odd tile of k-block j+2 into a buffer of
+// k-block j, whose fragments all waves hold by now, and reads the first fragments of k-block j+1.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
-__device__ __forceinline__ void half_odd(const char* gF, uint32_t* offF, char* __restrict__ fill, const char* __restrict__ cA,
-                                         const char* __restrict__ cB, const char* __restrict__ nA, const char* __restrict__ nB,
-                                         Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f0, Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f1,
-                                         f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], int wave, int wm, int wn, int lane) {
-  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN;
-  constexpr int NR = TM * (AKS ? 2 : 1) + TN * (BKS ? 2 : 1), NM = TM * TN;
-  constexpr int WF = b_first<AKS>() ? BN : BM;
-  issue_tile_loads<BK, WF, NW>(gF, offF, fill, wave);
-  f1.load(cA, cB, 3, wm, wn, lane);
-  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f0, acc);
-  interleave<0, NM, NR, WF / 8 / NW>();
+__device__ __forceinline__ void half_odd(const char* gS, uint32_t* offS, char* __restrict__ fill, const char* __restrict__ nA,
+                                         const char* __restrict__ nB, Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f0,
+                                         const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f1, f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16],
+                                         int wave, int wm, int wn, int lane) {
+  constexpr int NW = WGM * WGN, WF = b_first<AKS>() ? BN : BM, WS = b_first<AKS>() ? BM : BN;
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(WF / 8 / NW));
   __builtin_amdgcn_s_barrier();
-  f0.load(nA, nB, 0, wm, wn, lane);
-  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f1, acc);
-  interleave<0, NM, NR, 0>();
+  k_step<BK, BM, BN, WGM, WGN, AKS, BKS, WS / 8 / NW>([&](int i) { load16_to_lds(gS, offS[i], fill + (wave + NW * i) * 1024); }, nA, nB, 0, f1, f0,
+                                                      acc, wm, wn, lane);
 }
 
 }  // namespace k64
@@ -202,33 +264,24 @@ namespace k32 {
 constexpr int BK = 32;  // k-extent of one LDS stage (64 bytes of bf16)
 constexpr int NS = 4;   // stages in the LDS ring: loads run 3 stages ahead of the MFMAs
 
-// One stage (32 of k) of the pipeline.  On entry f0 holds the fragments of
-// k-step 0 of the current stage (cA, cB).  Starts the loads of the stage three
-// ahead into the ring slot that the previous stage just vacated (fA, fB),
-// multiplies k-step 0 while fetching k-step 1, then waits until the next stage
-// (nA, nB) has landed for the whole block (own loads by count: two later
-// stages may stay in flight; then the barrier) and refills f0 from it under the
-// MFMAs of k-step 1.  The restrict qualifiers tell the compiler that the three
-// slots are distinct, so LDS reads never wait for the loads in flight.
+// One stage (32 of k) of the pipeline; on entry f holds its fragments.  Waits until the next stage (nA, nB) has landed for the
+// whole block (own loads by count: two later stages may stay in flight; then the barrier), starts the loads of the stage four
+// ahead into this stage's slot (fA, fB), which every wave has read out, and reads the next stage's fragments into fn under the
+// MFMAs.  The restrict qualifiers tell the compiler that the two slots are distinct, so LDS reads never wait for the loads in flight.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
 __device__ __forceinline__ void ring_step(const char* gA, const char* gB, uint32_t* offA, uint32_t* offB,
-                                          char* __restrict__ fA, char* __restrict__ fB, const char* __restrict__ cA,
-                                          const char* __restrict__ cB, const char* __restrict__ nA, const char* __restrict__ nB,
-                                          Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f0, Frags<BK, BM, BN, WGM, WGN, AKS, BKS>& f1,
-                                          f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32], int wave, int wm, int wn, int lane) {
-  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN;
-  constexpr int NR = TM * (AKS ? 2 : 1) + TN * (BKS ? 2 : 1), NM = TM * TN;
-  constexpr int LPS = (BM + BN) / 16 / NW;  // loads per stage per wave
-  issue_tile_loads<BK, BM, NW>(gA, offA, fA, wave);
-  issue_tile_loads<BK, BN, NW>(gB, offB, fB, wave);
-  f1.load(cA, cB, 1, wm, wn, lane);
-  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f0, acc);
-  interleave<0, NM, NR, LPS>();
+                                          char* __restrict__ fA, char* __restrict__ fB, const char* __restrict__ nA, const char* __restrict__ nB,
+                                          const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f, Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& fn,
+                                          f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16], int wave, int wm, int wn, int lane) {
+  constexpr int NW = WGM * WGN, LA = BM / 16 / NW, LPS = (BM + BN) / 16 / NW;  // loads per stage per wave
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LPS));
   __builtin_amdgcn_s_barrier();
-  f0.load(nA, nB, 0, wm, wn, lane);
-  mma_step<BK, BM, BN, WGM, WGN, AKS, BKS>(f1, acc);
-  interleave<0, NM, NR, 0>();
+  k_step<BK, BM, BN, WGM, WGN, AKS, BKS, LPS>(
+      [&](int i) {
+        if (i < LA) load16_to_lds(gA, offA[i], fA + (wave + NW * i) * 1024);
+        else load16_to_lds(gB, offB[i - LA], fB + (wave + NW * (i - LA)) * 1024);
+      },
+      nA, nB, 0, f, fn, acc, wm, wn, lane);
 }
 
 }  // namespace k32
@@ -337,13 +390,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     gA = (const char*)((const bf16*)g.segA[piece0] + m0 + k0 * g.lda);
     gB = (const char*)((const bf16*)g.segB[piece0] + n0 + k0 * g.ldb);
   }
-  f32x16 acc[TM][TN];
+  // SPLIT: blocks of 32 x 32, otherwise of 16 x 16
+  using Acc = std::conditional_t<SPLIT, f32x16, f32x4>;
+  constexpr int AB = SPLIT ? 32 : 16;
+  Acc acc[BM / WGM / AB][BN / WGN / AB];
 #pragma unroll
-  for (int i = 0; i < TM; i++)
+  for (int i = 0; i < BM / WGM / AB; i++)
 #pragma unroll
-    for (int j = 0; j < TN; j++)
+    for (int j = 0; j < BN / WGN / AB; j++)
 #pragma unroll
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+      for (int r = 0; r < AB * AB / 64; r++) acc[i][j][r] = 0.f;
 
   if constexpr (SPLIT) {
     using namespace ksplit;
@@ -352,9 +408,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     const size_t stepB = (BKS ? (size_t)BK * g.ldb : (size_t)BK) * 2;
     uint32_t offA[LA], offB[LB];
 #pragma unroll
-    for (int i = 0; i < LA; i++) offA[i] = loader_src_offset<BK, BM, AKS>(wave + NW * i, lane, g.lda);
+    for (int i = 0; i < LA; i++) offA[i] = loader_src_offset<BK, BM, AKS, true>(wave + NW * i, lane, g.lda);
 #pragma unroll
-    for (int i = 0; i < LB; i++) offB[i] = loader_src_offset<BK, BN, BKS>(wave + NW * i, lane, g.ldb, GW, g.swiglu_F);
+    for (int i = 0; i < LB; i++) offB[i] = loader_src_offset<BK, BN, BKS, true>(wave + NW * i, lane, g.ldb, GW, g.swiglu_F);
     // The stage to be fetched next: pA, pB, moved on by scalar selects (a branch per stage would cut the loop into
     // basic blocks).  Past the last stage it stays there: that stage is fetched again into dead slots, which keeps
     // the number of loads in flight uniform for the counted wait.  Weight gradients may have their k axis in pieces
@@ -444,7 +500,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     const int nk = kext / BK;
     // The k axis may be cut into pieces that live in different buffers (kernels.h): the outer loop runs over the
     // pieces, the inner one over the stages of a piece (a multiple of 4).  The stage fetched during local step t
-    // is local stage t + 3; past the end of the piece that is a stage of the next piece, past the end of the last
+    // is local stage t + 4; past the end of the piece that is a stage of the next piece, past the end of the last
     // piece the last stage again (fetched into a dead slot, which keeps the in-flight load count uniform).  The
     // choice is a scalar select, so the inner loop stays one basic block.
     const int nseg = pieces;
@@ -455,30 +511,35 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     issue_tile_loads<BK, BN, NW>(gB + stepB, offB, sB1, wave);
     issue_tile_loads<BK, BM, NW>(gA + 2 * stepA, offA, sA2, wave);
     issue_tile_loads<BK, BN, NW>(gB + 2 * stepB, offB, sB2, wave);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * LPS));
+    issue_tile_loads<BK, BM, NW>(gA + 3 * stepA, offA, sA3, wave);
+    issue_tile_loads<BK, BN, NW>(gB + 3 * stepB, offB, sB3, wave);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(3 * LPS));
     __builtin_amdgcn_s_barrier();
 
-    Frags<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
+    Frags32<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
     f0.load(sA0, sB0, 0, wm, wn, lane);
     const char *curA = gA, *curB = gB;
-    for (int sg = 0; sg < nseg; sg++) {
+    int sg = 0;
+    do {   // (neither loop is ever empty: see the k64 pipeline)
       const bool last_piece = sg + 1 == nseg;
       const char* nxtA = last_piece ? curA : (const char*)((const bf16*)g.segA[piece0 + sg + 1] + m0);
       const char* nxtB = last_piece ? curB : (const char*)((const bf16*)g.segB[piece0 + sg + 1] + n0);
-      const int lim = last_piece ? seg_stages - 1 : seg_stages + 2;
+      const int lim = last_piece ? seg_stages - 1 : seg_stages + 3;
 #define AH_STAGE_PTRS(u)                                                                                              \
   (min((u), lim) >= seg_stages ? nxtA + (size_t)(min((u), lim) - seg_stages) * stepA : curA + (size_t)min((u), lim) * stepA), \
       (min((u), lim) >= seg_stages ? nxtB + (size_t)(min((u), lim) - seg_stages) * stepB : curB + (size_t)min((u), lim) * stepB)
-      for (int t = 0; t < seg_stages; t += 4) {
-        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 3), offA, offB, sA3, sB3, sA0, sB0, sA1, sB1, f0, f1, acc, wave, wm, wn, lane);
-        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 4), offA, offB, sA0, sB0, sA1, sB1, sA2, sB2, f0, f1, acc, wave, wm, wn, lane);
-        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 5), offA, offB, sA1, sB1, sA2, sB2, sA3, sB3, f0, f1, acc, wave, wm, wn, lane);
-        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 6), offA, offB, sA2, sB2, sA3, sB3, sA0, sB0, f0, f1, acc, wave, wm, wn, lane);
-      }
+      int t = 0;
+      do {
+        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 4), offA, offB, sA0, sB0, sA1, sB1, f0, f1, acc, wave, wm, wn, lane);
+        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 5), offA, offB, sA1, sB1, sA2, sB2, f1, f0, acc, wave, wm, wn, lane);
+        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 6), offA, offB, sA2, sB2, sA3, sB3, f0, f1, acc, wave, wm, wn, lane);
+        ring_step<BM, BN, WGM, WGN, AKS, BKS>(AH_STAGE_PTRS(t + 7), offA, offB, sA3, sB3, sA0, sB0, f1, f0, acc, wave, wm, wn, lane);
+        t += 4;
+      } while (t < seg_stages);
 #undef AH_STAGE_PTRS
       curA = nxtA;
       curB = nxtB;
-    }
+    } while (++sg < nseg);
   } else {
     using namespace k64;
     constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;     // loads per tile per wave
@@ -502,33 +563,44 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     uint32_t* offF = BF ? offB : offA;
     uint32_t* offS = BF ? offA : offB;
     const int np = g.K / BK, lastp = np - 1;
-    // During k-block j the tiles S_{j+1} and F_{j+2} are fetched.
+    // During k-block j the tiles F_{j+2} and S_{j+2} are fetched.
     issue_tile_loads<BK, WF, NW>(gF, offF, ring, wave);                                            // F_0 -> buffer 0
     issue_tile_loads<BK, WS, NW>(gS, offS, ring + BUF, wave);                                      // S_0 -> buffer 1
     issue_tile_loads<BK, WF, NW>(gF + (size_t)min(1, lastp) * stepF, offF, ring + 2 * BUF, wave);  // F_1 -> buffer 2
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(WF / 8 / NW));
+    issue_tile_loads<BK, WS, NW>(gS + (size_t)min(1, lastp) * stepS, offS, ring + 3 * BUF, wave);  // S_1 -> buffer 3
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((WF + WS) / 8 / NW));
     __builtin_amdgcn_s_barrier();
 
-    Frags<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
+    Frags32<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
     f0.load(ring + (BF ? BUF : 0), ring + (BF ? 0 : BUF), 0, wm, wn, lane);
     int jf = 0, js = 1;  // buffers of F_j and S_j
-    for (int j = 0; j < np; j++) {
+    int j = 0;
+    do {   // (np >= 2; a loop that might not run would have its accumulators copied at its exit, ahead of the wait below)
       const int nf = jf + 2 >= NB ? jf + 2 - NB : jf + 2;  // F_{j+1}
-      const int ns = js + 2 >= NB ? js + 2 - NB : js + 2;  // S_{j+1}: loaded now, into the buffer of F_{j-1}
-      const int ff = jf + 4 >= NB ? jf + 4 - NB : jf + 4;  // F_{j+2}: into the buffer of S_{j-1}
+      const int ns = js + 2 >= NB ? js + 2 - NB : js + 2;  // S_{j+1}
+      const int ff = jf + 4 >= NB ? jf + 4 - NB : jf + 4;  // F_{j+2}: into the buffer of S_{j-1}; S_{j+2} goes into that of F_j
       const char* cA = ring + (BF ? js : jf) * BUF;
       const char* cB = ring + (BF ? jf : js) * BUF;
       const char* nA = ring + (BF ? ns : nf) * BUF;
       const char* nB = ring + (BF ? nf : ns) * BUF;
-      const char* pS = gS + (size_t)min(j + 1, lastp) * stepS;
+      const char* pS = gS + (size_t)min(j + 2, lastp) * stepS;
       const char* pF = gF + (size_t)min(j + 2, lastp) * stepF;
-      half_even<BM, BN, WGM, WGN, AKS, BKS>(pS, offS, ring + ns * BUF, cA, cB, f0, f1, acc, wave, wm, wn, lane);
-      half_odd<BM, BN, WGM, WGN, AKS, BKS>(pF, offF, ring + ff * BUF, cA, cB, nA, nB, f0, f1, acc, wave, wm, wn, lane);
+      half_even<BM, BN, WGM, WGN, AKS, BKS>(pF, offF, ring + ff * BUF, cA, cB, f0, f1, acc, wave, wm, wn, lane);
+      half_odd<BM, BN, WGM, WGN, AKS, BKS>(pS, offS, ring + jf * BUF, nA, nB, f0, f1, acc, wave, wm, wn, lane);
       jf = nf;
       js = ns;
-    }
+    } while (++j < np);
   }
   __builtin_amdgcn_s_waitcnt(0);  // drain the redundant tail loads before the block's LDS is released
+  if constexpr (!SPLIT) {
+    // The compiler does not see that the accumulators come from matrix instructions: 16 wait states before the first read of
+    // the last one's result.
+    asm volatile("s_nop 15");
+#pragma unroll
+    for (int i = 0; i < BM / WGM / AB; i++)
+#pragma unroll
+      for (int j = 0; j < BN / WGN / AB; j++) asm volatile("" : "+a"(acc[i][j]));
+  }
 
   // ---- epilogue.  A lane holds C[m][n .. n+3] for 4 column groups of each 32x32 block: stores
   // straight from that layout would touch 32 rows per instruction, 16 bytes each.  Instead each
@@ -651,17 +723,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
         old1[it] = *(const f32x4*)(cptr + 4);
       }
     }
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int tr = 0; tr < SR / 32; tr++)
+      for (int tr = 0; tr < SR / 32; tr++)
 #pragma unroll
-      for (int tn = 0; tn < TN; tn++)
+        for (int tn = 0; tn < TN; tn++)
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const int col = tn * 32 + 8 * q + 4 * (lane >> 5);
-          const f32x16& a = acc[tm + tr][tn];
-          f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
-          *(f32x4*)(strip + (tr * 32 + (lane & 31)) * ROWB + col * 4) = v;
-        }
+          for (int q = 0; q < 4; q++) {
+            const int col = tn * 32 + 8 * q + 4 * (lane >> 5);
+            const f32x16& a = acc[tm + tr][tn];
+            f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+            *(f32x4*)(strip + (tr * 32 + (lane & 31)) * ROWB + col * 4) = v;
+          }
+    } else {
+#pragma unroll
+      for (int tr = 0; tr < 2; tr++)
+#pragma unroll
+        for (int tn = 0; tn < 2 * TN; tn++)
+          *(f32x4*)(strip + (tr * 16 + (lane & 15)) * ROWB + (tn * 16 + 4 * (lane >> 4)) * 4) = acc[2 * tm + tr][tn];
+    }
     if constexpr (SPLIT) {
       __syncthreads();
     } else {
