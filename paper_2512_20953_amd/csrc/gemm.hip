@@ -25,7 +25,7 @@
 namespace ah {
 
 // Three pipelines share the tile mapping, the LDS layouts, the fragment reads and the epilogue.  The forward and
-// input-gradient products (at least one k-contiguous operand) use 64-wide k tiles in a ring of five operand
+// input-gradient products (at least one k-contiguous operand) use 64-wide k tiles in a ring of operand
 // buffers, so that every loader instruction fetches whole 128-byte lines of the k-contiguous operand; the weight
 // gradient (both operands k-strided, rows of a tile are 256 or 512 bytes anyway) keeps 32-wide k stages in a ring of
 // four, whose loads all run 2.5 stages ahead.  Measured in the stage: the first is 2-13 % faster on the former
@@ -219,44 +219,52 @@ __device__ __forceinline__ void k_step(const L& load, const char* __restrict__ n
 
 namespace k64 {
 constexpr int BK = 64;  // k-extent of one operand tile in LDS (128 bytes per row of a k-contiguous operand: whole cache lines)
-constexpr int NB = 5;   // operand tiles in the LDS ring (A and B tiles alternate): 2.5 k-blocks of 64
+// DEPTH: k-blocks between the start of the second operand's loads and the wait for them (the first operand's: half a block more), for
+// which the ring has DEPTH + 1 buffers for tiles of the first and DEPTH for those of the second.
+//  256 x 256 tiles: 2, all of a CU's 160 KB.  128 x 256 and 256 x 128: 3, the same.
+//  128 x 128: 2 where two blocks share a CU (80 KB).  In a launch of at most 256 blocks, which have a CU each, 3 (112 KB): a k-block
+//    is 512 clocks of MFMA, and with 2 the loop waited for operands that come from HBM.  4096 x 1024 x 4096 49.4 -> 39.7 us from HBM,
+//    33.7 -> 32.9 from the memory-side cache (NN); 2048^3 28.1 -> 23.0 and 20.8 -> 19.3 (NT); 4 is no better (40.3, 23.4).  Beside a
+//    second stream (GemmArgs::beside) it keeps that stream's blocks off the CUs: BERT-Large stage with a group of 1, 1892 -> 1992 us.
+template <int BM, int BN, int DEPTH, bool BF>
+constexpr int ring_bytes() { return ((DEPTH + 1) * (BF ? BN : BM) + DEPTH * (BF ? BM : BN)) * 2 * BK; }
 
-// The pipeline.  Operand tiles of 64 k are numbered A_0, B_0, A_1, B_1, ...; tile n lives in ring buffer n % 5.
-// A k-block (A_j, B_j) is two k-steps of 32; fragments are double-buffered in registers (f0, f1), the fragments
+// The pipeline.  F is the operand whose tiles go first, S the other one (see b_first); the tiles of k-block j are F_j and S_j.
+// A k-block is two k-steps of 32; fragments are double-buffered in registers (f0, f1), the fragments
 // of a k-step being read from LDS under the MFMAs of the step before.  So all fragments of k-block j are in registers at its
 // middle: there the one barrier per k-block frees its two buffers, and, after a wait that counts the wave's own loads down to the
-// one tile issued last, says that k-block j+1 has landed for the whole block.  The second half of a k-block and the first half of
-// the next one each start the loads of one tile into the buffers so freed.
-// (In the code below the tile sequence is F_0, S_0, F_1, ...: F is A or B, see b_first.)
+// tiles issued after S_{j+1}, says that k-block j+1 has landed for the whole block.  The second half of k-block j starts the loads of
+// S_{j + DEPTH} into the buffer of S_j, the first half those of F_{j + DEPTH} into that of F_{j-1}.
 // The two halves are separate functions so that within each the buffer written is not one of the buffers read:
 // the restrict qualifiers then tell the compiler that LDS reads never wait for the loads in flight.
 
-// Which operand's tiles take the even numbers matters: an even tile is requested 1.5 k-blocks before the wait for it, an odd one 1.  The weights (B of the forward and input-gradient products) stream from HBM while
-// the activations were just written and mostly sit in the caches, so there B goes first.
-template <bool AKS>
-constexpr bool b_first() { return !AKS; }
+// F has the longer way to go.  The weights (B of the forward and input-gradient products) stream from HBM while
+// the activations were just written and mostly sit in the caches, so B goes first, unless its tiles are the larger ones, of which
+// the ring has no room for one more.
+template <int BM, int BN, bool AKS>
+constexpr bool b_first() { return !AKS && BN <= BM; }
 
-// First k-step of k-block j (f0 holds its fragments): starts the loads of the even tile of k-block j+2 and reads the
+// First k-step of k-block j (f0 holds its fragments): starts the loads of F_{j + DEPTH} and reads the
 // fragments of the second one.
 template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
 __device__ __forceinline__ void half_even(const char* gF, uint32_t* offF, char* __restrict__ fill, const char* __restrict__ cA,
                                           const char* __restrict__ cB, const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f0,
                                           Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f1, f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16],
                                           int wave, int wm, int wn, int lane) {
-  constexpr int NW = WGM * WGN, WF = b_first<AKS>() ? BN : BM;
+  constexpr int NW = WGM * WGN, WF = b_first<BM, BN, AKS>() ? BN : BM;
   k_step<BK, BM, BN, WGM, WGN, AKS, BKS, WF / 8 / NW>([&](int i) { load16_to_lds(gF, offF[i], fill + (wave + NW * i) * 1024); }, cA, cB, 1, f0, f1,
                                                       acc, wm, wn, lane);
 }
 
-// Second k-step of k-block j: waits for k-block j+1 (nA, nB), starts the loads of the odd tile of k-block j+2 into a buffer of
-// k-block j, whose fragments all waves hold by now, and reads the first fragments of k-block j+1.
-template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS>
+// Second k-step of k-block j: waits for k-block j+1 (nA, nB), starts the loads of S_{j + DEPTH} into the buffer of S_j, whose
+// fragments all waves hold by now, and reads the first fragments of k-block j+1.
+template <int BM, int BN, int WGM, int WGN, bool AKS, bool BKS, int DEPTH>
 __device__ __forceinline__ void half_odd(const char* gS, uint32_t* offS, char* __restrict__ fill, const char* __restrict__ nA,
                                          const char* __restrict__ nB, Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f0,
                                          const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f1, f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16],
                                          int wave, int wm, int wn, int lane) {
-  constexpr int NW = WGM * WGN, WF = b_first<AKS>() ? BN : BM, WS = b_first<AKS>() ? BM : BN;
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(WF / 8 / NW));
+  constexpr int NW = WGM * WGN, WF = b_first<BM, BN, AKS>() ? BN : BM, WS = b_first<BM, BN, AKS>() ? BM : BN;
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(((DEPTH - 1) * WF + (DEPTH - 2) * WS) / 8 / NW));
   __builtin_amdgcn_s_barrier();
   k_step<BK, BM, BN, WGM, WGN, AKS, BKS, WS / 8 / NW>([&](int i) { load16_to_lds(gS, offS[i], fill + (wave + NW * i) * 1024); }, nA, nB, 0, f1, f0,
                                                       acc, wm, wn, lane);
@@ -340,7 +348,7 @@ __device__ __forceinline__ void first_step(const char* __restrict__ cur, int ks,
 }  // namespace ksplit
 
 // One tile of a product: block `block` of the (M / BM) (N / BN) k_shares that cover it.
-template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI, int DEPTH = 2>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32, NW = WGM * WGN * WGK;
   static_assert(NW == 4, "four waves per block");
@@ -351,8 +359,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   constexpr bool SWIGLU = EPI == EPI_SWIGLU;
   constexpr int GW = SWIGLU ? BN / WGN / 2 : 0;
   static_assert(!SWIGLU || (!AKS && BKS), "the fused SwiGLU epilogue belongs to the forward layout");
-  constexpr int BUF = (BM > BN ? BM : BN) * 128;        // k64: one ring buffer holds an A or a B tile
-  constexpr int RING = SPLIT ? ksplit::stages<BM, BN>() * ksplit::stage_bytes<BM, BN>() : K32 ? k32::NS * (BM + BN) * 64 : k64::NB * BUF;
+  constexpr int RING = SPLIT ? ksplit::stages<BM, BN>() * ksplit::stage_bytes<BM, BN>() : K32 ? k32::NS * (BM + BN) * 64
+                           : k64::ring_bytes<BM, BN, DEPTH, k64::b_first<BM, BN, AKS>()>();
   // the epilogue reuses the ring as staging space
   __shared__ __attribute__((aligned(1024))) char ring[RING];
 
@@ -559,7 +567,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     // K is a multiple of 128: an even number of k-blocks.  Past the end the last k-block is fetched again into
     // dead buffers, which keeps the number of loads in flight uniform for the counted wait.
     // F = the operand whose tiles take the even numbers, S = the other one.
-    constexpr bool BF = b_first<AKS>();
+    constexpr bool BF = b_first<BM, BN, AKS>();
     constexpr int WF = BF ? BN : BM, WS = BF ? BM : BN;
     const char* gF = BF ? gB : gA;
     const char* gS = BF ? gA : gB;
@@ -567,30 +575,31 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     uint32_t* offF = BF ? offB : offA;
     uint32_t* offS = BF ? offA : offB;
     const int np = g.K / BK, lastp = np - 1;
-    // During k-block j the tiles F_{j+2} and S_{j+2} are fetched.
-    issue_tile_loads<BK, WF, NW>(gF, offF, ring, wave);                                            // F_0 -> buffer 0
-    issue_tile_loads<BK, WS, NW>(gS, offS, ring + BUF, wave);                                      // S_0 -> buffer 1
-    issue_tile_loads<BK, WF, NW>(gF + (size_t)min(1, lastp) * stepF, offF, ring + 2 * BUF, wave);  // F_1 -> buffer 2
-    issue_tile_loads<BK, WS, NW>(gS + (size_t)min(1, lastp) * stepS, offS, ring + 3 * BUF, wave);  // S_1 -> buffer 3
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((WF + WS) / 8 / NW));
+    // Ring: F_j in buffer j % (DEPTH + 1) of WF rows, S_j behind those in buffer j % DEPTH of WS rows.  During k-block j the tiles
+    // F_{j + DEPTH} and S_{j + DEPTH} are fetched.
+    constexpr int FB = WF * 2 * BK, SB = WS * 2 * BK, NF = DEPTH + 1, NSB = DEPTH;
+    char* const ringS = ring + NF * FB;
+#pragma unroll
+    for (int t = 0; t < DEPTH; t++) {
+      issue_tile_loads<BK, WF, NW>(gF + (size_t)min(t, lastp) * stepF, offF, ring + t * FB, wave);
+      issue_tile_loads<BK, WS, NW>(gS + (size_t)min(t, lastp) * stepS, offS, ringS + t * SB, wave);
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((DEPTH - 1) * (WF + WS) / 8 / NW));
     __builtin_amdgcn_s_barrier();
 
     Frags32<BK, BM, BN, WGM, WGN, AKS, BKS> f0, f1;
-    f0.load(ring + (BF ? BUF : 0), ring + (BF ? 0 : BUF), 0, wm, wn, lane);
-    int jf = 0, js = 1;  // buffers of F_j and S_j
+    f0.load(BF ? ringS : ring, BF ? ring : ringS, 0, wm, wn, lane);
+    int jf = 0, js = 0;  // buffers of F_j and S_j
     int j = 0;
     do {   // (np >= 2; a loop that might not run would have its accumulators copied at its exit, ahead of the wait below)
-      const int nf = jf + 2 >= NB ? jf + 2 - NB : jf + 2;  // F_{j+1}
-      const int ns = js + 2 >= NB ? js + 2 - NB : js + 2;  // S_{j+1}
-      const int ff = jf + 4 >= NB ? jf + 4 - NB : jf + 4;  // F_{j+2}: into the buffer of S_{j-1}; S_{j+2} goes into that of F_j
-      const char* cA = ring + (BF ? js : jf) * BUF;
-      const char* cB = ring + (BF ? jf : js) * BUF;
-      const char* nA = ring + (BF ? ns : nf) * BUF;
-      const char* nB = ring + (BF ? nf : ns) * BUF;
-      const char* pS = gS + (size_t)min(j + 2, lastp) * stepS;
-      const char* pF = gF + (size_t)min(j + 2, lastp) * stepF;
-      half_even<BM, BN, WGM, WGN, AKS, BKS>(pF, offF, ring + ff * BUF, cA, cB, f0, f1, acc, wave, wm, wn, lane);
-      half_odd<BM, BN, WGM, WGN, AKS, BKS>(pS, offS, ring + jf * BUF, nA, nB, f0, f1, acc, wave, wm, wn, lane);
+      const int nf = jf + 1 == NF ? 0 : jf + 1;    // F_{j+1}
+      const int ns = js + 1 == NSB ? 0 : js + 1;   // S_{j+1}
+      const int ff = jf == 0 ? NF - 1 : jf - 1;    // F_{j + DEPTH}: into the buffer of F_{j-1}; S_{j + DEPTH} goes into that of S_j
+      const char *cF = ring + jf * FB, *cS = ringS + js * SB, *nxF = ring + nf * FB, *nxS = ringS + ns * SB;
+      const char* pS = gS + (size_t)min(j + DEPTH, lastp) * stepS;
+      const char* pF = gF + (size_t)min(j + DEPTH, lastp) * stepF;
+      half_even<BM, BN, WGM, WGN, AKS, BKS>(pF, offF, ring + ff * FB, BF ? cS : cF, BF ? cF : cS, f0, f1, acc, wave, wm, wn, lane);
+      half_odd<BM, BN, WGM, WGN, AKS, BKS, DEPTH>(pS, offS, ringS + js * SB, BF ? nxS : nxF, BF ? nxF : nxS, f0, f1, acc, wave, wm, wn, lane);
       jf = nf;
       js = ns;
     } while (++j < np);
@@ -895,9 +904,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI, int DEPTH = 2>
 __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
-  gemm_tile<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI>(g, blockIdx.x);
+  gemm_tile<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI, DEPTH>(g, blockIdx.x);
 }
 
 // Several weight gradients over the same k axis in one launch, the blocks of one product after those of another (a block's
@@ -1087,11 +1096,11 @@ int raster_rows(int tiles_m) {
   return (tiles_m + groups - 1) / groups;
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WGM, int WGN, int WGK, bool AKS, bool BKS, int EPI, int DEPTH = 2>
 hipError_t run(GemmArgs a, hipStream_t s) {
   if (a.group <= 0) a.group = raster_rows(a.M / BM);
   dim3 grid((a.M / BM) * (a.N / BN) * (AKS && BKS && EPI == EPI_F32_SET ? a.k_shares : 1));
-  hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI>), grid, dim3(64 * WGM * WGN * WGK), 0, s, a);
+  hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, WGK, AKS, BKS, EPI, DEPTH>), grid, dim3(64 * WGM * WGN * WGK), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1099,9 +1108,14 @@ template <bool AKS, bool BKS, int EPI>
 hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
   switch (t) {
     case 0: return run<256, 256, 2, 2, 1, AKS, BKS, EPI>(a, s);
-    case 1: return run<256, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
-    case 2: return run<128, 256, 2, 2, 1, AKS, BKS, EPI>(a, s);
-    case 3: return run<128, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
+    // (depth 3 of the forward and input-gradient tiles: see k64; the weight gradient's pipeline has no such choice)
+    case 1: return run<256, 128, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
+    case 2: return run<128, 256, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
+    case 3:
+      if constexpr (!(AKS && BKS)) {
+        if (!a.beside && (a.M / 128) * (a.N / 128) <= 256) return run<128, 128, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
+      }
+      return run<128, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
     case kWholeCuTile:
       if constexpr (!(AKS && BKS)) return run<128, 128, 1, 1, 4, AKS, BKS, EPI>(a, s);
       else return hipErrorInvalidValue;

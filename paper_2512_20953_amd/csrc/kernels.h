@@ -44,6 +44,7 @@ struct GemmArgs {
   int rope_S, rope_d, rope_cols;
   int M, N, K;
   int beta;
+  int beside;          // kernels of another stream share the CUs: a launch of few tiles leaves them their LDS (same bits)
   int group, xcd_remap;  // tile rasterisation (set by launch_gemm; group 0: by the tile rows of the launch)
   // TN only: the k axis may be the concatenation of n_seg pieces of seg_k rows each (K = n_seg * seg_k), piece i
   // of A starting at segA[i] and of B at segB[i] (same leading dimensions).  n_seg == 0: one piece, A and B.

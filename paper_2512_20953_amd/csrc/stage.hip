@@ -400,8 +400,9 @@ ActPtrs act_ptrs(const ah_stage* s, int slot, int layer) {
 
 hipError_t gemm(ah_stage* s, int site, GemmLayout lay, GemmEpilogue epi, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N,
                 int K, const void* bias, const void* aux, int ld_aux, void* C2, int beta, hipStream_t st,
-                float* colsum_part = nullptr, int colsum_acc = 0) {
+                float* colsum_part = nullptr, int colsum_acc = 0, bool beside = false) {
   GemmArgs g = {};
+  g.beside = beside;
   g.colsum_part = colsum_part; g.ld_colsum = N; g.colsum_acc = colsum_acc;
   g.A = A; g.B = B; g.C = C; g.C2 = C2; g.bias = bias; g.aux = aux;
   g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.ld_aux = ld_aux; g.M = M; g.N = N; g.K = K; g.beta = beta;
@@ -572,6 +573,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   float *part_n2 = vp.n2, *part_n1 = vp.n1, *part_b1 = vp.b1, *part_bqkv = vp.bqkv;
   float* delta = (float*)(wsb + s->ws.delta);
   const bool rms = s->llama;
+  const bool beside = sd != st;
   hipEvent_t* ev = s->sync_ev;
 #define ON_SIDE(site, expr)              \
   do {                                   \
@@ -610,14 +612,14 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   TRY(wgrad(SITE_FC2_WGRAD, WG_FC2, a.g, dy, p.g_w2, F, h, false, SITE_MLP_WGRAD));
   if (!s->llama) {
     // du, and as a by-product of its epilogue the column sums of du per 64-row slab (for db1)
-    TRY(gemm(s, SITE_FC2_DGRAD, GEMM_NT, EPI_GELU_BWD, dy, h, p.w2, h, du, F, T, F, h, nullptr, a.u, F, nullptr, 0, st, part_b1, vp.acc));
+    TRY(gemm(s, SITE_FC2_DGRAD, GEMM_NT, EPI_GELU_BWD, dy, h, p.w2, h, du, F, T, F, h, nullptr, a.u, F, nullptr, 0, st, part_b1, vp.acc, beside));
     TRY(stream_order(st, sd, ev[1]));
     FOLD(add_b1);
   } else {
     // d(gate | up) straight from the product dm = dy Wd^T: the SwiGLU backward is the GEMM's epilogue
     GemmArgs g = {};
     g.A = dy; g.B = p.w2; g.C = du; g.aux = a.u;
-    g.lda = h; g.ldb = h; g.ldc = 2 * F; g.ld_aux = 2 * F; g.swiglu_F = F; g.M = T; g.N = F; g.K = h;
+    g.lda = h; g.ldb = h; g.ldc = 2 * F; g.ld_aux = 2 * F; g.swiglu_F = F; g.M = T; g.N = F; g.K = h; g.beside = beside;
     {
       SiteTimer t(s, SITE_FC2_DGRAD, st);
       TRY(launch_gemm(GEMM_NT, EPI_SWIGLU_BWD, g, st));
@@ -625,7 +627,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     TRY(stream_order(st, sd, ev[1]));
   }
   TRY(wgrad(SITE_FC1_WGRAD, WG_FC1, a.c, du, p.g_w1, h, Fu, true, SITE_MLP_WGRAD));
-  TRY(gemm(s, SITE_FC1_DGRAD, GEMM_NT, EPI_BF16, du, Fu, p.w1, Fu, dsm, h, T, h, Fu, nullptr, nullptr, 0, nullptr, 0, st));  // dc
+  TRY(gemm(s, SITE_FC1_DGRAD, GEMM_NT, EPI_BF16, du, Fu, p.w1, Fu, dsm, h, T, h, Fu, nullptr, nullptr, 0, nullptr, 0, st, nullptr, 0, beside));  // dc
   // The side stream is done with du.  Only attention backward may have to wait for that, and only where dqkv
   // shares du's buffer; an event nobody waits for is not recorded.
   const bool du_reused = sd != st && dqkv == du;
@@ -637,7 +639,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   FOLD(add_n2);
   // output projection
   TRY(wgrad(SITE_WO_WGRAD, WG_WO, a.o, dmid, p.g_wo, hl, h, false, SITE_ATTN_WGRAD));
-  TRY(gemm(s, SITE_WO_DGRAD, GEMM_NT, EPI_BF16, dmid, h, p.wo, h, dsm, hl, T, hl, h, nullptr, nullptr, 0, nullptr, 0, st));  // do
+  TRY(gemm(s, SITE_WO_DGRAD, GEMM_NT, EPI_BF16, dmid, h, p.wo, h, dsm, hl, T, hl, h, nullptr, nullptr, 0, nullptr, 0, st, nullptr, 0, beside));  // do
   // attention (where dqkv shares its buffer with du: wait until the first MLP matrix's weight gradient has read it)
   if (du_reused) TRY(hipStreamWaitEvent(st, ev[2], 0));
   TIMED(SITE_ATTN_BWD, launch_attention_bwd(a.qkv, a.o, (const float*)a.lse, dsm, dqkv, delta, B, S, s->nh, s->d, s->causal, st));
@@ -648,7 +650,7 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
     FOLD(add_bqkv);
   }
   TRY(wgrad(SITE_QKV_WGRAD, WG_QKV, a.a, dqkv, p.g_wqkv, h, 3 * hl, true, SITE_ATTN_WGRAD));
-  TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st));  // da
+  TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st, nullptr, 0, beside));  // da
   // first norm backward; dx = dx_mid + norm_bwd(da); column sums give d(gain), d(offset), d(bo)
   TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32));
   TRY(stream_order(st, sd, ev[5]));
