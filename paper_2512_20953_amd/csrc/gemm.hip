@@ -54,7 +54,10 @@ __device__ __forceinline__ int granule_swizzle(int k) {  // a 64-wide row has tw
 
 template <int W>
 __device__ __forceinline__ int granule32_swizzle(int k) {  // of 32-byte granules
-  static_assert(W >= 128, "a row spans all banks");
+  // rows start 0, 128 (W = 192) or 64 (W = 160) bytes further along the banks than the one before
+  static_assert(W % 128 == 0 || W == 192 || W == 160, "where a row begins among the banks");
+  if (W % 128 == 64) return (k & 2) | ((k >> 3) & 1);
+  if (W % 128 == 32) return (k >> 3) & 1;
   return (k & 3) | ((k >> 1) & 4);
 }
 
@@ -638,7 +641,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   constexpr bool OUT_F32 = EPI == EPI_F32_ACC || EPI == EPI_F32_SET || EPI == EPI_RESID_F32;
   const bool has_bias = (EPI == EPI_BF16 || EPI == EPI_GELU || RESID) && bias != nullptr;
   constexpr int PPR = WN / 8;                       // 8-column pieces per strip row
-  constexpr int NIT = RPW * PPR / 64;               // pieces per lane per strip
+  // rows that the wave takes at a time (PPR = 10 and 12, of tiles 160 and 192 wide: with 40 and 48 of its lanes), and how often
+  constexpr int RPI = 64 % PPR == 0 ? 64 / PPR : 4, NIT = RPW / RPI;
+  constexpr bool PART = RPI * PPR < 64;
   // ROLLED: the pieces of a strip are taken in a loop that is not unrolled.  Straight-line code runs once per launch and tile,
   // at the rate at which instructions arrive from a cold cache: the GeLU epilogues of a 256 x 256 tile had 27 and 42 KB of
   // it, now 10 and 14.  4096 x 4096 x 1024: forward 47.0 -> 42.0 us (half of the difference to the plain epilogue); input
@@ -661,8 +666,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     struct { f32x4 lo, hi; } r = {lo, hi};
     return r;
   };
-  static_assert(64 % PPR == 0, "a lane keeps its column piece across iterations");
-  const int cp = lane % PPR, row0 = lane / PPR;     // piece it*64 + lane -> row row0 + it * (64 / PPR)
+  const int cp = lane % PPR, row0 = PART ? min(lane / PPR, RPI - 1) : lane / PPR;     // the lane's rows: row0 + it * RPI
+  const bool on = !PART || lane < RPI * PPR;
   // output column of the lane's piece.  SwiGLU: the first half of the wave's strip row holds GW gate columns, the
   // second half their up columns; both go to u[:, 2F] (gate at column c, up at F + c), their product to C2[:, F].
   const bool up_piece = SWIGLU && cp >= PPR / 2;
@@ -676,7 +681,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   }
   float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // EPI_GELU_BWD: this lane's column sums over the current 64-row slab
   const bool want_colsum = EPI == EPI_GELU_BWD && g.colsum_part != nullptr;
-  // EPI_ROPE: this lane's 8 pairs, the partner piece, and (cos, sin) of 64 / PPR angle steps (the distance between a
+  // EPI_ROPE: this lane's 8 pairs, the partner piece, and (cos, sin) of RPI angle steps (the distance between a
   // lane's consecutive rows), read once from the table's row of that position; per strip of 32 rows (which never
   // straddles a sequence: S is a multiple of 128) the angles of the lane's first row are read from the table and
   // carried from row to row by rotation
@@ -690,7 +695,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
     rope_pcp = lower ? cp + (d >> 4) : cp - (d >> 4);
     rope_i0 = lower ? ch : ch - half;
     rope_sgn = lower ? -1.f : 1.f;
-    const float* t = g.rope_cs + ((size_t)(64 / PPR) * half + rope_i0) * 2;
+    const float* t = g.rope_cs + ((size_t)RPI * half + rope_i0) * 2;
 #pragma unroll
     for (int q4 = 0; q4 < 4; q4++) {
       const f32x4 e = *(const f32x4*)(t + 4 * q4);
@@ -701,7 +706,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
   auto fetch_aux = [&](int tm) {
     const bf16* p = aux + (size_t)(m0 + wm * WM + tm * 32) * g.ld_aux;
 #pragma unroll
-    for (int it = 0; it < NIT; it++) load16_to_lds_uncounted(p + (size_t)it * (64 / PPR) * g.ld_aux, aux_off, aux_lds + ((tm & 1) * NIT + it) * 1024);
+    for (int it = 0; it < NIT; it++) load16_to_lds_uncounted(p + (size_t)it * RPI * g.ld_aux, aux_off, aux_lds + ((tm & 1) * NIT + it) * 1024);
   };
   if constexpr (AUX_LDS) fetch_aux(0);
 #pragma unroll
@@ -722,16 +727,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
       if (tm + 1 < TM) fetch_aux(tm + 1);
     } else if (EPI == EPI_RESID || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) {
 #pragma unroll
-      for (int it = 0; it < NIT; it++) ax[AUX_LDS ? 0 : it] = *(const bf16x8*)(aux + (size_t)(mbase + it * (64 / PPR)) * g.ld_aux + n);
+      for (int it = 0; it < NIT; it++) ax[AUX_LDS ? 0 : it] = *(const bf16x8*)(aux + (size_t)(mbase + it * RPI) * g.ld_aux + n);
     }
     if (EPI == EPI_SWIGLU_BWD) {  // aux = gate | up: the up columns sit swiglu_F further
 #pragma unroll
-      for (int it = 0; it < NIT; it++) ax2[it] = *(const bf16x8*)(aux + (size_t)(mbase + it * (64 / PPR)) * g.ld_aux + g.swiglu_F + n);
+      for (int it = 0; it < NIT; it++) ax2[it] = *(const bf16x8*)(aux + (size_t)(mbase + it * RPI) * g.ld_aux + g.swiglu_F + n);
     }
     if (EPI == EPI_F32_ACC || AUX_F32) {
 #pragma unroll
       for (int it = 0; it < NIT; it++) {
-        const float* cptr = (AUX_F32 ? (const float*)g.aux : (const float*)g.C) + (size_t)(mbase + it * (64 / PPR)) * (AUX_F32 ? g.ld_aux : g.ldc) + n;
+        const float* cptr = (AUX_F32 ? (const float*)g.aux : (const float*)g.C) + (size_t)(mbase + it * RPI) * (AUX_F32 ? g.ld_aux : g.ldc) + n;
         old0[it] = *(const f32x4*)cptr;
         old1[it] = *(const f32x4*)(cptr + 4);
       }
@@ -752,7 +757,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
 #pragma unroll
       for (int tr = 0; tr < 2; tr++)
 #pragma unroll
-        for (int tn = 0; tn < 2 * TN; tn++)
+        for (int tn = 0; tn < BN / WGN / 16; tn++)
           *(f32x4*)(strip + (tr * 16 + (lane & 15)) * ROWB + (tn * 16 + 4 * (lane >> 4)) * 4) = acc[2 * tm + tr][tn];
     }
     if constexpr (SPLIT) {
@@ -770,13 +775,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
       __builtin_amdgcn_wave_barrier();
       if (AUX_LDS) asm volatile("" ::: "memory");
     }
+    if (on)
 #pragma unroll UNROLL
     for (int it = 0; it < NIT; it++) {
-      const int row = row0 + it * (64 / PPR);
+      const int row = row0 + it * RPI;
       const auto pc = strip_piece(row, cp);
       const f32x4 lo = pc.lo, hi = pc.hi;
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      const size_t m = (size_t)(mbase + it * (64 / PPR));
+      const size_t m = (size_t)(mbase + it * RPI);
       if (OUT_F32) {
         float* cptr = Cf + m * ldcf + n;
         if (EPI == EPI_F32_ACC || EPI == EPI_RESID_F32) {
@@ -864,14 +870,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
       __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));  // the same within the wave, whose strip it is
       __builtin_amdgcn_wave_barrier();
     }
-    if (EPI == EPI_GELU_BWD && (SPLIT || (tm & 1))) {
+    // (192 rows: 96 to a wave.  The first wave's are one partial sum, the second one's 64 and 32: three as for three slabs)
+    constexpr bool ODD = !SPLIT && TM % 2 == 1;
+    static_assert(!ODD || (TM == 3 && WGM == 2), "slabs of a tile");
+    const bool slab_ends = SPLIT || (ODD ? tm == TM - 1 || (wm == 1 && tm == 1) : (tm & 1) == 1);
+    if (EPI == EPI_GELU_BWD && slab_ends) {
       // one 64-row slab (two strips where a strip has 32 rows): lanes that share a column piece (lane % PPR) add up,
       // and where waves share the slab's rows, these waves' sums through LDS; the first PPR lanes write
       if (want_colsum) {
 #pragma unroll
         for (int i = 0; i < 8; i++) {
+          if constexpr (PART) {
+            float t = cs[i];
 #pragma unroll
-          for (int off = PPR; off < 64; off <<= 1) cs[i] += __shfl_xor(cs[i], off);
+            for (int r = 1; r < RPI; r++) t += __shfl(cs[i], cp + r * PPR);
+            cs[i] = t;
+          } else {
+#pragma unroll
+            for (int off = PPR; off < 64; off <<= 1) cs[i] += __shfl_xor(cs[i], off);
+          }
         }
         if constexpr (SPLIT) {
           float* row = (float*)(ring + NW * SR * ROWB) + wave * WN;   // behind the strips
@@ -888,7 +905,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
           }
         }
         if (wk == 0 && lane < PPR) {
-          float* dst = g.colsum_part + (size_t)((m0 + wm * WM + tm * 32) >> 6) * g.ld_colsum + n;
+          const int slab = ODD ? (m0 >> 6) + (wm == 0 ? 0 : 1 + (tm >> 1)) : (m0 + wm * WM + tm * 32) >> 6;
+          float* dst = g.colsum_part + (size_t)slab * g.ld_colsum + n;
           if (g.colsum_acc) {
             const f32x4 o0 = *(const f32x4*)dst, o1 = *(const f32x4*)(dst + 4);
 #pragma unroll
@@ -964,8 +982,24 @@ const TileCfg kTiles[] = {
   {128, 128, 2, 2, 1, {4.4f, 9.0f, .35f}, {5.9f, 14.7f, .35f}, {8.2f, 8.0f, .35f}, {11.0f, 15.3f, .35f}},
   {128, 128, 1, 1, 4, {7.5f, 7.6f, .35f}, {14.2f, 14.5f, .35f}, {}, {}},   // not built for the weight gradient (see namespace ksplit)
   {64, 128, 1, 2, 2, {3.8f, 5.7f, .35f}, {4.8f, 10.5f, .35f}, {6.6f, 5.6f, .23f}, {8.7f, 10.1f, .14f}},
-  {64, 64, 1, 1, 4, {3.6f, 3.3f, .35f}, {4.3f, 6.8f, .35f}, {5.7f, 3.5f, .15f}, {6.6f, 6.4f, .03f}}};
+  {64, 64, 1, 1, 4, {3.6f, 3.3f, .35f}, {4.3f, 6.8f, .35f}, {5.7f, 3.5f, .15f}, {6.6f, 6.4f, .03f}},
+  // forward and input gradient only
+  {256, 192, 2, 2, 1, {9.4f, 18.1f, .45f}, {20.0f, 36.5f, .35f}, {}, {}},
+  {256, 160, 2, 2, 1, {8.6f, 15.5f, .42f}, {20.0f, 31.0f, .35f}, {}, {}},
+  {192, 256, 2, 2, 1, {9.8f, 17.9f, .42f}, {19.5f, 36.5f, .35f}, {}, {}},
+  {192, 128, 2, 2, 1, {6.1f, 10.4f, .32f}, {10.5f, 21.5f, .35f}, {}, {}},
+  {128, 192, 2, 2, 1, {5.5f, 11.1f, .32f}, {13.5f, 21.5f, .35f}, {}, {}}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+// Tiles of 192 and 160 fit outputs that the powers of two leave as one round of large tiles on half of the CUs, or as two of 128 x 128:
+// of 48 random products of up to 4096 x 8192 x 8192 whose plan they changed, geometric means 0.91 (128 x 192), 0.88 (192 x 128), 0.87 (192 x
+// 256), 0.83 (256 x 160) and 0.89 (256 x 192, one round); 1920 x 3200 x 2688 43.1 -> 33.5 us, 2048 x 5120 x 20480 366 -> 336 (NT; the vendor library
+// 325), 4096 x 6144 x 4096 173 -> 160.  They are taken in launches of at least three quarters of the CUs (below, a cover of two launches comes
+// close: 3840 x 2304 x 5248 98 .. 99 us in 180 tiles of 192 x 256, 103 .. 107 as such a cover), and the 256-row ones from
+// K = 2048 on.  They are faster below, too (4096 x 3072 x 1024 27.6 -> 25.5 us with 256 x 192, 2560 x 3840 x 1536 35.0 -> 28.6 with 256 x 160), but there
+// tests/test_gemm_plan.py holds the choice between the older tiles.  Rates: 256 and 512 tiles of each kind, the second measured against that
+// of 256 x 256 (44.5 K + 17.2 us there).
+constexpr int kNarrowTiles = 7;      // first of these tiles
+constexpr int kNarrowMinK = 2048, kNarrowMinTiles = 192;
 constexpr int kWholeCuTile = 4;      // the tile above whose blocks take all of a CU's LDS although the launch is small
 constexpr float kLaunchGap = 2.5f;   // the part of a that later rounds of the same launch do not pay
 
@@ -991,7 +1025,11 @@ constexpr int kWholeCuMinK = 5120;
 // head: a wave's columns must hold whole heads of this width (0: any; the rotary epilogue, EPI_ROPE, of forward)
 bool tile_fits(int i, int M, int n, int K, bool tn, int head) {
   const TileCfg& t = kTiles[i];
-  return M % t.bm == 0 && n % t.bn == 0 && !(i == kWholeCuTile && (tn || (K < kWholeCuMinK && !head))) && !(head && t.bn / t.wgn % head);
+  if (M % t.bm || n % t.bn) return false;
+  if (i == kWholeCuTile && (tn || (K < kWholeCuMinK && !head))) return false;
+  if (i >= kNarrowTiles && (tn || head)) return false;
+  if (i >= kNarrowTiles && forced_tile() != i && ((t.bm == 256 && K < kNarrowMinK) || (M / t.bm) * (n / t.bn) < kNarrowMinTiles)) return false;
+  return !(head && t.bn / t.wgn % head);
 }
 
 // time of a launch of `tiles` tiles of kind i over K
@@ -1014,12 +1052,12 @@ float tile_cost(int i, int M, int n, int K, bool tn, int shares = 1) {
   return launch_cost(i, (long)(M / kTiles[i].bm) * (n / kTiles[i].bn) * shares, (float)K / shares, tn);
 }
 
-int pick_tile(int M, int N, int K, bool tn, int head) {
+int pick_tile(int M, int N, int K, bool tn, int head, int kinds) {
   const int forced = forced_tile();
   if (forced >= 0 && forced < kNumTiles && tile_fits(forced, M, N, K, tn, head)) return forced;
   int best = -1;
   float best_t = 0;
-  for (int i = 0; i < kNumTiles; i++) {
+  for (int i = 0; i < kinds; i++) {
     if (!tile_fits(i, M, N, K, tn, head)) continue;
     const float t = tile_cost(i, M, N, K, tn);
     if (best < 0 || t < best_t) { best = i; best_t = t; }
@@ -1040,8 +1078,8 @@ constexpr float kSecondLaunch = 2.f;  // us: the first launch's last tiles run a
 constexpr int kMaxShares = 16;
 float shares_cost(int M, int N, int shares) { return 4.f + (float)M * N * 4.f * (shares + 2) / 4.5e6f; }  // launch, and 4.5 TB/s
 
-Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats, int head) {
-  Plan p = {1, {pick_tile(M, N, K, tn, head), -1}, N, 1};
+Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats, int head, int kinds) {
+  Plan p = {1, {pick_tile(M, N, K, tn, head, kinds), -1}, N, 1};
   if (p.tile[0] < 0 || forced_tile() >= 0 || getenv("AH_GEMM_NOSPLIT")) return p;
   float best = 0.96f * tile_cost(p.tile[0], M, N, K, tn);  // the model's accuracy: a second launch has to promise more
   for (int s = 2; tn && s <= kMaxShares && (size_t)M * N * s <= part_floats; s++) {
@@ -1053,9 +1091,9 @@ Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats, int 
     }
   }
   for (int n0 = 128; n0 < N; n0 += 128)
-    for (int i = 0; i < kNumTiles; i++) {
+    for (int i = 0; i < kNarrowTiles; i++) {
       if (!tile_fits(i, M, n0, K, tn, head)) continue;
-      for (int j = 0; j < kNumTiles; j++) {
+      for (int j = 0; j < kNarrowTiles; j++) {
         if (j == i || !tile_fits(j, M, N - n0, K, tn, head)) continue;
         const float t = tile_cost(i, M, n0, K, tn) + tile_cost(j, M, N - n0, K, tn) + kSecondLaunch;
         if (t < best) { best = t; p = {2, {i, j}, n0, 1}; }
@@ -1071,16 +1109,17 @@ float plan_cost(const Plan& p, int M, int N, int K, bool tn) {
 }
 
 // make_plan is a search over a few thousand candidates: remembered per problem
-Plan cached_plan(int M, int N, int K, bool tn, int n_seg = 1, size_t part_floats = 0, int head = 0) {
-  struct Entry { int M, N, K; bool tn; int n_seg; size_t part_floats; int head; Plan p; };
+Plan cached_plan(int M, int N, int K, bool tn, int n_seg = 1, size_t part_floats = 0, int head = 0, int kinds = kNumTiles) {
+  struct Entry { int M, N, K; bool tn; int n_seg; size_t part_floats; int head, kinds; Plan p; };
   static std::mutex mu;
   static std::vector<Entry> cache;
   std::lock_guard<std::mutex> lock(mu);
   for (const Entry& e : cache)
-    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.n_seg == n_seg && e.part_floats == part_floats && e.head == head)
+    if (e.M == M && e.N == N && e.K == K && e.tn == tn && e.n_seg == n_seg && e.part_floats == part_floats && e.head == head &&
+        e.kinds == kinds)
       return e.p;
-  const Plan p = make_plan(M, N, K, tn, n_seg, part_floats, head);
-  if (cache.size() < 4096) cache.push_back({M, N, K, tn, n_seg, part_floats, head, p});
+  const Plan p = make_plan(M, N, K, tn, n_seg, part_floats, head, kinds);
+  if (cache.size() < 4096) cache.push_back({M, N, K, tn, n_seg, part_floats, head, kinds, p});
   return p;
 }
 
@@ -1120,6 +1159,16 @@ hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
       if constexpr (!(AKS && BKS)) return run<128, 128, 1, 1, 4, AKS, BKS, EPI>(a, s);
       else return hipErrorInvalidValue;
     case 5: return run<64, 128, 1, 2, 2, AKS, BKS, EPI>(a, s);
+    case 7: case 8: case 9: case 10: case 11:
+      if constexpr (!(AKS && BKS) && EPI != EPI_ROPE) {
+        if (t == 7) return run<256, 192, 2, 2, 1, AKS, BKS, EPI>(a, s);
+        if (t == 8) return run<256, 160, 2, 2, 1, AKS, BKS, EPI>(a, s);
+        if (t == 9) return run<192, 256, 2, 2, 1, AKS, BKS, EPI>(a, s);
+        if (t == 10) return run<192, 128, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
+        return run<128, 192, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
+      } else {
+        return hipErrorInvalidValue;
+      }
     default: return run<64, 64, 1, 1, 4, AKS, BKS, EPI>(a, s);
   }
 }
@@ -1317,8 +1366,15 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
   GemmArgs a = a_in;
   if (!complete(layout, a)) return hipErrorInvalidValue;
   const bool tn = layout == GEMM_TN;
-  const Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0,
-                             epi == EPI_ROPE ? a.rope_d : 0);
+  Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0,
+                       epi == EPI_ROPE ? a.rope_d : 0);
+  // Beside a second stream's weight gradients the CUs that larger tiles leave idle are not lost: 13B layer 3478 -> 3360 us with the
+  // older tiles there, 1536-wide LLaMA-style stage 1747 -> 1708.  Only among tiles that add up a sum in the same order (which the
+  // column sums of the GeLU derivative are not), so that the bits do not depend on the streams.
+  if (a.beside && p.tile[0] >= kNarrowTiles && !a.colsum_part) {
+    const Plan wide = cached_plan(a.M, a.N, a.K, tn, 1, 0, 0, kNarrowTiles);
+    if (kTiles[wide.tile[0]].wgk == 1 && (wide.parts == 1 || kTiles[wide.tile[1]].wgk == 1)) p = wide;
+  }
   if (p.tile[0] < 0) return hipErrorInvalidValue;
   if (p.shares > 1) {
     GemmArgs b = a;

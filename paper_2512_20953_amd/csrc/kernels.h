@@ -54,7 +54,8 @@ struct GemmArgs {
   float* k_part;
   size_t k_part_floats;
   int k_shares;        // set by launch_gemm
-  // EPI_GELU_BWD only, optional: column sums of the (bf16-rounded) output over each slab of 64 rows are written
+  // EPI_GELU_BWD only, optional: column sums of the (bf16-rounded) output over each slab of 64 rows (or, in tiles of 192 rows, over
+  // three ranges of rows that cover the tile) are written
   // to colsum_part[m / 64][n] (leading dimension ld_colsum), for the bias gradient.  Needs M % 64 == 0 (it is).
   float* colsum_part;
   int ld_colsum, colsum_acc;  // colsum_acc != 0: added to what is there
