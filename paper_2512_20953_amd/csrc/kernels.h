@@ -97,11 +97,16 @@ hipError_t launch_attention_bwd(const void* qkv, const void* o, const float* lse
 // keep, optional (x in bf16): a copy of x, in fp32 with keep_f32
 hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const void* beta, void* a, float* stats,
                            int T, int h, float eps, hipStream_t s, bool x_f32 = false, void* keep = nullptr, bool keep_f32 = false);
+// partial column sums of a bf16 matrix m[T, n] (n a multiple of 8) -> part[colsum_blocks(T)][n] (acc != 0: added to what is there)
+struct ColsumJob { const void* m; float* part; int n, acc; };
+hipError_t launch_colsum_partial(const ColsumJob& c, int T, hipStream_t s);
+int colsum_blocks(int T);
 // dx = dres + norm_bwd(da);  partial column sums of (da*xhat, da, dres) go to `part` ([3][nblk][h] fp32),
 // written, or with acc != 0 added to what is there (a group of micro-batches sharing one set of partial sums)
-// keep, optional: a copy of dres
+// keep, optional: a copy of dres;  job, optional: column sums of a matrix of T rows that run beside it (the bits of launch_colsum_partial)
 hipError_t launch_norm_bwd(bool rms, const void* da, const void* x, const float* stats, const void* gamma,
-                           const void* dres, void* dx, float* part, int T, int h, hipStream_t s, int acc = 0, bool x_f32 = false, void* keep = nullptr);
+                           const void* dres, void* dx, float* part, int T, int h, hipStream_t s, int acc = 0, bool x_f32 = false, void* keep = nullptr,
+                           const ColsumJob* job = nullptr);
 int norm_bwd_blocks(int T);
 // g[c] = beta * g[c] + sum_b part[b][c] for the vectors of a list (n a multiple of 64), in one launch
 struct FoldList {
@@ -123,9 +128,6 @@ struct FoldList {
   }
 };
 hipError_t launch_fold(const FoldList& a, int beta, hipStream_t s);
-// partial column sums of a bf16 matrix [T, n] -> part[nblk][n] (acc != 0: added to what is there)
-hipError_t launch_colsum_partial(const void* m, int T, int n, int ld, float* part, hipStream_t s, int acc = 0);
-int colsum_blocks(int T);
 // rotary embedding in place on the Q and K blocks of qkv[T, 3*nh*d]; sign = +1 forward, -1 backward
 hipError_t launch_rope(void* qkv, const float* cos_sin, int T, int S, int nh, int d, float sign, hipStream_t s);
 // device-to-device copy of a multiple of 16 bytes

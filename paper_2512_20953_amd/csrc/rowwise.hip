@@ -186,6 +186,56 @@ __global__ __launch_bounds__(NT, MAXI == 8 && KEEP == KEEP_BF16 ? 2 : 1) void no
   }
 }
 
+// ---------------------------------------------------------------- column sums
+// Partial sums: part[nblk][n], a row for each slab of 64 rows.  Four waves take 512 columns (16 bytes per lane, one
+// contiguous kilobyte per row) of a slab, each every fourth row; their sums meet in LDS.
+// The sums of dqkv are wanted once per layer and micro-batch.  In small stages, where a launch between two others costs more than
+// the sums, the first norm's backward takes them along in blocks behind its own (ColsumJob; the line is in layer_backward).
+constexpr int CS_ROWS = 64;  // rows per slab
+__device__ __forceinline__ void colsum_slab(const bf16* __restrict__ m, int T, int n, float* __restrict__ part, int acc, int cols, int slab,
+                                            float (*red)[512], int wave) {
+  const int lane = threadIdx.x & 63, col = cols * 512 + lane * 8;
+  const int r0 = slab * CS_ROWS, r1 = min(T, r0 + CS_ROWS);   // (no rows behind the last slab)
+  float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (col < n) {
+#pragma unroll 8
+    for (int r = r0 + wave; r < r1; r += 4) {
+      bf16x8 t = *(const bf16x8*)(m + (size_t)r * n + col);
+#pragma unroll
+      for (int j = 0; j < 8; j++) s[j] += bf2f(t[j]);
+    }
+  }
+  float* p = part + (size_t)slab * n + col;
+  const bool last = wave == 0 && col < n && r0 < T;
+  f32x4 old[2] = {};                 // the earlier micro-batches' sums, requested before the waves' sums meet
+  if (last && acc) { old[0] = *(const f32x4*)p; old[1] = *(const f32x4*)(p + 4); }
+  if (wave > 0) {
+#pragma unroll
+    for (int q = 0; q < 2; q++) *(f32x4*)&red[wave - 1][lane * 8 + 4 * q] = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
+  }
+  __syncthreads();
+  if (last) {
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      f32x4 v = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
+#pragma unroll
+      for (int w = 0; w < 3; w++) v += *(const f32x4*)&red[w][lane * 8 + 4 * q];
+      *(f32x4*)(p + 4 * q) = acc ? old[q] + v : v;
+    }
+  }
+}
+__global__ __launch_bounds__(NT) void colsum_partial_kernel(ColsumJob c, int T) {
+  __shared__ __attribute__((aligned(16))) float red[3][512];
+  colsum_slab((const bf16*)c.m, T, c.n, c.part, c.acc, blockIdx.x, blockIdx.y, red, threadIdx.x >> 6);
+}
+// Block `block` of those behind a norm backward's own: eight waves, two slabs.
+constexpr int kColsumLds = 2 * 3 * 512;   // floats
+int colsum_tail(const ColsumJob* c, int T) { return c ? (c->n + 511) / 512 * ((ah::colsum_blocks(T) + 1) / 2) : 0; }
+__device__ __forceinline__ void colsum_tail_block(const ColsumJob& c, int T, int block, float* red) {
+  const int wide = (c.n + 511) / 512, wave = threadIdx.x >> 6, half = wave >> 2;
+  colsum_slab((const bf16*)c.m, T, c.n, c.part, c.acc, block % wide, block / wide * 2 + half, (float(*)[512])(red + half * 3 * 512), wave & 3);
+}
+
 // ---------------------------------------------------------------- norm backward
 // keep, optional: a copy of dres (the stage's output gradient, which a group's weight gradients need after the call; 4096 x 4096:
 // 30.5 us with and 30.4 without, a copy kernel 13.0).
@@ -200,12 +250,14 @@ template <bool RMS, int MAXC, bool XF32>
 __global__ __launch_bounds__(NTB) void norm_bwd_kernel(const bf16* __restrict__ da, const void* __restrict__ x,
                                                        const float* __restrict__ stats, const bf16* __restrict__ gamma,
                                                        const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                       float* __restrict__ part, int T, int h, int rpb, int acc, bf16* __restrict__ keep) {
+                                                       float* __restrict__ part, int T, int h, int rpb, int acc, bf16* __restrict__ keep, int nblk, ColsumJob job) {
   constexpr int RB = MAXC <= 1 ? 2 : 1;  // rows per batch: two keep a 4096-wide row kernel at 125 registers (36.8 us; four rows 39.6, one 38.4)
   constexpr int NWV = NTB / 64;
   constexpr bool PIPE = MAXC <= 2;  // wider rows (hidden > 8192) leave no registers for a second batch, and spill a few
   __shared__ float red[2][NWV][2 * RB];                     // double-buffered: one block barrier per batch
-  const int nchunk = h >> 3, nblk = gridDim.x;
+  __shared__ __attribute__((aligned(16))) float job_red[kColsumLds];
+  if ((int)blockIdx.x >= nblk) return colsum_tail_block(job, T, blockIdx.x - nblk, job_red);
+  const int nchunk = h >> 3;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float inv_h = 1.f / h;
   // the gain stays packed (bf16x8 per chunk: a quarter of the registers of a float copy; rows wider than 8192 need the room)
@@ -365,9 +417,12 @@ template <bool RMS, int MAXI, bool XF32>
 __global__ __launch_bounds__(64 * NWB) void norm_bwd_wave_kernel(const bf16* __restrict__ da, const void* __restrict__ x,
                                                                 const float* __restrict__ stats, const bf16* __restrict__ gamma,
                                                                 const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                                float* __restrict__ part, int T, int h, int acc, bf16* __restrict__ keep) {
+                                                                float* __restrict__ part, int T, int h, int acc, bf16* __restrict__ keep, int nblk,
+                                                                ColsumJob job) {
   __shared__ __attribute__((aligned(16))) float red[NWB][MAXI * 512];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nchunk = h >> 3, nblk = gridDim.x;
+  static_assert(NWB * MAXI * 512 >= kColsumLds && NWB == 8, "room for the column sums");
+  if ((int)blockIdx.x >= nblk) return colsum_tail_block(job, T, blockIdx.x - nblk, &red[0][0]);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nchunk = h >> 3;
   const float inv_h = 1.f / h;
   bf16x8 gam[MAXI];
   float sums[3][MAXI][8];
@@ -457,46 +512,6 @@ __global__ __launch_bounds__(64 * NWB) void norm_bwd_wave_kernel(const bf16* __r
 #pragma unroll
       for (int w = 1; w < NWB; w++) v += *(const f32x4*)&red[w][c];
       *(f32x4*)(p + a * step) = v + old[a];
-    }
-  }
-}
-
-// ---------------------------------------------------------------- column sums
-// Partial sums: grid (ceil(n / 512), nblk).  A wave owns 512 columns (16 bytes per lane, one
-// contiguous kilobyte per row) and every fourth row of the block's slab; the four waves' sums
-// meet in LDS and leave as one row of part[nblk][n].
-constexpr int CS_ROWS = 64;  // rows per block
-__global__ __launch_bounds__(NT) void colsum_partial_kernel(const bf16* __restrict__ m, int T, int n, int ld,
-                                                            float* __restrict__ part, int acc) {
-  __shared__ __attribute__((aligned(16))) float red[3][512];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = blockIdx.x * 512 + lane * 8;
-  const int r0 = blockIdx.y * CS_ROWS, r1 = min(T, r0 + CS_ROWS);
-  float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (col < n) {
-#pragma unroll 8
-    for (int r = r0 + wave; r < r1; r += 4) {
-      bf16x8 t = *(const bf16x8*)(m + (size_t)r * ld + col);
-#pragma unroll
-      for (int j = 0; j < 8; j++) s[j] += bf2f(t[j]);
-    }
-  }
-  float* p = part + (size_t)blockIdx.y * n + col;
-  const bool last = wave == 0 && col < n;
-  f32x4 old[2] = {};                 // the earlier micro-batches' sums, requested before the waves' sums meet
-  if (last && acc) { old[0] = *(const f32x4*)p; old[1] = *(const f32x4*)(p + 4); }
-  if (wave > 0) {
-#pragma unroll
-    for (int q = 0; q < 2; q++) *(f32x4*)&red[wave - 1][lane * 8 + 4 * q] = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
-  }
-  __syncthreads();
-  if (last) {
-#pragma unroll
-    for (int q = 0; q < 2; q++) {
-      f32x4 v = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
-#pragma unroll
-      for (int w = 0; w < 3; w++) v += *(const f32x4*)&red[w][lane * 8 + 4 * q];
-      *(f32x4*)(p + 4 * q) = acc ? old[q] + v : v;
     }
   }
 }
@@ -593,27 +608,27 @@ void norm_fwd_go(const void* x, bool x_f32, const void* gamma, const void* beta,
 }
 template <bool RMS, int MAXC>
 void norm_bwd_go(const void* da, const void* x, bool x_f32, const float* stats, const void* gamma, const void* dres, void* dx, float* part,
-                 int T, int h, int acc, void* keep, hipStream_t s) {
+                 int T, int h, int acc, void* keep, const ColsumJob* job, hipStream_t s) {
   const int nblk = norm_bwd_blocks(T);
   const int rpb = (T + nblk - 1) / nblk;
   if (x_f32)
-    hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, true>), dim3(nblk), dim3(NTB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep);
+    hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, true>), dim3(nblk + colsum_tail(job, T)), dim3(NTB), 0, s, (const bf16*)da, x, stats,
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
   else
-    hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, false>), dim3(nblk), dim3(NTB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep);
+    hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, false>), dim3(nblk + colsum_tail(job, T)), dim3(NTB), 0, s, (const bf16*)da, x, stats,
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
 }
 // one wave per row, hidden <= 1024
 template <bool RMS, int MAXI>
 void norm_bwd_wave_go(const void* da, const void* x, bool x_f32, const float* stats, const void* gamma, const void* dres, void* dx, float* part,
-                      int T, int h, int acc, void* keep, hipStream_t s) {
+                      int T, int h, int acc, void* keep, const ColsumJob* job, hipStream_t s) {
   const int nblk = norm_bwd_blocks(T);
   if (x_f32)
-    hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, true>), dim3(nblk), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep);
+    hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, true>), dim3(nblk + colsum_tail(job, T)), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
   else
-    hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, false>), dim3(nblk), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep);
+    hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, false>), dim3(nblk + colsum_tail(job, T)), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
+                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
 }
 }  // namespace
 
@@ -663,15 +678,16 @@ hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const voi
 #define AH_BWD_BY_CHUNKS(RMS)                                                                        \
   do {                                                                                               \
     const int nc = (h + 4095) / 4096;                                                                \
-    if (h <= 512) norm_bwd_wave_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s);       \
-    else if (h <= 1024) norm_bwd_wave_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s); \
-    else if (nc <= 1) norm_bwd_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s);      \
-    else if (nc == 2) norm_bwd_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s); \
-    else norm_bwd_go<RMS, 4>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, s);              \
+    if (h <= 512) norm_bwd_wave_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, job, s);       \
+    else if (h <= 1024) norm_bwd_wave_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, job, s); \
+    else if (nc <= 1) norm_bwd_go<RMS, 1>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, job, s);      \
+    else if (nc == 2) norm_bwd_go<RMS, 2>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, job, s); \
+    else norm_bwd_go<RMS, 4>(da, x, x_f32, stats, gamma, dres, dx, part, T, h, acc, keep, job, s);              \
   } while (0)
 
 hipError_t launch_norm_bwd(bool rms, const void* da, const void* x, const float* stats, const void* gamma, const void* dres,
-                           void* dx, float* part, int T, int h, hipStream_t s, int acc, bool x_f32, void* keep) {
+                           void* dx, float* part, int T, int h, hipStream_t s, int acc, bool x_f32, void* keep, const ColsumJob* job) {
+  if (job && job->n % 8) return hipErrorInvalidValue;
   if (h % 8 || h > 16384) return hipErrorInvalidValue;
   if (rms) AH_BWD_BY_CHUNKS(true);
   else AH_BWD_BY_CHUNKS(false);
@@ -688,9 +704,9 @@ hipError_t launch_fold(const FoldList& a, int beta, hipStream_t s) {
 
 int colsum_blocks(int T) { return (T + CS_ROWS - 1) / CS_ROWS; }
 
-hipError_t launch_colsum_partial(const void* m, int T, int n, int ld, float* part, hipStream_t s, int acc) {
-  if (n % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((n + 511) / 512, colsum_blocks(T)), dim3(NT), 0, s, (const bf16*)m, T, n, ld, part, acc);
+hipError_t launch_colsum_partial(const ColsumJob& c, int T, hipStream_t s) {
+  if (c.n % 8) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(colsum_partial_kernel, dim3((c.n + 511) / 512, colsum_blocks(T)), dim3(NT), 0, s, c, T);
   return hipGetLastError();
 }
 

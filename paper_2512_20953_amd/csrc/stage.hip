@@ -645,14 +645,21 @@ hipError_t layer_backward(ah_stage* s, int layer, const ActPtrs& a, const void* 
   TIMED(SITE_ATTN_BWD, launch_attention_bwd(a.qkv, a.o, (const float*)a.lse, dsm, dqkv, delta, B, S, s->nh, s->d, s->causal, st));
   if (s->llama) TIMED(SITE_ROPE, launch_rope(dqkv, (const float*)P(s->bufs.workspace, s->ws.rope), T, S, s->nh, s->d, -1.f, st));
   TRY(stream_order(st, sd, ev[4]));
+  // The column sums of dqkv: on one stream a small matrix's run beside the first norm's backward, which saves a launch; a large one is
+  // read at once, while the caches hold it.  Stage, apart / together: smallest (0.4 MB) 320.9 / 311.2 us, 5-head (1.5 MB) 241.1 / 233.5,
+  // 512-wide (3.1 MB) 451.2 / 439.5, 896-wide (6.2 MB) 488.3 / 482.8, BERT-Large (25 MB) 3391 / 3407, 1.3B (25 MB) 5924 / 5947.
+  // (A trace times them by themselves.  The same bits either way.)
+  const ColsumJob sums = {dqkv, part_bqkv, 3 * hl, vp.acc};
+  const bool with_norm = !s->llama && !beside && !s->tracing && (size_t)T * 3 * hl * 2 <= (size_t)12 << 20;
   if (!s->llama) {
-    ON_SIDE(SITE_COLSUM, launch_colsum_partial(dqkv, T, 3 * hl, 3 * hl, part_bqkv, sd, vp.acc));
+    if (!with_norm) ON_SIDE(SITE_COLSUM, launch_colsum_partial(sums, T, sd));
     FOLD(add_bqkv);
   }
   TRY(wgrad(SITE_QKV_WGRAD, WG_QKV, a.a, dqkv, p.g_wqkv, h, 3 * hl, true, SITE_ATTN_WGRAD));
   TRY(gemm(s, SITE_QKV_DGRAD, GEMM_NT, EPI_BF16, dqkv, 3 * hl, p.wqkv, 3 * hl, dsm, h, T, h, 3 * hl, nullptr, nullptr, 0, nullptr, 0, st, nullptr, 0, beside));  // da
   // first norm backward; dx = dx_mid + norm_bwd(da); column sums give d(gain), d(offset), d(bo)
-  TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32));
+  TIMED(SITE_NORM_BWD, launch_norm_bwd(rms, dsm, a.x_in, (const float*)a.stats1, p.ln1_g, dmid, dx, part_n1, T, h, st, vp.acc, s->res32, nullptr,
+                                       with_norm ? &sums : nullptr));
   TRY(stream_order(st, sd, ev[5]));
   FOLD(add_n1);
   if (sd == st && folds.count > 0) ON_SIDE(SITE_COLSUM, launch_fold(folds, vp.beta, sd));   // one launch for the layer
