@@ -246,17 +246,20 @@ __device__ __forceinline__ void colsum_tail_block(const ColsumJob& c, int T, int
 // reduced, so that memory latency, the block reduction and the arithmetic overlap.
 constexpr int NTB = 512;  // threads per block of the norm backward; MAXC here = ceil(hidden / 4096)
 
-template <bool RMS, int MAXC, bool XF32>
+template <bool RMS, int MAXC, bool XF32, bool JOB>
 __global__ __launch_bounds__(NTB) void norm_bwd_kernel(const bf16* __restrict__ da, const void* __restrict__ x,
                                                        const float* __restrict__ stats, const bf16* __restrict__ gamma,
                                                        const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                       float* __restrict__ part, int T, int h, int rpb, int acc, bf16* __restrict__ keep, int nblk, ColsumJob job) {
+                                                       float* __restrict__ part, int T, int h, int rpb, int acc, bf16* __restrict__ keep, int nblk_job, ColsumJob job) {
+  const int nblk = JOB ? nblk_job : gridDim.x;
   constexpr int RB = MAXC <= 1 ? 2 : 1;  // rows per batch: two keep a 4096-wide row kernel at 125 registers (36.8 us; four rows 39.6, one 38.4)
   constexpr int NWV = NTB / 64;
   constexpr bool PIPE = MAXC <= 2;  // wider rows (hidden > 8192) leave no registers for a second batch, and spill a few
   __shared__ float red[2][NWV][2 * RB];                     // double-buffered: one block barrier per batch
-  __shared__ __attribute__((aligned(16))) float job_red[kColsumLds];
-  if ((int)blockIdx.x >= nblk) return colsum_tail_block(job, T, blockIdx.x - nblk, job_red);
+  if constexpr (JOB) {
+    __shared__ __attribute__((aligned(16))) float job_red[kColsumLds];
+    if ((int)blockIdx.x >= nblk) return colsum_tail_block(job, T, blockIdx.x - nblk, job_red);
+  }
   const int nchunk = h >> 3;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float inv_h = 1.f / h;
@@ -413,15 +416,18 @@ __global__ __launch_bounds__(NTB) void norm_bwd_kernel(const bf16* __restrict__ 
 // rate of a large copy), 256 x 256: 7.6 -> 4.5 us.  At 2048 columns the sums and two rows no longer fit the registers of
 // two waves to a SIMD, and the kernel above is the faster one (13.6 against 14.6 us for 2048 rows).
 constexpr int NWB = 8;  // waves per block
-template <bool RMS, int MAXI, bool XF32>
+template <bool RMS, int MAXI, bool XF32, bool JOB>
 __global__ __launch_bounds__(64 * NWB) void norm_bwd_wave_kernel(const bf16* __restrict__ da, const void* __restrict__ x,
                                                                 const float* __restrict__ stats, const bf16* __restrict__ gamma,
                                                                 const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                                float* __restrict__ part, int T, int h, int acc, bf16* __restrict__ keep, int nblk,
+                                                                float* __restrict__ part, int T, int h, int acc, bf16* __restrict__ keep, int nblk_job,
                                                                 ColsumJob job) {
+  const int nblk = JOB ? nblk_job : gridDim.x;
   __shared__ __attribute__((aligned(16))) float red[NWB][MAXI * 512];
-  static_assert(NWB * MAXI * 512 >= kColsumLds && NWB == 8, "room for the column sums");
-  if ((int)blockIdx.x >= nblk) return colsum_tail_block(job, T, blockIdx.x - nblk, &red[0][0]);
+  if constexpr (JOB) {
+    static_assert(NWB * MAXI * 512 >= kColsumLds && NWB == 8, "room for the column sums");
+    if ((int)blockIdx.x >= nblk) return colsum_tail_block(job, T, blockIdx.x - nblk, &red[0][0]);
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nchunk = h >> 3;
   const float inv_h = 1.f / h;
   bf16x8 gam[MAXI];
@@ -606,29 +612,28 @@ void norm_fwd_go(const void* x, bool x_f32, const void* gamma, const void* beta,
   else if (mode == KEEP_F32) go(norm_fwd_kernel<RMS, MAXC, false, KEEP_F32>);
   else go(norm_fwd_kernel<RMS, MAXC, false, KEEP_NONE>);
 }
+// (Instances of their own with a job: its code alone, never run, cost the block kernel 7 us at 4096 x 4096, 29.1 -> 36.4.)
 template <bool RMS, int MAXC>
 void norm_bwd_go(const void* da, const void* x, bool x_f32, const float* stats, const void* gamma, const void* dres, void* dx, float* part,
                  int T, int h, int acc, void* keep, const ColsumJob* job, hipStream_t s) {
   const int nblk = norm_bwd_blocks(T);
   const int rpb = (T + nblk - 1) / nblk;
-  if (x_f32)
-    hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, true>), dim3(nblk + colsum_tail(job, T)), dim3(NTB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
-  else
-    hipLaunchKernelGGL((norm_bwd_kernel<RMS, MAXC, false>), dim3(nblk + colsum_tail(job, T)), dim3(NTB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
+  auto kernel = x_f32 ? norm_bwd_kernel<RMS, MAXC, true, false> : norm_bwd_kernel<RMS, MAXC, false, false>;
+  if constexpr (!RMS)
+    if (job) kernel = x_f32 ? norm_bwd_kernel<RMS, MAXC, true, true> : norm_bwd_kernel<RMS, MAXC, false, true>;
+  hipLaunchKernelGGL(kernel, dim3(nblk + colsum_tail(job, T)), dim3(NTB), 0, s, (const bf16*)da, x, stats, (const bf16*)gamma, (const bf16*)dres,
+                     (bf16*)dx, part, T, h, rpb, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
 }
 // one wave per row, hidden <= 1024
 template <bool RMS, int MAXI>
 void norm_bwd_wave_go(const void* da, const void* x, bool x_f32, const float* stats, const void* gamma, const void* dres, void* dx, float* part,
                       int T, int h, int acc, void* keep, const ColsumJob* job, hipStream_t s) {
   const int nblk = norm_bwd_blocks(T);
-  if (x_f32)
-    hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, true>), dim3(nblk + colsum_tail(job, T)), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
-  else
-    hipLaunchKernelGGL((norm_bwd_wave_kernel<RMS, MAXI, false>), dim3(nblk + colsum_tail(job, T)), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats,
-                       (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, part, T, h, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
+  auto kernel = x_f32 ? norm_bwd_wave_kernel<RMS, MAXI, true, false> : norm_bwd_wave_kernel<RMS, MAXI, false, false>;
+  if constexpr (!RMS)
+    if (job) kernel = x_f32 ? norm_bwd_wave_kernel<RMS, MAXI, true, true> : norm_bwd_wave_kernel<RMS, MAXI, false, true>;
+  hipLaunchKernelGGL(kernel, dim3(nblk + colsum_tail(job, T)), dim3(64 * NWB), 0, s, (const bf16*)da, x, stats, (const bf16*)gamma, (const bf16*)dres,
+                     (bf16*)dx, part, T, h, acc, (bf16*)keep, nblk, job ? *job : ColsumJob{});
 }
 }  // namespace
 
@@ -687,7 +692,7 @@ hipError_t launch_norm_fwd(bool rms, const void* x, const void* gamma, const voi
 
 hipError_t launch_norm_bwd(bool rms, const void* da, const void* x, const float* stats, const void* gamma, const void* dres,
                            void* dx, float* part, int T, int h, hipStream_t s, int acc, bool x_f32, void* keep, const ColsumJob* job) {
-  if (job && job->n % 8) return hipErrorInvalidValue;
+  if (job && (rms || job->n % 8)) return hipErrorInvalidValue;   // (the RMS-norm stages have no such bias)
   if (h % 8 || h > 16384) return hipErrorInvalidValue;
   if (rms) AH_BWD_BY_CHUNKS(true);
   else AH_BWD_BY_CHUNKS(false);
