@@ -1185,9 +1185,12 @@ hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
 // whole heads, where the output would take others, cost more than that only on the smallest outputs (128-wide heads,
 // fused against kernel, us a layer: 128 rows x 256 hidden 36.6 / 32.5, 384 x 640 46.3 / 41.5, 1024 x 1024 61.1 / 62.3,
 // 4096 x 1024 116.8 / 126.1).
+// Compared are the tiles that hold heads with the others of their kind.  Those of 192 and 160, which are not built with this epilogue,
+// stay out: with them `any` is cheap enough that 93 of 2496 stages (128 .. 4096 rows x 256 .. 5120 hidden) would give up the rotation
+// on the fp32 sums for a narrower tile and round q and k to 16 bits before it.
 bool gemm_rope_pays(int M, int N, int K, int d, int rope_cols) {
   if (!gemm_shape_ok(M, N, K) || d <= 0 || d % 16) return false;
-  const Plan heads = cached_plan(M, N, K, false, 1, 0, d), any = cached_plan(M, N, K, false);
+  const Plan heads = cached_plan(M, N, K, false, 1, 0, d), any = cached_plan(M, N, K, false, 1, 0, 0, kNarrowTiles);
   if (heads.tile[0] < 0) return false;
   return plan_cost(heads, M, N, K, false) <= plan_cost(any, M, N, K, false) + 3.f + (float)M * rope_cols * 4.f / 4.5e6f;
 }

@@ -59,6 +59,26 @@ def test_no_raster_group_of_one_or_two_rows_in_small_outputs(layout, M, N, K):
             assert rows % group == 0 or rows % group >= 3, (rows, group)
 
 
+def _rotates_in_the_product(rows, hidden, head_dim):
+    return bool(lib._ZN2ah14gemm_rope_paysEiiiii(rows, 3 * hidden, hidden, head_dim, 2 * hidden) & 1)   # ah::gemm_rope_pays, a bool
+
+
+# LLaMA-style stages whose QKV product would fit tiles of 192 or 160 better than any that holds whole heads
+@pytest.mark.parametrize("rows,hidden", [(1920, 2048), (1280, 2560), (1152, 3072), (1024, 3200), (1536, 2176), (768, 3840), (384, 4096),
+                                         (512, 4096), (768, 4096), (768, 4608), (384, 5120), (768, 5120), (2688, 1280), (3456, 4096)])
+def test_narrow_tiles_take_no_rotation_off_the_fp32_sums(rows, hidden):
+    """The separate rotary kernel rounds q and k to 16 bits before it rotates them; the product's epilogue does not."""
+    assert _rotates_in_the_product(rows, hidden, 128)
+
+
+def test_rotation_over_the_range():
+    """Of 1248 stages with 128-wide heads 181 leave the rotation to its kernel, of those with 64-wide heads none: the tiles that hold whole heads
+    cost those more than the kernel does."""
+    grid = [(rows, hidden) for hidden in range(256, 5121, 128) for rows in range(128, 4097, 128)]
+    assert sum(not _rotates_in_the_product(r, h, 128) for r, h in grid) <= 181
+    assert all(_rotates_in_the_product(r, h, 64) for r, h in grid)
+
+
 @pytest.mark.parametrize("arch,hidden,heads,head_dim,ffn,seq,mb,group,deferred", [
     # what the rule says, and, measured, us per micro-batch and layer, products taken at once / deferred to the end of the group in
     # one launch (the rule prices the group's products as launches of their own and so says "at once" for some where deferring is faster)
