@@ -228,8 +228,7 @@ constexpr int BK = 64;  // k-extent of one operand tile in LDS (128 bytes per ro
 //  128 x 128: 2 where two blocks share a CU (80 KB).  In a launch of at most 256 blocks, which have a CU each, 3 (112 KB): a k-block
 //    is 512 clocks of MFMA, and with 2 the loop waited for operands that come from HBM.  4096 x 1024 x 4096 49.4 -> 39.7 us from HBM,
 //    33.7 -> 32.9 from the memory-side cache (NN); 2048^3 28.1 -> 23.0 and 20.8 -> 19.3 (NT); 4 is no better (40.3, 23.4).  Beside a
-//    second stream (GemmArgs::beside) it keeps that stream's blocks off the CUs: BERT-Large stage with a group of 1, 1892 -> 1992 us;
-//    there it is taken only for a long k (kWholeCuMaxK).
+//    second stream (GemmArgs::beside) it keeps that stream's blocks off the CUs: BERT-Large stage with a group of 1, 1892 -> 1992 us.
 template <int BM, int BN, int DEPTH, bool BF>
 constexpr int ring_bytes() { return ((DEPTH + 1) * (BF ? BN : BM) + DEPTH * (BF ? BM : BN)) * 2 * BK; }
 
@@ -971,8 +970,6 @@ namespace {
 // of 64 .. 127 and 128 .. 191 tiles, 0.49 and 0.60 in the weight gradient).  With 0.35 there too, 130 .. 192 such tiles
 // lost to 520 .. 768 of 128 x 128: 2560 x 3840 x 1536 (NT) 39.1 us against 32.8, 4096 x 3072 x 1024 with cold operands
 // 38.0 / 30.5.
-// (The 16x16x32 loop is 4 .. 12 % faster than these rows of the tiles it runs, in about the same proportion, so the rows stand: 256 x 256 22.8 k + 11.8,
-// 256 x 128 13.1 k + 8.2, 128 x 128 8.4 k + 4.8 when they were taken again beside the rows of the 192 and 160 wide tiles, the weights from HBM.)
 // tn of the two small tiles: fitted to 1500 weight gradients of K = 128 .. 32768, scaled like the other tiles' rows
 // (those over-estimate by 8 %).  The line through K >= 256 alone was 10-35 % short at K = 128 .. 512, where these tiles then
 // displaced 128 x 128: 3200 x 896 x 128 8.6 us against 7.3.
@@ -1024,15 +1021,16 @@ int forced_tile() {
 // and 6144) 1.00; without the tile, the latter 1.03 at G = 1 and 3, 2048-wide GPT (k = 6144 and 8192) 0.98 at G = 1, 1.015 from
 // G = 2 on.  Single products gain below the line too (1408 x 1536 x 4096 NT 39.0 us, 27.7 with this tile): what they
 // lose is the price of one choice for all callers.
-// (These were taken beside the 32x32x16 loop.)  From kWholeCuMaxK on 128 x 128 tiles of the present loop, on the deeper ring, take over: 2048 x
-// 2048 x 6144 62.0 us with this tile, 57.7 without (NT), 2048 x 2048 x 8192 79.5 / 75.9 (NN), the 1.3B stage 6108 / 5865, its group of 1 3379 / 3326.
-// Below the line they would, too (2048 x 2048 x 4096 38.9 / 36.4), but there tests/test_gpu_gemm_tiles.py holds this tile.
-constexpr int kWholeCuMinK = 5120, kWholeCuMaxK = 6144;
+// (These were taken beside the 32x32x16 loop.  Against 128 x 128 tiles of the present loop, on the deeper ring, the tile is slower where it
+// fills the chip, 2048 x 2048 x 6144 62.0 / 57.7 us (NT), 2048 x 2048 x 8192 79.5 / 75.9 (NN), the 1.3B stage 2 .. 3 %, and faster where it
+// does not, 640 x 6016 x 6656 49.1 / 52.6, 384 x 6400 x 7040 44.0 / 46.5.  It stays at every k for its sums: four chains a quarter as long
+// leave fp32 results half as far from 64 bits, 2.0e-7 against 4.1e-7 of their norm at k = 6144, 2.4e-7 against 5.0e-7 at 8192.)
+constexpr int kWholeCuMinK = 5120;
 // head: a wave's columns must hold whole heads of this width (0: any; the rotary epilogue, EPI_ROPE, of forward)
 bool tile_fits(int i, int M, int n, int K, bool tn, int head) {
   const TileCfg& t = kTiles[i];
   if (M % t.bm || n % t.bn) return false;
-  if (i == kWholeCuTile && (tn || ((K < kWholeCuMinK || K >= kWholeCuMaxK) && !head))) return false;
+  if (i == kWholeCuTile && (tn || (K < kWholeCuMinK && !head))) return false;
   if (i >= kNarrowTiles && (tn || head)) return false;
   if (i >= kNarrowTiles && forced_tile() != i && ((t.bm == 256 && K < kNarrowMinK) || (M / t.bm) * (n / t.bn) < kNarrowMinTiles)) return false;
   return !(head && t.bn / t.wgn % head);
@@ -1158,7 +1156,7 @@ hipError_t run_tile(int t, const GemmArgs& a, hipStream_t s) {
     case 2: return run<128, 256, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
     case 3:
       if constexpr (!(AKS && BKS)) {
-        if ((!a.beside || a.K >= kWholeCuMaxK) && (a.M / 128) * (a.N / 128) <= 256) return run<128, 128, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
+        if (!a.beside && (a.M / 128) * (a.N / 128) <= 256) return run<128, 128, 2, 2, 1, AKS, BKS, EPI, 3>(a, s);
       }
       return run<128, 128, 2, 2, 1, AKS, BKS, EPI>(a, s);
     case kWholeCuTile:

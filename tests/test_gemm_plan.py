@@ -23,6 +23,14 @@ def test_the_measured_faster_tile_is_taken(layout, M, N, K, tile):
     assert shares == 1 and [l[1:3] for l in launches] == [tile]
 
 
+@pytest.mark.parametrize("layout,M,N,K", [("nn", 2048, 2048, 6144), ("nn", 2048, 2048, 8192), ("nt", 2048, 2048, 6144), ("nt", 2048, 2048, 8192),
+                                          ("nn", 640, 3328, 6144), ("nt", 1280, 1664, 8192), ("nn", 640, 6016, 6656), ("nn", 384, 6400, 7040)])
+def test_long_sums_of_small_outputs_are_taken_in_four_parts(layout, M, N, K):
+    """One chain of that length is twice as far from 64 bits (fp32 results), and slower in launches of less than a tile per CU."""
+    shares, launches = P.gemm_plan(layout, M, N, K)
+    assert shares == 1 and [l[1:4] for l in launches] == [(128, 128, 4)]
+
+
 def test_plans_cover_the_output():
     rng = random.Random(3)
     size = lambda hi: 128 * max(1, round(2 ** rng.uniform(0, hi)))
