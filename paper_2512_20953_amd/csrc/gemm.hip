@@ -1082,9 +1082,19 @@ constexpr float kSecondLaunch = 2.f;  // us: the first launch's last tiles run a
 constexpr int kMaxShares = 16;
 float shares_cost(int M, int N, int shares) { return 4.f + (float)M * N * 4.f * (shares + 2) / 4.5e6f; }  // launch, and 4.5 TB/s
 
+bool one_chain(const Plan& p) { return kTiles[p.tile[0]].wgk == 1 && (p.parts == 1 || kTiles[p.tile[1]].wgk == 1); }
+
 Plan make_plan(int M, int N, int K, bool tn, int n_seg, size_t part_floats, int head, int kinds) {
   Plan p = {1, {pick_tile(M, N, K, tn, head, kinds), -1}, N, 1};
-  if (p.tile[0] < 0 || forced_tile() >= 0 || getenv("AH_GEMM_NOSPLIT")) return p;
+  if (p.tile[0] < 0 || forced_tile() >= 0) return p;
+  // Tiles of 192 and 160 add up a sum in one chain.  Where the plan without them takes the sums of some columns in parts (15 % of the
+  // products that would change to them), it stays although it is slower, because one chain is further from 64 bits (fp32 results, of their
+  // norm): 2304 x 2048 x 9088 in parts 2.6e-7 and 109.8 us, in tiles of 192 x 128 5.3e-7 and 94.4; 3456 x 3328 x 10240 5.0e-7 and 220 / 5.8e-7 and 187.
+  if (p.tile[0] >= kNarrowTiles) {
+    const Plan older = make_plan(M, N, K, tn, n_seg, part_floats, head, kNarrowTiles);
+    if (!one_chain(older)) return older;
+  }
+  if (getenv("AH_GEMM_NOSPLIT")) return p;
   float best = 0.96f * tile_cost(p.tile[0], M, N, K, tn);  // the model's accuracy: a second launch has to promise more
   for (int s = 2; tn && s <= kMaxShares && (size_t)M * N * s <= part_floats; s++) {
     if (n_seg > 1 ? n_seg % s : K % (128 * s)) continue;
@@ -1376,12 +1386,9 @@ hipError_t launch_gemm(GemmLayout layout, GemmEpilogue epi, const GemmArgs& a_in
   Plan p = cached_plan(a.M, a.N, a.K, tn, std::max(a.n_seg, 1), tn && a.k_part ? a.k_part_floats : 0,
                        epi == EPI_ROPE ? a.rope_d : 0);
   // Beside a second stream's weight gradients the CUs that larger tiles leave idle are not lost: 13B layer 3478 -> 3360 us with the
-  // older tiles there, 1536-wide LLaMA-style stage 1747 -> 1708.  Only among tiles that add up a sum in the same order (which the
-  // column sums of the GeLU derivative are not), so that the bits do not depend on the streams.
-  if (a.beside && p.tile[0] >= kNarrowTiles && !a.colsum_part) {
-    const Plan wide = cached_plan(a.M, a.N, a.K, tn, 1, 0, 0, kNarrowTiles);
-    if (kTiles[wide.tile[0]].wgk == 1 && (wide.parts == 1 || kTiles[wide.tile[1]].wgk == 1)) p = wide;
-  }
+  // older tiles there, 1536-wide LLaMA-style stage 1747 -> 1708.  They add up a sum in the same order (make_plan), which the column
+  // sums of the GeLU derivative are not, so the bits do not depend on the streams.
+  if (a.beside && p.tile[0] >= kNarrowTiles && !a.colsum_part) p = cached_plan(a.M, a.N, a.K, tn, 1, 0, 0, kNarrowTiles);
   if (p.tile[0] < 0) return hipErrorInvalidValue;
   if (p.shares > 1) {
     GemmArgs b = a;

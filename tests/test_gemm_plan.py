@@ -31,6 +31,16 @@ def test_long_sums_of_small_outputs_are_taken_in_four_parts(layout, M, N, K):
     assert shares == 1 and [l[1:4] for l in launches] == [(128, 128, 4)]
 
 
+@pytest.mark.parametrize("layout,M,N,K,cover", [
+    ("nn", 2304, 2048, 9088, [(64, 64, 4), (128, 128, 4)]), ("nt", 3456, 3328, 10240, [(128, 128, 4), (128, 256, 1)]),
+    ("nn", 3328, 2560, 5760, [(64, 64, 4), (128, 256, 1)]), ("nt", 3968, 4608, 6784, [(64, 128, 2), (128, 256, 1)]),
+    ("nn", 2048, 4480, 2176, [(64, 64, 4), (128, 256, 1)])])
+def test_narrow_tiles_take_no_sum_out_of_its_parts(layout, M, N, K, cover):
+    """Tiles of 192 and 160 add up a sum in one chain; covers whose tiles share the k axis among their waves are left to those."""
+    shares, launches = P.gemm_plan(layout, M, N, K)
+    assert shares == 1 and [l[1:4] for l in launches] == cover
+
+
 def test_plans_cover_the_output():
     rng = random.Random(3)
     size = lambda hi: 128 * max(1, round(2 ** rng.uniform(0, hi)))
