@@ -200,11 +200,14 @@ __device__ __forceinline__ void mma16(f32x4& acc, const bf16x8& a, const bf16x8&
 // 3, 4 or 8 eighths 1.005, 1.004 and 1.014 times as long, geometric mean over 56 products).  The loads of a short step, and those
 // of the weight gradient, whose operands come from far away, go out in its first half: 4096 x 1024 x 4096 36.3 -> 35.0 us (NT), 2048^3
 // 22.9 -> 22.1 (NN), 4096^3 111.8 -> 109.9 (TN); evenly they are 1 % better in the larger forward and input-gradient steps.
+// In the weight gradient's short steps (TN, up to 32 matrix instructions) the reads, two to a fragment, take all slots but the last two: beside the loads
+// the first three quarters made a wave that is alone on its SIMD wait for them.  Launches of up to a tile per CU, against the 32x32x16 loop that was
+// here before (geometric means, three boxes): 128 x 256 and 256 x 128 1.04 -> 0.98 .. 1.00, 128 x 128 1.03 -> 1.01; 3840 x 1152 x 5120 51.8 us there, 57.1 -> 53.6 here.
 template <int BK, int BM, int BN, int WGM, int WGN, bool AKS, bool BKS, int NV, class L>
 __device__ __forceinline__ void k_step(const L& load, const char* __restrict__ nA, const char* __restrict__ nB, int ks,
                                        const Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& f, Frags32<BK, BM, BN, WGM, WGN, AKS, BKS>& fn,
                                        f32x4 (&acc)[BM / WGM / 16][BN / WGN / 16], int wm, int wn, int lane) {
-  constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16, NM = TM * TN, NF = TM + TN, SPAN = NM * 3 / 4;
+  constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16, NM = TM * TN, NF = TM + TN, SPAN = AKS && BKS && NM <= 32 ? NM - 2 : NM * 3 / 4;
   constexpr int VSPAN = (AKS && BKS) || NM <= 16 ? NM / 2 : NM;
 #pragma unroll
   for (int i = 0; i < NM; i++) {
