@@ -22,16 +22,20 @@ def _bf16_normal(rng, shape, std):
     return SI.round_bf16((rng.standard_normal(shape, dtype=np.float32) * np.float32(std)))
 
 
-@pytest.mark.parametrize("layout,M,N,K", [
-    ("nn", 4096, 8192, 4096),   # first MLP matrix forward
-    ("nn", 4096, 6144, 4096),   # QKV forward: two launches over column ranges, 128 x 256 and 256 x 256 tiles
-    ("nt", 4096, 2048, 4096),   # out-projection input gradient (128 x 256 tiles)
-    ("nt", 4096, 4096, 8192),   # first MLP matrix input gradient
-    ("tn", 8192, 4096, 4096),   # second MLP matrix weight gradient
-    ("tn", 2048, 4096, 4096),   # out-projection weight gradient
-    ("tn", 4096, 6144, 4096),   # QKV weight gradient: 768 tiles of 128 x 256
+@pytest.mark.parametrize("layout,M,N,K,tiles", [
+    ("nn", 4096, 8192, 4096, [(256, 256)]),   # first MLP matrix forward
+    ("nn", 4096, 6144, 4096, [(256, 192)]),   # QKV forward
+    ("nn", 2048, 20480, 5120, [(128, 256), (256, 256)]),   # first MLP matrix forward of the 13B stage: two launches over column ranges
+    ("nn", 2048, 2048, 8192, [(128, 128)]),   # second MLP matrix forward of the 1.3B stage (four k shares)
+    ("nt", 2048, 5120, 20480, [(256, 160)]),  # first MLP matrix input gradient of the 13B stage
+    ("nt", 4096, 2048, 4096, [(128, 256)]),   # out-projection input gradient
+    ("nt", 4096, 4096, 8192, [(256, 256)]),   # first MLP matrix input gradient
+    ("tn", 8192, 4096, 4096, [(256, 256)]),   # second MLP matrix weight gradient
+    ("tn", 2048, 4096, 4096, [(128, 256)]),   # out-projection weight gradient
+    ("tn", 4096, 6144, 4096, [(128, 256)]),   # QKV weight gradient: 768 tiles
 ])
-def test_gemm_at_benchmark_shapes_sampled_entries(layout, M, N, K):
+def test_gemm_at_benchmark_shapes_sampled_entries(layout, M, N, K, tiles):
+    assert [l[1:3] for l in P.gemm_plan(layout, M, N, K)[1]] == tiles
     rng = np.random.default_rng(7)
     rows = np.sort(rng.choice(M, 48, replace=False))
     cols = np.sort(rng.choice(N, 48, replace=False))

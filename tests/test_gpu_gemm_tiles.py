@@ -184,6 +184,7 @@ def test_second_stream_by_size_changes_no_bit(arch, recompute, monkeypatch):
 def test_dx_depends_on_neither_streams_nor_groups(hidden, ffn, monkeypatch):
     """2048 x 2048 input gradients over k = 4224 .. 8192 (the longer ones' tile splits the k axis between its waves): with
     and without the second stream, and with the weight gradients of a group deferred or not, y and dx are the same bits."""
+    assert [P.gemm_plan("nt", 2048, hidden, k)[1][0][1:4] for k in (ffn, 3 * hidden)] == [T128K if ffn > 5120 else T128, T128K]
     res = []
     for group, gflop, defer, streams in ((1, "0", "1", 2), (1, "1e9", "1", 1), (2, "0", "1", 1), (2, "0", "0", 2)):
         monkeypatch.setenv("AH_SIDE_STREAM_MIN_GFLOP", gflop)   # both read when the stage is created
