@@ -220,7 +220,12 @@ int ah_stage_profile(ah_stage_t* st, int warmup, int iters, ah_stage_profile_t* 
  * roofline report (Section III-D's profiler only needs whole-layer times; this
  * is the finer view).  Between _begin and _end every launch site is bracketed
  * by a HIP event pair on the stream it is launched on; _end synchronises the
- * device and fills up to `capacity` entries, one per site that ran. */
+ * device and fills up to `capacity` entries, one per site that ran.  A trace
+ * times one kernel at a time, with the same results: backward stays on the
+ * caller's stream, and the column sums behind the QKV bias gradient, which small
+ * stages take in the launch of the first norm's backward, are a launch of their
+ * own.  So the sites of a stage that uses a second stream, or of a small one,
+ * add up to more than its untraced pass (ah_stage_profile times that one). */
 typedef struct {
   char name[32];            /* e.g. "gemm_nn.fc1_fwd", "attention_bwd", "norm_fwd" */
   int64_t launches;         /* event pairs recorded for this site */

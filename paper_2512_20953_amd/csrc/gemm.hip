@@ -28,7 +28,7 @@ namespace ah {
 // input-gradient products (at least one k-contiguous operand) use 64-wide k tiles in a ring of operand
 // buffers, so that every loader instruction fetches whole 128-byte lines of the k-contiguous operand; the weight
 // gradient (both operands k-strided, rows of a tile are 256 or 512 bytes anyway) keeps 32-wide k stages in a ring of
-// four, whose loads all run 2.5 stages ahead.  Measured in the stage: the first is 2-13 % faster on the former
+// four, whose loads all run three stages ahead.  Measured in the stage: the first is 2-13 % faster on the former
 // products, the second 1-5 % faster on the latter.  The third is that of the smallest tiles (namespace ksplit).
 
 // ---------------------------------------------------------------------------
@@ -313,7 +313,8 @@ namespace ksplit {
 //  128 x 128 with four shares: every wave owns the whole tile, so a k-block costs 32 KB of fragment reads instead of
 //    the 64 KB of four 64 x 64 sub-tiles.  Beside 512 clocks of MFMA the CU's path to and from the LDS was busy ~950
 //    (reads at 128 B per clock, the 32 KB fill at 1.7 times its bytes), now ~690; what bounds it then is the rate at
-//    which the loads arrive (64 B per clock and CU).  2048 x 2048 x 8192: 76 -> 61 us (NT).  The epilogue moves four
+//    which the loads arrive (64 B per clock and CU).  2048 x 2048 x 8192: 76 -> 61 us (NT; against the 32x32x16 loop:
+//    the present one has closed the gap, see kWholeCuMinK, and the tile is there for its shorter sums).  The epilogue moves four
 //    times the partial sums (3 us): at k = 2048 the two are level, and where two blocks of the 64 x 64 sub-tiles share
 //    a CU (more than 256 tiles) those are faster; in the weight gradient, whose transposing reads are half as long,
 //    there is no gain (67 against 67 us), so it is not built there.
@@ -572,7 +573,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
 
     // K is a multiple of 128: an even number of k-blocks.  Past the end the last k-block is fetched again into
     // dead buffers, which keeps the number of loads in flight uniform for the counted wait.
-    // F = the operand whose tiles take the even numbers, S = the other one.
+    // F = the operand whose tiles go first, S = the other one.
     constexpr bool BF = b_first<BM, BN, AKS>();
     constexpr int WF = BF ? BN : BM, WS = BF ? BM : BN;
     const char* gF = BF ? gB : gA;
@@ -621,8 +622,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
       for (int j = 0; j < BN / WGN / AB; j++) asm volatile("" : "+a"(acc[i][j]));
   }
 
-  // ---- epilogue.  A lane holds C[m][n .. n+3] for 4 column groups of each 32x32 block: stores
-  // straight from that layout would touch 32 rows per instruction, 16 bytes each.  Instead each
+  // ---- epilogue.  A lane holds C[m][n .. n+3] of each 16x16 block (for 4 column groups of each 32x32 block where waves split
+  // the k axis): stores straight from that layout would touch 16 (32) rows per instruction, 16 bytes each.  Instead each
   // wave passes its sub-tile through a private LDS strip, 32 rows at a time in fp32, and reads it
   // back row-major, so that every global access is 16 bytes per lane and whole rows per 16 lanes.
   // Where waves split the k axis, the WGK waves of a sub-tile leave 64 rows at a time, each its own partial sums, and
@@ -814,7 +815,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int block) {
 #pragma unroll
           for (int i = 0; i < 8; i++) {
             v[i] = v[i] * rc[i] + rope_sgn * pv[i] * rs[i];
-            // the lane's next row is 64 / PPR positions further: rotate (cos, sin) by that many steps of the angle
+            // the lane's next row is RPI positions further: rotate (cos, sin) by that many steps of the angle
             const float c2 = rc[i] * dcs_c[i] - rs[i] * dcs_s[i];
             rs[i] = rs[i] * dcs_c[i] + rc[i] * dcs_s[i];
             rc[i] = c2;
@@ -973,6 +974,10 @@ namespace {
 // of 64 .. 127 and 128 .. 191 tiles, 0.49 and 0.60 in the weight gradient).  With 0.35 there too, 130 .. 192 such tiles
 // lost to 520 .. 768 of 128 x 128: 2560 x 3840 x 1536 (NT) 39.1 us against 32.8, 4096 x 3072 x 1024 with cold operands
 // 38.0 / 30.5.
+// The rows of the first four tiles were taken with the 32x32x16 loop, which the next three still run.  One round of the first four, the weights
+// from HBM, on the present loop: 256 x 256 22.8 k + 11.8 (level at k = 1, 1 % less than its row at 16), 256 x 128 13.1 k + 8.2 (level, 6 %),
+// 128 x 128 8.4 k + 4.8 (2 %, 6 %).  The rows of the 192 and 160 wide tiles are of the present loop, their second ones measured against 256 x 256 at
+// 44.5 k + 17.2, so beside these the older tiles are priced up to 6 % too high.
 // tn of the two small tiles: fitted to 1500 weight gradients of K = 128 .. 32768, scaled like the other tiles' rows
 // (those over-estimate by 8 %).  The line through K >= 256 alone was 10-35 % short at K = 128 .. 512, where these tiles then
 // displaced 128 x 128: 3200 x 896 x 128 8.6 us against 7.3.
@@ -1000,7 +1005,7 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 // close: 3840 x 2304 x 5248 98 .. 99 us in 180 tiles of 192 x 256, 103 .. 107 as such a cover), and the 256-row ones from
 // K = 2048 on.  They are faster below, too (4096 x 3072 x 1024 27.6 -> 25.5 us with 256 x 192, 2560 x 3840 x 1536 35.0 -> 28.6 with 256 x 160), but there
 // tests/test_gemm_plan.py holds the choice between the older tiles.  Rates: 256 and 512 tiles of each kind, the second measured against that
-// of 256 x 256 (44.5 K + 17.2 us there).
+// of 256 x 256 (44.5 k + 17.2 us there).
 constexpr int kNarrowTiles = 7;      // first of these tiles
 constexpr int kNarrowMinK = 2048, kNarrowMinTiles = 192;
 constexpr int kWholeCuTile = 4;      // the tile above whose blocks take all of a CU's LDS although the launch is small
@@ -1015,8 +1020,8 @@ int forced_tile() {
   return forced;
 }
 
-// The choice knows the problem alone, not what runs beside it on another stream: the order of a sum's terms, and so its
-// last bits, depends on the tile.  kWholeCuTile's blocks leave no room on a CU for those of a second stream, so it is
+// The order of a sum's terms, and so its last bits, depends on the tile.  So the choice knows the problem alone, not what runs beside it on
+// another stream, but between tiles that add up in the same order (launch_gemm).  kWholeCuTile's blocks leave no room on a CU for those of a second stream, so it is
 // taken only from a k on where the gain is clear.  Stage times with the line elsewhere, against 5120 (G: micro-batches
 // per group; with G = 1 the second stream runs): at 3584, 1280-wide stage (k = 3840) 1.06 at G = 1, 1.02 at G = 2 and 3,
 // BERT-Large (k = 4096) 1.01 at G = 1, 0.98 at G = 8; at 2048, 768-wide BERT (k = 3072) 1.00 at G = 1, 0.98 at G = 3;
@@ -1024,10 +1029,10 @@ int forced_tile() {
 // and 6144) 1.00; without the tile, the latter 1.03 at G = 1 and 3, 2048-wide GPT (k = 6144 and 8192) 0.98 at G = 1, 1.015 from
 // G = 2 on.  Single products gain below the line too (1408 x 1536 x 4096 NT 39.0 us, 27.7 with this tile): what they
 // lose is the price of one choice for all callers.
-// (These were taken beside the 32x32x16 loop.  Against 128 x 128 tiles of the present loop, on the deeper ring, the tile is slower where it
-// fills the chip, 2048 x 2048 x 6144 62.0 / 57.7 us (NT), 2048 x 2048 x 8192 79.5 / 75.9 (NN), the 1.3B stage 2 .. 3 %, and faster where it
-// does not, 640 x 6016 x 6656 49.1 / 52.6, 384 x 6400 x 7040 44.0 / 46.5.  It stays at every k for its sums: four chains a quarter as long
-// leave fp32 results half as far from 64 bits, 2.0e-7 against 4.1e-7 of their norm at k = 6144, 2.4e-7 against 5.0e-7 at 8192.)
+// (These were taken beside the 32x32x16 loop.)  128 x 128 tiles of the present loop, on the deeper ring, are level with this one or faster (this / those, us,
+// operands from the caches): 2048 x 2048 x 6144 50.8 / 51.9 (NN) and 50.4 / 47.7 (NT), x 8192 64.9 / 67.6 and 62.8 / 60.7, 640 x 6016 x 6656 50.6 / 52.7 and
+// 50.8 / 47.4; the 1.3B stage, whose weights come from HBM, 6088 / 5861.  The tile stays at every k for its sums: four chains a quarter as long
+// leave fp32 results half as far from 64 bits, 2.0e-7 against 4.1e-7 of their norm at k = 6144, 2.4e-7 against 5.0e-7 at 8192.
 constexpr int kWholeCuMinK = 5120;
 // head: a wave's columns must hold whole heads of this width (0: any; the rotary epilogue, EPI_ROPE, of forward)
 bool tile_fits(int i, int M, int n, int K, bool tn, int head) {
